@@ -155,10 +155,10 @@ int spa2_pattern_full(const spa2_shape* shape, spa2_pattern* out, void* stream);
  *          largest error term of dQ when |K| is large.
  *   workspace  optional (NULL, 0 = none), 16-byte aligned, up to spa2_fwd_workspace_bytes(shape) bytes.  One
  *          workgroup walks one row of the pattern, so a launch cannot end before its longest row has; on layers
- *          with few rows per compute unit the longest rows then set the time.  With a workspace, lists longer than
- *          S = max(16, total tiles / 2048) entries are cut into parts of S that run as workgroups of their own;
- *          the parts' (O, m, l) are combined in part order by a second kernel (Alg. 1 step 18 makes that exact up
- *          to rounding), so results stay deterministic.  On large layers S exceeds every list and nothing changes.
+ *          with few rows per compute unit the longest rows then set the time.  With a workspace, lists longer than S
+ *          entries (8 to 48 on small and ordinary layers, total tiles / 8192 on large ones) are cut into equal parts
+ *          that run as workgroups of their own; the part that finishes last combines the (O, m, l) of all of them in
+ *          part order (Alg. 1 step 18 makes that exact up to rounding), so results stay deterministic.
  * Reads pattern->row_cnt / row_idx (and row_order if set). */
 int spa2_fwd(const void* q, const void* k, const void* v, const spa2_shape* shape,
              const spa2_pattern* pattern, float scale, void* o, void* o_res, float* lse,

@@ -47,19 +47,28 @@ BwdWs bwd_ws(const Dims& m) {
   BwdWs w;
   w.d_bytes = round256((size_t)m.B * m.H * m.N * sizeof(float));
   w.dq_off = w.d_bytes;
-  w.dq_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, dq_slot_bytes(m)));
+  w.dq_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m)));
   w.dkdv_off = w.dq_off + w.dq_bytes;
-  w.dkdv_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tn, dkdv_slot_bytes(m)));
+  w.dkdv_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tn, m.Tm, dkdv_slot_bytes(m)));
   w.total = w.dkdv_off + w.dkdv_bytes;
   return w;
 }
 size_t bwd_ws_min_bytes(const Dims& m) { return bwd_ws(m).d_bytes; }
 
 // the part of a workspace section that the caller's buffer really covers
-SplitPlan section_plan(void* ws, size_t ws_bytes, size_t off, size_t bytes, int64_t units, size_t slot_bytes) {
-  if (!ws || ws_bytes <= off) return split_layout(nullptr, 0, units, slot_bytes);
+SplitPlan section_plan(void* ws, size_t ws_bytes, size_t off, size_t bytes, int64_t units, int list_max,
+                       size_t slot_bytes) {
+  if (!ws || ws_bytes <= off) return split_layout(nullptr, 0, units, list_max, slot_bytes);
   const size_t have = ws_bytes - off < bytes ? ws_bytes - off : bytes;
-  return split_layout((char*)ws + off, have, units, slot_bytes);
+  return split_layout((char*)ws + off, have, units, list_max, slot_bytes);
+}
+SplitPlan dq_plan(const Dims& m, void* ws, size_t ws_bytes) {
+  const BwdWs w = bwd_ws(m);
+  return section_plan(ws, ws_bytes, w.dq_off, w.dq_bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m));
+}
+SplitPlan dkdv_plan(const Dims& m, void* ws, size_t ws_bytes) {
+  const BwdWs w = bwd_ws(m);
+  return section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, (int64_t)m.B * m.H * m.Tn, m.Tm, dkdv_slot_bytes(m));
 }
 
 }  // namespace
@@ -108,7 +117,7 @@ size_t spa2_bwd_workspace_min_bytes(const spa2_shape* shape) {
 size_t spa2_fwd_workspace_bytes(const spa2_shape* shape) {
   if (check_shape(shape) != SPA2_OK) return 0;
   const Dims m = make_dims(*shape);
-  return round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, fwd_slot_bytes(m)));
+  return round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m)));
 }
 
 int spa2_mask_pool(const void* q, const void* k, const spa2_shape* shape, void* workspace,
@@ -203,7 +212,7 @@ int spa2_fwd(const void* q, const void* k, const void* v, const spa2_shape* shap
   if (workspace && !aligned16(workspace)) return SPA2_ERR_ALIGN;
   const Dims m = make_dims(*shape);
   const SplitPlan plan = section_plan(workspace, workspace_bytes, 0, spa2_fwd_workspace_bytes(shape),
-                                      (int64_t)m.B * m.H * m.Tm, fwd_slot_bytes(m));
+                                      (int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m));
   if (launch_fwd(q, k, v, m, pattern->row_cnt, pattern->row_idx, pattern->row_order, scale, o, o_res, lse, plan,
                  (hipStream_t)stream) != hipSuccess)
     return SPA2_ERR_LAUNCH;
@@ -236,9 +245,7 @@ int spa2_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o, 
   const Dims m = make_dims(*shape);
   if (!workspace || workspace_bytes < bwd_ws_min_bytes(m)) return SPA2_ERR_WORKSPACE;
   if (!aligned16(workspace)) return SPA2_ERR_ALIGN;
-  const BwdWs w = bwd_ws(m);
-  const SplitPlan plan = section_plan(workspace, workspace_bytes, w.dkdv_off, w.dkdv_bytes, (int64_t)m.B * m.H * m.Tn,
-                                      dkdv_slot_bytes(m));
+  const SplitPlan plan = dkdv_plan(m, workspace, workspace_bytes);
   return launch_bwd_dkdv(q, k, v, d_o, lse, (const float*)workspace, m, pattern->col_cnt, pattern->col_idx,
                          pattern->col_order, scale, dk, dv, plan, (hipStream_t)stream) == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
 }
@@ -255,9 +262,7 @@ int spa2_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, co
   const Dims m = make_dims(*shape);
   if (!workspace || workspace_bytes < bwd_ws_min_bytes(m)) return SPA2_ERR_WORKSPACE;
   if (!aligned16(workspace)) return SPA2_ERR_ALIGN;
-  const BwdWs w = bwd_ws(m);
-  const SplitPlan plan = section_plan(workspace, workspace_bytes, w.dq_off, w.dq_bytes, (int64_t)m.B * m.H * m.Tm,
-                                      dq_slot_bytes(m));
+  const SplitPlan plan = dq_plan(m, workspace, workspace_bytes);
   return launch_bwd_dq(q, k, v, d_o, lse, (const float*)workspace, m, pattern->row_cnt, pattern->row_idx,
                        pattern->row_order, scale, dq, plan, (hipStream_t)stream) == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
 }
@@ -276,11 +281,18 @@ int spa2_bwd(const void* q, const void* k, const void* v, const void* o, const v
   const Dims m = make_dims(*shape);
   if (!workspace || workspace_bytes < bwd_ws_min_bytes(m)) return SPA2_ERR_WORKSPACE;
   if (!aligned16(workspace)) return SPA2_ERR_ALIGN;
-  rc = spa2_bwd_delta(o, o_res, d_o, shape, workspace, workspace_bytes, stream);
-  if (rc != SPA2_OK) return rc;
-  rc = spa2_bwd_dkdv(q, k, v, d_o, lse, shape, pattern, scale, dk, dv, workspace, workspace_bytes, stream);
-  if (rc != SPA2_OK) return rc;
-  return spa2_bwd_dq(q, k, v, d_o, lse, shape, pattern, scale, dq, workspace, workspace_bytes, stream);
+  // the sequence of the three stage calls, with both plans made in the launch that computes D
+  SplitPlan rows = dq_plan(m, workspace, workspace_bytes), cols = dkdv_plan(m, workspace, workspace_bytes);
+  float* delta = (float*)workspace;
+  hipStream_t st = (hipStream_t)stream;
+  if (launch_bwd_prepare(o, o_res, d_o, m, delta, pattern->row_cnt, rows, pattern->col_cnt, cols, st) != hipSuccess)
+    return SPA2_ERR_LAUNCH;
+  rows.planned = cols.planned = true;
+  if (launch_bwd_dkdv(q, k, v, d_o, lse, delta, m, pattern->col_cnt, pattern->col_idx, pattern->col_order, scale, dk, dv,
+                      cols, st) != hipSuccess)
+    return SPA2_ERR_LAUNCH;
+  return launch_bwd_dq(q, k, v, d_o, lse, delta, m, pattern->row_cnt, pattern->row_idx, pattern->row_order, scale, dq,
+                       rows, st) == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
 }
 
 

@@ -10,63 +10,20 @@
 //   dkdv_kernel   one workgroup per key block, walking the query blocks that selected it.
 // dQ is produced by a second, row-oriented pass instead of atomics: results are
 // deterministic and there is no fp32 dQ scratch tensor.
+#include "row_delta.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
 namespace spa2 {
 
 // ------------------------------------------------------------------ D = rowsum(dO * O)
-struct DeltaArgs {
-  const uint16_t* o; const uint16_t* o_res; const uint16_t* d_o; float* delta;
-  int H, N; int64_t sb, sh, sn;
-};
-
 template <int D>
-__global__ __launch_bounds__(256) void delta_kernel(DeltaArgs a) {
-  constexpr int LPR = D / 8, RP = 256 / LPR;
-  constexpr int NIT = 4;              // row groups per workgroup; all their loads are issued before the first use
-  const int bh = blockIdx.y;
-  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x;
-  const int col = (tid % LPR) * 8;
-  u32x4 x[NIT], y[NIT], z[NIT];
-  int row[NIT];
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    row[it] = (blockIdx.x * NIT + it) * RP + tid / LPR;
-    const int64_t off = base + (int64_t)min(row[it], a.N - 1) * a.sn + col;   // rows past the end: clamped, not stored
-    x[it] = *(const u32x4*)(a.o + off);
-    y[it] = *(const u32x4*)(a.d_o + off);
-    z[it] = u32x4{0, 0, 0, 0};
-  }
-  if (a.o_res) {
-#pragma unroll
-    for (int it = 0; it < NIT; ++it)
-      z[it] = *(const u32x4*)(a.o_res + base + (int64_t)min(row[it], a.N - 1) * a.sn + col);
-  }
-#pragma unroll
-  for (int it = 0; it < NIT; ++it) {
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float o0 = __builtin_bit_cast(float, x[it][e] << 16) + __builtin_bit_cast(float, z[it][e] << 16);
-      const float o1 = __builtin_bit_cast(float, x[it][e] & 0xffff0000u) + __builtin_bit_cast(float, z[it][e] & 0xffff0000u);
-      s = fmaf(o0, __builtin_bit_cast(float, y[it][e] << 16), s);
-      s = fmaf(o1, __builtin_bit_cast(float, y[it][e] & 0xffff0000u), s);
-    }
-#pragma unroll
-    for (int off = LPR / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-    if (row[it] < a.N && (tid % LPR) == 0) a.delta[(int64_t)bh * a.N + row[it]] = s;
-  }
-}
+__global__ __launch_bounds__(256) void delta_kernel(DeltaArgs a) { delta_block<D>(a, blockIdx.y, blockIdx.x); }
 
 hipError_t launch_bwd_delta(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
                             hipStream_t stream) {
-  DeltaArgs a;
-  a.o = (const uint16_t*)o; a.o_res = (const uint16_t*)o_res; a.d_o = (const uint16_t*)d_o; a.delta = delta;
-  a.H = m.H; a.N = m.N; a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
-  const int rows_per_wg = 4 * 256 / (m.d / 8);
-  const dim3 grid((unsigned)((m.N + rows_per_wg - 1) / rows_per_wg), (unsigned)(m.B * m.H)), block(256);
+  const DeltaArgs a = delta_args(o, o_res, d_o, m, delta);
+  const dim3 grid((unsigned)a.chunks, (unsigned)(m.B * m.H)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(delta_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(delta_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();
@@ -83,7 +40,7 @@ struct DqArgs {
   SplitPlan sp;         // long rows cut into parts (split.hip); sp.pool_slots == 0: every row is walked whole
 };
 
-// Partial result of one part of a split row: the fp32 accumulator of every thread of the workgroup.
+// Partial result of one part of a split row: the fp32 accumulators as [pair of registers][thread] (see fwd.hip).
 template <int D> constexpr int dq_slot_floats() { return 256 * (D / 2); }
 size_t dq_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dq_slot_floats<128>() : dq_slot_floats<64>()) * 4; }
 
@@ -123,20 +80,20 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   __shared__ __align__(16) uint16_t smem[2 * (C::K_ELEMS + C::V_ELEMS)];   // stage s: K tile, then V tile
   constexpr int STAGE = C::K_ELEMS + C::V_ELEMS;
 
-  // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the extra parts)
-  int bh, i, part = 0, slot = -1;
+  // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
+  int bh, i, part = 0, parts = 0, part_len = 0;
   if ((int)blockIdx.x < a.sp.pool_slots) {
     if ((int)blockIdx.x >= a.sp.header[0]) return;
-    const int unit = a.sp.part_table[2 * blockIdx.x];
-    part = a.sp.part_table[2 * blockIdx.x + 1];
+    const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
+    const int unit = pt[0];
+    part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
-    slot = a.sp.unit_slot[unit] + part;
   } else {
     const HeadBlock hb = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;
-    if (a.sp.pool_slots) slot = a.sp.unit_slot[(int64_t)bh * a.Tm + i];
+    if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tm + i] >= 0) return;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -144,10 +101,9 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   const int N = a.N;
   int cnt = min(max(a.row_cnt[(int64_t)bh * a.Tm + i], 0), a.Tn);   // clamped: see fwd.hip
   const int32_t* idx = a.row_idx + ((int64_t)bh * a.Tm + i) * a.Tn;
-  if (slot >= 0) {            // entries [part * S, (part + 1) * S) of the list
-    const int S = a.sp.header[1];
-    idx += part * S;
-    cnt = min(cnt - part * S, S);
+  if (parts) {                // entries [part * part_len, (part + 1) * part_len) of the list
+    idx += part * part_len;
+    cnt = min(cnt - part * part_len, part_len);
   }
   const int qrow = i * BQ + w * 32 + r32;
 
@@ -309,61 +265,32 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     __syncthreads();
   }
 
-  if (slot >= 0) {            // one part of a split row: leave the partial sum to the merge kernel
-    f32x4* pa = (f32x4*)(a.sp.pool + (int64_t)slot * a.sp.slot_floats + tid * (D / 2));
+  if (parts) {                // one part of a split row; the last one to arrive adds all of them in part order
+    const int64_t first = blockIdx.x - part;
+    const float* p0 = a.sp.pool + first * a.sp.slot_floats;
+    float* ps = a.sp.pool + (first + part) * a.sp.slot_floats;
 #pragma unroll
     for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        pa[mb * 4 + g] = f32x4{acc[mb][4 * g], acc[mb][4 * g + 1], acc[mb][4 * g + 2], acc[mb][4 * g + 3]};
-    return;
+      for (int g = 0; g < 8; ++g) part_store2(ps + ((mb * 8 + g) * 256 + tid) * 2, acc[mb][2 * g], acc[mb][2 * g + 1]);
+    if (!last_part(a.sp.arrive + first, parts, (int*)smem)) return;
+#pragma unroll
+    for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
+    for (int p = 0; p < parts; ++p) {
+      const float* pp = p0 + (int64_t)p * a.sp.slot_floats;
+      f32x2 x[D / 4];
+#pragma unroll
+      for (int c = 0; c < D / 4; ++c) x[c] = part_load2(pp + (c * 256 + tid) * 2);
+#pragma unroll
+      for (int c = 0; c < D / 4; ++c) {
+        acc[c / 8][2 * (c % 8)] += x[c][0];
+        acc[c / 8][2 * (c % 8) + 1] += x[c][1];
+      }
+    }
   }
   dq_store_rows<D>(a, base, qrow, hf, acc);
-}
-
-// Adds the parts of every split row in part order (fixed order: deterministic).  Same thread -> (row, channel)
-// mapping as dq_kernel; workgroup x takes split row x of the plan.
-template <int D>
-__device__ __forceinline__ void dq_merge_kernel_one(const DqArgs& a, int m_idx) {
-  const int unit = a.sp.merge_table[m_idx];
-  const int bh = unit / a.Tm, i = unit % a.Tm;
-  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int cnt = min(max(a.row_cnt[unit], 0), a.Tn);
-  const int S = a.sp.header[1];
-  const int parts = (cnt + S - 1) / S;
-  const float* p0 = a.sp.pool + (int64_t)a.sp.unit_slot[unit] * a.sp.slot_floats + tid * (D / 2);
-  f32x16 acc[D / 32];
-#pragma unroll
-  for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
-  // two parts per step: the loads of both are in flight together; the order of addition stays part 0, 1, 2, ...
-  for (int p = 0; p < parts; p += 2) {
-    const bool two = p + 1 < parts;
-    const f32x4* pa0 = (const f32x4*)(p0 + (int64_t)p * a.sp.slot_floats);
-    const f32x4* pa1 = (const f32x4*)(p0 + (int64_t)(two ? p + 1 : p) * a.sp.slot_floats);
-    f32x4 x0[D / 8], x1[D / 8];
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) { x0[c] = pa0[c]; x1[c] = pa1[c]; }
-#pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          acc[mb][4 * g + e] += x0[mb * 4 + g][e];
-          if (two) acc[mb][4 * g + e] += x1[mb * 4 + g][e];
-        }
-  }
-  dq_store_rows<D>(a, base, i * BQ + w * 32 + (lane & 31), lane >> 5, acc);
-}
-
-// (one workgroup per split list as a rule; the loop covers a launch with fewer workgroups than lists)
-template <int D>
-__global__ __launch_bounds__(256) void dq_merge_kernel(DqArgs a) {
-  const int n = a.sp.header[2];
-  for (int m_idx = blockIdx.x; m_idx < n; m_idx += gridDim.x) dq_merge_kernel_one<D>(a, m_idx);
 }
 
 hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
@@ -377,18 +304,13 @@ hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale = scale; a.scale_log2 = scale * LOG2E;
   a.sp = plan;
-  if (plan.pool_slots) {
-    const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_MIN_PART, plan, stream);
+  if (plan.pool_slots && !plan.planned) {
+    const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, plan, stream);
     if (e != hipSuccess) return e;
   }
   const dim3 grid((unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(dq_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dq_kernel<64>, grid, block, 0, stream, a);
-  if (plan.pool_slots) {
-    const dim3 mg((unsigned)(plan.pool_slots / 2));
-    if (m.d == 128) hipLaunchKernelGGL(dq_merge_kernel<128>, mg, block, 0, stream, a);
-    else            hipLaunchKernelGGL(dq_merge_kernel<64>, mg, block, 0, stream, a);
-  }
   return hipGetLastError();
 }
 

@@ -29,7 +29,7 @@ struct DkvArgs {
 };
 
 // Partial result of one part of a split column: the fp32 sums of the two waves, dK^T then dV^T, in the order
-// [tensor][finishing wave][output block][group of four registers][lane][register in the group].
+// [tensor][finishing wave][output block][pair of registers][lane][register in the pair].
 template <int D> constexpr int dkdv_slot_floats() { return 2 * 2 * (D / 32) * 16 * 64; }
 size_t dkdv_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dkdv_slot_floats<128>() : dkdv_slot_floats<64>()) * 4; }
 
@@ -75,21 +75,21 @@ void dkdv_kernel(DkvArgs a) {
   constexpr int VL = D == 128 ? DKDV_VL : 0;    // fragment f = kh * NK + kk of V^T is in LDS when f >= 2 NK - VL
   __shared__ __align__(1024) unsigned char vfrag_s[(VL ? VL : 1) * 1024];
 
-  // Which key block, and which part of its list (the first sp.pool_slots workgroups of the launch are the extra
-  // parts of split columns, part >= 1; the others take one key block each: the whole list, or part 0)
-  int bh, j, part = 0, slot = -1;
+  // Which key block, and which part of its list (the first sp.pool_slots workgroups of the launch are the parts of
+  // split columns; the others take one key block each, unless it is split)
+  int bh, j, part = 0, parts = 0, part_len = 0;
   if ((int)blockIdx.x < a.sp.pool_slots) {
     if ((int)blockIdx.x >= a.sp.header[0]) return;
-    const int unit = a.sp.part_table[2 * blockIdx.x];
-    part = a.sp.part_table[2 * blockIdx.x + 1];
+    const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
+    const int unit = pt[0];
+    part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tn; j = unit % a.Tn;
-    slot = a.sp.unit_slot[unit] + part;
   } else {
     const HeadBlock hbk = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tn, a.chunk);
     if (!hbk.valid) return;
     bh = hbk.bh;
     j = a.col_order ? min(max(a.col_order[(int64_t)bh * a.Tn + hbk.blk], 0), a.Tn - 1) : hbk.blk;
-    if (a.sp.pool_slots) slot = a.sp.unit_slot[(int64_t)bh * a.Tn + j];
+    if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tn + j] >= 0) return;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   const int tid = threadIdx.x, lane = tid & 63;
@@ -98,10 +98,9 @@ void dkdv_kernel(DkvArgs a) {
   const int N = a.N;
   int cnt = min(max(a.col_cnt[(int64_t)bh * a.Tn + j], 0), a.Tm);   // clamped: see fwd.hip
   const int32_t* idx = a.col_idx + ((int64_t)bh * a.Tn + j) * a.Tm;
-  if (slot >= 0) {            // entries [part * S, (part + 1) * S) of the list
-    const int S = a.sp.header[1];
-    idx += part * S;
-    cnt = min(cnt - part * S, S);
+  if (parts) {                // entries [part * part_len, (part + 1) * part_len) of the list
+    idx += part * part_len;
+    cnt = min(cnt - part * part_len, part_len);
   }
 
   const int key0 = j * BKV + r32;                    // this lane's key of half 0; half 1 is 32 further
@@ -360,7 +359,7 @@ void dkdv_kernel(DkvArgs a) {
         for (int v = 0; v < 16; ++v)
           mine[((kh * NMB + mb) * 16 + v) * 64] = round == 0 ? dk_acc[kh][mb][v] : dv_acc[kh][mb][v];
     __syncthreads();
-    if (key < N || slot >= 0) {     // (a part writes its whole slot, so that the merge never reads stale sums)
+    if (key < N || parts) {         // (a part writes its whole slot, so that the merge never reads stale sums)
       const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
       const float sc = round == 0 ? a.scale : 1.f;
 #pragma unroll
@@ -374,9 +373,10 @@ void dkdv_kernel(DkvArgs a) {
             const int at = ((w * NMB + mb) * 16 + 4 * g + e) * 64 + lane;
             x[e] = scratch[at] + scratch[REGION + at];
           }
-          if (slot >= 0) {      // one part of a split column: leave the sums to the merge kernel
-            float* ps = a.sp.pool + (int64_t)slot * a.sp.slot_floats + ((((round * 2 + w) * NMB + mb) * 4 + g) * 64 + lane) * 4;
-            *(f32x4*)ps = f32x4{x[0], x[1], x[2], x[3]};
+          if (parts) {          // one part of a split column: leave the sums to the last part
+            float* ps = a.sp.pool + (int64_t)blockIdx.x * a.sp.slot_floats + ((((round * 2 + w) * NMB + mb) * 4 + g) * 128 + lane) * 2;
+            part_store2(ps, x[0], x[1]);
+            part_store2(ps + 128, x[2], x[3]);
             continue;
           }
           u32x2 pk2 = {pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
@@ -386,57 +386,38 @@ void dkdv_kernel(DkvArgs a) {
     }
     __syncthreads();
   }
-}
-
-// Adds the parts of every split column in part order (fixed order: deterministic) and stores dK, dV.  Same thread
-// -> (key, channel) mapping as the end of dkdv_kernel; workgroup x takes split column x of the plan.
-template <int D>
-__device__ __forceinline__ void dkdv_merge_kernel_one(const DkvArgs& a, int m_idx) {
-  constexpr int NMB = D / 32;
-  const int unit = a.sp.merge_table[m_idx];
-  const int bh = unit / a.Tn, j = unit % a.Tn;
-  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, r32 = lane & 31, hf = lane >> 5;
-  const int cnt = min(max(a.col_cnt[unit], 0), a.Tm);
-  const int S = a.sp.header[1];
-  const int parts = (cnt + S - 1) / S;
-  const float* p0 = a.sp.pool + (int64_t)a.sp.unit_slot[unit] * a.sp.slot_floats;
-  const int key = j * BKV + r32 + 32 * w;
-  if (key >= a.N) return;
-  const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
-  // all sums of this thread at once, part after part (the 16-byte loads of one part are in flight together)
-  f32x4 x[2 * NMB * 4];
+  // the last part of a split column to arrive adds all of them in part order
+  if (parts) {
+    const int64_t first = blockIdx.x - part;
+    if (!last_part(a.sp.arrive + first, parts, (int*)smem) || key >= N) return;
+    const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
+    const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * lane;
 #pragma unroll
-  for (int c = 0; c < 2 * NMB * 4; ++c) x[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int p = 0; p < parts; ++p) {
-    const f32x4* ps = (const f32x4*)(p0 + (int64_t)p * a.sp.slot_floats) + lane;
+    for (int round = 0; round < 2; ++round) {
+      f32x2 x[NMB * 8];
 #pragma unroll
-    for (int round = 0; round < 2; ++round)
+      for (int c = 0; c < NMB * 8; ++c) x[c] = f32x2{0.f, 0.f};
+      for (int p = 0; p < parts; ++p) {
+        const float* ps = p0 + (int64_t)p * a.sp.slot_floats + (round * 2 + w) * NMB * 8 * 128;
+        f32x2 y[NMB * 8];
 #pragma unroll
-      for (int c = 0; c < NMB * 4; ++c)
-        x[round * NMB * 4 + c] += ps[((round * 2 + w) * NMB * 4 + c) * 64];
-  }
+        for (int c = 0; c < NMB * 8; ++c) y[c] = part_load2(ps + c * 128);
 #pragma unroll
-  for (int round = 0; round < 2; ++round) {
-    const float sc = round == 0 ? a.scale : 1.f;
+        for (int c = 0; c < NMB * 8; ++c) { x[c][0] += y[c][0]; x[c][1] += y[c][1]; }
+      }
+      const float sc = round == 0 ? a.scale : 1.f;
 #pragma unroll
-    for (int mb = 0; mb < NMB; ++mb) {
-      uint16_t* out = (round == 0 ? a.dk : a.dv) + out_off + 32 * mb;
+      for (int mb = 0; mb < NMB; ++mb) {
+        uint16_t* out = (round == 0 ? a.dk : a.dv) + out_off + 32 * mb;
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const f32x4 y = x[round * NMB * 4 + mb * 4 + g];
-        u32x2 pk2 = {pack_bf16(y[0] * sc, y[1] * sc), pack_bf16(y[2] * sc, y[3] * sc)};
-        *(u32x2*)(out + 8 * g) = pk2;
+        for (int g = 0; g < 4; ++g) {
+          const f32x2 lo = x[mb * 8 + 2 * g], hi = x[mb * 8 + 2 * g + 1];
+          u32x2 pk2 = {pack_bf16(lo[0] * sc, lo[1] * sc), pack_bf16(hi[0] * sc, hi[1] * sc)};
+          *(u32x2*)(out + 8 * g) = pk2;
+        }
       }
     }
   }
-}
-
-// (one workgroup per split list as a rule; the loop covers a launch with fewer workgroups than lists)
-template <int D>
-__global__ __launch_bounds__(128) void dkdv_merge_kernel(DkvArgs a) {
-  const int n = a.sp.header[2];
-  for (int m_idx = blockIdx.x; m_idx < n; m_idx += gridDim.x) dkdv_merge_kernel_one<D>(a, m_idx);
 }
 
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
@@ -451,18 +432,13 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale = scale; a.scale_log2 = scale * LOG2E;
   a.sp = plan;
-  if (plan.pool_slots) {
-    const hipError_t e = launch_split_plan(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_MIN_PART / 2, plan, stream);
+  if (plan.pool_slots && !plan.planned) {
+    const hipError_t e = launch_split_plan(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, plan, stream);
     if (e != hipSuccess) return e;
   }
   const dim3 grid((unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(128);
   if (m.d == 128) hipLaunchKernelGGL(dkdv_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dkdv_kernel<64>, grid, block, 0, stream, a);
-  if (plan.pool_slots) {
-    const dim3 mg((unsigned)(plan.pool_slots / 2));
-    if (m.d == 128) hipLaunchKernelGGL(dkdv_merge_kernel<128>, mg, block, 0, stream, a);
-    else            hipLaunchKernelGGL(dkdv_merge_kernel<64>, mg, block, 0, stream, a);
-  }
   return hipGetLastError();
 }
 

@@ -27,8 +27,9 @@ struct FwdArgs {
   SplitPlan sp;         // long rows cut into parts (split.hip); sp.pool_slots == 0: every row is walked whole
 };
 
-// Partial result of one part of a split row, per thread of the workgroup: the unnormalised accumulator, then
-// the running maximum (log2 units) and the row sum, both already combined over the two halves of the wave.
+// Partial result of one part of a split row: the unnormalised accumulator as [pair of accumulator registers][thread],
+// so that the 64 lanes of a wave write and read consecutive 8-byte pieces, then per thread the running maximum (log2
+// units) and the row sum, both already combined over the two halves of the wave.
 template <int D> constexpr int fwd_slot_floats() { return 256 * (D / 2) + 512; }
 size_t fwd_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? fwd_slot_floats<128>() : fwd_slot_floats<64>()) * 4; }
 
@@ -77,22 +78,22 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   __shared__ __align__(16) uint16_t Ks[2 * C::K_ELEMS];
   __shared__ __align__(16) uint16_t Vs[2 * C::V_ELEMS];
 
-  // Which row, and which part of its list.  The first sp.pool_slots workgroups of the launch are the extra parts of
-  // split rows (part >= 1); the others take one row each: the whole list, or part 0 if the row is split.
-  int bh, i, part = 0, slot = -1;
+  // Which row, and which part of its list.  The first sp.pool_slots workgroups of the launch are the parts of split
+  // rows; the others take one row each, unless it is split.
+  int bh, i, part = 0, parts = 0, part_len = 0;
   if ((int)blockIdx.x < a.sp.pool_slots) {
     if ((int)blockIdx.x >= a.sp.header[0]) return;
-    const int unit = a.sp.part_table[2 * blockIdx.x];
-    part = a.sp.part_table[2 * blockIdx.x + 1];
+    const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
+    const int unit = pt[0];
+    part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
-    slot = a.sp.unit_slot[unit] + part;
   } else {
     const HeadBlock hb = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     // optional launch order: position hb.blk of this head's schedule -> query block (clamped: caller data)
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;
-    if (a.sp.pool_slots) slot = a.sp.unit_slot[(int64_t)bh * a.Tm + i];
+    if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tm + i] >= 0) return;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -102,10 +103,9 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   // address memory outside the tensors
   int cnt = min(max(a.row_cnt[(int64_t)bh * a.Tm + i], 0), a.Tn);
   const int32_t* idx = a.row_idx + ((int64_t)bh * a.Tm + i) * a.Tn;
-  if (slot >= 0) {            // entries [part * S, (part + 1) * S) of the list (never empty: part < ceil(cnt / S))
-    const int S = a.sp.header[1];
-    idx += part * S;
-    cnt = min(cnt - part * S, S);
+  if (parts) {                // entries [part * part_len, (part + 1) * part_len) of the list (never empty)
+    idx += part * part_len;
+    cnt = min(cnt - part * part_len, part_len);
   }
   const int qrow = i * BQ + w * 32 + r32;
 
@@ -347,79 +347,48 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   }
 
   const float l_tot = sum_halves(l_run);
-  if (slot >= 0) {            // one part of a split row: leave the partial result to the merge kernel
-    float* ps = a.sp.pool + (int64_t)slot * a.sp.slot_floats;
-    f32x4* pa = (f32x4*)(ps + tid * (D / 2));
+  if (parts) {                // one part of a split row
+    const int64_t first = blockIdx.x - part;
+    float* ps = a.sp.pool + (first + part) * a.sp.slot_floats;
 #pragma unroll
     for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        pa[mb * 4 + g] = f32x4{oacc[mb][4 * g], oacc[mb][4 * g + 1], oacc[mb][4 * g + 2], oacc[mb][4 * g + 3]};
-    ps[256 * (D / 2) + tid] = m_run;
-    ps[256 * (D / 2) + 256 + tid] = l_tot;
+      for (int g = 0; g < 8; ++g) part_store2(ps + ((mb * 8 + g) * 256 + tid) * 2, oacc[mb][2 * g], oacc[mb][2 * g + 1]);
+    part_store2(ps + 256 * (D / 2) + 2 * tid, m_run, l_tot);
+    if (!last_part(a.sp.arrive + first, parts, (int*)Ks)) return;
+    // The last part to arrive combines all of them, in part order (so the result does not depend on which one that
+    // is): m = max m_p, l = sum l_p 2^(m_p - m), O = sum O_p 2^(m_p - m) / l.
+    const float* p0 = a.sp.pool + first * a.sp.slot_floats;
+    float m = -INFINITY, l = 0.f;
+    for (int p = 0; p < parts; p += 4) {       // four loads in flight per step
+      float mp[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) mp[x] = part_load2(p0 + (int64_t)min(p + x, parts - 1) * a.sp.slot_floats + 256 * (D / 2) + 2 * tid)[0];
+      m = fmaxf(fmaxf(m, fmaxf(mp[0], mp[1])), fmaxf(mp[2], mp[3]));
+    }
+#pragma unroll
+    for (int mb = 0; mb < D / 32; ++mb)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) oacc[mb][v] = 0.f;
+    for (int p = 0; p < parts; ++p) {
+      const float* pp = p0 + (int64_t)p * a.sp.slot_floats;
+      f32x2 x[D / 4];
+#pragma unroll
+      for (int c = 0; c < D / 4; ++c) x[c] = part_load2(pp + (c * 256 + tid) * 2);
+      const f32x2 ml = part_load2(pp + 256 * (D / 2) + 2 * tid);
+      const float sc = fast_exp2(ml[0] - m);
+      l = fmaf(ml[1], sc, l);
+#pragma unroll
+      for (int c = 0; c < D / 4; ++c) {
+        oacc[c / 8][2 * (c % 8)] = fmaf(x[c][0], sc, oacc[c / 8][2 * (c % 8)]);
+        oacc[c / 8][2 * (c % 8) + 1] = fmaf(x[c][1], sc, oacc[c / 8][2 * (c % 8) + 1]);
+      }
+    }
+    fwd_store_rows<D>(a, bh, base, qrow, hf, oacc, m, l);
     return;
   }
   // O_i = diag(l)^-1 O (step 18) and the log-sum-exp the backward pass needs
   fwd_store_rows<D>(a, bh, base, qrow, hf, oacc, m_run, l_tot);
-}
-
-// Combines the parts of every split row, in part order (so the result does not depend on which part finished
-// first): m = max m_p, l = sum l_p 2^(m_p - m), O = sum O_p 2^(m_p - m) / l.  Same thread -> (row, channel) mapping
-// as fwd_kernel.  Workgroup x takes split row x of the plan; there are at most pool_slots / 2 of them.
-template <int D>
-__device__ __forceinline__ void fwd_merge_kernel_one(const FwdArgs& a, int m_idx) {
-  const int unit = a.sp.merge_table[m_idx];
-  const int bh = unit / a.Tm, i = unit % a.Tm;
-  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int r32 = lane & 31, hf = lane >> 5;
-  const int cnt = min(max(a.row_cnt[unit], 0), a.Tn);
-  const int S = a.sp.header[1];
-  const int parts = (cnt + S - 1) / S;
-  const float* p0 = a.sp.pool + (int64_t)a.sp.unit_slot[unit] * a.sp.slot_floats;
-  float m = -INFINITY;
-  for (int p = 0; p < parts; p += 4) {       // four loads in flight per step
-    float mp[4];
-#pragma unroll
-    for (int x = 0; x < 4; ++x) mp[x] = p0[(int64_t)min(p + x, parts - 1) * a.sp.slot_floats + 256 * (D / 2) + tid];
-    m = fmaxf(fmaxf(m, fmaxf(mp[0], mp[1])), fmaxf(mp[2], mp[3]));
-  }
-  f32x16 oacc[D / 32];
-#pragma unroll
-  for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) oacc[mb][v] = 0.f;
-  float l = 0.f;
-  // two parts per step: the loads of both are in flight together (the chain of parts is what takes the time)
-  for (int p = 0; p < parts; p += 2) {
-    const bool two = p + 1 < parts;
-    const float* ps0 = p0 + (int64_t)p * a.sp.slot_floats;
-    const float* ps1 = p0 + (int64_t)(two ? p + 1 : p) * a.sp.slot_floats;
-    const float sc0 = fast_exp2(ps0[256 * (D / 2) + tid] - m);
-    const float sc1 = two ? fast_exp2(ps1[256 * (D / 2) + tid] - m) : 0.f;
-    l = fmaf(ps0[256 * (D / 2) + 256 + tid], sc0, l);
-    l = fmaf(ps1[256 * (D / 2) + 256 + tid], sc1, l);
-    const f32x4* pa0 = (const f32x4*)(ps0 + tid * (D / 2));
-    const f32x4* pa1 = (const f32x4*)(ps1 + tid * (D / 2));
-    f32x4 x0[D / 8], x1[D / 8];
-#pragma unroll
-    for (int c = 0; c < D / 8; ++c) { x0[c] = pa0[c]; x1[c] = pa1[c]; }
-#pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
-#pragma unroll
-      for (int g = 0; g < 4; ++g)
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          oacc[mb][4 * g + e] = fmaf(x1[mb * 4 + g][e], sc1, fmaf(x0[mb * 4 + g][e], sc0, oacc[mb][4 * g + e]));
-  }
-  fwd_store_rows<D>(a, bh, base, i * BQ + w * 32 + r32, hf, oacc, m, l);
-}
-
-// (one workgroup per split list as a rule; the loop covers a launch with fewer workgroups than lists)
-template <int D>
-__global__ __launch_bounds__(256) void fwd_merge_kernel(FwdArgs a) {
-  const int n = a.sp.header[2];
-  for (int m_idx = blockIdx.x; m_idx < n; m_idx += gridDim.x) fwd_merge_kernel_one<D>(a, m_idx);
 }
 
 hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m, const int32_t* row_cnt,
@@ -434,18 +403,13 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale_log2 = scale * LOG2E;
   a.sp = plan;
-  if (plan.pool_slots) {
-    const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_MIN_PART, plan, stream);
+  if (plan.pool_slots && !plan.planned) {
+    const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_FWD, plan, stream);
     if (e != hipSuccess) return e;
   }
   const dim3 grid((unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(fwd_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(fwd_kernel<64>, grid, block, 0, stream, a);
-  if (plan.pool_slots) {
-    const dim3 mg((unsigned)(plan.pool_slots / 2));
-    if (m.d == 128) hipLaunchKernelGGL(fwd_merge_kernel<128>, mg, block, 0, stream, a);
-    else            hipLaunchKernelGGL(fwd_merge_kernel<64>, mg, block, 0, stream, a);
-  }
   return hipGetLastError();
 }
 

@@ -25,20 +25,26 @@ inline Dims make_dims(const spa2_shape& s) {
 // Splitting of long rows / columns over several workgroups (split.hip).  All pointers lie in the caller's
 // workspace; pool_slots == 0 means "no splitting" and every other member is then null.
 constexpr int SPLIT_POOL_MAX = 2048;         // partial-result slots of one launch at most
-constexpr int SPLIT_MIN_PART = 16;           // a part has at least this many list entries
 struct SplitPlan {
-  const int32_t* header;       // [0] number of extra parts, [1] S = list entries per part, [2] number of split units
+  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
-  const int32_t* part_table;   // [pool_slots][2] (unit, part >= 1) of extra part g
-  const int32_t* merge_table;  // [pool_slots] unit of split unit m
+  const int32_t* part_table;   // [pool_slots][4] (unit, part, parts of the unit, list entries per part) of pool slot g
+  int32_t* arrive;             // [pool_slots] parts of the unit that have left their result, at its first slot
   float* pool;                 // [pool_slots][slot_floats] fp32 partial results
   int pool_slots;
   int slot_floats;
+  bool planned;                // the tables have been written already (launch_bwd_prepare): no plan launch of its own
 };
-size_t split_ws_bytes(int64_t units, size_t slot_bytes);
-SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, size_t slot_bytes);
-hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int cnt_max, int min_part, const SplitPlan& p,
+size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes);
+SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes);
+// Plan of the launch of kernel `kind`, which walks `units` lists of at most list_max entries.
+enum SplitKind { SPLIT_FWD, SPLIT_DQ, SPLIT_DKDV };
+hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p,
                              hipStream_t stream);
+// D = rowsum(dO * O) and the plans of the two backward kernels in one launch (split.hip).
+hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
+                              const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
+                              const SplitPlan& col_plan, hipStream_t stream);
 
 // Each launcher enqueues its kernels on `stream` and returns hipGetLastError().
 hipError_t launch_pool(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, hipStream_t stream);

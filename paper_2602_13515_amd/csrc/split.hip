@@ -2,15 +2,26 @@
 //
 // One workgroup walks one row of the pattern in the forward and dQ kernels (one column in the dK/dV kernel), so a
 // launch cannot finish before its longest row has.  On a layer with few rows per workgroup slot the longest rows
-// (Top-p-bound rows are ten times the Top-k length) then set the time.  This plan cuts every list longer than S
-// entries into parts of S entries.  Part 0 stays with the row's own workgroup, parts >= 1 are given to extra
-// workgroups at the front of the same launch; every part leaves an fp32 partial result in a pool slot and a small
-// merge kernel combines the parts of a row in part order, so results do not depend on the order of execution.
+// (Top-p-bound rows are ten times the Top-k length) then set the time, and on a small layer there are fewer rows than
+// compute units.  This plan cuts every list longer than S entries into equal parts of at most S entries.  The parts
+// are workgroups of their own at the front of the same launch; every part leaves an fp32 partial result in a pool slot
+// and counts itself in, and the part that arrives last adds up all of them in part order, so results do not depend on
+// the order of execution.
 //
 // The plan is computed on the device from the list lengths (the host never reads the pattern):
-//   T = total number of list entries of the launch,  S = max(min_part, ceil(T / 2048)),
-// i.e. a part is at most a quarter of the mean work of one of the 512 workgroup slots; on large launches S exceeds
-// every list and nothing is split.  Split units are taken in unit order for as long as pool slots last.
+//   T = total number of list entries of the launch,
+//   S = max(min(max(T / 512, lo), mid), min(T / 2048, 48), T / 8192)   (quotients rounded up),
+// with 512 the number of workgroups that run at a time (two per compute unit).  Small launches are cut until the slots
+// are filled, down to lo entries, below which a part is mostly prologue and merge; ordinary ones into quarters of the
+// mean work of a slot, but not below mid (parts of 8 instead of 16 cost more than they balance) nor above 48; on the
+// largest only lists of more than a sixteenth of a slot's mean work are cut, which the natural launch order would
+// otherwise start anywhere up to the end of the launch.
+// Measured (us, forward / dQ / dK,dV; before = parts of T / 2048 with part 0 in its row's place and merge kernels):
+//   75,600 tokens, 40 heads (T = 1.6 M):  8059 / 11248 / 14926 before, 7600 / 10610 / 14655 now
+//   32,760 tokens, 12 heads (T = 91 k):    474 /   615 /   936 before,  445 /   595 /   928 now
+//   20,010 tokens, 6 heads, d = 64:         99 /   109 /   184 before,   76 /    93 /   165 now
+//   32,760 tokens, 3 heads, every tile:   2267 before, 1663 now
+#include "row_delta.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
@@ -20,140 +31,201 @@ namespace {
 inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 }
 
+constexpr int SPLIT_CAP = 48;
+// lo and mid of the rule above.  An entry of a column is twice the work of one of a row.  Measured on 264 rows of 7
+// entries (dQ) and 504 columns of 3 to 9: lo = 8 / 4 takes 38 / 61 us, lo = 4 / 2 59 / 61 us, lo = 16 / 8 38 / 64 us;
+// on 32 rows of 29 and 64 columns of 14 (d = 64) 28 / 33, 28 / 36 and 34 / 41 us.  The forward kernel cuts that finely
+// only where most compute units would have no row at all: its parts round P against their own running maxima, and a
+// row of few tiles then shows the other rounding.
+static void split_range(SplitKind kind, int64_t units, int& lo, int& mid) {
+  if (kind == SPLIT_DKDV) { lo = 4; mid = 12; return; }
+  mid = 16;
+  lo = kind == SPLIT_DQ || units <= 128 ? 8 : 16;
+}
+
 // Pool sizes are powers of two from 8 to SPLIT_POOL_MAX (a multiple of 8 keeps the workgroup -> XCD phase of the
-// launch that the extra parts are put in front of).
-static int64_t pool_wanted(int64_t units) {
+// launch that the parts are put in front of): room for every list to be cut into 16 parts, or as many as it has pairs
+// of entries.
+static int64_t pool_wanted(int64_t units, int list_max) {
+  const int64_t per_unit = list_max / 2 < 1 ? 1 : (list_max / 2 > 16 ? 16 : list_max / 2);
   int64_t pool = 8;
-  while (pool < SPLIT_POOL_MAX && pool < 4 * units) pool *= 2;
+  while (pool < SPLIT_POOL_MAX && pool < per_unit * units) pool *= 2;
   return pool;
 }
 
-int split_pool_slots(int64_t units, size_t slot_bytes, size_t ws_bytes) {
-  // shrink the pool if the caller gave less than the full workspace
-  for (int64_t pool = pool_wanted(units); pool >= 8; pool /= 2) {
-    const size_t need = 256 + up256((size_t)units * 4) + up256((size_t)pool * 8) + up256((size_t)pool * 4) +
-                        (size_t)pool * slot_bytes;
-    if (need <= ws_bytes) return (int)pool;
-  }
-  return 0;
+static size_t tables_bytes(int64_t units, int64_t pool) {
+  return 256 + up256((size_t)units * 4) + up256((size_t)pool * 16) + up256((size_t)pool * 4);
 }
 
-size_t split_ws_bytes(int64_t units, size_t slot_bytes) {
-  const int64_t pool = pool_wanted(units);
-  return 256 + up256((size_t)units * 4) + up256((size_t)pool * 8) + up256((size_t)pool * 4) + (size_t)pool * slot_bytes;
+size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes) {
+  const int64_t pool = pool_wanted(units, list_max);
+  return tables_bytes(units, pool) + (size_t)pool * slot_bytes;
 }
 
-SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, size_t slot_bytes) {
+SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes) {
   SplitPlan p;
-  p.pool_slots = ws ? split_pool_slots(units, slot_bytes, ws_bytes) : 0;
-  if (p.pool_slots == 0) { p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.merge_table = nullptr; p.pool = nullptr; p.slot_floats = 0; return p; }
+  p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
+  p.pool_slots = 0; p.slot_floats = 0; p.planned = false;
+  if (!ws) return p;
+  // the pool shrinks if the caller gave less than the full workspace
+  int64_t pool = pool_wanted(units, list_max);
+  while (pool >= 8 && tables_bytes(units, pool) + (size_t)pool * slot_bytes > ws_bytes) pool /= 2;
+  if (pool < 8) return p;
   char* c = (char*)ws;
+  p.pool_slots = (int)pool;
   p.header = (int32_t*)c;                 c += 256;
   p.unit_slot = (int32_t*)c;              c += up256((size_t)units * 4);
-  p.part_table = (int32_t*)c;             c += up256((size_t)p.pool_slots * 8);
-  p.merge_table = (int32_t*)c;            c += up256((size_t)p.pool_slots * 4);
+  p.part_table = (int32_t*)c;             c += up256((size_t)pool * 16);
+  p.arrive = (int32_t*)c;                 c += up256((size_t)pool * 4);
   p.pool = (float*)c;
   p.slot_floats = (int)(slot_bytes / 4);
   return p;
 }
 
-// One workgroup of 1024 threads walks the units 1024 at a time (coalesced loads): first the total T, then, tile by
-// tile, an exclusive prefix sum over the units of (pool slots, extra parts, split units), carried from tile to tile.
-__device__ __forceinline__ int wave_incl_scan(int x, int lane) {
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int y = __shfl_up(x, off, 64);
-    if (lane >= off) x += y;
-  }
-  return x;
+// What one plan reads and writes.
+struct PlanArgs {
+  const int32_t* cnt;
+  int units, list_max, lo, mid, pool;
+  int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive;
+};
+
+static PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p) {
+  PlanArgs a;
+  a.cnt = cnt; a.units = (int)units; a.list_max = list_max;
+  split_range(kind, units, a.lo, a.mid);
+  a.pool = p.pool_slots;
+  a.header = (int32_t*)p.header; a.unit_slot = (int32_t*)p.unit_slot; a.part_table = (int32_t*)p.part_table;
+  a.arrive = p.arrive;
+  return a;
 }
 
-__global__ __launch_bounds__(1024) void split_plan_kernel(const int32_t* cnt, int units, int cnt_max, int pool,
-                                                          int min_part, int32_t* header, int32_t* unit_slot,
-                                                          int32_t* part_table, int32_t* merge_table) {
-  constexpr int UPT = 8;                                   // consecutive units per thread and tile (two 16-byte loads)
-  __shared__ unsigned long long tot_s[16];
-  __shared__ int wsum[3][16];
-  __shared__ int n_extra_s, n_split_s;
-  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-  if (t == 0) { n_extra_s = 0; n_split_s = 0; }
-  const bool vec_ok = ((uintptr_t)cnt & 15) == 0;
-  auto load4 = [&](int u, int (&c)[UPT]) {                 // lengths of units u .. u+UPT-1 (0 past the end), clamped
-    if (vec_ok && u + UPT <= units) {
-      typedef __attribute__((ext_vector_type(4))) int i32x4;
-      const i32x4 a = *(const i32x4*)(cnt + u), b = *(const i32x4*)(cnt + u + 4);
+typedef __attribute__((ext_vector_type(4))) int i32x4;
+
+template <int NT>
+__device__ __forceinline__ unsigned long long block_sum(unsigned long long x, unsigned long long* red) {
 #pragma unroll
-      for (int x = 0; x < 4; ++x) { c[x] = min(max(a[x], 0), cnt_max); c[4 + x] = min(max(b[x], 0), cnt_max); }
-    } else {
+  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
+  __syncthreads();                                   // (the previous sum has been read)
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  unsigned long long t = 0;
 #pragma unroll
-      for (int x = 0; x < UPT; ++x) c[x] = u + x < units ? min(max(cnt[u + x], 0), cnt_max) : 0;
+  for (int i = 0; i < NT / 64; ++i) t += red[i];
+  return t;
+}
+
+// One workgroup of NT threads makes one plan: sum of the lengths (fixes S), number of parts at S (S grows until they
+// fit the pool), then every split unit takes its slots with an LDS atomic.  Which slots a unit gets depends on that
+// race; which units are split, and into what parts, does not, and the slot is only where a partial result lies.
+// Latency-bound: three passes over the lengths (4 bytes a unit, from L2).
+template <int NT>
+__device__ __forceinline__ void plan_block(const PlanArgs& a) {
+  __shared__ unsigned long long red[NT / 64];
+  __shared__ int next_slot, next_item;
+  __shared__ uint16_t owner[SPLIT_POOL_MAX];         // slot -> entry of the list of split units
+  __shared__ i32x4 item[SPLIT_POOL_MAX / 2];         // (unit, first slot, parts, entries per part) of a split unit
+  const int t = threadIdx.x;
+  if (t == 0) { next_slot = 0; next_item = 0; }
+  const bool vec_ok = ((uintptr_t)a.cnt & 15) == 0;
+  auto load4 = [&](int u) -> i32x4 {                 // lengths of units u .. u+3 (0 past the end), clamped
+    i32x4 c = {0, 0, 0, 0};
+    if (vec_ok && u + 4 <= a.units) c = *(const i32x4*)(a.cnt + u);
+    else {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) if (u + x < a.units) c[x] = a.cnt[u + x];
     }
+#pragma unroll
+    for (int x = 0; x < 4; ++x) c[x] = min(max(c[x], 0), a.list_max);
+    return c;
   };
   unsigned long long mine = 0;
-  for (int u = UPT * t; u < units; u += UPT * 1024) {
-    int c[UPT]; load4(u, c);
-#pragma unroll
-    for (int x = 0; x < UPT; ++x) mine += (unsigned long long)c[x];
+#pragma unroll 4
+  for (int u = 4 * t; u < a.units; u += 4 * NT) {
+    const i32x4 c = load4(u);
+    mine += (unsigned long long)c[0] + c[1] + c[2] + c[3];
   }
+  const long long T = (long long)block_sum<NT>(mine, red);
+  const long long s_small = min(max((T + 511) / 512, (long long)a.lo), (long long)a.mid);
+  const long long s_large = max(min((T + 2047) / 2048, (long long)SPLIT_CAP), (T + 8191) / 8192);
+  int S = (int)max(min(max(s_small, s_large), (long long)a.list_max), 1ll);
+  for (;;) {
+    unsigned long long parts = 0;
+#pragma unroll 4
+    for (int u = 4 * t; u < a.units; u += 4 * NT) {
+      const i32x4 c = load4(u);
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
-  if (lane == 0) tot_s[wv] = mine;
-  __syncthreads();
-  long long T = 0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) T += (long long)tot_s[i];
-  const int S = (int)max((long long)min_part, (T + 2047) / 2048);
-
-  int base_slot = 0, base_extra = 0, base_split = 0;     // running totals of the tiles before this one
-  for (int u0 = 0; u0 < units; u0 += UPT * 1024) {
-    const int u = u0 + UPT * t;
-    int c[UPT], parts[UPT]; load4(u, c);
-    int v0 = 0, v1 = 0, v2 = 0;
-#pragma unroll
-    for (int x = 0; x < UPT; ++x) {
-      parts[x] = c[x] > S ? (c[x] + S - 1) / S : 0;
-      v0 += parts[x]; v1 += parts[x] ? parts[x] - 1 : 0; v2 += parts[x] ? 1 : 0;
+      for (int x = 0; x < 4; ++x) parts += c[x] > S ? (c[x] + S - 1) / S : 0;
     }
-    const int i0 = wave_incl_scan(v0, lane), i1 = wave_incl_scan(v1, lane), i2 = wave_incl_scan(v2, lane);
-    __syncthreads();                                     // (the sums of the previous tile have been read)
-    if (lane == 63) { wsum[0][wv] = i0; wsum[1][wv] = i1; wsum[2][wv] = i2; }
-    __syncthreads();
-    int p0 = 0, p1 = 0, p2 = 0, t0 = 0, t1 = 0, t2 = 0;
+    if (block_sum<NT>(parts, red) <= (unsigned long long)a.pool) break;
+    S += S / 4 + 1;                                  // (ends: no list is longer than list_max)
+  }
+#pragma unroll 2
+  for (int u = 4 * t; u < a.units; u += 4 * NT) {
+    const i32x4 c = load4(u);
+    i32x4 slot;
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      if (i < wv) { p0 += wsum[0][i]; p1 += wsum[1][i]; p2 += wsum[2][i]; }
-      t0 += wsum[0][i]; t1 += wsum[1][i]; t2 += wsum[2][i];
-    }
-    int slot = base_slot + p0 + i0 - v0, ex = base_extra + p1 + i1 - v1, ns = base_split + p2 + i2 - v2;
-#pragma unroll
-    for (int x = 0; x < UPT; ++x) {
-      if (u + x >= units) break;
-      int s = -1;
-      if (parts[x]) {
-        if (slot + parts[x] <= pool) {   // (slot only grows: the accepted units are a prefix of the split ones)
-          s = slot;
-          for (int p = 1; p < parts[x]; ++p) { part_table[2 * (ex + p - 1)] = u + x; part_table[2 * (ex + p - 1) + 1] = p; }
-          merge_table[ns] = u + x;
-          // the last accepted unit fixes the counts: every accepted unit reports, the largest values win
-          atomicMax(&n_extra_s, ex + parts[x] - 1);
-          atomicMax(&n_split_s, ns + 1);
-        }
-        slot += parts[x]; ex += parts[x] - 1; ++ns;
+    for (int x = 0; x < 4; ++x) {
+      slot[x] = -1;
+      if (c[x] > S) {
+        const int parts = (c[x] + S - 1) / S;
+        slot[x] = atomicAdd(&next_slot, parts);
+        const int m = atomicAdd(&next_item, 1);
+        item[m] = i32x4{u + x, slot[x], parts, (c[x] + parts - 1) / parts};
+        for (int p = 0; p < parts; ++p) owner[slot[x] + p] = (uint16_t)m;
       }
-      unit_slot[u + x] = s;
     }
-    base_slot += t0; base_extra += t1; base_split += t2;
+    if (u + 4 <= a.units) *(i32x4*)(a.unit_slot + u) = slot;
+    else {
+#pragma unroll
+      for (int x = 0; x < 4; ++x) if (u + x < a.units) a.unit_slot[u + x] = slot[x];
+    }
   }
   __syncthreads();
-  if (t == 0) { header[0] = n_extra_s; header[1] = S; header[2] = n_split_s; }
+  const int n = next_slot;
+  for (int g = t; g < n; g += NT) {
+    const i32x4 it = item[owner[g]];
+    *(i32x4*)(a.part_table + 4 * g) = i32x4{it[0], g - it[1], it[2], it[3]};
+    a.arrive[g] = 0;
+  }
+  if (t == 0) { a.header[0] = n; a.header[1] = S; }
 }
 
-hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int cnt_max, int min_part, const SplitPlan& p,
+__global__ __launch_bounds__(1024) void split_plan_kernel(PlanArgs a) { plan_block<1024>(a); }
+
+hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p,
                              hipStream_t stream) {
   if (p.pool_slots == 0) return hipSuccess;
-  hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, stream, cnt, (int)units, cnt_max, p.pool_slots,
-                     min_part, (int32_t*)p.header, (int32_t*)p.unit_slot, (int32_t*)p.part_table,
-                     (int32_t*)p.merge_table);
+  hipLaunchKernelGGL(split_plan_kernel, dim3(1), dim3(1024), 0, stream, plan_args(cnt, units, list_max, kind, p));
+  return hipGetLastError();
+}
+
+// The pass over O and dO with the two plans of the backward kernels in front of it (workgroups 0 .. n_plans-1): the
+// plans, one workgroup each, then cost no time of their own (two launches of 8 to 27 us before) wherever the pass
+// takes longer than they do.
+struct PrepareArgs { DeltaArgs d; PlanArgs plan[2]; int n_plans; };
+
+template <int D>
+__global__ __launch_bounds__(256) void bwd_prepare_kernel(PrepareArgs a) {
+  if ((int)blockIdx.x < a.n_plans) {
+    plan_block<256>(a.plan[blockIdx.x]);
+    return;
+  }
+  const int w = blockIdx.x - a.n_plans;
+  delta_block<D>(a.d, w / a.d.chunks, w % a.d.chunks);
+}
+
+hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
+                              const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
+                              const SplitPlan& col_plan, hipStream_t stream) {
+  PrepareArgs a;
+  a.d = delta_args(o, o_res, d_o, m, delta);
+  a.n_plans = 0;
+  if (col_plan.pool_slots) a.plan[a.n_plans++] = plan_args(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, col_plan);
+  if (row_plan.pool_slots) a.plan[a.n_plans++] = plan_args(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, row_plan);
+  for (int x = a.n_plans; x < 2; ++x) a.plan[x] = PlanArgs{};
+  const dim3 grid((unsigned)(a.n_plans + m.B * m.H * a.d.chunks)), block(256);
+  if (m.d == 128) hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, block, 0, stream, a);
+  else            hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();
 }
 

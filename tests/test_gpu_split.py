@@ -1,0 +1,73 @@
+"""Lists around the part length of the split plan: one entry, exactly one part, one entry more, last parts of one entry,
+the whole range; with the full workspace, with one whose pool is too small for the first choice of part length, and
+with none.  Each against the fp64 oracle, twice for the same bits."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2602_13515_amd as spa2
+from oracle import spa2_oracle as orc
+from paper_2602_13515_amd import workloads as wl
+
+from gpu_util import assert_close, dev, f64, pattern_from_mask
+
+pytestmark = pytest.mark.gpu
+
+
+def _mask(H, Tm, Tn):
+    """Row i of head h keeps lengths[(i + h) % len] blocks spread over the row; block 0 in every row (one long column)."""
+    lengths = [1, 2, 7, 8, 9, 15, 16, 17, 25, Tn]
+    m = np.zeros((1, H, Tm, Tn), np.uint8)
+    rng = np.random.default_rng(3)
+    for h in range(H):
+        for i in range(Tm):
+            n = min(lengths[(i + h) % len(lengths)], Tn)
+            m[0, h, i, 0] = 1
+            m[0, h, i, 1 + rng.permutation(Tn - 1)[:n - 1]] = 1
+    return m
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("N", [2500, 40])
+@pytest.mark.parametrize("space", ["full", "small", "none"])
+def test_part_edges(d, N, space):
+    w = wl.Workload("parts", 1, 2, N, d, 0.1, 0.5, "gaussian", True)
+    print(f"case d={d} N={N} workspace={space}", flush=True)
+    q, k, v, do = wl.make_inputs(w, seed=11)
+    mask = _mask(w.H, w.Tm, w.Tn)
+    qd, kd, vd, dod = (t.to(dev()) for t in (q, k, v, do))
+    pat = pattern_from_mask(mask, dev())
+    nf, nb, nmin = (f(qd) for f in (spa2.spa2_fwd_workspace_bytes, spa2.spa2_bwd_workspace_bytes, spa2.spa2_bwd_workspace_min_bytes))
+    if space == "small":        # room for a few slots only: the plan has to take longer parts
+        nf, nb = nf // 8, nmin + (nb - nmin) // 8
+    elif space == "none":
+        nf, nb = 0, nmin
+    runs = []
+    for _ in range(2):
+        ws_f = torch.full((nf,), 0xA5, dtype=torch.uint8, device=dev()) if nf else None
+        ws_b = torch.full((nb,), 0xA5, dtype=torch.uint8, device=dev())
+        o, o_res, dq, dk, dv = (torch.full_like(qd, float("nan")) for _ in range(5))
+        lse = torch.full((1, w.H, N), float("nan"), device=dev())
+        spa2.spa2_fwd(qd, kd, vd, pat, 1 / math.sqrt(d), o, lse, o_res, ws_f)
+        spa2.spa2_bwd(qd, kd, vd, o, dod, lse, pat, 1 / math.sqrt(d), dq, dk, dv, ws_b, o_res)
+        torch.cuda.synchronize()
+        runs.append((o, lse, o_res, dq, dk, dv))
+        # the stage calls make their own plans: same bits as the composite call
+        dq2, dk2, dv2 = (torch.full_like(qd, float("nan")) for _ in range(3))
+        spa2.spa2_bwd_delta(o, dod, ws_b, o_res)
+        spa2.spa2_bwd_dkdv(qd, kd, vd, dod, lse, pat, 1 / math.sqrt(d), dk2, dv2, ws_b)
+        spa2.spa2_bwd_dq(qd, kd, vd, dod, lse, pat, 1 / math.sqrt(d), dq2, ws_b)
+        torch.cuda.synchronize()
+        for a, b in zip((dq, dk, dv), (dq2, dk2, dv2)):
+            assert torch.equal(a, b)
+    for a, b in zip(*runs):
+        assert torch.equal(a, b), "results must not depend on the order in which parts finish"
+    o, lse, o_res, dq, dk, dv = runs[0]
+    r_dq, r_dk, r_dv, r_o, r_lse = orc.attention_bwd_bh(f64(q), f64(k), f64(v), mask, f64(do))
+    assert_close("O", f64(o), r_o)
+    assert np.abs(f64(lse) - r_lse).max() <= 2e-3
+    assert_close("dQ", f64(dq), r_dq)
+    assert_close("dK", f64(dk), r_dk)
+    assert_close("dV", f64(dv), r_dv)
