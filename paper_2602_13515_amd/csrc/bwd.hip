@@ -89,7 +89,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
-    const HeadBlock hb = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
+    const HeadBlock hb = xcd_map_rows(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;

@@ -88,7 +88,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
     part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
-    const HeadBlock hb = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
+    const HeadBlock hb = xcd_map_rows(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     // optional launch order: position hb.blk of this head's schedule -> query block (clamped: caller data)

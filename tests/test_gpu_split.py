@@ -71,3 +71,28 @@ def test_part_edges(d, N, space):
     assert_close("dQ", f64(dq), r_dq)
     assert_close("dK", f64(dk), r_dk)
     assert_close("dV", f64(dv), r_dv)
+
+
+@pytest.mark.parametrize("rows", [8, 17, 25, 32, 33, 40, 59])
+def test_every_row_is_launched_once(rows):
+    """Rows per XCD (rows / 8, rounded up) around the groups of four that the launch order rotates: one block per row,
+    so that every row's result is its own and a row that is left out or taken for another one shows."""
+    N, H, d = 128 * rows - 5, 3, 64
+    w = wl.Workload("order", 1, H, N, d, 0.1, 0.5, "gaussian", True)
+    print(f"case rows={rows}", flush=True)
+    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=rows))
+    mask = np.zeros((1, H, w.Tm, w.Tn), np.uint8)
+    for h in range(H):
+        for i in range(w.Tm):
+            mask[0, h, i, (7 * i + h) % w.Tn] = 1
+    pat = pattern_from_mask(mask, dev())
+    o, o_res, dq, dk, dv = (torch.full_like(q, float("nan")) for _ in range(5))
+    lse = torch.full((1, H, N), float("nan"), device=dev())
+    ws = torch.empty(spa2.spa2_bwd_workspace_bytes(q), dtype=torch.uint8, device=dev())
+    spa2.spa2_fwd(q, k, v, pat, 1 / math.sqrt(d), o, lse, o_res)
+    spa2.spa2_bwd(q, k, v, o, do, lse, pat, 1 / math.sqrt(d), dq, dk, dv, ws, o_res)
+    torch.cuda.synchronize()
+    r_dq, r_dk, r_dv, r_o, r_lse = orc.attention_bwd_bh(f64(q), f64(k), f64(v), mask, f64(do))
+    assert np.abs(f64(lse) - r_lse).max() <= 2e-3
+    for name, got, ref in (("O", o, r_o), ("dQ", dq, r_dq), ("dK", dk, r_dk), ("dV", dv, r_dv)):
+        assert_close(name, f64(got), ref)
