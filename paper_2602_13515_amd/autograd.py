@@ -131,7 +131,9 @@ def sparge_attn2(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, k_frac: floa
     scale = 1.0 / math.sqrt(q.shape[-1]) if scale is None else float(scale)
     # Without a backward pass to come (sampling) nobody reads the column lists or the output's residual: two kernels
     # and one tensor's writes fewer.  75,600 tokens, 40 heads: 4.85 -> 4.51 ms; 1,000 tokens, two heads: 68 -> 50 us.
-    training = torch.is_grad_enabled() and (q.requires_grad or k.requires_grad or v.requires_grad)
+    # (Inside a forward-mode level the call goes through the autograd function too, which refuses inputs with tangents.)
+    training = (torch.is_grad_enabled() and (q.requires_grad or k.requires_grad or v.requires_grad)
+                or torch.autograd.forward_ad._current_level >= 0)
     if pattern is None:
         with torch.no_grad():
             pattern = build_pattern(q.detach(), k.detach(), k_frac, top_p, scale, columns=training or return_pattern)

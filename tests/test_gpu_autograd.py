@@ -88,3 +88,16 @@ def test_two_stream_backward_gives_the_same_bits():
                 assert torch.equal(a, b), name
     r_dq, r_dk, r_dv, _, _ = _oracle(q, k, v, do, pat.mask.cpu().numpy())
     assert_close("dQ", f64(grads[0]), r_dq, max_abs=LOWRANK_MAX_ABS); assert_close("dK", f64(grads[1]), r_dk); assert_close("dV", f64(grads[2]), r_dv)
+
+
+@pytest.mark.parametrize("grad", [False, True])
+def test_forward_mode_is_refused_with_and_without_grad(grad):
+    """The operator has no forward-mode derivative: inputs with tangents raise instead of losing them."""
+    import torch.autograd.forward_ad as fwad
+    q, k, v = (torch.randn(1, 1, 200, 64, device=dev(), dtype=torch.bfloat16) for _ in range(3))
+    ref = spa2.sparge_attn2(q, k, v, 0.5, 0.5)
+    with torch.set_grad_enabled(grad), fwad.dual_level():
+        assert torch.equal(spa2.sparge_attn2(q, k, v, 0.5, 0.5), ref)      # no tangents: as outside
+        dual = fwad.make_dual(q, torch.ones_like(q))
+        with pytest.raises(RuntimeError):
+            spa2.sparge_attn2(dual, k, v, 0.5, 0.5)
