@@ -715,37 +715,51 @@ __global__ __launch_bounds__(64 * COL_SEGS) void columns_kernel(const uint8_t* m
   if (seg == COL_SEGS - 1) col_cnt[(int64_t)bh * Tn + j] = at;
 }
 
-// Launch order of the key blocks of one head for the dK/dV kernel: longest column first, dealt round-robin
-// to the eight XCD chunks of the schedule (position x*chunk + s belongs to XCD x), so that every XCD gets the
-// same mix of long and short columns and the long ones start early.  One workgroup per head.
+// Launch order of the key blocks of one head for the dK/dV kernel: longest column first (equal lengths: lower index
+// first), dealt round-robin to the eight XCD chunks of the schedule (position x*chunk + s belongs to XCD x), so that
+// every XCD gets the same mix of long and short columns and the long ones start early.
+// A column's rank is the number of columns that precede it in that order, counted directly: a workgroup ranks 64
+// columns of a head against all of them, RANK_SEGS threads a column, the head's keys in LDS.  (T_n^2 comparisons, but
+// no chain of dependent steps: the bitonic sort of a head by one workgroup before took 11.6 us at 512 columns of 12
+// heads and 23.6 us at 2048 columns of 4, this takes 4.8 and 5.5 us.)
+constexpr int RANK_SEGS = 16;
 template <int NP>
-__global__ __launch_bounds__(NP / 2 < 1024 ? NP / 2 : 1024) void col_order_kernel(const int32_t* col_cnt, int Tn, int32_t* col_order) {
-  __shared__ uint32_t keys[NP];
-  constexpr int BT = NP / 2 < 1024 ? NP / 2 : 1024;     // one compare-exchange per thread and step where that fits
-  const int bh = blockIdx.x, tid = threadIdx.x;
-  for (int j = tid; j < NP; j += BT)
+__global__ __launch_bounds__(64 * RANK_SEGS) void col_order_kernel(const int32_t* col_cnt, int Tn, int32_t* col_order) {
+  constexpr int PER = NP / RANK_SEGS;                  // keys that one thread compares with
+  __shared__ __align__(16) uint32_t keys[NP];
+  __shared__ uint32_t before[RANK_SEGS][64];
+  const int bh = blockIdx.y, tid = threadIdx.x, c = tid & 63, seg = tid >> 6;
+  for (int j = tid; j < NP; j += 64 * RANK_SEGS)       // distinct keys: length, then lower index; padding below all
     keys[j] = j < Tn ? ((uint32_t)min(col_cnt[(int64_t)bh * Tn + j], 0xffff) << 16) | (uint32_t)(0xffff - j) : 0u;
   __syncthreads();
-  for (int k = 2; k <= NP; k <<= 1)
-    for (int st = k >> 1; st > 0; st >>= 1) {
-      for (int pr = tid; pr < NP / 2; pr += BT) {
-        const int lo = 2 * st * (pr / st) + (pr % st), hi = lo + st;
-        const bool desc = (lo & k) == 0;
-        const uint32_t x = keys[lo], y = keys[hi];
-        if ((x < y) == desc) { keys[lo] = y; keys[hi] = x; }
-      }
-      __syncthreads();
-    }
-  const int chunk = (Tn + 7) / 8;
-  for (int pos = tid; pos < Tn; pos += BT) {
-    const int x = pos / chunk, sidx = pos % chunk;
-    int rank = 0;                                  // how many schedule positions are dealt before this one
-    for (int xx = 0; xx < 8; ++xx) {
-      const int len = min(max(Tn - xx * chunk, 0), chunk);
-      rank += min(len, sidx) + ((xx < x && sidx < len) ? 1 : 0);
-    }
-    col_order[(int64_t)bh * Tn + pos] = 0xffff - (int)(keys[rank] & 0xffffu);
+  const int j = blockIdx.x * 64 + c;
+  const uint32_t mine = keys[min(j, NP - 1)];
+  uint32_t n = 0;
+  for (int x = seg * PER; x < min((seg + 1) * PER, Tn); x += 4) {       // (a wave reads one address: broadcast)
+    const u32x4 k4 = *(const u32x4*)(keys + x);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) n += k4[e] > mine ? 1u : 0u;
   }
+  before[seg][c] = n;
+  __syncthreads();
+  if (seg != 0 || j >= Tn) return;
+  uint32_t rank = 0;
+#pragma unroll
+  for (int x = 0; x < RANK_SEGS; ++x) rank += before[x][c];
+  // the schedule position that is dealt as number `rank`: rounds of all XCDs while the shortest chunk lasts, then of
+  // those that still have positions (chunk x has min(chunk, T_n - x * chunk) of them)
+  const int chunk = (Tn + 7) / 8;
+  int left = (int)rank, s = 0, live = 8;
+  while (live > 0) {
+    const int len = min(max(Tn - (live - 1) * chunk, 0), chunk);        // the last live chunk is the shortest
+    const int rounds = max(len - s, 0);
+    if (left < rounds * live) break;
+    left -= rounds * live;
+    s += rounds;
+    --live;
+  }
+  const int pos = (left % live) * chunk + s + left / live;
+  col_order[(int64_t)bh * Tn + pos] = j;
 }
 
 hipError_t launch_columns(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx,
@@ -753,10 +767,10 @@ hipError_t launch_columns(const uint8_t* mask, const Dims& m, int32_t* col_cnt, 
   const dim3 grid((unsigned)((m.Tn + 63) / 64), (unsigned)(m.B * m.H)), block(256);
   hipLaunchKernelGGL(columns_kernel, grid, dim3(64 * COL_SEGS), 0, stream, mask, m.Tm, m.Tn, col_cnt, col_idx);
   if (col_order) {
-    const dim3 g2((unsigned)(m.B * m.H));
-    if (m.Tn <= 512)       hipLaunchKernelGGL(col_order_kernel<512>, g2, dim3(256), 0, stream, col_cnt, m.Tn, col_order);
-    else if (m.Tn <= 2048) hipLaunchKernelGGL(col_order_kernel<2048>, g2, dim3(1024), 0, stream, col_cnt, m.Tn, col_order);
-    else                   hipLaunchKernelGGL(col_order_kernel<8192>, g2, dim3(1024), 0, stream, col_cnt, m.Tn, col_order);
+    const dim3 b2(64 * RANK_SEGS);
+    if (m.Tn <= 512)       hipLaunchKernelGGL(col_order_kernel<512>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
+    else if (m.Tn <= 2048) hipLaunchKernelGGL(col_order_kernel<2048>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
+    else                   hipLaunchKernelGGL(col_order_kernel<8192>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
   }
   return hipGetLastError();
 }

@@ -96,3 +96,26 @@ def test_every_row_is_launched_once(rows):
     assert np.abs(f64(lse) - r_lse).max() <= 2e-3
     for name, got, ref in (("O", o, r_o), ("dQ", dq, r_dq), ("dK", dk, r_dk), ("dV", dv, r_dv)):
         assert_close(name, f64(got), ref)
+
+
+@pytest.mark.parametrize("rows,cols", [(1, 1), (1, 9), (3, 63), (2, 64), (5, 65), (2, 511), (3, 513), (1, 2049), (2, 8192)])
+def test_column_order_is_longest_first_dealt_to_the_xcds(rows, cols):
+    """col_order against a host sort, at the edges of the workgroups (64 columns) and of the instantiated widths."""
+    B, H, N = 1, 2, 64 * cols
+    like = torch.empty((B, H, N, 64), dtype=torch.bfloat16, device=dev())
+    pat = spa2.alloc_pattern(B, H, N, dev())
+    Tm, Tn = pat.mask.shape[-2:]
+    print(f"case Tm={Tm} Tn={Tn}", flush=True)
+    rng = np.random.default_rng(cols)
+    mask = (rng.random((B, H, Tm, Tn)) < rng.random(Tn) ** rows).astype(np.uint8)
+    pat.mask.copy_(torch.from_numpy(mask))
+    spa2.spa2_mask_columns(like, pat)
+    torch.cuda.synchronize()
+    cnt = mask.sum(axis=2)
+    assert np.array_equal(pat.col_cnt.cpu().numpy(), cnt)
+    chunk = -(-Tn // 8)
+    dealt = [x * chunk + s for s in range(chunk) for x in range(8) if s < min(max(Tn - x * chunk, 0), chunk)]
+    for h in range(H):
+        want = np.empty(Tn, np.int64)
+        want[dealt] = np.argsort(-cnt[0, h].astype(np.int64), kind="stable")
+        assert np.array_equal(pat.col_order[0, h].cpu().numpy(), want)
