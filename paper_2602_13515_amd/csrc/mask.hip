@@ -8,7 +8,7 @@
 //                   (Pbar descending, block index ascending), cumulative sum in
 //                   that order, n = max(1, k_cnt, n_p), mask row + ascending
 //                   index list.  The row never leaves LDS/registers.
-//   select16_kernel the same for rows of up to 1536 blocks, sixteen rows per workgroup, with the
+//   select16_kernel the same for rows of up to 2048 blocks, sixteen rows per workgroup, with the
 //                   score product on the fp64 matrix cores.
 //   columns_kernel  the same pattern listed per key block (for dK/dV).
 #include "spa2_device.h"
@@ -16,12 +16,19 @@
 
 namespace spa2 {
 
-// Which of the two selection kernels a shape gets (the pooled keys are laid out for it by the pooling pass):
-// sixteen rows per workgroup with the scores on the fp64 matrix cores where a row has at most 1536 blocks (the scores
-// of sixteen rows fit the registers) and the launch still has four workgroups per compute unit, else four rows per
-// workgroup on the vector ALU.
-static bool select16_applies(const Dims& m) {
-  return m.Tn <= 1536 && (int64_t)m.B * m.H * ((m.Tm + 15) / 16) >= 1024;
+// Which of the two selection kernels a shape gets (the pooled keys are laid out for it by the pooling pass): 0 for four
+// rows per workgroup on the vector ALU, else sixteen rows per workgroup with the scores on the fp64 matrix cores and
+// the number of waves that share them.  Sixteen rows where a row has at most 2048 blocks (the scores fit the registers)
+// and either the launch has 128 such workgroups or a row is so short that the score product is nothing; with fewer
+// workgroups and longer rows more, smaller ones are faster.  Four waves where the launch fills the chip and the scores
+// fit.  Measured, us (selection on four rows / on sixteen; the row-major keys of the latter also save the pooling pass
+// 5 to 15 %): 20,010 tokens d = 64, 20 groups of sixteen rows 15.7 / 19.7, 240 groups 36.4 / 21.9; 32,760 tokens
+// d = 128, 32 groups 21.2 / 31.4, 192 groups 34.3 / 32.1; 75,600 tokens d = 128, 222 groups 86 / 57; 131,042 tokens
+// d = 64, 128 groups 57 / 65, 256 groups 109 / 70; 16 blocks a row 13.5 / 9.7.
+static int select16_waves(const Dims& m) {
+  const int64_t wgs = (int64_t)m.B * m.H * ((m.Tm + 15) / 16);
+  if (m.Tn > 2048 || (wgs < 128 && m.Tn > 128)) return 0;
+  return wgs >= 1024 && m.Tn <= (m.d == 128 ? 1280 : 1536) ? 4 : 8;
 }
 
 // ------------------------------------------------------------------ pooling
@@ -97,7 +104,7 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
 hipError_t launch_pool(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, hipStream_t stream) {
   PoolArgs a;
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.qbar = qbar; a.kbar_t = kbar;
-  a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.TnP = m.Tn; a.k_rows = select16_applies(m) ? 1 : 0;
+  a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.TnP = m.Tn; a.k_rows = select16_waves(m) ? 1 : 0;
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   const dim3 grid((unsigned)((int64_t)m.B * m.H * (m.Tm + m.Tn))), block(256);
   if (m.d == 128) hipLaunchKernelGGL(pool_kernel<128>, grid, block, 0, stream, a);
@@ -171,7 +178,7 @@ __device__ __forceinline__ uint32_t wave_scan_add(uint32_t x) {
 // extends the key prefix of the row by it and clears the bins for the next pass.
 __device__ __forceinline__ void sel_scan_pass(int pass, int sh, int lane, int r, uint32_t (*h_cnt)[256],
                                               uint64_t (*h_mass)[256], uint64_t* st_key, uint32_t* st_cnt,
-                                              uint64_t* st_mass, uint32_t kc, uint64_t p_fx, uint32_t* st_done = nullptr) {
+                                              uint64_t* st_mass, uint32_t kc, uint64_t p_fx, uint32_t* st_done) {
   uint32_t c4[4]; uint64_t m4[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
@@ -211,8 +218,23 @@ __device__ __forceinline__ void sel_scan_pass(int pass, int sh, int lane, int r,
     st_key[r] = key; st_cnt[r] = b_c; st_mass[r] = b_m;
     // A boundary bin with a single entry needs no further passes: that entry is selected (it is the bin's top entry),
     // so the lower end of the bin, which is what the key prefix with zeros below it says, already is a threshold.
-    if (st_done) st_done[r] = b_n == 1u ? 1u : 0u;
+    st_done[r] = b_n == 1u ? 1u : 0u;
   }
+}
+
+// The selection only uses the order of the probabilities, so their bit patterns are mapped, row by row, onto the whole
+// 32-bit range: b -> (b - b_min) << (leading zeros of b_max - b_min), with b_min / b_max the patterns of the row's
+// smallest / largest probability (non-negative floats order like their patterns; the map is increasing and keeps ties).
+// The top eight bits of a probability are its sign and seven exponent bits, the same three or four values for almost
+// every entry of a row: unmapped, the first pass of the descent would tell almost nothing apart, and its LDS atomics
+// would collide; mapped, a pass spreads a row over all 256 bins, the boundary bin holds a single entry after two passes
+// for most rows, and the row's descent stops there (see sel_scan_pass).
+// e_min: the row's smallest exponential, tot: their sum (the largest exponential is exp(0) = 1).  Two patterns of margin
+// on either side keep the map inside 32 bits whatever the last bit of the two divisions is.
+__device__ __forceinline__ void spread_range(float e_min, float tot, uint32_t& b_min, int& shift) {
+  const uint32_t lo = __builtin_bit_cast(uint32_t, e_min / tot), hi = __builtin_bit_cast(uint32_t, 1.0f / tot);
+  b_min = lo >= 2u ? lo - 2u : 0u;
+  shift = __builtin_clz((max(hi, lo) + 2u - b_min) | 1u);
 }
 
 // Mask rows and ascending index lists of up to R rows from their flags (R * NP bytes in LDS): thread t compacts E
@@ -256,8 +278,8 @@ __device__ __forceinline__ void sel_compact(const SelArgs& a, int bh, int i0, in
 // n_p = shortest prefix with sum >= p" is the same as
 //        e selected  <=>  cnt_gt(e) < max(1, k_cnt)  or  mass_gt(e) < p,
 // a predicate that is monotone in the key, so the selected set is {key >= T}.  T is found by a radix
-// descent over the key, 8 bits per pass (6 passes: four over the bits of Pbar, two over the index bits
-// that break ties): per pass a 256-bin histogram of count and mass of the entries that match the prefix
+// descent over the key with the bits of Pbar spread (see spread_range), 8 bits per pass (at most 6 passes: four over
+// the bits of Pbar, two over the index bits that break ties): per pass a 256-bin histogram of count and mass of the entries that match the prefix
 // found so far, then one wave per row walks the bins from the top and picks the lowest bin whose top
 // entry is still selected.
 constexpr int score_group(int jj) {
@@ -279,10 +301,12 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
   __shared__ __align__(16) double qd[128][R];
   __shared__ uint8_t flag[R * NP];
   __shared__ float redf[R][4];
+  __shared__ float redm[R][4];
   __shared__ int sm4i[4];
   __shared__ uint64_t st_key[R];          // key prefix found so far (lower bits zero)
   __shared__ uint32_t st_cnt[R];          // number of entries above the prefix range
   __shared__ uint64_t st_mass[R];         // their mass
+  __shared__ uint32_t st_done[R];         // the row's threshold is final (see sel_scan_pass)
 
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int bh = blockIdx.x / a.groups;
@@ -296,7 +320,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
   }
   for (int x = tid; x < R * NP; x += 256) flag[x] = 0;
   for (int x = tid; x < R * 256; x += 256) { h_cnt[x >> 8][x & 255] = 0; h_mass[x >> 8][x & 255] = 0; }
-  if (tid < R) { st_key[tid] = 0; st_cnt[tid] = 0; st_mass[tid] = 0; }
+  // (rows past the end take no part: their scores are all equal, every pass of the descent would be one bin's atomics)
+  if (tid < R) { st_key[tid] = 0; st_cnt[tid] = 0; st_mass[tid] = 0; st_done[tid] = tid < nrows ? 0 : 1; }
   __syncthreads();
 
   // ---- Sbar = Qbar Kbar^T * scale: fp32 pooled values, fp64 accumulation, rounded once to fp32
@@ -359,21 +384,28 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
   __syncthreads();
 #pragma unroll
   for (int r = 0; r < R; ++r) {
-    float sum = 0.f;
+    float sum = 0.f, emin = INFINITY;
 #pragma unroll
     for (int jj = 0; jj < JJ; ++jj) {
-      const float e = (tid + 256 * jj) < Tn ? expf(s[r][jj] - rowmax[r]) : 0.f;
+      const bool in_row = (tid + 256 * jj) < Tn;
+      const float e = in_row ? expf(s[r][jj] - rowmax[r]) : 0.f;
       s[r][jj] = e;
       sum += e;
+      emin = in_row ? fminf(emin, e) : emin;
     }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if (lane == 0) redf[r][w] = sum;
+    for (int off = 32; off > 0; off >>= 1) {
+      sum += __shfl_xor(sum, off, 64);
+      emin = fminf(emin, __shfl_xor(emin, off, 64));
+    }
+    if (lane == 0) { redf[r][w] = sum; redm[r][w] = emin; }
   }
   __syncthreads();
+  uint32_t bmin[R]; int bsh[R];
 #pragma unroll
   for (int r = 0; r < R; ++r) {
     const float tot = (redf[r][0] + redf[r][1]) + (redf[r][2] + redf[r][3]);
+    spread_range(fminf(fminf(redm[r][0], redm[r][1]), fminf(redm[r][2], redm[r][3])), tot, bmin[r], bsh[r]);
 #pragma unroll
     for (int jj = 0; jj < JJ; ++jj) {
       const int j = tid + 256 * jj;
@@ -395,13 +427,17 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
     // accumulate: entries that match the prefix found so far
 #pragma unroll
     for (int r = 0; r < R; ++r) {
+      if (st_done[r]) continue;           // (uniform over the workgroup)
       const uint64_t pre = st_key[r];
 #pragma unroll
       for (int jj = 0; jj < JJ; ++jj) {
         const int j = tid + 256 * jj;
         if (j < Tn) {
-          const uint32_t fb = __builtin_bit_cast(uint32_t, s[r][jj]);
-          const uint64_t key = ((uint64_t)fb << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
+          uint32_t fb = __builtin_bit_cast(uint32_t, s[r][jj]);
+#if defined(__HIP_DEVICE_COMPILE__)
+          asm volatile("" : "+v"(fb));     // (keeps keys and masses from being held in registers across the passes)
+#endif
+          const uint64_t key = ((uint64_t)((fb - bmin[r]) << bsh[r]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
           const bool match = pass == 0 ? true : (((key ^ pre) >> (sh + 8)) == 0);
           if (match) {
             const int dig = (int)((key >> sh) & 255u);
@@ -412,8 +448,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
       }
     }
     __syncthreads();
-    sel_scan_pass(pass, sh, lane, w, h_cnt, h_mass, st_key, st_cnt, st_mass, kc, p_fx);
-    __syncthreads();
+    if (st_done[w] == 0) sel_scan_pass(pass, sh, lane, w, h_cnt, h_mass, st_key, st_cnt, st_mass, kc, p_fx, st_done);
+    if (__syncthreads_and(st_done[tid & (R - 1)] != 0)) break;        // every row of the workgroup has its threshold
   }
 
   // ---- flags: key >= threshold
@@ -424,7 +460,8 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
     for (int jj = 0; jj < JJ; ++jj) {
       const int j = tid + 256 * jj;
       if (j < Tn) {
-        const uint64_t key = ((uint64_t)__builtin_bit_cast(uint32_t, s[r][jj]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
+        const uint64_t key = ((uint64_t)((__builtin_bit_cast(uint32_t, s[r][jj]) - bmin[r]) << bsh[r]) << 32) |
+                             (uint64_t)(0xffffffffu - (uint32_t)j);
         if (key >= thr) flag[r * NP + j] = 1;
       }
     }
@@ -434,49 +471,53 @@ __global__ __launch_bounds__(256) void select_kernel(SelArgs a) {
   sel_compact<NP, R>(a, bh, i0, nrows, tid, flag, sm4i);
 }
 
-// The same selection with the score product on the fp64 matrix cores, for rows of up to 1536 blocks.  A workgroup
-// takes 16 rows of the pooled map: Sbar (16 x NP) = Qbar (16 x d) Kbar^T in tiles of 16 x 16 by
+// The same selection with the score product on the fp64 matrix cores, for rows of up to 2048 blocks.  A workgroup of
+// WV waves takes 16 rows of the pooled map: Sbar (16 x NP) = Qbar (16 x d) Kbar^T in tiles of 16 x 16 by
 // v_mfma_f64_16x16x4_f64 (A[m][k]: lane l holds m = l % 16, k = l / 16; B[k][n]: k = l / 16, n = l % 16;
 // C[m][n]: n = l % 16, m = l / 16 + 4 v for accumulator element v), so a pooled key value that is loaded and widened
-// serves 16 rows instead of 4 and the products no longer run on the vector ALU.  Wave w takes the column tiles
-// w, w + 4, ...; its accumulators then hold, for each of the four row batches v = 0..3 (rows 4v .. 4v + 3 of the
-// workgroup), the scores of ONE row per lane (row l / 16 of the batch) at the columns 16 (w + 4 t) + l % 16.  The
-// sixteen rows are selected together exactly as in select_kernel (same keys, histograms, threshold rule and
-// compaction), with that row / column assignment in place of (all four rows, columns tid + 256 jj).
+// serves 16 rows instead of 4 and the products do not run on the vector ALU.  Wave w takes the column tiles
+// w, w + WV, ...; its accumulators then hold, for each of the four row batches v = 0..3 (rows 4v .. 4v + 3 of the
+// workgroup), the scores of ONE row per lane (row l / 16 of the batch) at the columns 16 (w + WV t) + l % 16.  The
+// sixteen rows are selected together by the rule of select_kernel (same order, histograms and thresholds), with that
+// row / column assignment in place of (all four rows, columns tid + 256 jj).
 // fp64 sums of the same products in a different order than select_kernel's chain of FMAs: the scores of the two
 // kernels may differ in the last bit of their fp32 rounding.
 typedef __attribute__((ext_vector_type(4))) double f64x4;
-template <int NP, int D>
-__global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
-  constexpr int R = 4, RW = 16;
-  constexpr int NT = NP / 64;             // column tiles per wave
+template <int NP, int D, int WV>
+__global__ __launch_bounds__(64 * WV, 2) void select16_kernel(SelArgs a) {
+  constexpr int RW = 16;
+  constexpr int NT = NP / (16 * WV);      // column tiles per wave
   constexpr int KS = D / 4;               // contraction steps of 4 channels
-  __shared__ uint32_t h_cnt[RW][256];
-  __shared__ uint64_t h_mass[RW][256];
-  __shared__ uint8_t flag[RW * NP];
-  __shared__ float redf[RW][4];
-  __shared__ float redm[RW][4];
-  __shared__ int sm4i[4];
+  __shared__ __align__(16) uint32_t h_cnt[RW][256];
+  __shared__ __align__(16) uint64_t h_mass[RW][256];
+  __shared__ __align__(8) uint16_t sel[RW][NP / 16];      // selected columns, one bit each
+  __shared__ float redf[RW][WV];
+  __shared__ float redm[RW][WV];
   __shared__ uint64_t st_key[RW];
   __shared__ uint32_t st_cnt[RW];
   __shared__ uint64_t st_mass[RW];
   __shared__ uint32_t st_done[RW];        // the row's threshold is final (see sel_scan_pass)
 
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lg = lane >> 4, ln = lane & 15;
   const int bh = blockIdx.x / a.groups;
   const int iw = (blockIdx.x % a.groups) * RW;        // first row of the workgroup
   const int nrows_w = min(RW, a.Tm - iw);
   const int Tn = a.Tn;
 
-  for (int x = tid; x < RW * 256; x += 256) { h_cnt[x >> 8][x & 255] = 0; h_mass[x >> 8][x & 255] = 0; }
-  for (int x = tid; x < RW * NP; x += 256) flag[x] = 0;
-  if (tid < RW) { st_key[tid] = 0; st_cnt[tid] = 0; st_mass[tid] = 0; st_done[tid] = 0; }
-
   // ---- Sbar = Qbar Kbar^T * scale: fp32 pooled values widened to fp64, fp64 products and sums, rounded once to fp32
   // Contraction step c = 4g + e takes the four channels 16g + 4k + e, k = 0..3 (which channels make up a step is free
   // as long as both operands agree): lane (k = lg) then needs the channels 16g + 4lg + 0..3 for the steps 4g .. 4g+3,
   // one 16-byte load from the row-major pooled keys.
+  const float* kb = a.kbar_t + (int64_t)bh * Tn * D + 4 * lg;
+  auto load_tile = [&](int t, f32x4 (&kr)[KS / 4]) {      // B operand of tile t (columns past the row: clamped)
+    const float* kc = kb + (int64_t)min(16 * (w + WV * t) + ln, Tn - 1) * D;
+#pragma unroll
+    for (int g = 0; g < KS / 4; ++g) kr[g] = *(const f32x4*)(kc + 16 * g);
+  };
+  f32x4 krA[KS / 4], krB[KS / 4];         // the loads of tile t+1 are in flight during the products of tile t
+  load_tile(0, krA);
   double af[KS];                          // A operand: row iw + ln
   {
     const float* qrow = a.qbar + ((int64_t)bh * a.Tm + iw + min(ln, nrows_w - 1)) * D + 4 * lg;
@@ -487,21 +528,21 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
       for (int e = 0; e < 4; ++e) af[4 * g + e] = ln < nrows_w ? (double)q4[e] : 0.0;
     }
   }
-  float sv[4][NT];                        // [row batch][tile]: this lane's row of the batch, column 16 (w + 4t) + ln
-  const float* kb = a.kbar_t + (int64_t)bh * Tn * D + 4 * lg;
-  auto load_tile = [&](int t, f32x4 (&kr)[KS / 4]) {      // B operand of tile t (columns past the row: clamped)
-    const float* kc = kb + (int64_t)min(16 * (w + 4 * t) + ln, Tn - 1) * D;
-#pragma unroll
-    for (int g = 0; g < KS / 4; ++g) kr[g] = *(const f32x4*)(kc + 16 * g);
-  };
-  f32x4 krA[KS / 4], krB[KS / 4];         // the loads of tile t+1 are in flight during the products of tile t
-  load_tile(0, krA);
+  // (the state of the selection is cleared while the loads are on their way)
+  for (int x = tid; x < RW * 64; x += 64 * WV) {
+    ((u32x4*)h_cnt)[x] = u32x4{0, 0, 0, 0};
+    ((u32x4*)h_mass)[2 * x] = u32x4{0, 0, 0, 0};
+    ((u32x4*)h_mass)[2 * x + 1] = u32x4{0, 0, 0, 0};
+  }
+  // (rows past the end take no part: their scores are all equal, every pass of the descent would be one bin's atomics)
+  if (tid < RW) { st_key[tid] = 0; st_cnt[tid] = 0; st_mass[tid] = 0; st_done[tid] = tid < nrows_w ? 0 : 1; }
+  float sv[4][NT];                        // [row batch][tile]: this lane's row of the batch, column 16 (w + WV t) + ln
   auto tile = [&](auto T, f32x4 (&kr)[KS / 4], f32x4 (&kn)[KS / 4]) {
     constexpr int t = decltype(T)::v;
     if constexpr (t + 1 < NT) load_tile(t + 1, kn);
-    const int col = 16 * (w + 4 * t) + ln;
+    const int col = 16 * (w + WV * t) + ln;
     f64x4 acc = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};      // two chains: even and odd contraction steps
-    if (16 * (w + 4 * t) < Tn) {          // (uniform per wave: tiles past the end of the row are skipped)
+    if (16 * (w + WV * t) < Tn) {         // (uniform per wave: tiles past the end of the row are skipped)
 #pragma unroll
       for (int c = 0; c < KS; c += 2) {
         acc = __builtin_amdgcn_mfma_f64_16x16x4f64(af[c], (double)kr[c / 4][c % 4], acc, 0, 0, 0);
@@ -515,15 +556,14 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
   static_for<0, NT>([&](auto T) {
     if constexpr ((decltype(T)::v & 1) == 0) tile(T, krA, krB); else tile(T, krB, krA);
   });
-  __syncthreads();
 
   const uint32_t kc = (uint32_t)max(1, a.k_cnt);
   uint64_t p_fx = fixed62(__builtin_bit_cast(uint32_t, a.top_p));
   if (a.top_p > 0.f && p_fx == 0) p_fx = 1;
 
   // ---- selection of all sixteen rows together; of batch v (rows 4v .. 4v+3) this lane holds row 4v + lg
-  // Pbar = softmax(Sbar) per row, fp32: maximum and sum over the 16 lanes of the row in this wave, then over the four
-  // waves through LDS
+  // Pbar = softmax(Sbar) per row, fp32: maximum and sum over the 16 lanes of the row in this wave, then over the waves
+  // through LDS
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     float mx = sv[v][0];
@@ -538,7 +578,9 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int r = 4 * v + lg;
-    rowmax[v] = fmaxf(fmaxf(redf[r][0], redf[r][1]), fmaxf(redf[r][2], redf[r][3]));
+    rowmax[v] = redf[r][0];
+#pragma unroll
+    for (int x = 1; x < WV; ++x) rowmax[v] = fmaxf(rowmax[v], redf[r][x]);
   }
   __syncthreads();
 #pragma unroll
@@ -546,7 +588,7 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
     float sum = 0.f, emin = INFINITY;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const bool in_row = (16 * (w + 4 * t) + ln) < Tn;
+      const bool in_row = (16 * (w + WV * t) + ln) < Tn;
       const float e = in_row ? expf(sv[v][t] - rowmax[v]) : 0.f;
       sv[v][t] = e;
       sum += e;
@@ -560,27 +602,17 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
     if (ln == 0) { redf[4 * v + lg][w] = sum; redm[4 * v + lg][w] = emin; }
   }
   __syncthreads();
-  // The selection below only uses the order of the probabilities, so their bit patterns are first mapped, row by
-  // row, onto the whole 32-bit range: b -> (b - b_min) << (leading zeros of b_max - b_min), with b_min / b_max the
-  // patterns of the row's smallest / largest probability (non-negative floats order like their patterns; the map is
-  // increasing and keeps ties).  The top eight bits of a probability are its sign and seven exponent bits, the same
-  // three or four values for almost every entry of a row: unmapped, the first pass of the descent would tell almost
-  // nothing apart; mapped, a pass spreads a row over all 256 bins, the boundary bin holds a single entry after two
-  // passes for most rows, and the row's descent stops there (see sel_scan_pass).
   uint32_t bmin[4]; int bsh[4];
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int r = 4 * v + lg;
-    const float tot = (redf[r][0] + redf[r][1]) + (redf[r][2] + redf[r][3]);
-    const float emin = fminf(fminf(redm[r][0], redm[r][1]), fminf(redm[r][2], redm[r][3]));
-    // (the smallest / largest e over the same sum; the largest e is exp(0) = 1.  Two patterns of margin on either
-    // side, so that the map stays inside 32 bits whatever the last bit of these two divisions is.)
-    const uint32_t lo = __builtin_bit_cast(uint32_t, emin / tot), hi = __builtin_bit_cast(uint32_t, 1.0f / tot);
-    bmin[v] = lo >= 2u ? lo - 2u : 0u;
-    bsh[v] = __builtin_clz((max(hi, lo) + 2u - bmin[v]) | 1u);
+    float tot = redf[r][0], emin = redm[r][0];
+#pragma unroll
+    for (int x = 1; x < WV; ++x) { tot += redf[r][x]; emin = fminf(emin, redm[r][x]); }
+    spread_range(emin, tot, bmin[v], bsh[v]);
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int j = 16 * (w + 4 * t) + ln;
+      const int j = 16 * (w + WV * t) + ln;
       if (j < Tn) {
         const float p = sv[v][t] / tot;
         sv[v][t] = p;                                  // from here on sv holds Pbar
@@ -589,7 +621,7 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
     }
   }
 
-  // radix descent for the threshold key of each row (see select_kernel); wave w scans the histograms of rows 4w .. 4w+3
+  // radix descent for the threshold key of each row (see select_kernel); wave w scans the histograms of RW / WV rows
 #pragma unroll 1
   for (int pass = 0; pass < 6; ++pass) {
     const int sh = pass < 4 ? 56 - 8 * pass : (pass == 4 ? 8 : 0);
@@ -600,11 +632,11 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
       const bool open = st_done[r] == 0;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        const int j = 16 * (w + 4 * t) + ln;
+        const int j = 16 * (w + WV * t) + ln;
         if (j < Tn && open) {
           uint32_t fb = __builtin_bit_cast(uint32_t, sv[v][t]);
 #if defined(__HIP_DEVICE_COMPILE__)
-          asm volatile("" : "+v"(fb));     // (keeps the keys and fixed-point masses of all 80 entries from being
+          asm volatile("" : "+v"(fb));     // (keeps the keys and fixed-point masses of all entries from being
                                            // computed once and held in registers across the passes)
 #endif
           const uint64_t key = ((uint64_t)((fb - bmin[v]) << bsh[v]) << 32) | (uint64_t)(0xffffffffu - (uint32_t)j);
@@ -619,31 +651,46 @@ __global__ __launch_bounds__(256) void select16_kernel(SelArgs a) {
     }
     __syncthreads();
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-      if (st_done[4 * w + x] == 0) sel_scan_pass(pass, sh, lane, 4 * w + x, h_cnt, h_mass, st_key, st_cnt, st_mass, kc, p_fx, st_done);
+    for (int x = 0; x < RW / WV; ++x) {
+      const int r = RW / WV * w + x;
+      if (st_done[r] == 0) sel_scan_pass(pass, sh, lane, r, h_cnt, h_mass, st_key, st_cnt, st_mass, kc, p_fx, st_done);
+    }
     if (__syncthreads_and(st_done[tid & (RW - 1)] != 0)) break;       // every row of the workgroup has its threshold
   }
 
-  // flags: key >= threshold
+  // selected: key >= threshold.  A ballot holds 16 columns of each of the four rows of a batch.
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int r = 4 * v + lg;
     const uint64_t thr = st_key[r];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const int j = 16 * (w + 4 * t) + ln;
-      if (j < Tn) {
-        const uint64_t key = ((uint64_t)((__builtin_bit_cast(uint32_t, sv[v][t]) - bmin[v]) << bsh[v]) << 32) |
-                             (uint64_t)(0xffffffffu - (uint32_t)j);
-        if (key >= thr) flag[r * NP + j] = 1;
-      }
+      const int j = 16 * (w + WV * t) + ln;
+      const uint64_t key = ((uint64_t)((__builtin_bit_cast(uint32_t, sv[v][t]) - bmin[v]) << bsh[v]) << 32) |
+                           (uint64_t)(0xffffffffu - (uint32_t)j);
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(j < Tn && key >= thr);
+      if (ln == 0) sel[r][w + WV * t] = (uint16_t)(bal >> (16 * lg));
     }
   }
   __syncthreads();
-  // mask rows and index lists, four rows at a time
-  for (int v = 0; v < 4 && 4 * v < nrows_w; ++v) {
-    sel_compact<NP, R>(a, bh, iw + 4 * v, min(R, nrows_w - 4 * v), tid, flag + 4 * v * NP, sm4i);
-    __syncthreads();                                   // (the scan scratch is reused)
+  // mask rows and ascending index lists, one row per wave: lane l holds the bits of columns 64 l .., 64 columns a step
+  for (int r = w; r < nrows_w; r += WV) {
+    const uint64_t mine = *(const uint64_t*)&sel[r][4 * min(lane, NP / 64 - 1)];
+    const int64_t row = (int64_t)bh * a.Tm + iw + r;
+    uint8_t* mrow = a.mask + row * Tn;
+    int32_t* irow = a.row_idx + row * Tn;
+    int n = 0;
+#pragma unroll 2
+    for (int e = 0; 64 * e < Tn; ++e) {
+      const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)mine, e);
+      const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(mine >> 32), e);
+      const int j = 64 * e + lane;
+      const bool f = ((lane < 32 ? lo >> lane : hi >> (lane - 32)) & 1u) != 0;
+      if (j < Tn) mrow[j] = f ? 1 : 0;
+      if (f) irow[n + (int)__builtin_amdgcn_mbcnt_hi(hi, __builtin_amdgcn_mbcnt_lo(lo, 0))] = j;
+      n += __builtin_popcount(lo) + __builtin_popcount(hi);
+    }
+    if (lane == 0) a.row_cnt[row] = n;
   }
 }
 
@@ -654,12 +701,13 @@ static void launch_select_t(const SelArgs& a0, int BH, hipStream_t stream) {
   hipLaunchKernelGGL((select_kernel<NP, R>), dim3((unsigned)(BH * a.groups)), dim3(256), 0, stream, a);
 }
 
-template <int NP>
+template <int NP, int WV>
 static void launch_select16_t(const SelArgs& a0, int BH, hipStream_t stream) {
   SelArgs a = a0;
   a.groups = (a.Tm + 15) / 16;
-  if (a.d == 128) hipLaunchKernelGGL((select16_kernel<NP, 128>), dim3((unsigned)(BH * a.groups)), dim3(256), 0, stream, a);
-  else            hipLaunchKernelGGL((select16_kernel<NP, 64>), dim3((unsigned)(BH * a.groups)), dim3(256), 0, stream, a);
+  const dim3 grid((unsigned)(BH * a.groups)), block(64 * WV);
+  if (a.d == 128) hipLaunchKernelGGL((select16_kernel<NP, 128, WV>), grid, block, 0, stream, a);
+  else            hipLaunchKernelGGL((select16_kernel<NP, 64, WV>), grid, block, 0, stream, a);
 }
 
 hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, int topk_blocks, float top_p,
@@ -670,16 +718,18 @@ hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, in
   a.d = m.d; a.Tm = m.Tm; a.Tn = m.Tn; a.TnP = m.Tn; a.groups = 0;
   a.k_cnt = topk_blocks; a.top_p = top_p; a.scale = scale;
   const int BH = m.B * m.H;
-  // the smallest instantiated width that holds the row: steps of 256 up to 2048, then of 512, then of 1024
-  if (select16_applies(m)) {        // (the pooling pass has laid out the pooled keys for this kernel)
-#define SPA2_SELECT16_CASE(np) if (m.Tn <= np) { launch_select16_t<np>(a, BH, stream); return hipGetLastError(); }
-    SPA2_SELECT16_CASE(256)  SPA2_SELECT16_CASE(512)  SPA2_SELECT16_CASE(768)  SPA2_SELECT16_CASE(1024)
-    SPA2_SELECT16_CASE(1280) SPA2_SELECT16_CASE(1536)
+  // the smallest instantiated width that holds the row: steps of 256 up to 2048, of 512 up to 4096, then of 1024
+  const int waves = select16_waves(m);        // (the pooling pass has laid out the pooled keys for this kernel)
+#define SPA2_SELECT16_CASE(wv, np) if (waves == wv && m.Tn <= np) { launch_select16_t<np, wv>(a, BH, stream); return hipGetLastError(); }
+  SPA2_SELECT16_CASE(4, 256)  SPA2_SELECT16_CASE(4, 512)  SPA2_SELECT16_CASE(4, 768)  SPA2_SELECT16_CASE(4, 1024)
+  SPA2_SELECT16_CASE(4, 1280) SPA2_SELECT16_CASE(4, 1536)
+  SPA2_SELECT16_CASE(8, 256)  SPA2_SELECT16_CASE(8, 512)  SPA2_SELECT16_CASE(8, 768)  SPA2_SELECT16_CASE(8, 1024)
+  SPA2_SELECT16_CASE(8, 1280) SPA2_SELECT16_CASE(8, 1536) SPA2_SELECT16_CASE(8, 1792) SPA2_SELECT16_CASE(8, 2048)
 #undef SPA2_SELECT16_CASE
-  }
 #define SPA2_SELECT_CASE(np) if (m.Tn <= np) { launch_select_t<np, 4>(a, BH, stream); return hipGetLastError(); }
   SPA2_SELECT_CASE(256)  SPA2_SELECT_CASE(512)  SPA2_SELECT_CASE(768)  SPA2_SELECT_CASE(1024)
-  SPA2_SELECT_CASE(1280) SPA2_SELECT_CASE(1536) SPA2_SELECT_CASE(1792) SPA2_SELECT_CASE(2048) SPA2_SELECT_CASE(2560) SPA2_SELECT_CASE(3072) SPA2_SELECT_CASE(3584) SPA2_SELECT_CASE(4096)
+  SPA2_SELECT_CASE(1280) SPA2_SELECT_CASE(1536) SPA2_SELECT_CASE(1792) SPA2_SELECT_CASE(2048)
+  SPA2_SELECT_CASE(2560) SPA2_SELECT_CASE(3072) SPA2_SELECT_CASE(3584) SPA2_SELECT_CASE(4096)
   SPA2_SELECT_CASE(5120) SPA2_SELECT_CASE(6144) SPA2_SELECT_CASE(7168)
 #undef SPA2_SELECT_CASE
   launch_select_t<8192, 4>(a, BH, stream);
