@@ -10,6 +10,7 @@
 
 namespace spa2 {
 
+constexpr int64_t VD_CACHE_BYTES = 256ll << 20;      // memory-side cache of the card
 constexpr int VD_MAX_WGS = 2048;      // workgroups of the loss pass = partial sums kept in the workspace
 
 __device__ __forceinline__ float vd_bf16_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
@@ -68,22 +69,35 @@ __global__ __launch_bounds__(256) void vd_loss_kernel(const void* us, const void
   if (tid == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-__global__ __launch_bounds__(64) void vd_loss_finish(const double* part, int count, double weight, double* loss) {
-  double s = 0.0;
-  for (int c = threadIdx.x; c < count; c += 64) s += part[c];
+// Adds the partial sums in a fixed order.  Bound: one load latency (all of a thread's loads are in flight together; one
+// wave that walked them took 9.2 us for 2048, this takes 4.6 us).
+__global__ __launch_bounds__(256) void vd_loss_finish(const double* part, int count, double weight, double* loss) {
+  constexpr int PER = VD_MAX_WGS / 256;
+  __shared__ double red[4];
+  double x[PER], s = 0.0;
+#pragma unroll
+  for (int c = 0; c < PER; ++c) x[c] = part[min((int)threadIdx.x + 256 * c, count - 1)];
+#pragma unroll
+  for (int c = 0; c < PER; ++c) s += (int)threadIdx.x + 256 * c < count ? x[c] : 0.0;
 #pragma unroll
   for (int k = 32; k >= 1; k >>= 1) s += __shfl_xor(s, k, 64);
-  if (threadIdx.x == 0) *loss = weight * s;
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) *loss = weight * (((red[0] + red[1]) + red[2]) + red[3]);
 }
 
-template <bool BF16>
+template <bool BF16, bool PAST_CACHE>
 __global__ __launch_bounds__(256) void vd_grad_kernel(const void* us, const void* uf, int64_t n, double coef,
                                                       const double* upstream, void* grad) {
   constexpr int VEC = BF16 ? 8 : 4;
   const int tid = threadIdx.x;
   const int64_t nvec = n / VEC;
   const float g = (float)(upstream ? coef * *upstream : coef);
-  for (int64_t v = (int64_t)blockIdx.x * 256 + tid; v < nvec; v += (int64_t)gridDim.x * 256) {
+  // From the end to the start, and past the cache (PAST_CACHE) where the three tensors do not fit in it: the gradient
+  // pass then begins with what the loss pass has read last, and what it has read last itself, the start of the
+  // predictions, is still there for the next pass over them.  Measured with 2 x 201 MB of fp32: gradient 99 us either
+  // way, loss 90 -> 66 us where the same predictions come again, 90 us on new ones.
+  for (int64_t v = nvec - 1 - ((int64_t)blockIdx.x * 256 + tid); v >= 0; v -= (int64_t)gridDim.x * 256) {
     float d[8];
     vd_diffs<BF16>(us, uf, v, d);
     u32x4 out;
@@ -92,7 +106,8 @@ __global__ __launch_bounds__(256) void vd_grad_kernel(const void* us, const void
       if (BF16) out[c] = vd_to_bf16(g * d[2 * c]) | (vd_to_bf16(g * d[2 * c + 1]) << 16);
       else      out[c] = __builtin_bit_cast(uint32_t, g * d[c]);
     }
-    ((u32x4*)grad)[v] = out;
+    if (PAST_CACHE) __builtin_nontemporal_store(out, (u32x4*)grad + v);
+    else            ((u32x4*)grad)[v] = out;
   }
   if (blockIdx.x == 0 && nvec * VEC + tid < n) {
     const int64_t e = nvec * VEC + tid;
@@ -117,15 +132,17 @@ hipError_t launch_vd_loss(const void* us, const void* uf, int64_t n, bool bf16, 
   else      hipLaunchKernelGGL(vd_loss_kernel<false>, dim3(grid), dim3(256), 0, stream, us, uf, n, (double*)ws);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(vd_loss_finish, dim3(1), dim3(64), 0, stream, (const double*)ws, (int)grid, weight, loss);
+  hipLaunchKernelGGL(vd_loss_finish, dim3(1), dim3(256), 0, stream, (const double*)ws, (int)grid, weight, loss);
   return hipGetLastError();
 }
 
 hipError_t launch_vd_grad(const void* us, const void* uf, int64_t n, bool bf16, double weight, const double* upstream,
                           void* grad, hipStream_t stream) {
   const unsigned grid = vd_grid(n, bf16);
-  if (bf16) hipLaunchKernelGGL(vd_grad_kernel<true>, dim3(grid), dim3(256), 0, stream, us, uf, n, 2.0 * weight, upstream, grad);
-  else      hipLaunchKernelGGL(vd_grad_kernel<false>, dim3(grid), dim3(256), 0, stream, us, uf, n, 2.0 * weight, upstream, grad);
+  const bool past_cache = 3 * n * (bf16 ? 2 : 4) > VD_CACHE_BYTES;
+  const auto kernel = bf16 ? (past_cache ? vd_grad_kernel<true, true> : vd_grad_kernel<true, false>)
+                           : (past_cache ? vd_grad_kernel<false, true> : vd_grad_kernel<false, false>);
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, us, uf, n, 2.0 * weight, upstream, grad);
   return hipGetLastError();
 }
 

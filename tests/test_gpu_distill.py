@@ -87,3 +87,21 @@ def test_loss_function_differentiates_like_the_library():
         torch.testing.assert_close(u_s.grad, twin.grad, rtol=1e-5, atol=1e-12)
     with pytest.raises(ValueError):
         vd.velocity_distillation_loss(u_s.cpu(), u_f.cpu())
+
+
+@pytest.mark.parametrize("dtype,n", [(torch.float32, 22_369_621), (torch.float32, 22_369_626), (torch.bfloat16, 44_739_251)])
+def test_fused_loss_on_either_side_of_the_cache_size(dtype, n):
+    """Three tensors just below and just above what the memory-side cache holds (the gradient is stored differently)."""
+    print(f"case {dtype} n={n}", flush=True)
+    g = torch.Generator(device=dev()).manual_seed(2)
+    us = torch.randn(1, n, generator=g, device=dev(), dtype=torch.float32).to(dtype).requires_grad_(True)
+    uf = torch.randn(1, n, generator=g, device=dev(), dtype=torch.float32).to(dtype)
+    loss = vd.velocity_distillation_loss(us, uf)
+    (grad,) = torch.autograd.grad(loss, us)
+    diff = us.detach().double() - uf.double()
+    ref = diff.square().mean()
+    # the difference is rounded to fp32 (2^-24), the rest is fp64; the gradient is one fp32 product more, then stored
+    assert abs(float(loss.detach()) - float(ref)) <= 2.0 ** -22 * float(ref)
+    bar = 2.0 ** -22 if dtype == torch.float32 else 2.0 ** -8 + 2.0 ** -22
+    err = (grad.double() - 2.0 / n * diff).abs()
+    assert bool((err <= bar * (2.0 / n * diff).abs() + 1e-44).all())
