@@ -28,6 +28,13 @@ def _match(x: torch.Tensor, ref: torch.Tensor) -> torch.Tensor:
     return y
 
 
+def _same_place(q: torch.Tensor, *others: torch.Tensor) -> None:
+    """Shape, type and device of q (the strides are _match's)."""
+    for t in others:
+        if t.shape != q.shape or t.dtype != q.dtype or t.device != q.device:
+            raise ValueError("all token tensors of one call share shape, strides, dtype and device")
+
+
 def _check_inputs(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor) -> None:
     for name, t in (("q", q), ("k", k), ("v", v)):
         if not t.is_cuda:
@@ -47,10 +54,12 @@ def build_pattern(q: torch.Tensor, k: torch.Tensor, k_frac: float, top_p: float,
     B, H, N, d = q.shape
     scale = 1.0 / math.sqrt(d) if scale is None else float(scale)
     k = _match(k, q)
+    lay = _b._layout_of(q)
+    _same_place(q, k)
     pat = _b.alloc_pattern(B, H, N, q.device, columns=columns)
-    ws = torch.empty(_b.spa2_mask_workspace_bytes(q), dtype=torch.uint8, device=q.device)
-    k_cnt = _b.spa2_topk_blocks(float(k_frac), -(-N // _b.BKV))
-    _b.spa2_mask(q, k, k_cnt, float(top_p), scale, pat, None, ws)
+    ws = torch.empty(lay.mask_ws, dtype=torch.uint8, device=q.device)
+    k_cnt = _b.spa2_topk_blocks(float(k_frac), lay.Tn)
+    _b._mask_call(lay, q, k, k_cnt, float(top_p), scale, pat, ws, _b._stream(q))
     return pat
 
 
@@ -89,11 +98,12 @@ def backward_two_streams(q, k, v, o, d_o, lse, pattern, scale, dq, dk, dv, works
 def _forward(q, k, v, scale, pattern, residual: bool):
     """(k, v in q's layout), O, its bf16 residual (or None) and LSE."""
     k, v = _match(k, q), _match(v, q)
-    B, H, N, _ = q.shape
+    lay = _b._layout_of(q)
+    _same_place(q, k, v)
     o, o_res = _like(q), _like(q) if residual else None
-    lse = torch.empty((B, H, N), dtype=torch.float32, device=q.device)
-    ws_f = torch.empty(_b.spa2_fwd_workspace_bytes(q), dtype=torch.uint8, device=q.device)   # long rows split
-    _b.spa2_fwd(q, k, v, pattern, scale, o, lse, o_res, ws_f)
+    lse = torch.empty(q.shape[:3], dtype=torch.float32, device=q.device)
+    ws_f = torch.empty(lay.fwd_ws, dtype=torch.uint8, device=q.device)   # long rows split
+    _b._fwd_call(lay, q, k, v, pattern, scale, o, o_res, lse, ws_f, _b._stream(q))
     return k, v, o, o_res, lse
 
 
@@ -109,12 +119,14 @@ class _SpargeAttn2(torch.autograd.Function):
     def backward(ctx, d_o):
         q, k, v, o, o_res, lse = ctx.saved_tensors
         d_o = _match(d_o.to(torch.bfloat16), q)
+        lay = _b._layout_of(q)
+        _same_place(q, d_o)
         dq, dk, dv = _like(q), _like(q), _like(q)
-        ws = torch.empty(_b.spa2_bwd_workspace_bytes(q), dtype=torch.uint8, device=q.device)
+        ws = torch.empty(lay.bwd_ws, dtype=torch.uint8, device=q.device)
         if ctx.overlap:
             backward_two_streams(q, k, v, o, d_o, lse, ctx.pattern, ctx.scale, dq, dk, dv, ws, o_res)
         else:
-            _b.spa2_bwd(q, k, v, o, d_o, lse, ctx.pattern, ctx.scale, dq, dk, dv, ws, o_res)
+            _b._bwd_call(lay, q, k, v, o, o_res, d_o, lse, ctx.pattern, ctx.scale, dq, dk, dv, ws, _b._stream(q))
         return dq, dk, dv, None, None, None
 
 

@@ -11,6 +11,7 @@ from __future__ import annotations
 
 import ctypes
 import dataclasses
+import functools
 import os
 from typing import Optional
 
@@ -155,6 +156,32 @@ def _shape_of(x: torch.Tensor) -> _Shape:
     return _Shape(B, H, N, d, BQ, BKV, x.stride(0), x.stride(1), x.stride(2))
 
 
+class _Layout:
+    """The C description of a token tensor's layout and the workspace sizes that follow from it."""
+    __slots__ = ("shape", "ref", "Tm", "Tn", "mask_ws", "fwd_ws", "bwd_ws")
+
+    def __init__(self, sizes, strides):
+        B, H, N, d = sizes
+        self.shape = _Shape(B, H, N, d, BQ, BKV, strides[0], strides[1], strides[2])
+        self.ref = ctypes.byref(self.shape)
+        self.Tm, self.Tn = -(-N // BQ), -(-N // BKV)
+        lib = _load()
+        self.mask_ws = int(lib.spa2_mask_workspace_bytes(self.ref))
+        self.fwd_ws = int(lib.spa2_fwd_workspace_bytes(self.ref))
+        self.bwd_ws = int(lib.spa2_bwd_workspace_bytes(self.ref))
+
+
+# one per sizes and strides (values, not tensors; never written after it is made, so threads may share it)
+_layout_for = functools.lru_cache(maxsize=256)(_Layout)
+
+
+def _layout_of(x: torch.Tensor) -> _Layout:
+    """_shape_of with the sizes that go with it; the operator asks once per call instead of once per C function."""
+    if x.dim() != 4 or x.dtype != torch.bfloat16 or x.stride(3) != 1:
+        _shape_of(x)                      # raises
+    return _layout_for(tuple(x.shape), x.stride())
+
+
 def _same_layout(ref: torch.Tensor, *others: torch.Tensor):
     for t in others:
         if t.shape != ref.shape or t.stride() != ref.stride() or t.dtype != ref.dtype or t.device != ref.device:
@@ -163,6 +190,27 @@ def _same_layout(ref: torch.Tensor, *others: torch.Tensor):
 
 def _stream(x: torch.Tensor) -> int:
     return torch.cuda.current_stream(x.device).cuda_stream
+
+
+def _ptr(x: Optional[torch.Tensor]) -> Optional[int]:
+    return None if x is None else x.data_ptr()
+
+
+# ------------------------------------------------------------------ the operator's calls: layouts checked by the caller
+def _mask_call(lay: _Layout, q, k, topk_blocks: int, top_p: float, scale: float, out: "Pattern", ws, stream: int) -> None:
+    _check(_load().spa2_mask(q.data_ptr(), k.data_ptr(), lay.ref, topk_blocks, top_p, scale, ctypes.byref(out._c()), None,
+                             ws.data_ptr(), lay.mask_ws, stream), "spa2_mask")
+
+
+def _fwd_call(lay: _Layout, q, k, v, pattern: "Pattern", scale: float, o, o_res, lse, ws, stream: int) -> None:
+    _check(_load().spa2_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), lay.ref, ctypes.byref(pattern._c()), scale,
+                            o.data_ptr(), _ptr(o_res), lse.data_ptr(), ws.data_ptr(), lay.fwd_ws, stream), "spa2_fwd")
+
+
+def _bwd_call(lay: _Layout, q, k, v, o, o_res, d_o, lse, pattern: "Pattern", scale: float, dq, dk, dv, ws, stream: int) -> None:
+    _check(_load().spa2_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), _ptr(o_res), d_o.data_ptr(),
+                            lse.data_ptr(), lay.ref, ctypes.byref(pattern._c()), scale, dq.data_ptr(), dk.data_ptr(),
+                            dv.data_ptr(), ws.data_ptr(), lay.bwd_ws, stream), "spa2_bwd")
 
 
 def _check(rc: int, where: str):
