@@ -25,10 +25,11 @@ namespace spa2 {
 // 5 to 15 %): 20,010 tokens d = 64, 20 groups of sixteen rows 15.7 / 19.7, 240 groups 36.4 / 21.9; 32,760 tokens
 // d = 128, 32 groups 21.2 / 31.4, 192 groups 34.3 / 32.1; 75,600 tokens d = 128, 222 groups 86 / 57; 131,042 tokens
 // d = 64, 128 groups 57 / 65, 256 groups 109 / 70; 16 blocks a row 13.5 / 9.7.
+constexpr int SEL16_FOUR_D64 = 1536, SEL16_FOUR_D128 = 1280;     // widest rows of the four-wave workgroups
 static int select16_waves(const Dims& m) {
   const int64_t wgs = (int64_t)m.B * m.H * ((m.Tm + 15) / 16);
   if (m.Tn > 2048 || (wgs < 128 && m.Tn > 128)) return 0;
-  return wgs >= 1024 && m.Tn <= (m.d == 128 ? 1280 : 1536) ? 4 : 8;
+  return wgs >= 1024 && m.Tn <= (m.d == 128 ? SEL16_FOUR_D128 : SEL16_FOUR_D64) ? 4 : 8;
 }
 
 // ------------------------------------------------------------------ pooling
@@ -706,8 +707,9 @@ static void launch_select16_t(const SelArgs& a0, int BH, hipStream_t stream) {
   SelArgs a = a0;
   a.groups = (a.Tm + 15) / 16;
   const dim3 grid((unsigned)(BH * a.groups)), block(64 * WV);
-  if (a.d == 128) hipLaunchKernelGGL((select16_kernel<NP, 128, WV>), grid, block, 0, stream, a);
-  else            hipLaunchKernelGGL((select16_kernel<NP, 64, WV>), grid, block, 0, stream, a);
+  if (a.d == 64) hipLaunchKernelGGL((select16_kernel<NP, 64, WV>), grid, block, 0, stream, a);
+  else if constexpr (WV == 8 || NP <= SEL16_FOUR_D128)
+    hipLaunchKernelGGL((select16_kernel<NP, 128, WV>), grid, block, 0, stream, a);
 }
 
 hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, int topk_blocks, float top_p,
