@@ -124,7 +124,10 @@ class _SpargeAttn2(torch.autograd.Function):
         q, k, v, o, o_res, lse = ctx.saved_tensors
         d_o = _match(d_o.to(torch.bfloat16), q)
         lay = _b._layout_of(q)
-        _same_place(q, d_o)
+        # (all of them, not d_o alone: saved-tensor hooks may bring a tensor back in another layout)
+        _b._same_layout(q, k, v, o, o_res, d_o)
+        if not lse.is_contiguous():
+            raise ValueError("the log-sum-exp must be contiguous")
         dq, dk, dv = _like(q), _like(q), _like(q)
         ws = torch.empty(lay.bwd_ws, dtype=torch.uint8, device=q.device)
         if ctx.overlap:

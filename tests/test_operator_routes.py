@@ -91,3 +91,35 @@ def test_inputs_with_tangents_are_refused(grad):
         assert torch.equal(_attention(q, k, v), v)
         with pytest.raises(RuntimeError):
             _attention(q, k, fwad.make_dual(v, torch.ones_like(v)))
+
+
+def _relaid(x):
+    """The same values in memory of another layout (what a hook that packs with .contiguous() makes of a view)."""
+    return x.transpose(1, 2).contiguous().transpose(1, 2)
+
+
+@pytest.mark.parametrize("which", ["q", "k", "v", "o", "o_res", "lse"])
+def test_saved_tensors_that_come_back_in_another_layout_are_refused(which):
+    """The backward kernels take one stride triple for all token tensors: a saved-tensor hook that changes one of them
+    must not be read through the strides of another."""
+    n = 0
+
+    def pack(x):
+        nonlocal n
+        n += 1                                        # saved in this order: q, k, v, o, o_res, lse
+        return _relaid(x.detach()) if n - 1 == ("q", "k", "v", "o", "o_res", "lse").index(which) else x.detach()
+
+    q, k, v = (t.requires_grad_(True) for t in _qkv(6))
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda x: x):
+        o = _attention(q, k, v)
+    assert n == 6
+    with pytest.raises(ValueError):
+        o.backward(torch.ones_like(o))
+
+
+def test_saved_tensors_that_come_back_as_copies_are_accepted():
+    q, k, v = (t.requires_grad_(True) for t in _qkv(7))
+    with torch.autograd.graph.saved_tensors_hooks(lambda x: x.detach().clone(), lambda x: x.clone()):
+        o = _attention(q, k, v)
+    (dv,) = torch.autograd.grad(o, v, torch.ones_like(o))
+    assert torch.equal(dv, torch.ones_like(v))
