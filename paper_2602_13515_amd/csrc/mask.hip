@@ -703,13 +703,16 @@ static void launch_select_t(const SelArgs& a0, int BH, hipStream_t stream) {
 }
 
 template <int NP, int WV>
-static void launch_select16_t(const SelArgs& a0, int BH, hipStream_t stream) {
+static hipError_t launch_select16_t(const SelArgs& a0, int BH, hipStream_t stream) {
   SelArgs a = a0;
   a.groups = (a.Tm + 15) / 16;
   const dim3 grid((unsigned)(BH * a.groups)), block(64 * WV);
   if (a.d == 64) hipLaunchKernelGGL((select16_kernel<NP, 64, WV>), grid, block, 0, stream, a);
   else if constexpr (WV == 8 || NP <= SEL16_FOUR_D128)
     hipLaunchKernelGGL((select16_kernel<NP, 128, WV>), grid, block, 0, stream, a);
+  else
+    return hipErrorInvalidConfiguration;      // (select16_waves asked for a width that is not instantiated)
+  return hipGetLastError();
 }
 
 hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, int topk_blocks, float top_p,
@@ -722,12 +725,13 @@ hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, in
   const int BH = m.B * m.H;
   // the smallest instantiated width that holds the row: steps of 256 up to 2048, of 512 up to 4096, then of 1024
   const int waves = select16_waves(m);        // (the pooling pass has laid out the pooled keys for this kernel)
-#define SPA2_SELECT16_CASE(wv, np) if (waves == wv && m.Tn <= np) { launch_select16_t<np, wv>(a, BH, stream); return hipGetLastError(); }
+#define SPA2_SELECT16_CASE(wv, np) if (waves == wv && m.Tn <= np) return launch_select16_t<np, wv>(a, BH, stream);
   SPA2_SELECT16_CASE(4, 256)  SPA2_SELECT16_CASE(4, 512)  SPA2_SELECT16_CASE(4, 768)  SPA2_SELECT16_CASE(4, 1024)
   SPA2_SELECT16_CASE(4, 1280) SPA2_SELECT16_CASE(4, 1536)
   SPA2_SELECT16_CASE(8, 256)  SPA2_SELECT16_CASE(8, 512)  SPA2_SELECT16_CASE(8, 768)  SPA2_SELECT16_CASE(8, 1024)
   SPA2_SELECT16_CASE(8, 1280) SPA2_SELECT16_CASE(8, 1536) SPA2_SELECT16_CASE(8, 1792) SPA2_SELECT16_CASE(8, 2048)
 #undef SPA2_SELECT16_CASE
+  if (waves) return hipErrorInvalidConfiguration;        // (as above; the four-row kernels read the keys in another layout)
 #define SPA2_SELECT_CASE(np) if (m.Tn <= np) { launch_select_t<np, 4>(a, BH, stream); return hipGetLastError(); }
   SPA2_SELECT_CASE(256)  SPA2_SELECT_CASE(512)  SPA2_SELECT_CASE(768)  SPA2_SELECT_CASE(1024)
   SPA2_SELECT_CASE(1280) SPA2_SELECT_CASE(1536) SPA2_SELECT_CASE(1792) SPA2_SELECT_CASE(2048)

@@ -121,8 +121,9 @@ MASK_CASES = [
     ("very-short", _small("vs", 100, 64, H=1), 0.5, 0.5),
     ("longest-row", _small("max", 64 * 8192 - 30, 64, kind="lowrank", H=1), 0.01, 0.3),   # Tn = 8192, the widest row
     ("everything", _small("all", 3000, 128, H=2), 1.0, 1.0),                              # k = 100 %: full mask
-    # layers with many (batch, head) pairs and rows of at most 1536 blocks take the sixteen-rows-per-workgroup
-    # selection kernel (scores on the fp64 matrix cores), like the 75,600-token layer of test_gpu_fullsize.py:
+    # layers with many (batch, head) pairs and rows of at most 2048 blocks take the sixteen-rows-per-workgroup
+    # selection kernel (scores on the fp64 matrix cores; four or eight waves by launch and width, see
+    # test_gpu_select.py), like the 75,600-token layer of test_gpu_fullsize.py:
     # both head dimensions, ragged last row group and last column tile, hybrid / Top-p-only / Top-k-only
     ("many-heads-d64", _small("mh64", 16384 - 37, 64, kind="lowrank", H=16, B=8), 0.1, 0.7),        # T_n = 256
     ("many-heads-d64-topp-only", _small("mh64p", 16384 - 37, 64, kind="lowrank", H=16, B=8), 0.0, 0.6),

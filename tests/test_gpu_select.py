@@ -1,5 +1,6 @@
-"""The selection kernels at the edges of their ranges: row widths on either side of an instantiation, of the rule that
-chooses between four and sixteen rows per workgroup, and of the sixteen-row kernel's last row group."""
+"""The selection kernels at the edges of their ranges: row widths and launch sizes on either side of the rules that choose
+between four and sixteen rows per workgroup and between four and eight waves for the latter, and the sixteen-row
+kernel's last row group."""
 import numpy as np
 import pytest
 
@@ -23,6 +24,16 @@ CASES = [                                   # H, N, d, kind
     (1, 64 * 2048, 128, "stress"),          # widest row of the sixteen-row kernel, too few workgroups for it
     (2, 64 * 2049 - 64, 64, "gaussian"),    # 2048 blocks
     (2, 64 * 2049, 64, "lowrank"),          # 2049: four rows per workgroup
+    # launches of 1024 groups of sixteen rows and more: four waves up to 1536 (d = 64) and 1280 (d = 128) blocks a row
+    (1023, 64 * 20, 64, "gaussian"),        # one group short
+    (1024, 64 * 20 - 7, 128, "lowrank"),
+    (32, 64 * 1025 - 3, 64, "lowrank"),     # 1056 groups, the last of one row
+    (26, 64 * 1280, 64, "stress"),          # the 1280-wide instantiation filled
+    (25, 64 * 1281 - 60, 64, "lowrank"),    # 1025 groups; the widest four-wave instantiation, and its last row
+    (22, 64 * 1536, 64, "lowrank"),
+    (22, 64 * 1537, 64, "lowrank"),         # eight waves
+    (26, 64 * 1280 - 1, 128, "lowrank"),    # d = 128: the widest row of the four-wave workgroups
+    (25, 64 * 1281, 128, "stress"),         # eight waves
 ]
 
 
@@ -30,7 +41,7 @@ CASES = [                                   # H, N, d, kind
 def test_selection_at_the_edges(H, N, d, kind):
     print(f"case H={H} N={N} d={d} {kind}", flush=True)
     w = wl.Workload("edge", 1, H, N, d, 0.05, 0.7, kind, False)
-    q, k, _, _ = wl.make_inputs(w, seed=6, need_do=False)
+    q, k, _, _ = wl.make_inputs(w, seed=6, need_do=False, device="cpu" if H <= 16 else dev())     # (the large ones: drawn there)
     k_cnt = spa2.spa2_topk_blocks(w.k_frac, w.Tn)
     pat, pbar = gpu_mask(q.to(dev()), k.to(dev()), k_cnt, w.top_p, columns=False)
     mask, cnt, idx = (t.cpu().numpy() for t in (pat.mask, pat.row_cnt, pat.row_idx))
@@ -38,5 +49,5 @@ def test_selection_at_the_edges(H, N, d, kind):
     for h in sorted({0, H - 1}):
         for i in range(w.Tm):
             assert np.array_equal(idx[0, h, i, :cnt[0, h, i]], np.flatnonzero(mask[0, h, i]))
-        r = mask_protocol(mask[0, h], pbar[0, h].cpu().numpy(), orc.pooled_map(f64(q)[0, h], f64(k)[0, h]), k_cnt, w.top_p)
+        r = mask_protocol(mask[0, h], pbar[0, h].cpu().numpy(), orc.pooled_map(f64(q[0, h]), f64(k[0, h])), k_cnt, w.top_p)
         assert r["stage1_max_rel"] <= 1e-5 and r["stage2_unexplained"] == 0 and r["stage3_unexplained"] == 0, r
