@@ -99,7 +99,41 @@ def gpu_mask(q, k, k_cnt, top_p, scale=None, want_pbar=True, columns=True):
     return pat, pbar
 
 
-def gpu_fwd(q, k, v, pat, scale=None, residual=False, split=True):
+# ---- what a call's split plans say (header of a plan: number of parts, list entries per part at most).  The forward
+# workspace is one plan section, the backward workspace holds D, the section of the dQ kernel and that of the dK/dV one.
+def _plan_section_bytes(units, list_max, slot_floats):
+    up = lambda x: -(-x // 256) * 256
+    per_unit = min(max(list_max // 2, 1), 16)
+    pool = 8
+    while pool < 2048 and pool < per_unit * units:
+        pool *= 2
+    return up(256 + up(units * 4) + up(pool * 16) + up(pool * 4) + pool * slot_floats * 4)
+
+
+def plan_offsets(q):
+    B, H, N, d = q.shape
+    Tm, Tn = -(-N // spa2.BQ), -(-N // spa2.BKV)
+    at = spa2.spa2_bwd_workspace_min_bytes(q)
+    return {"fwd": 0, "dq": at, "dkdv": at + _plan_section_bytes(B * H * Tm, Tn, 256 * (d // 2))}
+
+
+def plan_headers(q, ws, names=("dq", "dkdv")):
+    """{name: (parts, entries per part)} of the plans in a forward (names = ("fwd",)) or backward workspace."""
+    off = plan_offsets(q)
+    return {n: tuple(ws[off[n]:off[n] + 8].view(torch.int32).tolist()) for n in names}
+
+
+def check_plan(name, header, lengths):
+    """The plan cut every list longer than its part length, and no other.  Returns the part length."""
+    parts, S = header
+    lengths = lengths.astype(np.int64)
+    cut = lengths[lengths > S]
+    print(f"{name}: parts of at most {S} entries; {cut.size} of {lengths.size} lists cut into {parts} parts", flush=True)
+    assert parts == int((-(-cut // S)).sum()), (name, header)
+    return S
+
+
+def gpu_fwd(q, k, v, pat, scale=None, residual=False, split=True, plans=None):
     B, H, N, d = q.shape
     scale = 1.0 / math.sqrt(d) if scale is None else scale
     g = Guarded()
@@ -111,10 +145,12 @@ def gpu_fwd(q, k, v, pat, scale=None, residual=False, split=True):
     spa2.spa2_fwd(q, k, v, pat, scale, o, lse, o_res, ws)
     torch.cuda.synchronize()
     g.check("spa2_fwd")
+    if plans is not None:
+        plans.update(plan_headers(q, ws, ("fwd",)))
     return (o, lse, o_res) if residual else (o, lse)
 
 
-def gpu_bwd(q, k, v, o, do, lse, pat, scale=None, o_res=None, split=True):
+def gpu_bwd(q, k, v, o, do, lse, pat, scale=None, o_res=None, split=True, plans=None):
     d = q.shape[-1]
     scale = 1.0 / math.sqrt(d) if scale is None else scale
     g = Guarded()
@@ -124,6 +160,8 @@ def gpu_bwd(q, k, v, o, do, lse, pat, scale=None, o_res=None, split=True):
     spa2.spa2_bwd(q, k, v, o, do, lse, pat, scale, dq, dk, dv, ws, o_res)
     torch.cuda.synchronize()
     g.check("spa2_bwd")
+    if plans is not None:
+        plans.update(plan_headers(q, ws))
     return dq, dk, dv
 
 

@@ -12,7 +12,7 @@ import paper_2602_13515_amd as spa2
 from oracle import spa2_oracle as orc
 from paper_2602_13515_amd import workloads as wl
 
-from gpu_util import (LOWRANK_MAX_ABS, assert_close, check_pattern_consistency, dev, f64, gpu_bwd, gpu_fwd, gpu_mask,
+from gpu_util import (LOWRANK_MAX_ABS, assert_close, check_pattern_consistency, check_plan, dev, f64, gpu_bwd, gpu_fwd, gpu_mask,
                       mask_protocol, pattern_from_mask)
 
 pytestmark = pytest.mark.gpu
@@ -355,9 +355,9 @@ def test_whole_step_replays_from_a_hip_graph():
 
 def test_long_rows_and_columns_are_split_and_merged():
     """A small layer whose longest rows and columns are several times the split length (Top-p-bound rows of the
-    low-rank recipe, hot key blocks): with the workspaces, lists longer than S = max(16, tiles / 2048) are walked by
+    low-rank recipe, hot key blocks): with the workspaces, lists longer than the plan's part length are walked by
     several workgroups and merged in part order (Alg. 1 step 18: the final division makes the merge of (O, m, l)
-    exact up to rounding).  Results must match the oracle to the same bars as the unsplit path, agree with the
+    exact up to rounding).  The plans are read back: every such list was cut.  Results must match the oracle to the same bars as the unsplit path, agree with the
     unsplit path to rounding, and be bit-identical from run to run."""
     w = _small("split", 9000, 128, kind="lowrank", H=2, k=0.05, p=0.8)          # T_m = 71, T_n = 141
     q, k, v, do = wl.make_inputs(w, seed=21)
@@ -366,16 +366,15 @@ def test_long_rows_and_columns_are_split_and_merged():
     pat, _ = gpu_mask(qd, kd, k_cnt, w.top_p, want_pbar=False)
     mask = check_pattern_consistency(pat)
     rc, cc = mask.sum(-1), mask.sum(-2)
-    tiles = int(mask.sum())
-    S_rows, S_cols = max(16, -(-tiles // 2048)), max(8, -(-tiles // 2048))
-    print(f"tiles {tiles}; longest row {rc.max()} (split length {S_rows}), longest column {cc.max()} (split length {S_cols}); "
-          f"rows split {(rc > S_rows).sum()}, columns split {(cc > S_cols).sum()}", flush=True)
-    assert rc.max() > 3 * S_rows and cc.max() > 3 * S_cols, "the case must exercise several parts per list"
     runs = []
     for split in (True, True, False):
-        o, lse, o_res = gpu_fwd(qd, kd, vd, pat, residual=True, split=split)
-        dq, dk, dv = gpu_bwd(qd, kd, vd, o, dod, lse, pat, o_res=o_res, split=split)
+        plans = {} if split else None
+        o, lse, o_res = gpu_fwd(qd, kd, vd, pat, residual=True, split=split, plans=plans)
+        dq, dk, dv = gpu_bwd(qd, kd, vd, o, dod, lse, pat, o_res=o_res, split=split, plans=plans)
         runs.append((o, lse, o_res, dq, dk, dv))
+        if split:
+            for name, lengths in (("fwd", rc), ("dq", rc), ("dkdv", cc)):
+                assert lengths.max() > 3 * check_plan(name, plans[name], lengths), "the case must exercise several parts per list"
     for a, b in zip(runs[0], runs[1]):
         assert torch.equal(a, b), "split results must not depend on the order in which parts finish"
     r_dq, r_dk, r_dv, r_o, r_lse = orc.attention_bwd_bh(f64(q), f64(k), f64(v), mask, f64(do))

@@ -1,6 +1,7 @@
 """Lists around the part length of the split plan: one entry, exactly one part, one entry more, last parts of one entry,
-the whole range; with the full workspace, with one whose pool is too small for the first choice of part length, and
-with none.  Each against the fp64 oracle, twice for the same bits."""
+the whole range; with the full workspace, with ones whose pool (of the forward and the dQ kernel, of the dK/dV kernel)
+is too small for the first choice of part length, and with none.  Each against the fp64 oracle, twice for the same
+bits."""
 import math
 
 import numpy as np
@@ -11,7 +12,7 @@ import paper_2602_13515_amd as spa2
 from oracle import spa2_oracle as orc
 from paper_2602_13515_amd import workloads as wl
 
-from gpu_util import assert_close, dev, f64, pattern_from_mask
+from gpu_util import assert_close, check_plan, dev, f64, pattern_from_mask, plan_headers, plan_offsets
 
 pytestmark = pytest.mark.gpu
 
@@ -31,7 +32,7 @@ def _mask(H, Tm, Tn):
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("N", [2500, 40])
-@pytest.mark.parametrize("space", ["full", "small", "none"])
+@pytest.mark.parametrize("space", ["full", "small", "columns", "none"])
 def test_part_edges(d, N, space):
     w = wl.Workload("parts", 1, 2, N, d, 0.1, 0.5, "gaussian", True)
     print(f"case d={d} N={N} workspace={space}", flush=True)
@@ -40,8 +41,11 @@ def test_part_edges(d, N, space):
     qd, kd, vd, dod = (t.to(dev()) for t in (q, k, v, do))
     pat = pattern_from_mask(mask, dev())
     nf, nb, nmin = (f(qd) for f in (spa2.spa2_fwd_workspace_bytes, spa2.spa2_bwd_workspace_bytes, spa2.spa2_bwd_workspace_min_bytes))
-    if space == "small":        # room for a few slots only: the plan has to take longer parts
-        nf, nb = nf // 8, nmin + (nb - nmin) // 8
+    dkdv_at = plan_offsets(qd)["dkdv"]
+    if space == "small":        # room for a few slots only: the plans have to take longer parts (none for the columns)
+        nf, nb = nf // 8, nmin + (nb - nmin) // 32
+    elif space == "columns":    # the same for the columns alone
+        nb = dkdv_at + (nb - dkdv_at) // 16
     elif space == "none":
         nf, nb = 0, nmin
     runs = []
@@ -53,6 +57,16 @@ def test_part_edges(d, N, space):
         spa2.spa2_fwd(qd, kd, vd, pat, 1 / math.sqrt(d), o, lse, o_res, ws_f)
         spa2.spa2_bwd(qd, kd, vd, o, dod, lse, pat, 1 / math.sqrt(d), dq, dk, dv, ws_b, o_res)
         torch.cuda.synchronize()
+        if space == "full" or (space != "none" and N > 40):      # (40 tokens: nothing to cut, and no room for small plans)
+            plans = plan_headers(qd, ws_b, ("dq",) if space == "small" else ("dq", "dkdv")) | plan_headers(qd, ws_f, ("fwd",))
+            for name, header in plans.items():
+                lengths = mask.sum(-2 if name == "dkdv" else -1)
+                S = check_plan(name, header, lengths)
+                assert N == 40 or lengths.max() > S, f"{name}: the case must cut some lists"
+                if N > 40:      # the part length that the rule asks for on this pattern, longer where the pool is small
+                    small = space == "small" or (space == "columns" and name == "dkdv")
+                    first = {"fwd": 8, "dq": 8, "dkdv": 4}[name]
+                    assert S > first if small else S == first, (name, header)
         runs.append((o, lse, o_res, dq, dk, dv))
         # the stage calls make their own plans: same bits as the composite call
         dq2, dk2, dv2 = (torch.full_like(qd, float("nan")) for _ in range(3))
