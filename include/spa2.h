@@ -101,7 +101,9 @@ int32_t spa2_topk_blocks(double k_frac, int32_t Tn);
  *   spa2_bwd_workspace_bytes       full backward workspace: D, then plans and partial results of split rows
  *                                  (dQ) and split columns (dK, dV).
  *   spa2_bwd_workspace_min_bytes   the mandatory leading part of it (D only).  With a buffer between the two
- *                                  sizes the backward kernels split as many lists as the rest of it holds. */
+ *                                  sizes the kernels take longer parts, so that their results fit (as spa2_fwd does).
+ * The optional parts hold up to 16 fp32 partial results a list, 2048 in all: about 132 MiB a kernel (forward, dQ,
+ * dK/dV) on all but small layers (two heads of 2,048 tokens, d = 128: forward 33 MiB, backward 64 MiB). */
 size_t spa2_mask_workspace_bytes(const spa2_shape* shape);
 size_t spa2_fwd_workspace_bytes(const spa2_shape* shape);
 size_t spa2_bwd_workspace_bytes(const spa2_shape* shape);
@@ -156,9 +158,10 @@ int spa2_pattern_full(const spa2_shape* shape, spa2_pattern* out, void* stream);
  *   workspace  optional (NULL, 0 = none), 16-byte aligned, up to spa2_fwd_workspace_bytes(shape) bytes.  One
  *          workgroup walks one row of the pattern, so a launch cannot end before its longest row has; on layers
  *          with few rows per compute unit the longest rows then set the time.  With a workspace, lists longer than S
- *          entries (8 to 48 on small and ordinary layers, total tiles / 8192 on large ones) are cut into equal parts
- *          that run as workgroups of their own; the part that finishes last combines the (O, m, l) of all of them in
- *          part order (Alg. 1 step 18 makes that exact up to rounding), so results stay deterministic.
+ *          entries (8 to 48 on small and ordinary layers, total tiles / 8192 on large ones, more where the workspace
+ *          holds fewer partial results) are cut into equal parts that run as workgroups of their own; the part that
+ *          finishes last combines the (O, m, l) of all of them in part order (Alg. 1 step 18 makes that exact up to
+ *          rounding), so results stay deterministic.
  * Reads pattern->row_cnt / row_idx (and row_order if set). */
 int spa2_fwd(const void* q, const void* k, const void* v, const spa2_shape* shape,
              const spa2_pattern* pattern, float scale, void* o, void* o_res, float* lse,
@@ -175,7 +178,7 @@ int spa2_bwd(const void* q, const void* k, const void* v, const void* o, const v
              const void* d_o, const float* lse, const spa2_shape* shape, const spa2_pattern* pattern,
              float scale, void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes, void* stream);
 
-/* The three stages of spa2_bwd, callable one by one (spa2_bwd is exactly their sequence; a caller
+/* The three stages of spa2_bwd, callable one by one (spa2_bwd gives exactly the results of their sequence; a caller
  * that needs only dQ, or only dK and dV, skips the other):
  *   spa2_bwd_delta  D = rowsum(dO * (o + o_res)), fp32 [B,H,N], left in `workspace`;
  *   spa2_bwd_dkdv   dK, dV: one pass per key block over the query blocks listed in col_idx;

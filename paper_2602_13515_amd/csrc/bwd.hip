@@ -4,7 +4,8 @@
 //   P = exp(S - LSE) on selected tiles,  dV = P^T dO,  dP = dO V^T,  D = rowsum(dO * O),
 //   dS = P * (dP - D),  dQ = dS K * scale,  dK = dS^T Q * scale.
 //
-//   delta_kernel  D, one pass over O and dO.
+//   delta_kernel  D, one pass over O and dO (as a stage call; spa2_bwd makes the split plans in the same launch, see
+//                 bwd_prepare_kernel in split.hip).
 //   dq_kernel     one workgroup per query block, walking its row of the mask (same shape
 //                 as the forward kernel: a lane owns one query row).
 //   dkdv_kernel   one workgroup per key block, walking the query blocks that selected it.

@@ -93,10 +93,13 @@ __global__ __launch_bounds__(256) void vd_grad_kernel(const void* us, const void
   const int tid = threadIdx.x;
   const int64_t nvec = n / VEC;
   const float g = (float)(upstream ? coef * *upstream : coef);
-  // From the end to the start, and past the cache (PAST_CACHE) where the three tensors do not fit in it: the gradient
-  // pass then begins with what the loss pass has read last, and what it has read last itself, the start of the
-  // predictions, is still there for the next pass over them.  Measured with 2 x 201 MB of fp32: gradient 99 us either
-  // way, loss 90 -> 66 us where the same predictions come again, 90 us on new ones.
+  // From the end to the start: the pass then begins with what the loss pass has read last and ends with the part of the
+  // gradient that its reader, the student's backward pass, begins with.  Stored past the cache (PAST_CACHE) where the
+  // three tensors do not fit in it: the gradient then pushes no predictions out before they are read.  Measured on
+  // predictions that are new every time, gradient pass + an elementwise reader of the gradient (from the start, plain /
+  // from the end, plain / from the end, past the cache): 2 x 201 MB of fp32 107 + 64 / 105 + 63 / 103 + 60 us, 2 x 671 MB
+  // 393 + 214 / 383 + 212 / 381 + 205, 2 x 774 MB of bf16 419 + 244 / 413 + 245 / 407 + 238; 2 x 49 MB of fp32 29 + 17 all
+  // three ways.
   for (int64_t v = nvec - 1 - ((int64_t)blockIdx.x * 256 + tid); v >= 0; v -= (int64_t)gridDim.x * 256) {
     float d[8];
     vd_diffs<BF16>(us, uf, v, d);

@@ -227,9 +227,10 @@ __device__ __forceinline__ void sel_scan_pass(int pass, int sh, int lane, int r,
 // 32-bit range: b -> (b - b_min) << (leading zeros of b_max - b_min), with b_min / b_max the patterns of the row's
 // smallest / largest probability (non-negative floats order like their patterns; the map is increasing and keeps ties).
 // The top eight bits of a probability are its sign and seven exponent bits, the same three or four values for almost
-// every entry of a row: unmapped, the first pass of the descent would tell almost nothing apart, and its LDS atomics
-// would collide; mapped, a pass spreads a row over all 256 bins, the boundary bin holds a single entry after two passes
-// for most rows, and the row's descent stops there (see sel_scan_pass).
+// every entry of a row: unmapped, the first pass of the descent would tell almost nothing apart; mapped, a pass spreads
+// a row over all 256 bins, the boundary bin holds a single entry after two passes for most rows, and the row's descent
+// stops there (see sel_scan_pass).  The stop is the gain, fewer passes (0.39 -> 0.33 ms on 40 heads of 591 x 1182 blocks):
+// the map without it changes nothing.
 // e_min: the row's smallest exponential, tot: their sum (the largest exponential is exp(0) = 1).  Two patterns of margin
 // on either side keep the map inside 32 bits whatever the last bit of the two divisions is.
 __device__ __forceinline__ void spread_range(float e_min, float tot, uint32_t& b_min, int& shift) {

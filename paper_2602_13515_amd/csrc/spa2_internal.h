@@ -26,7 +26,7 @@ inline Dims make_dims(const spa2_shape& s) {
 // workspace; pool_slots == 0 means "no splitting" and every other member is then null.
 constexpr int SPLIT_POOL_MAX = 2048;         // partial-result slots of one launch at most
 struct SplitPlan {
-  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most
+  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection)
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
   const int32_t* part_table;   // [pool_slots][4] (unit, part, parts of the unit, list entries per part) of pool slot g
   int32_t* arrive;             // [pool_slots] parts of the unit that have left their result, at its first slot
