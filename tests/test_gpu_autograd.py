@@ -101,3 +101,22 @@ def test_forward_mode_is_refused_with_and_without_grad(grad):
         dual = fwad.make_dual(q, torch.ones_like(q))
         with pytest.raises(RuntimeError):
             spa2.sparge_attn2(dual, k, v, 0.5, 0.5)
+
+
+def test_traced_call_replays_on_new_inputs():
+    """A recorded call runs the kernels on the inputs of the replay, with gradients where those ask for them."""
+    def inputs(seed):
+        g = torch.Generator().manual_seed(seed)
+        return [torch.randn((1, 2, 300, 64), generator=g).bfloat16().to(dev()) for _ in range(4)]
+
+    pat = spa2.alloc_pattern(1, 2, 300, dev())
+    q, k, v, _ = inputs(1)
+    spa2.spa2_pattern_full(q, pat)
+    call = lambda q, k, v: spa2.sparge_attn2(q, k, v, 0.0, 0.0, pattern=pat)
+    with torch.no_grad():
+        traced = torch.jit.trace(call, (q, k, v), check_trace=False)
+    q, k, v, do = inputs(2)
+    assert torch.equal(traced(q, k, v), call(q, k, v))
+    leaves = [t.requires_grad_(True) for t in (q, k, v)]
+    for got, want in zip(*(torch.autograd.grad(f(*leaves), leaves, do) for f in (traced, call))):
+        assert torch.equal(got, want)
