@@ -44,10 +44,20 @@ size_t dkdv_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dkdv_slot_f
 //   dV^T (d x keys) += dO_i^T P      A = dO^T through transposing LDS reads, B = P  (registers)
 //   dK^T (d x keys) += Q_i^T dS      A = Q^T  through transposing LDS reads, B = dS (registers)
 // Because no wave reads another wave's rows, each wave stages its own rows (global -> LDS directly, XOR-swizzled,
-// double-buffered one step ahead) and waits only for its own copies: there is no workgroup barrier in the loop.
-// With a single wave per SIMD the vector arithmetic has to hide behind that wave's own MFMAs: the order is
-// S products, then dP products with exp(S - LSE) between them, dS of the first 16 queries, then the dV / dK
-// products of those 16 queries with the dS arithmetic of the other 16 between them.
+// double-buffered) and waits only for its own copies: there is no workgroup barrier in the loop.  Q rows, LSE and D of
+// the next step are requested between the S products and dO rows between the dP products, so every copy has a whole
+// step to land and the texture unit is not asked for sixteen of them at once.
+// With a single wave per SIMD the vector arithmetic has to hide behind that wave's own MFMAs.  The order of a step is
+//   16 S products          | copies; D is read from LDS into the accumulators of dP
+//   16 dP products         | exp(S - LSE) of the first 20 of the 32 values of a lane
+//   16 dV products         | the other exponentials (first half), dS of the first 16 queries (second half)
+//   16 dK products         | dS of the other 16 queries, first row fragments of the next step
+// (counts for d = 128).  dV comes before dK because it needs P alone: dS is never waited for.  dP starts from D and
+// V^T is held negated, so that the products give D - dP and dS costs one multiplication an element.
+// Bound: the board's power, then issue slots: 3480 cycles a step for 2048 of matrix products (4170 before this order,
+// when dS of the first 16 queries had no product to hide behind, LSE and D were waited for as they were read and every
+// copy stood behind a branch), 1.80 instead of 1.95 GHz.  Measured, us, before / after: 75,600 tokens, 40 heads
+// 14772 / 13440; 32,760 tokens, 12 heads 1026 / 921; 20,010 tokens, 6 heads, d = 64 155 / 134.
 // The two waves add their partial sums through LDS at the end of the column.
 template <int D>
 __global__ __attribute__((amdgpu_flat_work_group_size(128, 128), amdgpu_waves_per_eu(1, 1)))
@@ -59,22 +69,11 @@ void dkdv_kernel(DkvArgs a) {
   constexpr int CPR = D / 8;                         // 16-byte chunks per row
   constexpr int RPI = 64 / CPR;                      // rows that one wave-wide copy instruction covers
   constexpr int NCP = QW / RPI;                      // copy instructions per tensor and step
-  constexpr int NOFF = 16 / RPI;                     // the swizzle repeats every 16 rows: distinct lane offsets
   constexpr int TILE_B = QW * D * 2;                 // bytes of one wave's 32-row tile
   constexpr int STAGE_B = 2 * TILE_B;                // Q rows, then dO rows
   constexpr int STAT_B = 512;                        // LSE of the 32 rows at +0, D at +256
   __shared__ __align__(1024) unsigned char smem[2 * 2 * STAGE_B];   // (aligned: compile-time parts are XORed into addresses)   // wave w, stage s at (2w + s) * STAGE_B
   __shared__ __align__(1024) unsigned char stat_s[2 * 2 * STAT_B];  // wave w, stage s
-  // The registers hold 512 values per lane: 256 accumulators, 128 for K^T / V^T, 64 for S / dP, and what is left
-  // does not quite hold the operand rings, the packed P / dS and the addresses.  The last VL fragments of V^T
-  // (key half 1) therefore live in LDS in fragment order (lane l's 16 bytes at 16 l: conflict-free) and are read
-  // just before their product, like the Q / dO fragments.
-#ifndef DKDV_VL
-#define DKDV_VL 0
-#endif
-  constexpr int VL = D == 128 ? DKDV_VL : 0;    // fragment f = kh * NK + kk of V^T is in LDS when f >= 2 NK - VL
-  __shared__ __align__(1024) unsigned char vfrag_s[(VL ? VL : 1) * 1024];
-
   // Which key block, and which part of its list (the first sp.pool_slots workgroups of the launch are the parts of
   // split columns; the others take one key block each, unless it is split)
   int bh, j, part = 0, parts = 0, part_len = 0;
@@ -104,7 +103,6 @@ void dkdv_kernel(DkvArgs a) {
   }
 
   const int key0 = j * BKV + r32;                    // this lane's key of half 0; half 1 is 32 further
-  const bool keys_short = (j + 1) * BKV > N;         // uniform: the block reaches past the last token
 
   if (cnt == 0) {   // no query block selected this key block: zero gradients (wave w writes key half w)
     const int key = key0 + 32 * w;
@@ -119,21 +117,18 @@ void dkdv_kernel(DkvArgs a) {
     return;
   }
 
-  const uint32_t vfrag_addr = lds_addr_of(vfrag_s) + 16 * lane;
-  // K^T / V^T fragments (B operands): lane = key, 8 consecutive channels per 16-wide k step
+  // K^T / V^T fragments (B operands): lane = key, 8 consecutive channels per 16-wide k step.  (Keys past N, in a short
+  // last key block, repeat the last token: a key's column of every product is its own, and theirs are not stored.)
   bf16x8 kf[2][NK], vf[2][NK];
 #pragma unroll
   for (int kh = 0; kh < 2; ++kh) {
-    const int key = min(key0 + 32 * kh, N - 1);
-    const int64_t off = base + (int64_t)key * a.sn + 8 * hf;
+    const int64_t off = base + (int64_t)min(key0 + 32 * kh, N - 1) * a.sn + 8 * hf;
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
       kf[kh][kk] = *(const bf16x8*)(a.k + off + 16 * kk);
-      if (kh * NK + kk < 2 * NK - VL) vf[kh][kk] = *(const bf16x8*)(a.v + off + 16 * kk);
-      else if (w == 0) *(bf16x8*)(vfrag_s + (kh * NK + kk - (2 * NK - VL)) * 1024 + 16 * lane) = *(const bf16x8*)(a.v + off + 16 * kk);
+      vf[kh][kk] = *(const bf16x8*)(a.v + off + 16 * kk);
     }
   }
-  if (VL) __syncthreads();
 
   f32x16 dk_acc[2][NMB], dv_acc[2][NMB];
 #pragma unroll
@@ -145,16 +140,22 @@ void dkdv_kernel(DkvArgs a) {
 
   // global -> LDS copies of this wave's 32 rows.  A wave-wide 16-byte-per-lane copy lands linearly (wave base +
   // 16 * lane), i.e. lane l fills chunk position l % CPR of row RPI * r + l / CPR for copy instruction r; the
-  // swizzle is applied on the source side (the lane fetches logical chunk position ^ swz(row)).  swz repeats every
-  // 16 rows, so NOFF lane offsets cover all instructions; everything else of a request is wave-uniform: four
-  // 64-bit bases per step (Q and dO, rows 0.. and 16..) and compile-time LDS offsets.
-  uint32_t loff[NOFF];
+  // swizzle is applied on the source side (the lane fetches logical chunk position ^ swz(row)).  Everything else of a
+  // request is wave-uniform: one 64-bit base per tensor and step and compile-time LDS offsets.  Rows past N (32 rows
+  // that reach past the last token) are clamped to the last token, in the lane offsets, which are computed again only
+  // when the number of valid rows changes.
+  uint32_t voff[NCP], soff = 0;
+  int rows_set = -1;
+  auto set_rows = [&](int last) {            // last: last valid row of the 32 (uniform)
+    if (last == rows_set) return;
+    rows_set = last;
 #pragma unroll
-  for (int b = 0; b < NOFF; ++b) {
-    const int row_l = RPI * b + lane / CPR;
-    loff[b] = (uint32_t)((row_l * a.sn + (((lane % CPR) ^ swz<D>(row_l)) * 8)) * 2);
-  }
-  const uint32_t soff = (uint32_t)(r32 * 4);
+    for (int r = 0; r < NCP; ++r) {
+      const int row_l = RPI * r + lane / CPR;
+      voff[r] = (uint32_t)((min(row_l, last) * a.sn + (((lane % CPR) ^ swz<D>(row_l)) * 8)) * 2);
+    }
+    soff = (uint32_t)(min(r32, last) * 4);
+  };
   const char* q_head = (const char*)(a.q + base);
   const char* o_head = (const char*)(a.d_o + base);
   const char* lse_head = (const char*)(a.lse + (int64_t)bh * N);
@@ -162,29 +163,21 @@ void dkdv_kernel(DkvArgs a) {
   const uint64_t row_bytes = (uint64_t)a.sn * 2;
   const uint32_t wsm = lds_addr_of(smem) + 2 * w * STAGE_B;       // uniform LDS byte addresses
   const uint32_t wstat = lds_addr_of(stat_s) + 2 * w * STAT_B;
-
-  // the same for 32 rows that reach past N: rows are clamped to the last token (their P is zeroed below)
-  auto request_ragged = [&](int row0, uint32_t stage_addr, uint32_t stat_addr) {
-#pragma unroll
-    for (int r = 0; r < NCP; ++r) {
-      const int first = min(row0 + RPI * r, N - 1);                       // uniform
-      const int row_l = lane / CPR;
-      const int sw_row = RPI * r + row_l;                                 // the row of the LDS tile being filled
-      const uint32_t off = (uint32_t)((min(row_l, N - 1 - first) * a.sn + (((lane % CPR) ^ swz<D>(sw_row)) * 8)) * 2);
-      raw_copy16_to_lds_at<0>(q_head + (uint64_t)first * row_bytes, off, stage_addr + r * 1024);
-      raw_copy16_to_lds_at<0>(o_head + (uint64_t)first * row_bytes, off, stage_addr + TILE_B + r * 1024);
-    }
-    const int first = min(row0, N - 1);
-    const uint32_t so = (uint32_t)(min(r32, N - 1 - first) * 4);
-    raw_copy4_to_lds_at<0>(lse_head + (uint64_t)first * 4, so, stat_addr);
-    raw_copy4_to_lds_at<256>(dlt_head + (uint64_t)first * 4, so, stat_addr);
+  auto copy_stats = [&](int row, uint32_t stat_addr) {
+    raw_copy4_to_lds_at<0>(lse_head + (uint64_t)row * 4, soff, stat_addr);
+    raw_copy4_to_lds_at<256>(dlt_head + (uint64_t)row * 4, soff, stat_addr);
+  };
+  // Query rows past N get an LSE of +infinity once their copy has landed: their P is then exactly zero.
+  auto mark_rows_past_end = [&](int row0, uint32_t stat_addr) {
+    if (row0 + QW > N && row0 + r32 >= N) lds_stf(stat_addr + 4 * r32, INFINITY);
   };
 
   // the index list, 64 entries at a time in one register (lane l holds entry 64c + l): reading entry t is a
   // lane read, not a memory access
   int idx_v = idx[min(lane, cnt - 1)];
-  auto list_entry = [&](int t) -> int {      // t uniform, inside the chunk that idx_v holds
-    return min(max(__builtin_amdgcn_readlane(idx_v, t & 63), 0), a.Tm - 1);
+  auto step_row = [&](int u) -> int {        // first row of step u (uniform, inside the chunk that idx_v holds)
+    const int i = min(max(__builtin_amdgcn_readlane(idx_v, (u >> 1) & 63), 0), a.Tm - 1);
+    return i * BQ + (u & 1) * HQ + QW * w;
   };
 
   // per-lane LDS byte offsets inside a 32-row tile.  Row reads: row r32, logical chunk 2kk + hf (the part that
@@ -197,199 +190,203 @@ void dkdv_kernel(DkvArgs a) {
 
   const int steps = 2 * cnt;                 // step u: half u & 1 of list entry u >> 1
   {
-    const int row0 = list_entry(0) * BQ + QW * w;
-    request_ragged(row0, wsm, wstat);        // (the general form; the loop uses the cheaper one for full tiles)
+    const int row0 = step_row(0), row_b = min(row0, N - 1);
+    set_rows(min(QW - 1, N - 1 - row_b));
+    copy_stats(row_b, wstat);
+    static_for<0, NCP>([&](auto R) {
+      constexpr int r = decltype(R)::v;
+      raw_copy16_to_lds_at<r * 1024>(q_head + (uint64_t)row_b * row_bytes, voff[r], wsm);
+      raw_copy16_to_lds_at<TILE_B + r * 1024>(o_head + (uint64_t)row_b * row_bytes, voff[r], wsm);
+    });
+    raw_copies_done();
+    mark_rows_past_end(row0, wstat);
   }
-  raw_copies_done();
+  // -V^T: the dP products then give -dO V^T on top of D, so that dS = P (dP - D) needs no subtraction (the sign of dS
+  // is taken back with the scale of dK)
+#pragma unroll
+  for (int kh = 0; kh < 2; ++kh)
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) vf[kh][kk] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[kh][kk]) ^ 0x80008000u);
 
-  constexpr int PD = 4;                      // how many operand fragments ahead an LDS read is issued
+  constexpr int PD = 4;                      // how many row fragments ahead an LDS read is issued
+  constexpr int NX = 2 * NMB, PDT = 2;       // transposed fragments of a tile, and how many ahead they are read
+  constexpr int EB = D == 128 ? 10 : 8;      // exp units (below) that run between the dP products
+  bf16x8 fr[PD];
+#pragma unroll
+  for (int x = 0; x < PD; ++x) fr[x] = lds_ld16((wsm + a_off) ^ (x << 5));
+
   for (int u = 0; u < steps; ++u) {
     const int st = u & 1;
-    const int row_cur = list_entry(u >> 1) * BQ + (u & 1) * HQ + QW * w;
     const int un = min(u + 1, steps - 1);    // past the end the last step is requested again (nobody reads it)
-    if (((u + 1) & 127) == 0 && u + 1 < steps) idx_v = idx[min(((u + 1) >> 1) + lane, cnt - 1)];   // next 64 entries
-    const int row_nx = list_entry(un >> 1) * BQ + (un & 1) * HQ + QW * w;
-    const bool piecewise = row_nx + QW <= N;
+    if (((u + 1) & 127) == 0 && u + 1 < steps) idx_v = list_load(idx, min(((u + 1) >> 1) + lane, cnt - 1));   // next 64 entries
+    const int row_nx = step_row(un), row_b = min(row_nx, N - 1);
+    set_rows(min(QW - 1, N - 1 - row_b));
     const uint32_t nx_stage = wsm + (st ^ 1) * STAGE_B, nx_stat = wstat + (st ^ 1) * STAT_B;
-    // uniform bases of the next step's request
-    const char* qn0 = q_head + (uint64_t)row_nx * row_bytes;
-    const char* on0 = o_head + (uint64_t)row_nx * row_bytes;
-    const char* qn1 = qn0 + 16 * row_bytes;
-    const char* on1 = on0 + 16 * row_bytes;
-    if (!piecewise) {
-      request_ragged(row_nx, nx_stage, nx_stat);
-    } else {
-      raw_copy4_to_lds_at<0>(lse_head + (uint64_t)row_nx * 4, soff, nx_stat);
-      raw_copy4_to_lds_at<256>(dlt_head + (uint64_t)row_nx * 4, soff, nx_stat);
-    }
-    // piece P of the request for 32 full rows: Q chunk rows, dO chunk rows alternately
-    auto request_piece = [&](auto P) {
-      constexpr int p = decltype(P)::v, r = p >> 1, aa = r / NOFF, b = r % NOFF;
-      const char* src = (p & 1) ? (aa ? on1 : on0) : (aa ? qn1 : qn0);
-      raw_copy16_to_lds_at<(p & 1) * TILE_B + r * 1024>(src, loff[b], nx_stage);
-    };
+    const char* qn = q_head + (uint64_t)row_b * row_bytes;
+    const char* on = o_head + (uint64_t)row_b * row_bytes;
     // this step's operand addresses (one add per step; the XOR of the compile-time part is one more op per read)
     const uint32_t q_rd = wsm + st * STAGE_B + a_off, q_t0 = wsm + st * STAGE_B + t_off0, q_t1 = wsm + st * STAGE_B + t_off1;
     const uint32_t lb = wstat + st * STAT_B + 16 * hf;
+    uint32_t lb1 = lb;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(lb1));            // (D is read into both key halves' accumulators, not read once and copied)
+#endif
 
-    // ---- S = Q K^T, then dP = dO V^T; fragment y of the sequence is Q chunk y (y < NK) or dO chunk y - NK
+    // fragment y of the sequence is Q chunk y (y < NK) or dO chunk y - NK
     auto row_frag = [&](int y) -> bf16x8 { return lds_ld16((q_rd ^ ((y % NK) << 5)) + (y < NK ? 0 : TILE_B)); };
-    f32x16 s[2], dp[2];
-    bf16x8 fr[PD];
-#pragma unroll
-    for (int x = 0; x < PD; ++x) fr[x] = row_frag(x);
-    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    static_for<0, NK>([&](auto Y) {
-      constexpr int y = decltype(Y)::v;
-      s[0] = mfma32(fr[y % PD], kf[0][y], y == 0 ? zero : s[0]);
-      s[1] = mfma32(fr[y % PD], kf[1][y], y == 0 ? zero : s[1]);
-      fr[y % PD] = row_frag(y + PD);
-      if (piecewise) {
-        constexpr int PER = (2 * NCP) / NK;
-        static_for<0, PER>([&](auto C) { request_piece(Int<y * PER + decltype(C)::v>{}); });
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    // exp(S - LSE) in groups of four queries (accumulator registers 4g .. 4g+3), between the dP products
-    constexpr int GPS = 8 / NK;                // (key half, query group) pairs handled per dP step
-    f32x4 l4;
-    auto v_frag = [&](int kh, int kk) -> bf16x8 {     // from registers or, for the last VL fragments, from LDS
-      const int f = kh * NK + kk;
-      return f < 2 * NK - VL ? vf[kh][kk] : lds_ld16(vfrag_addr + (f - (2 * NK - VL)) * 1024);
-    };
-    static_for<NK, 2 * NK>([&](auto Y) {
-      constexpr int y = decltype(Y)::v, kk = y - NK;
-      dp[0] = mfma32(fr[y % PD], v_frag(0, kk), kk == 0 ? zero : dp[0]);
-      dp[1] = mfma32(fr[y % PD], v_frag(1, kk), kk == 0 ? zero : dp[1]);
-      if constexpr (y + PD < 2 * NK) fr[y % PD] = row_frag(y + PD);
-#pragma unroll
-      for (int x = 0; x < GPS; ++x) {
-        const int pair = kk * GPS + x, g = pair >> 1, kh = pair & 1;
-        if (kh == 0) l4 = lds_ldf4(lb + 32 * g);
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-          s[kh][4 * g + e] = fast_exp2(fmaf(s[kh][4 * g + e], a.scale_log2, -LOG2E * l4[e]));
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    // keys past N (short last key block) and query rows past N (short last query block): P = 0
-    if (keys_short) {
-#pragma unroll
-      for (int kh = 0; kh < 2; ++kh)
-        if (key0 + 32 * kh >= N) {
-#pragma unroll
-          for (int v = 0; v < 16; ++v) s[kh][v] = 0.f;
-        }
-    }
-    if (row_cur + QW > N) {
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        if (row_cur + 8 * (v >> 2) + 4 * hf + (v & 3) >= N) { s[0][v] = 0.f; s[1][v] = 0.f; }
-    }
-    // ---- dS = P * (dP - D), P and dS packed to bf16: pk[kh][2g], pk[kh][2g+1] hold the four queries of group g
-    uint32_t pk[2][8], dsk[2][8];
-    auto finish_group = [&](int g, int kh) {
-      const f32x4 d4 = lds_ldf4(lb + 256 + 32 * g);
-      float ds[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) ds[e] = s[kh][4 * g + e] * (dp[kh][4 * g + e] - d4[e]);
-      pk[kh][2 * g] = pack_bf16(s[kh][4 * g], s[kh][4 * g + 1]);
-      pk[kh][2 * g + 1] = pack_bf16(s[kh][4 * g + 2], s[kh][4 * g + 3]);
-      dsk[kh][2 * g] = pack_bf16(ds[0], ds[1]);
-      dsk[kh][2 * g + 1] = pack_bf16(ds[2], ds[3]);
-    };
     auto tr_frag = [&](int tile, int x) -> bf16x8 {     // tile 0 = Q, 1 = dO; x = c * NMB + mb
       const int c = x / NMB, mb = x % NMB;
       const uint32_t o = tile * TILE_B + 32 * c * D;
       return join_tr(lds_tr4_at((q_t0 ^ (mb << 6)) + o), lds_tr4_at((q_t1 ^ (mb << 6)) + o));
     };
-    constexpr int NX = 2 * NMB, PDT = 2;
-    bf16x8 fo[PDT], fq[PDT];
-    finish_group(0, 0); finish_group(0, 1);
-    __builtin_amdgcn_sched_barrier(0);
+    f32x16 s[2], dp[2];
+    f32x4 l_raw, l_neg;
+    uint32_t pk[2][8], dsk[2][8];
+    // exp unit e: two queries of accumulator group g = e / 4 (registers 4g .. 4g+3), key half (e / 2) % 2
+    auto exp_unit = [&](auto E) {
+      constexpr int e = decltype(E)::v, g = e >> 2, kh = (e >> 1) & 1, v = 4 * g + 2 * (e & 1);
+      if constexpr ((e & 3) == 0) {
 #pragma unroll
-    for (int x = 0; x < PDT; ++x) { fo[x] = tr_frag(1, x); fq[x] = tr_frag(0, x); }
-    finish_group(1, 0); finish_group(1, 1);
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- dV^T += dO^T P and dK^T += Q^T dS.  Step x = (c, mb): the 16 queries 16c.. (accumulator registers
-    // 8c .. 8c+7), output block mb; each transposed fragment feeds both key halves.  The dS arithmetic of the
-    // second 16 queries runs between the products of the first 16.
+        for (int x = 0; x < 4; ++x) l_neg[x] = -LOG2E * l_raw[x];
+        if constexpr (g < 3) l_raw = lds_ldf4(lb + 32 * (g + 1));
+      }
+      s[kh][v] = fast_exp2(fmaf(s[kh][v], a.scale_log2, l_neg[v & 3]));
+      s[kh][v + 1] = fast_exp2(fmaf(s[kh][v + 1], a.scale_log2, l_neg[(v & 3) + 1]));
+      pk[kh][v >> 1] = pack_bf16(s[kh][v], s[kh][v + 1]);
+    };
+    auto ds_unit = [&](auto E) {             // the same two queries of -dS = P * (D - dP)
+      constexpr int e = decltype(E)::v, g = e >> 2, kh = (e >> 1) & 1, v = 4 * g + 2 * (e & 1);
+      dsk[kh][v >> 1] = pack_bf16(s[kh][v] * dp[kh][v], s[kh][v + 1] * dp[kh][v + 1]);
+    };
+    auto quad = [](const uint32_t (&p)[8], int c) -> bf16x8 {
+      return __builtin_bit_cast(bf16x8, u32x4{p[4 * c], p[4 * c + 1], p[4 * c + 2], p[4 * c + 3]});
+    };
+
+    // ---- S = Q K^T; the next step's LSE, D and Q rows are requested
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    static_for<0, NK>([&](auto Y) {
+      constexpr int y = decltype(Y)::v;
+      s[0] = mfma32(fr[y % PD], kf[0][y], y == 0 ? zero : s[0]);
+      s[1] = mfma32(fr[y % PD], kf[1][y], y == 0 ? zero : s[1]);
+      if constexpr (y == 0) copy_stats(row_b, nx_stat);
+      raw_copy16_to_lds_at<y * 1024>(qn, voff[y], nx_stage);
+      if constexpr (y + PD == NK) raw_copies_left<2 + y + 1>();      // this step's dO rows have landed
+      fr[y % PD] = row_frag(y + PD);
+      if constexpr (y >= NK - 4) {           // D, as the initial value of dP
+        constexpr int g = y - (NK - 4);
+        const f32x4 d0 = lds_ldf4(lb + 256 + 32 * g), d1 = lds_ldf4(lb1 + 256 + 32 * g);
 #pragma unroll
-    for (int x = 0; x < NX; ++x) {
-      const int c = x / NMB, mb = x % NMB;
-      const u32x4 p0 = {pk[0][4 * c], pk[0][4 * c + 1], pk[0][4 * c + 2], pk[0][4 * c + 3]};
-      const u32x4 p1 = {pk[1][4 * c], pk[1][4 * c + 1], pk[1][4 * c + 2], pk[1][4 * c + 3]};
-      const u32x4 d0 = {dsk[0][4 * c], dsk[0][4 * c + 1], dsk[0][4 * c + 2], dsk[0][4 * c + 3]};
-      const u32x4 d1 = {dsk[1][4 * c], dsk[1][4 * c + 1], dsk[1][4 * c + 2], dsk[1][4 * c + 3]};
-      mfma32_acc(fo[x % PDT], __builtin_bit_cast(bf16x8, p0), dv_acc[0][mb]);
-      mfma32_acc(fo[x % PDT], __builtin_bit_cast(bf16x8, p1), dv_acc[1][mb]);
-      if (x + PDT < NX) fo[x % PDT] = tr_frag(1, x + PDT);
-      mfma32_acc(fq[x % PDT], __builtin_bit_cast(bf16x8, d0), dk_acc[0][mb]);
-      mfma32_acc(fq[x % PDT], __builtin_bit_cast(bf16x8, d1), dk_acc[1][mb]);
-      if (x + PDT < NX) fq[x % PDT] = tr_frag(0, x + PDT);
-      if (c == 0) {                             // groups 2, 3 of both key halves, spread over the NMB steps
-        constexpr int PER = 4 / NMB;
+        for (int x = 0; x < 4; ++x) { dp[0][4 * g + x] = d0[x]; dp[1][4 * g + x] = d1[x]; }
+      }
+      if constexpr (y == NK - 1) l_raw = lds_ldf4(lb);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- D - dP = D + dO (-V)^T, with exp(S - LSE) between the products; the next step's dO rows are requested
+    bf16x8 ft[PDT];
+    static_for<0, NK>([&](auto Y) {
+      constexpr int y = decltype(Y)::v;
+      dp[0] = mfma32(fr[y % PD], vf[0][y], dp[0]);
+      dp[1] = mfma32(fr[y % PD], vf[1][y], dp[1]);
+      if constexpr (y + PD < NK) fr[y % PD] = row_frag(NK + y + PD);
+      raw_copy16_to_lds_at<TILE_B + y * 1024>(on, voff[y], nx_stage);
+      static_for<y * EB / NK, (y + 1) * EB / NK>(exp_unit);
+      if constexpr (y >= NK - PDT) ft[y - (NK - PDT)] = tr_frag(1, y - (NK - PDT));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- dV^T += dO^T P.  Step x = (c, mb): the 16 queries 16c.. (accumulator registers 8c .. 8c+7), output block mb;
+    // each transposed fragment feeds both key halves.  The remaining exponentials run between the first half of the
+    // products, dS of the first 16 queries between the second.
+    static_for<0, NX>([&](auto X) {
+      constexpr int x = decltype(X)::v, c = x / NMB, mb = x % NMB;
+      mfma32_acc(ft[x % PDT], quad(pk[0], c), dv_acc[0][mb]);
+      mfma32_acc(ft[x % PDT], quad(pk[1], c), dv_acc[1][mb]);
+      ft[x % PDT] = x + PDT < NX ? tr_frag(1, x + PDT) : tr_frag(0, x + PDT - NX);
+      if constexpr (c == 0) static_for<EB + mb * (16 - EB) / NMB, EB + (mb + 1) * (16 - EB) / NMB>(exp_unit);
+      else                  static_for<mb * 8 / NMB, (mb + 1) * 8 / NMB>(ds_unit);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- -dK^T += Q^T (-dS), the same way, with dS of the other 16 queries between the first half; then the next
+    // step's Q rows, LSE and D have landed (its dO rows, the last NCP copies, may be in flight) and its first row
+    // fragments are read
+    static_for<0, NX>([&](auto X) {
+      constexpr int x = decltype(X)::v, c = x / NMB, mb = x % NMB;
+      mfma32_acc(ft[x % PDT], quad(dsk[0], c), dk_acc[0][mb]);
+      mfma32_acc(ft[x % PDT], quad(dsk[1], c), dk_acc[1][mb]);
+      if constexpr (x + PDT < NX) ft[x % PDT] = tr_frag(0, x + PDT);
+      if constexpr (c == 0) static_for<8 + mb * 8 / NMB, 8 + (mb + 1) * 8 / NMB>(ds_unit);
+      if constexpr (x == NMB) {
+        raw_copies_left<NCP>();
+        mark_rows_past_end(row_nx, nx_stat);
+      }
+      if constexpr (c == 1) {
 #pragma unroll
-        for (int t = 0; t < PER; ++t) finish_group(2 + ((mb * PER + t) >> 1), (mb * PER + t) & 1);
+        for (int f = mb * PD / NMB; f < (mb + 1) * PD / NMB; ++f) fr[f] = lds_ld16((nx_stage + a_off) ^ (f << 5));
       }
       __builtin_amdgcn_sched_barrier(0);
-    }
-    raw_copies_done();      // the copies requested in this step have landed in the other stage
+    });
   }
 
   // the accumulators are read by ordinary vector instructions from here on: let the last products finish first
-  // (the compiler does not know that mfma32_acc is a matrix instruction and inserts no wait states for it)
+  // (the compiler does not know that mfma32_acc is a matrix instruction and inserts no wait states for it); and the
+  // copies of the step past the end have to be out of the way of the exchange below
+  raw_copies_done();
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #endif
-  // sum the partial results of the two waves: first pass dK, second pass dV.  Wave w writes its partial
-  // into its own staging area and then finishes key half w.
+  // The two waves' partial sums are added: wave w hands its sums of key half 1 - w over, through its own staging area,
+  // and finishes key half w.  16-byte pieces [tensor][output block][group][lane], one exchange for both tensors (two of
+  // all sums before, four bytes at a time: with the order of the step above, 54 -> 47 us for 504 columns of 4 entries).
+  constexpr int REGION = 2 * NMB * 4 * 64 * 4;        // floats per wave
+  static_assert(REGION * 4 == 2 * STAGE_B, "the sums that a wave hands over fill exactly its two stages");
   float* scratch = (float*)smem;
-  constexpr int REGION = 2 * NMB * 16 * 64;           // floats per wave
-  static_assert(REGION * 4 == 2 * STAGE_B, "a wave's partial sums fill exactly its two stages");
   const int key = key0 + 32 * w;
-#pragma unroll
-  for (int round = 0; round < 2; ++round) {
-    float* mine = scratch + w * REGION + lane;
-#pragma unroll
-    for (int kh = 0; kh < 2; ++kh)
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-          mine[((kh * NMB + mb) * 16 + v) * 64] = round == 0 ? dk_acc[kh][mb][v] : dv_acc[kh][mb][v];
-    __syncthreads();
-    if (key < N || parts) {         // (a part writes its whole slot, so that the merge never reads stale sums)
-      const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
-      const float sc = round == 0 ? a.scale : 1.f;
-#pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) {
-        uint16_t* out = (round == 0 ? a.dk : a.dv) + out_off + 32 * mb;
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float x[4];
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int at = ((w * NMB + mb) * 16 + 4 * g + e) * 64 + lane;
-            x[e] = scratch[at] + scratch[REGION + at];
-          }
-          if (parts) {          // one part of a split column: leave the sums to the last part
-            float* ps = a.sp.pool + (int64_t)blockIdx.x * a.sp.slot_floats + ((((round * 2 + w) * NMB + mb) * 4 + g) * 128 + lane) * 2;
-            part_store2(ps, x[0], x[1]);
-            part_store2(ps + 128, x[2], x[3]);
-            continue;
-          }
-          u32x2 pk2 = {pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
-          *(u32x2*)(out + 8 * g) = pk2;
-        }
-      }
-    }
-    __syncthreads();
+  auto hand_over = [&](auto KH) {
+    f32x4* out = (f32x4*)(scratch + w * REGION) + lane;
+    static_for<0, 8 * NMB>([&](auto C) {
+      constexpr int c = decltype(C)::v, mb = (c / 4) % NMB, v = 4 * (c % 4);
+      const f32x16& x = c < 4 * NMB ? dk_acc[decltype(KH)::v][mb] : dv_acc[decltype(KH)::v][mb];
+      out[64 * c] = f32x4{x[v], x[v + 1], x[v + 2], x[v + 3]};
+      if constexpr (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  // put(tensor, output block, group, sums) of every piece that this wave finishes
+  auto finish = [&](auto KH, auto&& put) {
+    const f32x4* in = (const f32x4*)(scratch + (1 - w) * REGION) + lane;
+    static_for<0, 8 * NMB>([&](auto C) {
+      constexpr int c = decltype(C)::v, mb = (c / 4) % NMB, v = 4 * (c % 4);
+      const f32x16& x = c < 4 * NMB ? dk_acc[decltype(KH)::v][mb] : dv_acc[decltype(KH)::v][mb];
+      put(c / (4 * NMB), mb, c % 4, f32x4{x[v], x[v + 1], x[v + 2], x[v + 3]} + in[64 * c]);
+      if constexpr (c % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+    });
+  };
+  if (w == 0) hand_over(Int<1>{});
+  else        hand_over(Int<0>{});
+  __syncthreads();
+  if (parts) {                  // one part of a split column: leave the sums to the last part (the whole slot is
+    float* ps = a.sp.pool + (int64_t)blockIdx.x * a.sp.slot_floats + 2 * lane;       // written: the merge reads it)
+    auto put = [&](int t, int mb, int g, f32x4 x) {
+      float* p = ps + (((t * 2 + w) * NMB + mb) * 4 + g) * 256;
+      part_store2(p, x[0], x[1]);
+      part_store2(p + 128, x[2], x[3]);
+    };
+    if (w == 0) finish(Int<0>{}, put);
+    else        finish(Int<1>{}, put);
+  } else {
+    if (key >= N) return;
+    const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
+    auto put = [&](int t, int mb, int g, f32x4 x) {
+      const float sc = t == 0 ? -a.scale : 1.f;
+      const u32x2 pk2 = {pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
+      *(u32x2*)((t == 0 ? a.dk : a.dv) + out_off + 32 * mb + 8 * g) = pk2;
+    };
+    if (w == 0) finish(Int<0>{}, put);
+    else        finish(Int<1>{}, put);
+    return;
   }
   // the last part of a split column to arrive adds all of them in part order
-  if (parts) {
+  {
     const int64_t first = blockIdx.x - part;
-    if (!last_part(a.sp.arrive + first, parts, (int*)smem) || key >= N) return;
+    if (!last_part(a.sp.arrive + first, parts, (int*)stat_s) || key >= N) return;
     const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
     const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * lane;
 #pragma unroll
@@ -405,7 +402,7 @@ void dkdv_kernel(DkvArgs a) {
 #pragma unroll
         for (int c = 0; c < NMB * 8; ++c) { x[c][0] += y[c][0]; x[c][1] += y[c][1]; }
       }
-      const float sc = round == 0 ? a.scale : 1.f;
+      const float sc = round == 0 ? -a.scale : 1.f;
 #pragma unroll
       for (int mb = 0; mb < NMB; ++mb) {
         uint16_t* out = (round == 0 ? a.dk : a.dv) + out_off + 32 * mb;

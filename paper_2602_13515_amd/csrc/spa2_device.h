@@ -101,16 +101,35 @@ __device__ __forceinline__ void raw_copies_done() {
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 #endif
 }
+// All but the last COUNT vector-memory operations of the wave are done (they complete in order).
+template <int COUNT>
+__device__ __forceinline__ void raw_copies_left() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(COUNT) : "memory");
+#endif
+}
+
+// Entry `at` of an index list into a register, waited for here: a load inside a branch that is first used behind it would
+// make the compiler wait for every outstanding memory operation there, copies included, also where the branch is not taken.
+__device__ __forceinline__ int list_load(const int32_t* idx, int at) {
+  int x = idx[at];
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" : "+v"(x));
+#endif
+  return x;
+}
 
 // LDS accesses by 32-bit byte address.  A generic pointer into LDS is turned into its LDS address once
 // (lds_addr_of); from then on addresses are plain integers, so that address arithmetic stays 32-bit and constant
 // parts can be folded into the instructions' offset fields, and no generic-pointer null checks are generated.
 typedef __attribute__((address_space(3))) const bf16x8 lds_cbf16x8;
 typedef __attribute__((address_space(3))) const f32x4 lds_cf32x4;
+typedef __attribute__((address_space(3))) float lds_f32;
 __device__ __forceinline__ uint32_t lds_addr_of(const void* p) { return (uint32_t)(size_t)(lptr_t*)p; }
 #if defined(__HIP_DEVICE_COMPILE__)      // (LDS pointers are 32 bits wide only in the device pass)
 __device__ __forceinline__ bf16x8 lds_ld16(uint32_t addr) { return *(lds_cbf16x8*)addr; }
 __device__ __forceinline__ f32x4 lds_ldf4(uint32_t addr) { return *(lds_cf32x4*)addr; }
+__device__ __forceinline__ void lds_stf(uint32_t addr, float x) { *(lds_f32*)addr = x; }
 __device__ __forceinline__ u32x2 lds_tr4_at(uint32_t addr) {
   s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)addr);
   return __builtin_bit_cast(u32x2, v);
@@ -118,6 +137,7 @@ __device__ __forceinline__ u32x2 lds_tr4_at(uint32_t addr) {
 #else
 __device__ bf16x8 lds_ld16(uint32_t addr);
 __device__ f32x4 lds_ldf4(uint32_t addr);
+__device__ void lds_stf(uint32_t addr, float x);
 __device__ u32x2 lds_tr4_at(uint32_t addr);
 #endif
 // Direct global -> LDS copies as above, with the (wave-uniform) LDS byte address given as an integer.
