@@ -62,24 +62,25 @@ __device__ __forceinline__ void dq_store_rows(const DqArgs& a, int64_t base, int
   }
 }
 
-template <int D>
-struct DqCfg {
-  // K and V tiles, XOR-swizzled and unpadded (the layout a direct global -> LDS copy can write): K is read
-  // along rows (S^T) and transposed (dQ^T), V along rows (dP^T)
-  static constexpr int K_ELEMS = BKV * D;
-  static constexpr int V_ELEMS = BKV * D;
-  static constexpr int CH = BKV * D / 8 / 256;
-};
-
 // Transposed formulation, a lane owns one query row (see fwd.hip):
 //   S^T  = K_j Q_i^T        P^T  = exp(S^T - LSE)
 //   dP^T = V_j dO_i^T       dS^T = P^T * (dP^T - D)
 //   dQ^T += K_j^T dS^T      (K^T through transposing LDS reads)
+// The key block is taken in halves of 32 keys: S, dP of half 0, S, dP of half 1, then dQ of both.  The exponentials of a
+// half run between its dP products and its dS between the products after those, and dP starts from -D, held in registers
+// as a first accumulator, so dS costs one multiplication an element.
+// Bound: the board's power (1.54 GHz) with the matrix cores busy 78 % of the cycles: 3960 cycles a tile and wave at two
+// waves per SIMD for 1536 of matrix products (5200 before, when the mask of a short last block was worked out for every
+// tile, 128 of 336 vector instructions, the copies multiplied out their offsets, and all exponentials stood in one run).
+// Measured, us, before / after: 75,600 tokens, 40 heads 10877 / 9674; 32,760 tokens, 12 heads 662 / 574; 32,768 tokens,
+// 24 heads, half the rows long 6466 / 5435; 20,010 tokens, 6 heads, d = 64 89 / 78.
 template <int D>
 __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
-  using C = DqCfg<D>;
-  __shared__ __align__(16) uint16_t smem[2 * (C::K_ELEMS + C::V_ELEMS)];   // stage s: K tile, then V tile
-  constexpr int STAGE = C::K_ELEMS + C::V_ELEMS;
+  constexpr int NK = D / 16, NMB = D / 32;           // contraction steps of S and dP, output blocks of dQ
+  // K and V tiles, XOR-swizzled and unpadded (the layout a direct global -> LDS copy can write): K is read along rows
+  // (S^T) and transposed (dQ^T), V along rows (dP^T).  (Aligned: compile-time parts are XORed into addresses.)
+  constexpr int TILE_B = BKV * D * 2, STAGE_B = 2 * TILE_B;
+  __shared__ __align__(1024) unsigned char smem[2 * STAGE_B];   // stage s: K tile, then V tile
 
   // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
   int bh, i, part = 0, parts = 0, part_len = 0;
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tm + i] >= 0) return;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform, in a scalar register
   const int r32 = lane & 31, hf = lane >> 5;
   const int N = a.N;
   int cnt = min(max(a.row_cnt[(int64_t)bh * a.Tm + i], 0), a.Tn);   // clamped: see fwd.hip
@@ -134,36 +136,55 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   // 16-byte-per-lane copy is linear (wave base + 16 * lane), so the swizzle is applied on the source side: the
   // lane that fills chunk position pc of a row fetches logical chunk pc ^ swz(row).  Thread t fills chunk
   // position t % CPR of rows t / CPR + r * RSTEP; RSTEP is a multiple of 16 rows, so the swizzle term is the
-  // same for every r.  Rows past N (short last block) are clamped to the last token: their P is zero.
-  constexpr int CPR = D / 8, RSTEP = 256 / CPR;
-  const int ld_row = tid / CPR;
-  int ld_c8 = ((tid % CPR) ^ swz<D>(ld_row)) * 8;
-  auto copy_piece = [&](int p, int buf, const char* kp, const char* vp, int last) {   // p in [0, 2 CH)
-    const int r = p >> 1;
-    const uint32_t off = (uint32_t)((min(ld_row + RSTEP * r, last) * a.sn + ld_c8) * 2);
-    const uint16_t* dst = smem + buf * STAGE + (p & 1) * C::K_ELEMS + (r * 256 + w * 64) * 8;   // wave-uniform
-    raw_copy16_to_lds((p & 1) ? vp : kp, off, dst);
+  // same for every r.  Rows past N (short last block) are clamped to the last token (their P is made zero); the lane
+  // offsets are computed again only when the number of valid rows changes.
+  constexpr int CPR = D / 8, RSTEP = 256 / CPR, CH = BKV / RSTEP;
+  // (what the rare paths of the loop need of the thread's number is worked out there, from the number itself: held in
+  // registers over the loop it would cost spills)
+  auto fresh_tid = [&]() -> int {
+    int t = tid;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(t));
+#endif
+    return t;
   };
-  constexpr int NPIECE = 2 * C::CH;
-
-  f32x16 acc[D / 32];
+  uint32_t voff[CH];
+  int rows_set = -1;
+  auto set_rows = [&](int last) {            // last: last valid row of the tile (uniform)
+    if (last == rows_set) return;
+    rows_set = last;
+    const int t = fresh_tid(), ld_row = t / CPR, ld_c8 = ((t % CPR) ^ swz<D>(ld_row)) * 8;
 #pragma unroll
-  for (int mb = 0; mb < D / 32; ++mb)
+    for (int r = 0; r < CH; ++r) voff[r] = (uint32_t)((min(ld_row + RSTEP * r, last) * a.sn + ld_c8) * 2);
+  };
+  const uint32_t sm = lds_addr_of(smem);
+  const char* k_head = (const char*)(a.k + base);
+  const char* v_head = (const char*)(a.v + base);
+  const uint64_t tile_bytes = (uint64_t)a.sn * (2 * BKV);
+  constexpr int NPIECE = 2 * CH;             // piece p of a tile's copies: rows p / 2 of K (p even) or V
+  auto copy_piece = [&](auto P, const char* kp, const char* vp, uint32_t stage) {
+    constexpr int p = decltype(P)::v, r = p >> 1;
+    raw_copy16_to_lds_at<(p & 1) * TILE_B + r * 4096>((p & 1) ? vp : kp, voff[r], stage + w * 1024);
+  };
+
+  f32x16 acc[NMB];
+#pragma unroll
+  for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[mb][v] = 0.f;
+  f32x16 neg_d;                              // -D of this lane's query: the initial value of dP
+#pragma unroll
+  for (int v = 0; v < 16; ++v) neg_d[v] = -dlt;
 
-  // per-lane LDS element offsets.  K row reads: row 32kb + r32, logical chunk 2kk + hf; the part of the
-  // chunk index that depends on kk is XORed in as (kk << 4).
-  int ka_base = swz_idx<D>(r32, 8 * hf);       // the V row reads use the same offsets
+  // per-lane LDS byte offsets inside a stage.  K row reads: row 32kb + r32, logical chunk 2kk + hf; the part of the
+  // chunk index that depends on kk is XORed in as (kk << 5); the V row reads use the same offsets.
   // K transposing reads: rows (16-row group) + 8*which + 4hf + (s16>>2), columns 32mb + 16hb + 4(s16&3);
-  // the part that depends on mb is XORed in as (mb << 5)
+  // the part that depends on mb is XORed in as (mb << 6)
   const int s16 = lane & 15, hb16 = (lane >> 4) & 1;
-  int kt_base0 = swz_idx<D>(4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
-  int kt_base1 = swz_idx<D>(8 + 4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
+  const uint32_t ka_off = sm + 2 * swz_idx<D>(r32, 8 * hf);
+  const uint32_t kt_off0 = sm + 2 * swz_idx<D>(4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
+  const uint32_t kt_off1 = sm + 2 * swz_idx<D>(8 + 4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
 
-  // The copies of tile t+1 are handed out between the MFMAs of the S^T / dP^T products of iteration t: issued
-  // back to back they keep the wave at the issue stage until the texture unit has taken the last one.  They are
-  // unconditional (past the end of the list the last tile is requested again, into the buffer nobody reads).
   // the index list, 64 entries at a time in one register (lane l holds entry 64c + l): reading an entry is
   // a lane read, not a memory access whose result the loop would have to wait for
   int idx_v = idx[min(lane, cnt - 1)];
@@ -171,97 +192,88 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     return min(max(__builtin_amdgcn_readlane(idx_v, t & 63), 0), a.Tn - 1);
   };
   int j_cur = list_entry(0);
-  {
-    const int64_t tile0 = (base + (int64_t)j_cur * BKV * a.sn) * 2;
-    const int last0 = min(BKV - 1, N - 1 - j_cur * BKV);
-#pragma unroll
-    for (int p = 0; p < NPIECE; ++p) copy_piece(p, 0, (const char*)a.k + tile0, (const char*)a.v + tile0, last0);
-  }
+  set_rows(min(BKV - 1, N - 1 - j_cur * BKV));
+  static_for<0, NPIECE>([&](auto P) { copy_piece(P, k_head + j_cur * tile_bytes, v_head + j_cur * tile_bytes, sm); });
   raw_copies_done();
   __syncthreads();
 
   for (int t = 0; t < cnt; ++t) {
     const int j = j_cur;
-    if (((t + 1) & 63) == 0 && t + 1 < cnt) idx_v = idx[min(t + 1 + lane, cnt - 1)];     // next 64 entries
-    const int j_nxt = list_entry(min(t + 1, cnt - 1));
-    const int64_t tile_n = (base + (int64_t)j_nxt * BKV * a.sn) * 2;      // uniform
-    const char* kpn = (const char*)a.k + tile_n;
-    const char* vpn = (const char*)a.v + tile_n;
-    const int last_n = min(BKV - 1, N - 1 - j_nxt * BKV);
-    j_cur = j_nxt;
-    const uint16_t* Kb = smem + (t & 1) * STAGE;
-    const uint16_t* Vb = Kb + C::K_ELEMS;
+    if (((t + 1) & 63) == 0 && t + 1 < cnt) idx_v = list_load(idx, min(t + 1 + (fresh_tid() & 63), cnt - 1));     // next 64 entries
+    // The copies of tile t+1 are handed out between the MFMAs of the S^T / dP^T products of iteration t: issued
+    // back to back they keep the wave at the issue stage until the texture unit has taken the last one.  They are
+    // unconditional (past the end of the list the last tile is requested again, into the buffer nobody reads).
+    j_cur = list_entry(min(t + 1, cnt - 1));
+    set_rows(min(BKV - 1, N - 1 - j_cur * BKV));
+    const char* kpn = k_head + j_cur * tile_bytes;
+    const char* vpn = v_head + j_cur * tile_bytes;
+    const uint32_t nx_stage = sm + ((t + 1) & 1) * STAGE_B;
+    uint32_t ka = ka_off + (t & 1) * STAGE_B, kt0 = kt_off0 + (t & 1) * STAGE_B, kt1 = kt_off1 + (t & 1) * STAGE_B;
+#if defined(__HIP_DEVICE_COMPILE__)
+    // (keeps the XORed operand addresses out of loop-invariant hoisting: one VALU op per read instead of a dozen live
+    // registers)
+    asm volatile("" : "+v"(ka), "+v"(kt0), "+v"(kt1));
+#endif
 
-    // keep the XORed operand addresses out of loop-invariant hoisting (one VALU op per read instead of
-    // a dozen live registers)
-    asm volatile("" : "+v"(ka_base), "+v"(kt_base0), "+v"(kt_base1), "+v"(ld_c8));
-
-    // ---- S^T and dP^T: for each 32-key block D/16 MFMAs of K Q^T, then D/16 of V dO^T.  LDS operands run
-    // PDQ MFMAs ahead of their use; request piece p of tile t+1 goes out after MFMA p * NM1 / NPIECE.
-    constexpr int NM1 = 4 * (D / 16), PDQ = 4;
+    // ---- S^T and dP^T - D: for each 32-key block NK MFMAs of K Q^T, then NK of V dO^T on top of -D.  LDS operands run
+    // PDQ MFMAs ahead of their use; copy piece p of tile t+1 goes out after MFMA p * NM1 / NPIECE.
+    constexpr int NM1 = 4 * NK, PDQ = 4, PDT = 2;
     auto frag1 = [&](int y) -> bf16x8 {
-      const int kb = y / (2 * (D / 16)), rem = y % (2 * (D / 16)), kk = rem % (D / 16);
-      return *(const bf16x8*)((rem < D / 16 ? Kb : Vb) + (ka_base ^ (kk << 4)) + kb * 32 * D);
+      const int kb = y / (2 * NK), rem = y % (2 * NK), kk = rem % NK;
+      return lds_ld16((ka ^ (kk << 5)) + (rem < NK ? 0 : TILE_B) + kb * 32 * D * 2);
     };
-    f32x16 s[2], dp[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) { s[kb][v] = 0.f; dp[kb][v] = 0.f; }
-    {
-      bf16x8 fr[PDQ];
-#pragma unroll
-      for (int x = 0; x < PDQ; ++x) fr[x] = frag1(x);
-#pragma unroll
-      for (int y = 0; y < NM1; ++y) {
-        const int kb = y / (2 * (D / 16)), rem = y % (2 * (D / 16)), kk = rem % (D / 16);
-        if (rem < D / 16) s[kb] = mfma32(fr[y % PDQ], qf[kk], s[kb]);
-        else              dp[kb] = mfma32(fr[y % PDQ], dof[kk], dp[kb]);
-        if (y + PDQ < NM1) fr[y % PDQ] = frag1(y + PDQ);
-        if (y % (NM1 / NPIECE) == 0) copy_piece(y / (NM1 / NPIECE), (t + 1) & 1, kpn, vpn, last_n);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // first K^T operands of the dQ^T product are requested now, so that they arrive during the dS arithmetic
-    constexpr int NM2 = 4 * (D / 32);
+    constexpr int NM2 = 4 * NMB;
     auto frag2 = [&](int y) -> bf16x8 {
-      const int kb = y / (2 * (D / 32)), cc = (y / (D / 32)) % 2, mb = y % (D / 32);
-      const uint16_t* krow = Kb + (32 * kb + 16 * cc) * D;
-      return join_tr(lds_read_tr4(krow + (kt_base0 ^ (mb << 5))), lds_read_tr4(krow + (kt_base1 ^ (mb << 5))));
+      const int kb = y / (2 * NMB), cc = (y / NMB) % 2, mb = y % NMB;
+      const int o = (32 * kb + 16 * cc) * D * 2;
+      return join_tr(lds_tr4_at((kt0 ^ (mb << 6)) + o), lds_tr4_at((kt1 ^ (mb << 6)) + o));
     };
-    bf16x8 f2[PDQ];
-#pragma unroll
-    for (int x = 0; x < PDQ; ++x) f2[x] = frag2(x);
-    __builtin_amdgcn_sched_barrier(0);
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
     const bool tail = (j + 1) * BKV > N;
+    f32x16 s[2], dp[2];
     uint32_t dsk[2][8];
+    auto exp_unit = [&](auto KB, auto U) {   // P^T of two keys
+      constexpr int kb = decltype(KB)::v, v = 2 * decltype(U)::v;
+      s[kb][v] = fast_exp2(fmaf(s[kb][v], a.scale_log2, -lse2));
+      s[kb][v + 1] = fast_exp2(fmaf(s[kb][v + 1], a.scale_log2, -lse2));
+    };
+    auto mask_tail = [&](auto KB) {          // keys past N (short last block): P = 0
+      constexpr int kb = decltype(KB)::v;
+      if (tail) {                            // (a branch: as selects it cost four instructions an element and tile)
+        const int valid = N - j * BKV - kb * 32 - 4 * ((fresh_tid() & 63) >> 5);
 #pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        float ds2[2];
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int v = 2 * u + e;
-          float p = fast_exp2(fmaf(s[kb][v], a.scale_log2, -lse2));
-          if (tail) {
-            const int key = j * BKV + kb * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
-            if (key >= N) p = 0.f;
-          }
-          ds2[e] = p * (dp[kb][v] - dlt);     // dS^T
-        }
-        dsk[kb][u] = pack_bf16(ds2[0], ds2[1]);
+        for (int v = 0; v < 16; ++v)
+          if (8 * (v >> 2) + (v & 3) >= valid) s[kb][v] = 0.f;
       }
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- dQ^T += K^T dS^T
+    };
+    auto ds_unit = [&](auto KB, auto U) {    // dS^T of two keys
+      constexpr int kb = decltype(KB)::v, u = decltype(U)::v;
+      dsk[kb][u] = pack_bf16(s[kb][2 * u] * dp[kb][2 * u], s[kb][2 * u + 1] * dp[kb][2 * u + 1]);
+    };
+    bf16x8 fr[PDQ], f2[PDT];
 #pragma unroll
-    for (int y = 0; y < NM2; ++y) {
-      const int kb = y / (2 * (D / 32)), cc = (y / (D / 32)) % 2, mb = y % (D / 32);
-      const u32x4 du = {dsk[kb][4 * cc], dsk[kb][4 * cc + 1], dsk[kb][4 * cc + 2], dsk[kb][4 * cc + 3]};
-      acc[mb] = mfma32(f2[y % PDQ], __builtin_bit_cast(bf16x8, du), acc[mb]);
-      if (y + PDQ < NM2) f2[y % PDQ] = frag2(y + PDQ);
+    for (int x = 0; x < PDQ; ++x) fr[x] = frag1(x);
+    static_for<0, NM1>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, kb = y / (2 * NK), rem = y % (2 * NK), kk = rem % NK;
+      if constexpr (rem < NK) s[kb] = mfma32(fr[y % PDQ], qf[kk], kk == 0 ? zero : s[kb]);
+      else                    dp[kb] = mfma32(fr[y % PDQ], dof[kk], kk == 0 ? neg_d : dp[kb]);
+      if constexpr (y + PDQ < NM1) fr[y % PDQ] = frag1(y + PDQ);
+      if constexpr (y % (NM1 / NPIECE) == 0) copy_piece(Int<y / (NM1 / NPIECE)>{}, kpn, vpn, nx_stage);
+      if constexpr (rem >= NK) static_for<kk * 8 / NK, (kk + 1) * 8 / NK>([&](auto U) { exp_unit(Int<kb>{}, U); });
+      if constexpr (rem == 2 * NK - 1) mask_tail(Int<kb>{});
+      if constexpr (kb == 1 && rem < NK) static_for<kk * 8 / NK, (kk + 1) * 8 / NK>([&](auto U) { ds_unit(Int<0>{}, U); });
+      if constexpr (y >= NM1 - PDT) f2[y - (NM1 - PDT)] = frag2(y - (NM1 - PDT));
       __builtin_amdgcn_sched_barrier(0);
-    }
+    });
+    // ---- dQ^T += K^T dS^T
+    static_for<0, NM2>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, kb = y / (2 * NMB), cc = (y / NMB) % 2, mb = y % NMB;
+      const u32x4 du = {dsk[kb][4 * cc], dsk[kb][4 * cc + 1], dsk[kb][4 * cc + 2], dsk[kb][4 * cc + 3]};
+      acc[mb] = mfma32(f2[y % PDT], __builtin_bit_cast(bf16x8, du), acc[mb]);
+      if constexpr (y + PDT < NM2) f2[y % PDT] = frag2(y + PDT);
+      if constexpr (kb == 0) static_for<(y * 8) / (2 * NMB), ((y + 1) * 8) / (2 * NMB)>([&](auto U) { ds_unit(Int<1>{}, U); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
     raw_copies_done();    // the copies requested in this iteration have landed
     __syncthreads();
   }
