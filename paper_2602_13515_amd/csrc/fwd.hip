@@ -63,20 +63,12 @@ __device__ __forceinline__ void fwd_store_rows(const FwdArgs& a, int bh, int64_t
 }
 
 template <int D>
-struct FwdCfg {
-  static constexpr int KP = D + 8;      // K tile row pitch (elements): row-wise 16-byte reads, conflict-free
-  static constexpr int VP = D + 32;     // V tile row pitch: transposing 8-byte reads, conflict-free
-  static constexpr int K_ELEMS = BKV * KP;
-  static constexpr int V_ELEMS = BKV * VP;
-  static constexpr int CH = BKV * D / 8 / 256;   // 16-byte chunks per thread per tile
-};
-constexpr int PD = 4;   // how many MFMAs ahead an LDS operand is requested
-
-template <int D>
 __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
-  using C = FwdCfg<D>;
-  __shared__ __align__(16) uint16_t Ks[2 * C::K_ELEMS];
-  __shared__ __align__(16) uint16_t Vs[2 * C::V_ELEMS];
+  constexpr int NK = D / 16, NMB = D / 32;           // contraction steps of S, output blocks of O
+  // Three K and two V tiles, XOR-swizzled and unpadded (the layout a direct global -> LDS copy can write); two
+  // workgroups of 80 KB share a compute unit.  (Aligned: compile-time parts are XORed into addresses.)
+  constexpr int TILE_B = BKV * D * 2, V_SLOTS = 3 * TILE_B;
+  __shared__ __align__(1024) unsigned char smem[5 * TILE_B];
 
   // Which row, and which part of its list.  The first sp.pool_slots workgroups of the launch are the parts of split
   // rows; the others take one row each, unless it is split.
@@ -96,7 +88,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
     if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tm + i] >= 0) return;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform, in a scalar register
   const int r32 = lane & 31, hf = lane >> 5;
   const int N = a.N;
   // counts and indices come from the caller's pattern: clamp them so that a corrupt list cannot
@@ -133,68 +126,58 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
     for (int kk = 0; kk < D / 16; ++kk) qf[kk] = *(const bf16x8*)(qp + 16 * kk);
   }
 
-  // global -> register staging of one K/V tile.  Thread t moves 16-byte chunk (row, col) with
-  // row = t / (D/8) + r * 256 / (D/8).  Rows past N (short last block) are clamped to the last
-  // token: their keys are masked out of the softmax below and their P is exactly zero, so the
-  // duplicated K/V rows never contribute.
-  constexpr int RSTEP = 256 / (D / 8);
-  const int ld_row = tid / (D / 8), ld_col = (tid % (D / 8)) * 8;
-  uint32_t goff[C::CH];          // byte offset of this thread's chunks inside a full tile
-#pragma unroll
-  for (int r = 0; r < C::CH; ++r) goff[r] = (uint32_t)(((ld_row + RSTEP * r) * a.sn + ld_col) * 2);
-  const int lds_k = ld_row * C::KP + ld_col, lds_v = ld_row * C::VP + ld_col;
-  // Two staging sets: a tile is requested two iterations before it is needed, so that a request has
-  // two tiles' worth of compute to come back from L2 / HBM (one is not enough under load).
-  struct Stage { u32x4 k[C::CH], v[C::CH]; };
-  Stage stA, stB;
-  auto load_tile = [&](Stage& st, int j) {
-    j = min(max(j, 0), a.Tn - 1);
-    const int64_t tile = (base + (int64_t)j * BKV * a.sn) * 2;       // uniform
-    const char* kp = (const char*)a.k + tile;
-    const char* vp = (const char*)a.v + tile;
-    if ((j + 1) * BKV <= N) {
-#pragma unroll
-      for (int r = 0; r < C::CH; ++r) {
-        st.k[r] = *(const u32x4*)(kp + goff[r]);
-        st.v[r] = *(const u32x4*)(vp + goff[r]);
-      }
-    } else {
-      const int last = N - 1 - j * BKV;
-#pragma unroll
-      for (int r = 0; r < C::CH; ++r) {
-        const uint32_t o2 = (uint32_t)((min(ld_row + RSTEP * r, last) * a.sn + ld_col) * 2);
-        st.k[r] = *(const u32x4*)(kp + o2);
-        st.v[r] = *(const u32x4*)(vp + o2);
-      }
-    }
+  // K/V tiles are copied global -> LDS directly.  The destination of a wave-wide 16-byte-per-lane copy is linear (wave
+  // base + 16 * lane), so the swizzle is applied on the source side: the lane that fills chunk position pc of a row
+  // fetches logical chunk pc ^ swz(row).  Thread t fills chunk position t % CPR of rows t / CPR + r * RSTEP; RSTEP is a
+  // multiple of 16 rows, so the swizzle term is the same for every r.  Rows past N (short last block) are clamped to the
+  // last token: their keys are masked out of the softmax and their P is exactly zero.  The lane offsets are computed
+  // again only when the number of valid rows changes.
+  constexpr int CPR = D / 8, RSTEP = 256 / CPR, CH = BKV / RSTEP;
+  // (what the rare paths of the loop need of the thread's number is worked out there, from the number itself: held in
+  // registers over the loop it would cost spills)
+  auto fresh_tid = [&]() -> int {
+    int t = tid;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(t));
+#endif
+    return t;
   };
-  auto store_tile = [&](const Stage& st, int buf) {
+  uint32_t voff[CH];
+  int rows_set = -1;
+  auto set_rows = [&](int j) {               // for the tile of key block j (uniform)
+    const int last = min(BKV - 1, N - 1 - j * BKV);
+    if (last == rows_set) return;
+    rows_set = last;
+    const int t = fresh_tid(), ld_row = t / CPR, ld_c8 = ((t % CPR) ^ swz<D>(ld_row)) * 8;
 #pragma unroll
-    for (int r = 0; r < C::CH; ++r) {
-      *(u32x4*)(Ks + buf * C::K_ELEMS + lds_k + RSTEP * r * C::KP) = st.k[r];
-      *(u32x4*)(Vs + buf * C::V_ELEMS + lds_v + RSTEP * r * C::VP) = st.v[r];
-    }
+    for (int r = 0; r < CH; ++r) voff[r] = (uint32_t)((min(ld_row + RSTEP * r, last) * a.sn + ld_c8) * 2);
+  };
+  const uint32_t sm = lds_addr_of(smem), sm_w = sm + w * 1024;
+  const char* k_head = (const char*)(a.k + base);
+  const char* v_head = (const char*)(a.v + base);
+  const uint64_t tile_bytes = (uint64_t)a.sn * (2 * BKV);
+  auto copy_tile = [&](const char* src, uint32_t slot) {
+    static_for<0, CH>([&](auto R) { raw_copy16_to_lds_at<decltype(R)::v * 4096>(src, voff[decltype(R)::v], sm_w + slot); });
   };
 
-  f32x16 oacc[D / 32];
+  f32x16 oacc[NMB];
 #pragma unroll
-  for (int mb = 0; mb < D / 32; ++mb)
+  for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
     for (int v = 0; v < 16; ++v) oacc[mb][v] = 0.f;
   float m_run = -INFINITY;   // running maximum, in log2 units (already multiplied by scale_log2)
   float l_run = 0.f;         // running sum over THIS lane's keys; the two halves are added at the end
 
-  // per-lane offsets inside a tile
-  const int k_off = r32 * C::KP + 8 * hf;                                   // K row read (A operand of S^T)
-  const int s16 = lane & 15, blk16 = lane >> 4;
-  const int v_off = (4 * hf + (s16 >> 2)) * C::VP + 16 * (blk16 & 1) + 4 * (s16 & 3);  // V transposing read
+  // per-lane LDS byte offsets inside a tile.  K row reads: row 32kb + r32, logical chunk 2kk + hf; the part of the chunk
+  // index that depends on kk is XORed in as (kk << 5).  V transposing reads: rows (16-row group) + 8*which + 4hf +
+  // (s16>>2), columns 32mb + 16hb + 4(s16&3); the part that depends on mb is XORed in as (mb << 6).
+  const int s16 = lane & 15, hb16 = (lane >> 4) & 1;
+  const uint32_t k_off = sm + 2 * swz_idx<D>(r32, 8 * hf);
+  const uint32_t v_off0 = sm + V_SLOTS + 2 * swz_idx<D>(4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
+  const uint32_t v_off1 = sm + V_SLOTS + 2 * swz_idx<D>(8 + 4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
 
-  // Pipeline: tile T is requested during iteration T-3 into the staging set of its parity, written to
-  // LDS buffer T&1 during iteration T-1 (that buffer held tile T-2, fully consumed before the barrier that
-  // ended iteration T-2), and consumed in iteration T.  Two tiles are in flight at any time and one
-  // barrier per tile is enough.
-  // The list of selected key blocks is read with scalar loads, one entry per iteration and one iteration
-  // ahead of its use: jw[m] is the (clamped) block of tile t+m, jpre the entry that becomes jw[3] next.
+  // The list of selected key blocks, 64 entries at a time in one register (lane l holds entry 64c + l): reading an entry
+  // is a lane read, not a memory access whose result the loop would have to wait for.
   // Where in its list a row starts is a free choice (the online softmax does not depend on the order of the
   // tiles, up to rounding), and it is used to keep the rows that run on one XCD at the same time close
   // together in key space: query block i starts at the first selected block at or after (i mod 64) / 64 of
@@ -202,149 +185,201 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   // free up, one row-duration spread over its 64 slots; so a row that starts 1/64 of a row-duration later
   // also starts 1/64 of the key range further on: all of them sweep the keys together and share K/V tiles
   // through the XCD's L2.  The start depends on the row alone, so results do not depend on the launch order.
-  int t0 = 0;
+  int pos = 0, idx_v = 0;                    // place in the list of the next entry, and the 64 entries around it
   {
     const int start_blk = (int)(((int64_t)(i & 63) * a.Tn) >> 6);
     for (int c = 0; c < cnt; c += 64) {
-      const int e = c + lane;
-      const bool below = e < cnt && idx[min(e, cnt - 1)] < start_blk;
-      t0 += __builtin_popcountll(__builtin_amdgcn_ballot_w64(below));
+      idx_v = idx[min(c + lane, cnt - 1)];
+      pos += __builtin_popcountll(__builtin_amdgcn_ballot_w64(c + lane < cnt && idx_v < start_blk));
     }
-    t0 = __builtin_amdgcn_readfirstlane(t0);
-    if (t0 >= cnt) t0 = 0;
+    pos = __builtin_amdgcn_readfirstlane(pos);
+    if (pos >= cnt) pos = 0;
+    if (cnt > 64) idx_v = list_load(idx, min((pos & ~63) + lane, cnt - 1));
   }
-  auto rot = [&](int t) -> int { const int p = min(t, cnt - 1) + t0; return p >= cnt ? p - cnt : p; };
-  auto list_at = [&](int t) -> int { return min(max(idx[rot(t)], 0), a.Tn - 1); };
-  int jw[4] = {list_at(0), list_at(1), list_at(2), list_at(3)};
-  int jpre = idx[rot(4)];      // raw: clamped when it is used, so that nothing waits for it here
-  // One piece of the staging work of an iteration: chunk r of K (p even) or V (p odd) of `next` goes to LDS
-  // buffer `buf` (tile t+1, requested two iterations ago), then the same registers request tile t+3.  The
-  // pieces are handed out between the MFMAs of the S^T loop: issued back to back, the eight requests would
-  // keep the wave at the issue stage until the texture unit has taken the last one.
-  // Both halves are unconditional (past the end of the list the last tile is requested again and the store
-  // goes to a buffer nobody reads): a branch around a memory operation inside the loop would make the
-  // compiler wait for every outstanding request at each store.
-  auto stage_piece = [&](Stage& st, int p, int buf, const char* kp, const char* vp, int last) {
-    const int r = p >> 1;
-    const uint32_t off = (uint32_t)((min(ld_row + RSTEP * r, last) * a.sn + ld_col) * 2);
-    if (p & 1) {
-      *(u32x4*)(Vs + buf * C::V_ELEMS + lds_v + RSTEP * r * C::VP) = st.v[r];
-      st.v[r] = *(const u32x4*)(vp + off);
-    } else {
-      *(u32x4*)(Ks + buf * C::K_ELEMS + lds_k + RSTEP * r * C::KP) = st.k[r];
-      st.k[r] = *(const u32x4*)(kp + off);
+  int left = cnt - 1;                        // entries behind the one at pos (past the end the last one is taken again)
+  auto next_entry = [&]() -> int {
+    const int j = min(max(__builtin_amdgcn_readlane(idx_v, pos & 63), 0), a.Tn - 1);
+    if (left > 0) {
+      --left;
+      pos = pos + 1 == cnt ? 0 : pos + 1;
+      if (cnt > 64 && (pos & 63) == 0) idx_v = list_load(idx, min(pos + (fresh_tid() & 63), cnt - 1));
     }
+    return j;
   };
-  load_tile(stA, jw[0]);
-  store_tile(stA, 0);
-  load_tile(stB, jw[1]);
-  load_tile(stA, jw[2]);
-  __syncthreads();
 
-  auto iteration = [&](int t, Stage& next, Stage& /*unused*/) {
-    const int j = jw[0], j3 = jw[3];
-    const int64_t tile3 = (base + (int64_t)j3 * BKV * a.sn) * 2;       // uniform
-    const char* kp3 = (const char*)a.k + tile3;
-    const char* vp3 = (const char*)a.v + tile3;
-    const int last3 = min(BKV - 1, N - 1 - j3 * BKV);
-    jw[0] = jw[1]; jw[1] = jw[2]; jw[2] = jw[3]; jw[3] = min(max(jpre, 0), a.Tn - 1);
-    jpre = idx[rot(t + 5)];
-    const uint16_t* Kb = Ks + (t & 1) * C::K_ELEMS;
-    const uint16_t* Vb = Vs + (t & 1) * C::V_ELEMS;
-
-    // S^T = K_j Q_i^T : two 32-key blocks.  LDS operand reads run PD MFMAs ahead of their use.
-    f32x16 s[2];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) s[kb][v] = 0.f;
-    {
-      constexpr int NQK = 2 * (D / 16);
-      bf16x8 kfr[PD];
-#pragma unroll
-      for (int x = 0; x < PD; ++x)
-        kfr[x] = *(const bf16x8*)(Kb + k_off + (x / (D / 16)) * 32 * C::KP + 16 * (x % (D / 16)));
-#pragma unroll
-      for (int x = 0; x < NQK; ++x) {
-        const int kb = x / (D / 16), kk = x % (D / 16);
-        s[kb] = mfma32(kfr[x % PD], qf[kk], s[kb]);
-        if (x + PD < NQK) {
-          const int y = x + PD;
-          kfr[x % PD] = *(const bf16x8*)(Kb + k_off + (y / (D / 16)) * 32 * C::KP + 16 * (y % (D / 16)));
-        }
-        if (x % 2 == 0) stage_piece(next, x / 2, (t + 1) & 1, kp3, vp3, last3);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    // first V^T operands of the second product are requested now, so that they arrive during the softmax
-    constexpr int NPV = 4 * (D / 32);
-    bf16x8 vfr[PD];
-    auto v_frag = [&](int y) {
-      const int kb = y / (2 * (D / 32)), cc = (y / (D / 32)) % 2, mb = y % (D / 32);
-      const uint16_t* vrow = Vb + v_off + (32 * kb + 16 * cc) * C::VP + 32 * mb;
-      return join_tr(lds_read_tr4(vrow), lds_read_tr4(vrow + 8 * C::VP));
-    };
-#pragma unroll
-    for (int x = 0; x < PD; ++x) vfr[x] = v_frag(x);
-    __builtin_amdgcn_sched_barrier(0);
-    // keys past N (short last block) do not take part in the softmax
+  const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  constexpr int PD = 4, PDV = 4;             // how many MFMAs ahead an LDS operand is requested
+  uint32_t pk[2][8];
+  // P^T = exp(S^T - m) (step 12) of two keys, rounded to bf16 for the second product; the row sum (step 13) is taken
+  // over the rounded values, so numerator and denominator use the same weights
+  auto exp_unit = [&](const f32x16 (&s)[2], auto U) {
+    constexpr int kb = decltype(U)::v / 8, u = decltype(U)::v % 8;
+    const float p0 = fast_exp2(fmaf(s[kb][2 * u], a.scale_log2, -m_run));
+    const float p1 = fast_exp2(fmaf(s[kb][2 * u + 1], a.scale_log2, -m_run));
+    pk[kb][u] = pack_bf16(p0, p1);
+    l_run = dot2_ones(pk[kb][u], l_run);
+  };
+  // keys past N (short last block) do not take part in the softmax
+  auto mask_tail = [&](f32x16 (&s)[2], int j) {
     if ((j + 1) * BKV > N) {
+      const int valid = N - j * BKV - 4 * ((fresh_tid() & 63) >> 5);
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) {
-          const int key = j * BKV + kb * 32 + 8 * (v >> 2) + 4 * hf + (v & 3);
-          if (key >= N) s[kb][v] = -INFINITY;
-        }
+        for (int v = 0; v < 16; ++v)
+          if (kb * 32 + 8 * (v >> 2) + (v & 3) >= valid) s[kb][v] = -INFINITY;
     }
-    // running maximum (Alg. 1 step 11)
-    float mx = s[0][0];
-#pragma unroll
-    for (int v = 1; v < 16; ++v) mx = fmaxf(mx, s[0][v]);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) mx = fmaxf(mx, s[1][v]);
+  };
+  // running maximum (Alg. 1 step 11); the accumulators are rescaled (steps 13-14) only when some row's maximum moved:
+  // after the first few tiles it rarely does, and the branch is uniform over the wave
+  auto new_max = [&](float mx) {
     mx = max_halves(mx);
     const float m_new = fmaxf(m_run, mx * a.scale_log2);
-    // rescale the accumulators (steps 13-14) only when some row's maximum moved: after the first
-    // few tiles it rarely does, and the branch is uniform over the wave
     if (__builtin_amdgcn_ballot_w64(m_new != m_run) != 0) {
       const float alpha = fast_exp2(m_run - m_new);
       l_run *= alpha;
 #pragma unroll
-      for (int mb = 0; mb < D / 32; ++mb)
+      for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int v = 0; v < 16; ++v) oacc[mb][v] *= alpha;
       m_run = m_new;
     }
-    // P^T = exp(S^T - m) (step 12), rounded to bf16 for the second product; the row sum (step 13)
-    // is taken over the rounded values, so numerator and denominator use the same weights
-    uint32_t pk[2][8];
-#pragma unroll
-    for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const float p0 = fast_exp2(fmaf(s[kb][2 * u], a.scale_log2, -m_run));
-        const float p1 = fast_exp2(fmaf(s[kb][2 * u + 1], a.scale_log2, -m_run));
-        pk[kb][u] = pack_bf16(p0, p1);
-        l_run = dot2_ones(pk[kb][u], l_run);
-      }
-    // O^T += V^T P^T (step 14).  MFMA x uses key slots 32kb + 16cc + 4hf + {0..3} and + 8 (the order the
-    // accumulator of S^T holds them in) of output block mb.
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int x = 0; x < NPV; ++x) {
-      const int kb = x / (2 * (D / 32)), cc = (x / (D / 32)) % 2, mb = x % (D / 32);
-      const u32x4 pu = {pk[kb][4 * cc], pk[kb][4 * cc + 1], pk[kb][4 * cc + 2], pk[kb][4 * cc + 3]};
-      oacc[mb] = mfma32(vfr[x % PD], __builtin_bit_cast(bf16x8, pu), oacc[mb]);
-      if (x + PD < NPV) vfr[x % PD] = v_frag(x + PD);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    __syncthreads();
   };
-  for (int t = 0; t < cnt; t += 2) {
-    iteration(t, stB, stA);                       // tile t+1 (odd) lives in set B
-    if (t + 1 < cnt) iteration(t + 1, stA, stB);  // tile t+2 (even) lives in set A
+  auto k_frag = [&](uint32_t ka, int y) -> bf16x8 {            // y = kb * NK + kk
+    return lds_ld16((ka ^ ((y % NK) << 5)) + (y / NK) * 32 * D * 2);
+  };
+  auto v_frag = [&](uint32_t v0, uint32_t v1, int x) -> bf16x8 {       // x = (kb, cc, mb)
+    const int o = (x / NMB) * 16 * D * 2, mb = x % NMB;
+    return join_tr(lds_tr4_at((v0 ^ (mb << 6)) + o), lds_tr4_at((v1 ^ (mb << 6)) + o));
+  };
+  auto p_frag = [&](int x) -> bf16x8 {       // P^T of the 16 keys (kb, cc)
+    const int kb = x / (2 * NMB), cc = (x / NMB) % 2;
+    return __builtin_bit_cast(bf16x8, u32x4{pk[kb][4 * cc], pk[kb][4 * cc + 1], pk[kb][4 * cc + 2], pk[kb][4 * cc + 3]});
+  };
+
+  // Bound: the board's power (1.70 GHz).  Pipeline: iteration t computes S of tile t+1 with the exponentials of tile t between the products, then adds
+  // V P of tile t with the rest of them and the maximum of tile t+1 between: a wave's vector arithmetic runs behind its
+  // own products.  Meanwhile V of tile t+1 (whose slot tile t-1 has left) and K of tile t+3 (slot of tile t) are on
+  // their way; all but the latter have landed at the barrier that ends the iteration.  The copies are handed out between
+  // the products: issued back to back they would keep the wave at the issue stage until the texture unit has taken the
+  // last one.  They are unconditional (past the end of the list its last tile is requested again).
+  // Measured against S, softmax and V P one after the other with tiles staged through registers, us, before / after
+  // (same bits): 75,600 tokens, 40 heads at 94 % / 97 % sparsity 8042 / 7800 and 4235 / 4085; 32,760 tokens, 12 heads
+  // 904 / 870, 3 heads and every tile 1661 / 1604; 3500 instead of 3700 cycles a tile and wave at two waves per SIMD.
+  uint32_t ks0 = 0, ks1 = TILE_B, ks2 = 2 * TILE_B;            // slots of K of tiles t, t+1, t+2
+  int j1, j2, j3;                                              // key blocks of tiles t+1, t+2, t+3
+  f32x16 sA[2], sB[2];
+  {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+    for (int kk = 0; kk < NK; ++kk) asm volatile("" : "+v"(qf[kk]));   // (Q is waited for before the copies, not with them)
+#endif
+    const int j0 = next_entry();
+    j1 = next_entry(); j2 = next_entry();
+    set_rows(j0);
+    copy_tile(k_head + j0 * tile_bytes, ks0);
+    copy_tile(v_head + j0 * tile_bytes, V_SLOTS);
+    set_rows(j1);
+    copy_tile(k_head + j1 * tile_bytes, ks1);
+    set_rows(j2);
+    copy_tile(k_head + j2 * tile_bytes, ks2);
+    j3 = next_entry();
+    raw_copies_left<3 * CH>();
+    __syncthreads();
+    bf16x8 fr[PD];
+#pragma unroll
+    for (int x = 0; x < PD; ++x) fr[x] = k_frag(k_off, x);
+    static_for<0, 2 * NK>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, kb = y / NK, kk = y % NK;
+      sA[kb] = mfma32(fr[y % PD], qf[kk], kk == 0 ? zero : sA[kb]);
+      if constexpr (y + PD < 2 * NK) fr[y % PD] = k_frag(k_off, y + PD);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    mask_tail(sA, j0);
+    float mx = sA[0][0];
+#pragma unroll
+    for (int v = 1; v < 32; ++v) mx = fmaxf(mx, sA[v / 16][v % 16]);
+    m_run = max_halves(mx) * a.scale_log2;
+    raw_copies_left<CH>();
+    __syncthreads();
   }
+  auto step = [&](const f32x16 (&sc)[2], f32x16 (&sn)[2], int t) {     // sc: S of tile t, sn: of tile t+1
+    constexpr int E1 = D == 128 ? 10 : 8;    // exponential units (of 16) that run between the S products
+    uint32_t ka = k_off + ks1, v0 = v_off0 + (t & 1) * TILE_B, v1 = v_off1 + (t & 1) * TILE_B;
+#if defined(__HIP_DEVICE_COMPILE__)
+    // (keeps the XORed operand addresses out of loop-invariant hoisting: one VALU op per read instead of a dozen live
+    // registers)
+    asm volatile("" : "+v"(ka), "+v"(v0), "+v"(v1));
+#endif
+    const char* vpn = v_head + j1 * tile_bytes;
+    const char* kpn = k_head + j3 * tile_bytes;
+    const uint32_t v_dst = sm_w + V_SLOTS + ((t + 1) & 1) * TILE_B, k_dst = sm_w + ks0;
+    bf16x8 fr[PD], vf[PDV];
+#pragma unroll
+    for (int x = 0; x < PD; ++x) fr[x] = k_frag(ka, x);
+    set_rows(j1);
+    // S^T = K_j Q_i^T of tile t+1: two 32-key blocks
+    static_for<0, 2 * NK>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, kb = y / NK, kk = y % NK, piece = y / 2;
+      sn[kb] = mfma32(fr[y % PD], qf[kk], kk == 0 ? zero : sn[kb]);
+      if constexpr (y + PD < 2 * NK) fr[y % PD] = k_frag(ka, y + PD);
+      if constexpr (y == 2 * CH) set_rows(j3);
+      if constexpr (y % 2 == 0) {
+        if constexpr (piece < CH) raw_copy16_to_lds_at<piece * 4096>(vpn, voff[piece], v_dst);
+        else                      raw_copy16_to_lds_at<(piece - CH) * 4096>(kpn, voff[piece - CH], k_dst);
+      }
+      static_for<y * E1 / (2 * NK), (y + 1) * E1 / (2 * NK)>([&](auto U) { exp_unit(sc, U); });
+      if constexpr (y >= 2 * NK - PDV) vf[y - (2 * NK - PDV)] = v_frag(v0, v1, y - (2 * NK - PDV));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    mask_tail(sn, j1);
+    // O^T += V^T P^T of tile t (step 14).  MFMA x uses key slots 32kb + 16cc + 4hf + {0..3} and + 8 (the order the
+    // accumulator of S^T holds them in) of output block mb.
+    float mx = -INFINITY;
+    static_for<0, 4 * NMB>([&](auto X) {
+      constexpr int x = decltype(X)::v, mb = x % NMB, H = 2 * NMB;
+      oacc[mb] = mfma32(vf[x % PDV], p_frag(x), oacc[mb]);
+      if constexpr (x + PDV < 4 * NMB) vf[x % PDV] = v_frag(v0, v1, x + PDV);
+      if constexpr (x < H) {
+        static_for<E1 + x * (16 - E1) / H, E1 + (x + 1) * (16 - E1) / H>([&](auto U) { exp_unit(sc, U); });
+      } else {
+        static_for<(x - H) * 32 / H, (x - H + 1) * 32 / H>([&](auto V) { mx = fmaxf(mx, sn[decltype(V)::v / 16][decltype(V)::v % 16]); });
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    raw_copies_left<CH>();
+    __syncthreads();
+    new_max(mx);
+    const uint32_t k = ks0; ks0 = ks1; ks1 = ks2; ks2 = k;
+    j1 = j2; j2 = j3; j3 = next_entry();
+  };
+  auto last_step = [&](const f32x16 (&sc)[2], int t) {         // V P of the last tile
+    const uint32_t v0 = v_off0 + (t & 1) * TILE_B, v1 = v_off1 + (t & 1) * TILE_B;
+    bf16x8 vf[PDV];
+#pragma unroll
+    for (int x = 0; x < PDV; ++x) vf[x] = v_frag(v0, v1, x);
+    static_for<0, 8>([&](auto U) { exp_unit(sc, U); });
+    static_for<0, 4 * NMB>([&](auto X) {
+      constexpr int x = decltype(X)::v, mb = x % NMB, H = 2 * NMB;
+      oacc[mb] = mfma32(vf[x % PDV], p_frag(x), oacc[mb]);
+      if constexpr (x + PDV < 4 * NMB) vf[x % PDV] = v_frag(v0, v1, x + PDV);
+      if constexpr (x < H) static_for<8 + x * 8 / H, 8 + (x + 1) * 8 / H>([&](auto U) { exp_unit(sc, U); });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    raw_copies_done();       // (nothing may land in the LDS once this workgroup is through with it)
+  };
+  int t = 0;
+  for (; t + 2 < cnt; t += 2) {
+    step(sA, sB, t);
+    step(sB, sA, t + 1);
+  }
+  if (t + 1 < cnt) {
+    step(sA, sB, t);
+    ++t;
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb) sA[kb] = sB[kb];
+  }
+  last_step(sA, t);
 
   const float l_tot = sum_halves(l_run);
   if (parts) {                // one part of a split row
@@ -355,7 +390,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
 #pragma unroll
       for (int g = 0; g < 8; ++g) part_store2(ps + ((mb * 8 + g) * 256 + tid) * 2, oacc[mb][2 * g], oacc[mb][2 * g + 1]);
     part_store2(ps + 256 * (D / 2) + 2 * tid, m_run, l_tot);
-    if (!last_part(a.sp.arrive + first, parts, (int*)Ks)) return;
+    if (!last_part(a.sp.arrive + first, parts, (int*)smem)) return;
     // The last part to arrive combines all of them, in part order (so the result does not depend on which one that
     // is): m = max m_p, l = sum l_p 2^(m_p - m), O = sum O_p 2^(m_p - m) / l.
     const float* p0 = a.sp.pool + first * a.sp.slot_floats;
