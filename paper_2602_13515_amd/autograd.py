@@ -7,6 +7,8 @@ input of the attention call).  PyTorch allocates the buffers; every step runs in
 """
 from __future__ import annotations
 
+import functools
+import importlib
 import math
 from typing import Optional, Tuple
 
@@ -45,6 +47,26 @@ def _check_inputs(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor) -> None:
         raise ValueError("self-attention: q, k, v share one shape")
     if q.stride(3) != 1:
         raise ValueError("the head dimension must be contiguous")
+
+
+@functools.lru_cache(maxsize=None)
+def _operator():
+    """The operators in native code (csrc/operator.cpp)."""
+    _b._load()
+    try:
+        return importlib.import_module(__package__ + "._operator")
+    except ImportError as e:
+        raise RuntimeError("_operator.so is missing or does not load: build it with `python -m paper_2602_13515_amd.build`") from e
+
+
+def _plain(*tensors: torch.Tensor) -> bool:
+    """Whether the native operators may take these tensors: plain CUDA tensors, outside tracing, compilation and function
+    transforms (which have to see, or refuse, a Python autograd function)."""
+    for t in tensors:
+        if type(t) is not torch.Tensor and type(t) is not torch.nn.Parameter or not t.is_cuda:
+            return False
+    return (torch._C._get_tracing_state() is None and not torch._C._are_functorch_transforms_active()
+            and not torch.compiler.is_compiling())
 
 
 def build_pattern(q: torch.Tensor, k: torch.Tensor, k_frac: float, top_p: float,
@@ -146,6 +168,15 @@ def sparge_attn2(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, k_frac: floa
     `x.permute(0, 2, 1, 3)` without a copy.  k_frac, top_p in [0, 1].  `pattern`, when given, is used instead
     of building one from (q, k).  `overlap_backward` runs the two backward kernels at the same time on two
     streams (same results).  Returns O with q's shape and strides (and the pattern on request)."""
+    if (pattern is not None or not return_pattern) and not overlap_backward and _plain(q, k, v):
+        # The same in native code.  Passes (us): two heads, 1,000 tokens, sampling 46 -> 28; 2,048 tokens, forward and
+        # backward 226 -> 90; 24 heads, 1,281 tokens 223 -> 133.
+        if scale is None:
+            scale = 1.0 / math.sqrt(q.shape[-1]) if q.dim() and q.shape[-1] else 1.0      # (those are refused there)
+        given = [] if pattern is None else [pattern.mask, pattern.row_cnt, pattern.row_idx, pattern.col_cnt,
+                                            pattern.col_idx, pattern.row_order, pattern.col_order]
+        o = _operator().attention(q, k, v, float(k_frac), float(top_p), float(scale), given)
+        return (o, pattern) if return_pattern else o
     _check_inputs(q, k, v)
     scale = 1.0 / math.sqrt(q.shape[-1]) if scale is None else float(scale)
     # Without a backward pass to come (sampling) nobody reads the column lists or the output's residual: two kernels

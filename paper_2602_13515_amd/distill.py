@@ -14,7 +14,7 @@ from typing import Callable, Dict, Iterable, Optional, Tuple
 import torch
 
 from . import binding as _b
-from .autograd import sparge_attn2
+from .autograd import _operator, _plain, sparge_attn2
 
 
 class ToyBlock(torch.nn.Module):
@@ -96,6 +96,8 @@ def velocity_distillation_loss(u_sparse: torch.Tensor, u_full: torch.Tensor, red
     if not u_sparse.is_cuda:
         raise ValueError("spa2 runs on the GPU only: predictions must be CUDA tensors")
     u_full = u_full.to(u_sparse.dtype)
+    if _plain(u_sparse, u_full):
+        return _operator().velocity_loss(u_sparse, u_full, weight)
     return _VelocityDistillationLoss.apply(u_sparse.contiguous(), u_full.contiguous(), weight)
 
 

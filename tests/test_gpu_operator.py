@@ -1,0 +1,87 @@
+"""The operators' native route (plain CUDA tensors) against the Python autograd functions behind the other calls."""
+import pytest
+import torch
+
+import paper_2602_13515_amd as spa2
+from paper_2602_13515_amd import autograd
+from paper_2602_13515_amd import workloads as wl
+from paper_2602_13515_amd.distill import _VelocityDistillationLoss, velocity_distillation_loss
+
+from gpu_util import dev
+
+pytestmark = pytest.mark.gpu
+
+# 32 and 504 key blocks take no launch order, 513 and 632 do; a query block and a key block that end early; k and v in
+# another layout than q
+CASES = [(1, 2, 1000, 64, "bhnd"), (1, 1, 64 * 513, 64, "bhnd"), (4, 6, 1281, 128, "bnhd"), (2, 2, 10090, 128, "mixed")]
+
+
+def _inputs(B, H, N, d, layout):
+    w = wl.Workload("op", B, H, N, d, 0.1, 0.6, "lowrank", True)
+    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=3))
+    bnhd = lambda t: t.permute(0, 2, 1, 3).contiguous().permute(0, 2, 1, 3)
+    if layout == "bnhd":
+        q, k, v, do = (bnhd(t) for t in (q, k, v, do))
+    elif layout == "mixed":
+        k = bnhd(k)
+    return q, k, v, do
+
+
+@pytest.mark.parametrize("B,H,N,d,layout", CASES)
+def test_native_route_gives_the_bits_of_the_python_route(B, H, N, d, layout, monkeypatch):
+    q, k, v, do = _inputs(B, H, N, d, layout)
+    got, full = {}, spa2.build_pattern(q, k, 0.05, 0.3)
+    for native in (True, False):
+        if not native:
+            monkeypatch.setattr(autograd, "_plain", lambda *t: False)
+        with torch.no_grad():
+            sampled = spa2.sparge_attn2(q, k, v, 0.1, 0.6)
+        leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+        o = spa2.sparge_attn2(*leaves, 0.1, 0.6)
+        assert ("CppNode" in o.grad_fn.name()) == native
+        assert o.stride() == q.stride()
+        got[native] = (sampled, o.detach(), *torch.autograd.grad(o, leaves, do))
+        o = spa2.sparge_attn2(*leaves, 0.0, 0.0, pattern=full)
+        got[native] += (o.detach(), *torch.autograd.grad(o, leaves, do))
+    for a, b in zip(*got.values()):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("rows,dtype,reduction", [(1, torch.float32, "mean"), (777, torch.bfloat16, "batch")])
+def test_native_loss_gives_the_bits_of_the_python_route(rows, dtype, reduction):
+    g = torch.Generator().manual_seed(1)
+    us, uf = (torch.randn((2, rows, 65), generator=g).to(dev(), dtype) for _ in range(2))
+    a, b = us.clone().requires_grad_(True), us.clone().requires_grad_(True)
+    loss = velocity_distillation_loss(a, uf, reduction)
+    ref = _VelocityDistillationLoss.apply(b, uf, 1.0 / (us.numel() if reduction == "mean" else 2))
+    assert torch.equal(loss, ref)
+    (3.0 * loss).backward(); (3.0 * ref).backward()
+    assert torch.equal(a.grad, b.grad)
+
+
+def test_native_route_refuses_what_the_python_route_refuses():
+    q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
+    call = lambda *t: spa2.sparge_attn2(*t, 0.1, 0.6)
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda x: call(q, k, v) + x)(torch.ones(3, device=dev()))
+    for bad in ((q.cpu(), k, v), (q, k.cpu(), v), (q, k.float(), v), (q, k[:, :, :299], v), (q[0], k[0], v[0]),
+                (q, k, v.transpose(2, 3).contiguous())):
+        with pytest.raises(ValueError):
+            call(*bad)
+    rows = spa2.build_pattern(q, k, 0.1, 0.6, columns=False)       # no lists for the backward pass
+    o = spa2.sparge_attn2(*(t.detach().requires_grad_(True) for t in (q, k, v)), 0.0, 0.0, pattern=rows)
+    with pytest.raises(spa2.Spa2Error):
+        o.backward(do)
+    with pytest.raises(spa2.Spa2Error) as e:                       # head dimension 32
+        call(*(t[..., :32].contiguous() for t in (q, k, v)))
+    assert e.value.code < 0
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    relaid = lambda x: x.transpose(1, 2).contiguous().transpose(1, 2) if x.dim() == 4 and x.data_ptr() == leaves[1].data_ptr() else x
+    with torch.autograd.graph.saved_tensors_hooks(relaid, lambda x: x):      # k comes back in another layout
+        o = call(*leaves)
+    with pytest.raises(ValueError):
+        o.backward(do)
+    o = call(*leaves)
+    o.backward(do)
+    with pytest.raises(RuntimeError):                              # a second time without retain_graph
+        o.backward(do)
