@@ -68,7 +68,8 @@ SplitPlan dq_plan(const Dims& m, void* ws, size_t ws_bytes) {
 }
 SplitPlan dkdv_plan(const Dims& m, void* ws, size_t ws_bytes) {
   const BwdWs w = bwd_ws(m);
-  return section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, (int64_t)m.B * m.H * m.Tn, m.Tm, dkdv_slot_bytes(m));
+  const int64_t units = (int64_t)m.B * m.H * m.Tn;
+  return with_queue(section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, units, m.Tm, dkdv_slot_bytes(m)), units);
 }
 
 }  // namespace

@@ -4,6 +4,7 @@
 // accumulators are pinned to the accumulation registers through mfma32_acc below.
 #include "spa2_device.h"
 #include "spa2_internal.h"
+#include "work_queue.h"
 
 namespace spa2 {
 
@@ -22,7 +23,7 @@ struct DkvArgs {
   const uint16_t* q; const uint16_t* k; const uint16_t* v; const uint16_t* d_o;
   const float* lse; const float* delta; uint16_t* dk; uint16_t* dv;
   const int32_t* col_cnt; const int32_t* col_idx; const int32_t* col_order;
-  int H, N, Tm, Tn, chunk;
+  int BH, H, N, Tm, Tn, chunk;
   int64_t sb, sh, sn;
   float scale, scale_log2;
   SplitPlan sp;         // long columns cut into parts (split.hip); sp.pool_slots == 0: every column is walked whole
@@ -60,8 +61,8 @@ size_t dkdv_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dkdv_slot_f
 // 14772 / 13440; 32,760 tokens, 12 heads 1026 / 921; 20,010 tokens, 6 heads, d = 64 155 / 134.
 // The two waves add their partial sums through LDS at the end of the column.
 template <int D>
-__global__ __attribute__((amdgpu_flat_work_group_size(128, 128), amdgpu_waves_per_eu(1, 1)))
-void dkdv_kernel(DkvArgs a) {
+__device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item, Walk& walk, unsigned char* smem,
+                                          unsigned char* stat_s) {
   constexpr int QW = 32;                             // query rows per wave and step
   constexpr int HQ = 64;                             // query rows per workgroup and step
   constexpr int NK = D / 16;                         // 16-wide contraction steps over the head dimension
@@ -72,27 +73,9 @@ void dkdv_kernel(DkvArgs a) {
   constexpr int TILE_B = QW * D * 2;                 // bytes of one wave's 32-row tile
   constexpr int STAGE_B = 2 * TILE_B;                // Q rows, then dO rows
   constexpr int STAT_B = 512;                        // LSE of the 32 rows at +0, D at +256
-  __shared__ __align__(1024) unsigned char smem[2 * 2 * STAGE_B];   // (aligned: compile-time parts are XORed into addresses)   // wave w, stage s at (2w + s) * STAGE_B
-  __shared__ __align__(1024) unsigned char stat_s[2 * 2 * STAT_B];  // wave w, stage s
-  // Which key block, and which part of its list (the first sp.pool_slots workgroups of the launch are the parts of
-  // split columns; the others take one key block each, unless it is split)
-  int bh, j, part = 0, parts = 0, part_len = 0;
-  if ((int)blockIdx.x < a.sp.pool_slots) {
-    if ((int)blockIdx.x >= a.sp.header[0]) return;
-    const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
-    const int unit = pt[0];
-    part = pt[1]; parts = pt[2]; part_len = pt[3];
-    bh = unit / a.Tn; j = unit % a.Tn;
-  } else {
-    const HeadBlock hbk = xcd_map(blockIdx.x - a.sp.pool_slots, a.Tn, a.chunk);
-    if (!hbk.valid) return;
-    bh = hbk.bh;
-    j = a.col_order ? min(max(a.col_order[(int64_t)bh * a.Tn + hbk.blk], 0), a.Tn - 1) : hbk.blk;
-    if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tn + j] >= 0) return;
-  }
+  const int bh = item.bh, j = item.blk, part = item.part, parts = item.parts, part_len = item.part_len;
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform, in a scalar register
+  const int lane = fresh_lane(), w = walk.wave;
   const int r32 = lane & 31, hf = lane >> 5;
   const int N = a.N;
   int cnt = min(max(a.col_cnt[(int64_t)bh * a.Tn + j], 0), a.Tm);   // clamped: see fwd.hip
@@ -149,12 +132,13 @@ void dkdv_kernel(DkvArgs a) {
   auto set_rows = [&](int last) {            // last: last valid row of the 32 (uniform)
     if (last == rows_set) return;
     rows_set = last;
+    const int l = fresh_lane();
 #pragma unroll
     for (int r = 0; r < NCP; ++r) {
-      const int row_l = RPI * r + lane / CPR;
-      voff[r] = (uint32_t)((min(row_l, last) * a.sn + (((lane % CPR) ^ swz<D>(row_l)) * 8)) * 2);
+      const int row_l = RPI * r + l / CPR;
+      voff[r] = (uint32_t)((min(row_l, last) * a.sn + (((l % CPR) ^ swz<D>(row_l)) * 8)) * 2);
     }
-    soff = (uint32_t)(min(r32, last) * 4);
+    soff = (uint32_t)(min(l & 31, last) * 4);
   };
   const char* q_head = (const char*)(a.q + base);
   const char* o_head = (const char*)(a.d_o + base);
@@ -169,7 +153,9 @@ void dkdv_kernel(DkvArgs a) {
   };
   // Query rows past N get an LSE of +infinity once their copy has landed: their P is then exactly zero.
   auto mark_rows_past_end = [&](int row0, uint32_t stat_addr) {
-    if (row0 + QW > N && row0 + r32 >= N) lds_stf(stat_addr + 4 * r32, INFINITY);
+    if (row0 + QW <= N) return;
+    const int row_l = fresh_lane() & 31;
+    if (row0 + row_l >= N) lds_stf(stat_addr + 4 * row_l, INFINITY);
   };
 
   // the index list, 64 entries at a time in one register (lane l holds entry 64c + l): reading entry t is a
@@ -218,7 +204,7 @@ void dkdv_kernel(DkvArgs a) {
   for (int u = 0; u < steps; ++u) {
     const int st = u & 1;
     const int un = min(u + 1, steps - 1);    // past the end the last step is requested again (nobody reads it)
-    if (((u + 1) & 127) == 0 && u + 1 < steps) idx_v = list_load(idx, min(((u + 1) >> 1) + lane, cnt - 1));   // next 64 entries
+    if (((u + 1) & 127) == 0 && u + 1 < steps) idx_v = list_load(idx, min(((u + 1) >> 1) + fresh_lane(), cnt - 1));   // next 64 entries
     const int row_nx = step_row(un), row_b = min(row_nx, N - 1);
     set_rows(min(QW - 1, N - 1 - row_b));
     const uint32_t nx_stage = wsm + (st ^ 1) * STAGE_B, nx_stat = wstat + (st ^ 1) * STAT_B;
@@ -330,6 +316,7 @@ void dkdv_kernel(DkvArgs a) {
   // (the compiler does not know that mfma32_acc is a matrix instruction and inserts no wait states for it); and the
   // copies of the step past the end have to be out of the way of the exchange below
   raw_copies_done();
+  walk.draw(a.sp);
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
 #endif
@@ -339,9 +326,9 @@ void dkdv_kernel(DkvArgs a) {
   constexpr int REGION = 2 * NMB * 4 * 64 * 4;        // floats per wave
   static_assert(REGION * 4 == 2 * STAGE_B, "the sums that a wave hands over fill exactly its two stages");
   float* scratch = (float*)smem;
-  const int key = key0 + 32 * w;
+  const int le = fresh_lane(), he = le >> 5, key = j * BKV + 32 * w + (le & 31);
   auto hand_over = [&](auto KH) {
-    f32x4* out = (f32x4*)(scratch + w * REGION) + lane;
+    f32x4* out = (f32x4*)(scratch + w * REGION) + le;
     static_for<0, 8 * NMB>([&](auto C) {
       constexpr int c = decltype(C)::v, mb = (c / 4) % NMB, v = 4 * (c % 4);
       const f32x16& x = c < 4 * NMB ? dk_acc[decltype(KH)::v][mb] : dv_acc[decltype(KH)::v][mb];
@@ -351,7 +338,7 @@ void dkdv_kernel(DkvArgs a) {
   };
   // put(tensor, output block, group, sums) of every piece that this wave finishes
   auto finish = [&](auto KH, auto&& put) {
-    const f32x4* in = (const f32x4*)(scratch + (1 - w) * REGION) + lane;
+    const f32x4* in = (const f32x4*)(scratch + (1 - w) * REGION) + le;
     static_for<0, 8 * NMB>([&](auto C) {
       constexpr int c = decltype(C)::v, mb = (c / 4) % NMB, v = 4 * (c % 4);
       const f32x16& x = c < 4 * NMB ? dk_acc[decltype(KH)::v][mb] : dv_acc[decltype(KH)::v][mb];
@@ -363,7 +350,7 @@ void dkdv_kernel(DkvArgs a) {
   else        hand_over(Int<0>{});
   __syncthreads();
   if (parts) {                  // one part of a split column: leave the sums to the last part (the whole slot is
-    float* ps = a.sp.pool + (int64_t)blockIdx.x * a.sp.slot_floats + 2 * lane;       // written: the merge reads it)
+    float* ps = a.sp.pool + (int64_t)item.slot * a.sp.slot_floats + 2 * le;       // written: the merge reads it)
     auto put = [&](int t, int mb, int g, f32x4 x) {
       float* p = ps + (((t * 2 + w) * NMB + mb) * 4 + g) * 256;
       part_store2(p, x[0], x[1]);
@@ -373,7 +360,7 @@ void dkdv_kernel(DkvArgs a) {
     else        finish(Int<1>{}, put);
   } else {
     if (key >= N) return;
-    const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
+    const int64_t out_off = base + (int64_t)key * a.sn + 4 * he;
     auto put = [&](int t, int mb, int g, f32x4 x) {
       const float sc = t == 0 ? -a.scale : 1.f;
       const u32x2 pk2 = {pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
@@ -385,10 +372,10 @@ void dkdv_kernel(DkvArgs a) {
   }
   // the last part of a split column to arrive adds all of them in part order
   {
-    const int64_t first = blockIdx.x - part;
+    const int64_t first = item.slot - part;
     if (!last_part(a.sp.arrive + first, parts, (int*)stat_s) || key >= N) return;
-    const int64_t out_off = base + (int64_t)key * a.sn + 4 * hf;
-    const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * lane;
+    const int64_t out_off = base + (int64_t)key * a.sn + 4 * he;
+    const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * le;
 #pragma unroll
     for (int round = 0; round < 2; ++round) {
       f32x2 x[NMB * 8];
@@ -417,6 +404,23 @@ void dkdv_kernel(DkvArgs a) {
   }
 }
 
+template <int D>
+__global__ __attribute__((amdgpu_flat_work_group_size(128, 128), amdgpu_waves_per_eu(1, 1)))
+void dkdv_kernel(DkvArgs) {
+  // (aligned: compile-time parts are XORed into addresses)
+  __shared__ __align__(1024) unsigned char smem[2 * 2 * 2 * 32 * D * 2];    // wave w, stage s at (2w + s) * STAGE_B
+  __shared__ __align__(1024) unsigned char stat_s[2 * 2 * 512];             // wave w, stage s
+  __shared__ int word;
+  Walk walk(&word);
+  for (;;) {
+    const DkvArgs& a = fresh_args<DkvArgs>();
+    WorkItem item;
+    if (!walk.take(item, a.sp, a.Tn, a.chunk, a.BH, a.col_order)) return;
+    dkdv_item<D>(a, item, walk, smem, stat_s);
+    if (!walk.advance(a.sp)) return;
+  }
+}
+
 hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                            const float* delta, const Dims& m, const int32_t* col_cnt, const int32_t* col_idx,
                            const int32_t* col_order, float scale, void* dk, void* dv, const SplitPlan& plan,
@@ -425,7 +429,7 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.lse = lse; a.delta = delta; a.dk = (uint16_t*)dk; a.dv = (uint16_t*)dv;
   a.col_cnt = col_cnt; a.col_idx = col_idx; a.col_order = col_order;
-  a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.chunk = (m.Tn + 7) / 8;
+  a.BH = m.B * m.H; a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.chunk = (m.Tn + 7) / 8;
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale = scale; a.scale_log2 = scale * LOG2E;
   a.sp = plan;
@@ -433,7 +437,7 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
     const hipError_t e = launch_split_plan(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid((unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(128);
+  const dim3 grid(plan.queue ? QUEUE_WGS : (unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(128);
   if (m.d == 128) hipLaunchKernelGGL(dkdv_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dkdv_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

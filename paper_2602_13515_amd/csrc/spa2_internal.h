@@ -25,16 +25,27 @@ inline Dims make_dims(const spa2_shape& s) {
 // Splitting of long rows / columns over several workgroups (split.hip).  All pointers lie in the caller's
 // workspace; pool_slots == 0 means "no splitting" and every other member is then null.
 constexpr int SPLIT_POOL_MAX = 2048;         // partial-result slots of one launch at most
+constexpr int QUEUE_STRIDE = 64;             // ints between the counters of two XCDs (atomics on one line stand in a row)
+constexpr int QUEUE_WGS = 512;               // workgroups of a queue launch: two per compute unit
 struct SplitPlan {
   const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection)
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
   const int32_t* part_table;   // [pool_slots][4] (unit, part, parts of the unit, list entries per part) of pool slot g
   int32_t* arrive;             // [pool_slots] parts of the unit that have left their result, at its first slot
   float* pool;                 // [pool_slots][slot_floats] fp32 partial results
+  int32_t* queue;              // counters of a queue launch (work_queue.h), QUEUE_STRIDE apart, in the last slot's place; or
+                               // null: direct launch
   int pool_slots;
   int slot_floats;
   bool planned;                // the tables have been written already (launch_bwd_prepare): no plan launch of its own
 };
+// Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
+// queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
+// 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.
+inline SplitPlan with_queue(SplitPlan p, int64_t units) {
+  if (p.pool_slots && units > 4 * QUEUE_WGS) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
+  return p;
+}
 size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes);
 SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes);
 // Plan of the launch of kernel `kind`, which walks `units` lists of at most list_max entries.

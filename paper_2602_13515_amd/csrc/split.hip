@@ -65,6 +65,7 @@ size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes) {
 SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes) {
   SplitPlan p;
   p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
+  p.queue = nullptr;
   p.pool_slots = 0; p.slot_floats = 0; p.planned = false;
   if (!ws) return p;
   // the pool shrinks if the caller gave less than the full workspace
@@ -86,14 +87,15 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
 struct PlanArgs {
   const int32_t* cnt;
   int units, list_max, lo, mid, pool;
-  int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive;
+  int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive; int32_t* queue;
 };
 
 static PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p) {
   PlanArgs a;
   a.cnt = cnt; a.units = (int)units; a.list_max = list_max;
   split_range(kind, units, a.lo, a.mid);
-  a.pool = p.pool_slots;
+  a.pool = p.queue ? p.pool_slots - 1 : p.pool_slots;
+  a.queue = p.queue;
   a.header = (int32_t*)p.header; a.unit_slot = (int32_t*)p.unit_slot; a.part_table = (int32_t*)p.part_table;
   a.arrive = p.arrive;
   return a;
@@ -226,6 +228,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a) {
     a.arrive[g] = 0;
   }
   if (t == 0) { a.header[0] = n; a.header[1] = S; }
+  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = QUEUE_WGS / 8;      // (the first ones go by workgroup number)
 }
 
 template <int NT>
