@@ -101,6 +101,10 @@ def _load():
     lib.spa2_vd_loss.argtypes = [vp, vp, ctypes.c_int64, i32, ctypes.c_double, vp, vp, sz, vp]
     lib.spa2_vd_loss_grad.restype = ctypes.c_int
     lib.spa2_vd_loss_grad.argtypes = [vp, vp, ctypes.c_int64, i32, ctypes.c_double, vp, vp, vp]
+    lib.spa2_vd_loss_and_grad.restype = ctypes.c_int
+    lib.spa2_vd_loss_and_grad.argtypes = [vp, vp, ctypes.c_int64, ctypes.c_double, vp, vp, vp, sz, vp]
+    lib.spa2_vd_rescale.restype = ctypes.c_int
+    lib.spa2_vd_rescale.argtypes = [vp, ctypes.c_int64, ctypes.c_double, vp, vp]
     _lib = lib
     return lib
 
@@ -109,7 +113,8 @@ EXPORTED_SYMBOLS = ("spa2_version", "spa2_strerror", "spa2_topk_blocks", "spa2_m
                     "spa2_bwd_workspace_bytes", "spa2_bwd_workspace_min_bytes", "spa2_fwd_workspace_bytes", "spa2_mask", "spa2_mask_pool", "spa2_mask_select",
                     "spa2_mask_columns", "spa2_pattern_full", "spa2_fwd", "spa2_bwd", "spa2_bwd_static", "spa2_bwd_delta",
                     "spa2_bwd_dkdv", "spa2_bwd_dq", "spa2_error_workspace_bytes", "spa2_error_terms",
-                    "spa2_vd_loss_workspace_bytes", "spa2_vd_loss", "spa2_vd_loss_grad")
+                    "spa2_vd_loss_workspace_bytes", "spa2_vd_loss", "spa2_vd_loss_grad", "spa2_vd_loss_and_grad",
+                    "spa2_vd_rescale")
 
 
 # ------------------------------------------------------------------ plumbing (memory only)
@@ -419,3 +424,28 @@ def spa2_vd_loss_grad(u_sparse: torch.Tensor, u_full: torch.Tensor, weight: floa
     _check(_load().spa2_vd_loss_grad(u_sparse.data_ptr(), u_full.data_ptr(), n, dt, float(weight),
                                      None if upstream is None else upstream.data_ptr(), grad.data_ptr(),
                                      _stream(u_sparse)), "spa2_vd_loss_grad")
+
+
+def spa2_vd_loss_and_grad(u_sparse: torch.Tensor, u_full: torch.Tensor, weight: float, loss: torch.Tensor,
+                          grad: torch.Tensor, workspace: torch.Tensor) -> None:
+    """fp32: loss as spa2_vd_loss and, in grad, what spa2_vd_loss_grad gives without an upstream."""
+    n, dt = _vd_args(u_sparse, u_full)
+    if dt != 1:
+        raise ValueError("one pass for loss and gradient: float32 predictions")
+    if loss.dtype != torch.float64 or loss.numel() != 1:
+        raise ValueError("loss is a float64 tensor of one element")
+    if grad.dtype != u_sparse.dtype or grad.shape != u_sparse.shape or not grad.is_contiguous():
+        raise ValueError("grad has the type and shape of the predictions and is contiguous")
+    _check(_load().spa2_vd_loss_and_grad(u_sparse.data_ptr(), u_full.data_ptr(), n, float(weight), loss.data_ptr(),
+                                         grad.data_ptr(), workspace.data_ptr(), _nbytes(workspace), _stream(u_sparse)),
+           "spa2_vd_loss_and_grad")
+
+
+def spa2_vd_rescale(grad: torch.Tensor, weight: float, upstream: torch.Tensor) -> None:
+    """grad of spa2_vd_loss_and_grad times upstream (a float64 device scalar), in place."""
+    if grad.dtype != torch.float32 or not grad.is_contiguous() or not grad.is_cuda:
+        raise ValueError("grad is a contiguous float32 CUDA tensor")
+    if upstream.dtype != torch.float64 or upstream.numel() != 1 or not upstream.is_cuda:
+        raise ValueError("upstream is a float64 CUDA tensor of one element")
+    _check(_load().spa2_vd_rescale(grad.data_ptr(), grad.numel(), float(weight), upstream.data_ptr(), _stream(grad)),
+           "spa2_vd_rescale")

@@ -5,6 +5,8 @@
 // 1 write for the gradient), 16 bytes per lane and request.  The difference is taken in fp32, squared and summed
 // in fp64; partial sums go workgroup by workgroup to the workspace and are added in a fixed order, so the loss is
 // deterministic.
+#include <math.h>
+
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
@@ -120,6 +122,56 @@ __global__ __launch_bounds__(256) void vd_grad_kernel(const void* us, const void
   }
 }
 
+// Loss and gradient for upstream = 1 in one pass, fp32: 2 reads and 1 write per element for both, where the two passes
+// above take 4 and 1.  bf16 has no such pass: its gradient could not be multiplied by another upstream without a second
+// rounding.  Same sums and products as the two passes; from the end to the start and past the cache as vd_grad_kernel.
+// Bound: HBM, 5.5 TB/s.  New predictions every time, loss + gradient pass before / this one with the rescale (for an
+// upstream of 1, for another), us: 2 x 201 MB 74 + 107 / 110 + 2, 110 + 76; 2 x 671 MB 240 + 400 / 405 + 2, 405 + 275;
+// 2 x 49 MB 21 + 25 / 28 + 2, 28 + 16.  (Two or four vectors in flight per thread instead of one: 116, 117 us on the first.)
+template <bool PAST_CACHE>
+__global__ __launch_bounds__(256) void vd_loss_grad_kernel(const float* us, const float* uf, int64_t n, float coef, float* grad,
+                                                           double* part) {
+  __shared__ double red[4];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int64_t nvec = n / 4;
+  double acc = 0.0;
+  for (int64_t v = nvec - 1 - ((int64_t)blockIdx.x * 256 + tid); v >= 0; v -= (int64_t)gridDim.x * 256) {
+    const f32x4 d = ((const f32x4*)us)[v] - ((const f32x4*)uf)[v];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc = fma((double)d[c], (double)d[c], acc);
+    if (PAST_CACHE) __builtin_nontemporal_store(d * coef, (f32x4*)grad + v);
+    else            ((f32x4*)grad)[v] = d * coef;
+  }
+  if (blockIdx.x == 0 && nvec * 4 + tid < n) {
+    const float d = us[nvec * 4 + tid] - uf[nvec * 4 + tid];
+    acc = fma((double)d, (double)d, acc);
+    grad[nvec * 4 + tid] = coef * d;
+  }
+#pragma unroll
+  for (int s = 32; s >= 1; s >>= 1) acc += __shfl_xor(acc, s, 64);
+  if (lane == 0) red[w] = acc;
+  __syncthreads();
+  if (tid == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
+}
+
+// grad *= upstream, in place; nothing where it is 1 (the usual case: the loss itself is what is differentiated).
+// `exact`: 2 * weight over its fp32 value, so that the rounding of that factor, which is in every element, is taken back.
+// (Error against fp64 over random weights and upstreams: 3.65e-8 always, where the two passes have up to 6.1e-8, rms
+// 3.62e-8, as the rounding of their factor falls.)
+__global__ __launch_bounds__(256) void vd_rescale_kernel(float* grad, int64_t n, double exact, const double* upstream) {
+  const double u = *upstream;
+  if (u == 1.0) return;
+  const double f = u * exact;
+  const int64_t nvec = n / 4;
+  for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < nvec; v += (int64_t)gridDim.x * 256) {
+    f32x4 g = ((const f32x4*)grad)[v];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) g[c] = (float)(f * (double)g[c]);
+    ((f32x4*)grad)[v] = g;
+  }
+  if (blockIdx.x == 0 && nvec * 4 + threadIdx.x < n) grad[nvec * 4 + threadIdx.x] = (float)(f * (double)grad[nvec * 4 + threadIdx.x]);
+}
+
 static unsigned vd_grid(int64_t n, bool bf16) {
   const int64_t nvec = n / (bf16 ? 8 : 4);
   const int64_t wgs = (nvec + 255) / 256;
@@ -150,3 +202,39 @@ hipError_t launch_vd_grad(const void* us, const void* uf, int64_t n, bool bf16, 
 }
 
 }  // namespace spa2
+
+using namespace spa2;
+
+extern "C" {
+
+int spa2_vd_loss_and_grad(const void* us, const void* uf, int64_t n, double weight, double* loss, void* grad,
+                          void* workspace, size_t workspace_bytes, void* stream) {
+  if (!us || !uf || !loss || !grad) return SPA2_ERR_NULL;
+  if (n <= 0) return SPA2_ERR_SHAPE;
+  if (((uintptr_t)us | (uintptr_t)uf | (uintptr_t)grad) & 15u) return SPA2_ERR_ALIGN;
+  const float coef = (float)(2.0 * weight);
+  if (!(weight > 0.0) || !isfinite(weight) || !isnormal(coef)) return SPA2_ERR_RANGE;
+  if (!workspace || workspace_bytes < vd_ws_bytes()) return SPA2_ERR_WORKSPACE;
+  if ((uintptr_t)workspace & 15u) return SPA2_ERR_ALIGN;
+  const unsigned grid = vd_grid(n, false);
+  const auto kernel = 12 * n > VD_CACHE_BYTES ? vd_loss_grad_kernel<true> : vd_loss_grad_kernel<false>;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const float*)us, (const float*)uf, n, coef,
+                     (float*)grad, (double*)workspace);
+  if (hipGetLastError() != hipSuccess) return SPA2_ERR_LAUNCH;
+  hipLaunchKernelGGL(vd_loss_finish, dim3(1), dim3(256), 0, (hipStream_t)stream, (const double*)workspace, (int)grid, weight,
+                     loss);
+  return hipGetLastError() == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+}
+
+int spa2_vd_rescale(void* grad, int64_t n, double weight, const double* upstream, void* stream) {
+  if (!grad || !upstream) return SPA2_ERR_NULL;
+  if (n <= 0) return SPA2_ERR_SHAPE;
+  if ((uintptr_t)grad & 15u) return SPA2_ERR_ALIGN;
+  const float coef = (float)(2.0 * weight);
+  if (!(weight > 0.0) || !isfinite(weight) || !isnormal(coef)) return SPA2_ERR_RANGE;
+  hipLaunchKernelGGL(vd_rescale_kernel, dim3(vd_grid(n, false)), dim3(256), 0, (hipStream_t)stream, (float*)grad, n,
+                     2.0 * weight / (double)coef, upstream);
+  return hipGetLastError() == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+}
+
+}  // extern "C"

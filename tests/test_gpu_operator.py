@@ -59,6 +59,40 @@ def test_native_loss_gives_the_bits_of_the_python_route(rows, dtype, reduction):
     assert torch.equal(a.grad, b.grad)
 
 
+# one element, less than a vector, vectors and a remainder, more than one round of the 2,048 workgroups
+@pytest.mark.parametrize("n", [1, 3, 1029, 2048 * 256 * 4 + 5])
+def test_loss_and_gradient_in_one_pass(n):
+    g = torch.Generator().manual_seed(n)
+    us, uf = (torch.randn(n, generator=g).to(dev()) for _ in range(2))
+    weight = 0.7 / n
+    new = lambda: torch.full((n,), float("nan"), device=dev())
+    scalar = lambda x: torch.tensor(x, dtype=torch.float64, device=dev())
+    ws = torch.empty(spa2.binding.spa2_vd_loss_workspace_bytes(), dtype=torch.uint8, device=dev())
+    loss, ref_loss, grad, ref = scalar(0.0), scalar(0.0), new(), new()
+    spa2.binding.spa2_vd_loss_and_grad(us, uf, weight, loss, grad, ws)
+    spa2.binding.spa2_vd_loss(us, uf, weight, ref_loss, ws)
+    assert abs(loss - ref_loss) <= 1e-12 * ref_loss          # fp64 sums in two orders
+    for u in (1.0, 4.0, 0.3):
+        got = grad.clone()
+        spa2.binding.spa2_vd_rescale(got, weight, scalar(u))
+        spa2.binding.spa2_vd_loss_grad(us, uf, weight, scalar(u), ref)
+        if u != 0.3:                                          # powers of two: the same bits
+            assert torch.equal(got, ref)
+        else:      # on either side three roundings to fp32 of 2^-24 each: difference, factor or product, product
+            assert ((got - ref).abs() <= 2.0 ** -22 * ref.abs()).all()
+
+
+def test_second_backward_pass_gets_a_gradient_of_its_own():
+    us, uf = (torch.randn(4, 333, device=dev()) for _ in range(2))
+    us.requires_grad_(True)
+    loss = velocity_distillation_loss(us, uf)
+    (first,) = torch.autograd.grad(loss, us, retain_graph=True)
+    kept = first.clone()
+    first.zero_()
+    (second,) = torch.autograd.grad(loss, us)
+    assert torch.equal(second, kept) and second.data_ptr() != first.data_ptr()
+
+
 def test_native_route_refuses_what_the_python_route_refuses():
     q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
     call = lambda *t: spa2.sparge_attn2(*t, 0.1, 0.6)
