@@ -10,6 +10,7 @@
 //                   index list.  The row never leaves LDS/registers.
 //   select16_kernel the same for rows of up to 2048 blocks, sixteen rows per workgroup, with the
 //                   score product on the fp64 matrix cores.
+//   select_small_kernel  the same for rows of up to 64 blocks, one wave a row after the score product.
 //   columns_kernel  the same pattern listed per key block (for dK/dV).
 #include "spa2_device.h"
 #include "spa2_internal.h"
@@ -696,6 +697,87 @@ __global__ __launch_bounds__(64 * WV, 2) void select16_kernel(SelArgs a) {
   }
 }
 
+// The same selection for rows of up to 64 blocks: sixteen rows a workgroup, sixteen waves.  The first four waves make the
+// scores, 16 columns each, as select16_kernel does; then a wave takes one row, a lane one column: it counts the entries
+// that precede its own, and the masses are summed in that order by one scan.  No histograms, no barriers.  Scores, softmax (same
+// order of the sums) and masses are those of select16_kernel<256, D, 8>, bit for bit.
+// Bound: latency.  us, select16_kernel / this: 16 blocks a row, 2 heads 12.1 / 8.1; 21 blocks, 24 heads 12.8 / 7.6; 63 blocks,
+// 9 heads 14.5 / 10.0 (back to back launches).
+template <int D>
+__global__ __launch_bounds__(1024) void select_small_kernel(SelArgs a) {
+  constexpr int KS = D / 4;               // contraction steps of 4 channels
+  __shared__ float sc[16][64];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lg = lane >> 4, ln = lane & 15;
+  const int bh = blockIdx.x / a.groups;
+  const int iw = (blockIdx.x % a.groups) * 16;        // first row of the workgroup
+  const int nrows = min(16, a.Tm - iw);
+  const int Tn = a.Tn;
+  if (16 * w < Tn) {                      // (w < 4)
+    const float* kc = a.kbar_t + ((int64_t)bh * Tn + min(16 * w + ln, Tn - 1)) * D + 4 * lg;
+    const float* qrow = a.qbar + ((int64_t)bh * a.Tm + iw + min(ln, nrows - 1)) * D + 4 * lg;
+    f32x4 kr[KS / 4], qr[KS / 4];
+#pragma unroll
+    for (int g = 0; g < KS / 4; ++g) { kr[g] = *(const f32x4*)(kc + 16 * g); qr[g] = *(const f32x4*)(qrow + 16 * g); }
+    f64x4 acc = {0.0, 0.0, 0.0, 0.0}, acc1 = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int c = 0; c < KS; c += 2) {
+      acc = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qr[c / 4][c % 4], (double)kr[c / 4][c % 4], acc, 0, 0, 0);
+      acc1 = __builtin_amdgcn_mfma_f64_16x16x4f64((double)qr[(c + 1) / 4][(c + 1) % 4], (double)kr[(c + 1) / 4][(c + 1) % 4],
+                                                  acc1, 0, 0, 0);
+    }
+    acc += acc1;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sc[4 * v + lg][16 * w + ln] = (float)(acc[v] * (double)a.scale);
+  }
+  __syncthreads();
+  if (w >= nrows) return;
+  const bool in_row = lane < Tn;
+  const float s = in_row ? sc[w][lane] : -INFINITY;
+  float mx = s;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+  const float e = in_row ? expf(s - mx) : 0.f;
+  float sum = e;
+#pragma unroll
+  for (int off = 8; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+  auto of_lane = [](float x, int l) -> float {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
+  };
+  const float tot = ((of_lane(sum, 0) + of_lane(sum, 16)) + of_lane(sum, 32)) + of_lane(sum, 48);
+  const float p = e / tot;
+  const int64_t row = (int64_t)bh * a.Tm + iw + w;
+  if (a.pbar_out && in_row) a.pbar_out[row * Tn + lane] = p;
+  const uint32_t kcnt = (uint32_t)max(1, a.k_cnt);
+  uint64_t p_fx = fixed62(__builtin_bit_cast(uint32_t, a.top_p));
+  if (a.top_p > 0.f && p_fx == 0) p_fx = 1;
+  // place of this entry in the order (Pbar descending, index ascending): entries before it, counted one column a step
+  const uint32_t fb = __builtin_bit_cast(uint32_t, p);
+  uint32_t place = 0;
+#pragma unroll 4
+  for (int k = 0; k < Tn; ++k) {
+    const uint32_t kb = (uint32_t)__builtin_amdgcn_readlane((int)fb, k);
+    place += (k < lane ? kb >= fb : kb > fb) ? 1u : 0u;
+  }
+  if (!in_row) place = lane;              // (lanes without a column: behind all others)
+  // the masses in that order and the sum of those before each (see sel_scan_pass), the rule for every place, and the last
+  // place it holds for
+  const uint64_t mass = in_row ? fixed62(fb) : 0;
+  const uint32_t m_lo = (uint32_t)__builtin_amdgcn_ds_permute(4 * (int)place, (int)(uint32_t)mass);
+  const uint32_t m_hi = (uint32_t)__builtin_amdgcn_ds_permute(4 * (int)place, (int)(uint32_t)(mass >> 32));
+  const uint64_t m = ((uint64_t)m_hi << 32) | m_lo;
+  const uint64_t upto = (uint64_t)wave_scan_add((uint32_t)(m & 0x1fffffu)) +
+                        ((uint64_t)wave_scan_add((uint32_t)((m >> 21) & 0x1fffffu)) << 21) +
+                        ((uint64_t)wave_scan_add((uint32_t)(m >> 42)) << 42);
+  const uint64_t holds = __builtin_amdgcn_ballot_w64(lane < Tn && ((uint32_t)lane < kcnt || upto - m < p_fx));
+  const uint32_t n = 64u - (uint32_t)__builtin_clzll(holds);        // (never 0: the first place always holds)
+  const bool f = in_row && place < n;
+  const uint64_t bits = __builtin_amdgcn_ballot_w64(f);
+  if (in_row) a.mask[row * Tn + lane] = f ? 1 : 0;
+  if (f) a.row_idx[row * Tn + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0))] = lane;
+  if (lane == 0) a.row_cnt[row] = __builtin_popcountll(bits);
+}
+
 template <int NP, int R>
 static void launch_select_t(const SelArgs& a0, int BH, hipStream_t stream) {
   SelArgs a = a0;
@@ -726,6 +808,13 @@ hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, in
   const int BH = m.B * m.H;
   // the smallest instantiated width that holds the row: steps of 256 up to 2048, of 512 up to 4096, then of 1024
   const int waves = select16_waves(m);        // (the pooling pass has laid out the pooled keys for this kernel)
+  if (m.Tn <= 64) {                           // (row-major keys: waves is not 0 there)
+    a.groups = (m.Tm + 15) / 16;
+    const dim3 grid((unsigned)(BH * a.groups)), block(1024);
+    if (m.d == 128) hipLaunchKernelGGL(select_small_kernel<128>, grid, block, 0, stream, a);
+    else            hipLaunchKernelGGL(select_small_kernel<64>, grid, block, 0, stream, a);
+    return hipGetLastError();
+  }
 #define SPA2_SELECT16_CASE(wv, np) if (waves == wv && m.Tn <= np) return launch_select16_t<np, wv>(a, BH, stream);
   SPA2_SELECT16_CASE(4, 256)  SPA2_SELECT16_CASE(4, 512)  SPA2_SELECT16_CASE(4, 768)  SPA2_SELECT16_CASE(4, 1024)
   SPA2_SELECT16_CASE(4, 1280) SPA2_SELECT16_CASE(4, 1536)
