@@ -167,6 +167,12 @@ int spa2_fwd(const void* q, const void* k, const void* v, const spa2_shape* shap
              const spa2_pattern* pattern, float scale, void* o, void* o_res, float* lse,
              void* workspace, size_t workspace_bytes, void* stream);
 
+/* spa2_mask and spa2_fwd as one call, with their results; the workspace (spa2_mask_fwd_workspace_bytes) serves both. */
+size_t spa2_mask_fwd_workspace_bytes(const spa2_shape* shape);
+int spa2_mask_fwd(const void* q, const void* k, const void* v, const spa2_shape* shape, int32_t topk_blocks, float top_p,
+                  float scale, spa2_pattern* out, void* o, void* o_res /* or NULL */, float* lse, void* workspace,
+                  size_t workspace_bytes, void* stream);
+
 /* Backward of spa2_fwd for upstream gradient d_o, mask held constant.  With
  * P = exp(S - lse) on selected tiles:  dV = P^T dO,  dP = dO V^T,
  * D = rowsum(dO * O),  dS = P * (dP - D),  dQ = dS K * scale,  dK = dS^T Q * scale.

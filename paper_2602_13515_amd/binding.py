@@ -71,6 +71,10 @@ def _load():
     lib.spa2_fwd_workspace_bytes.argtypes = [shp]
     lib.spa2_mask.restype = ctypes.c_int
     lib.spa2_mask.argtypes = [vp, vp, shp, i32, f32, f32, pat, vp, vp, sz, vp]
+    lib.spa2_mask_fwd_workspace_bytes.restype = sz
+    lib.spa2_mask_fwd_workspace_bytes.argtypes = [shp]
+    lib.spa2_mask_fwd.restype = ctypes.c_int
+    lib.spa2_mask_fwd.argtypes = [vp, vp, vp, shp, i32, f32, f32, pat, vp, vp, vp, vp, sz, vp]
     lib.spa2_pattern_full.restype = ctypes.c_int
     lib.spa2_pattern_full.argtypes = [shp, pat, vp]
     lib.spa2_fwd.restype = ctypes.c_int
@@ -114,6 +118,7 @@ EXPORTED_SYMBOLS = ("spa2_version", "spa2_strerror", "spa2_topk_blocks", "spa2_m
                     "spa2_mask_columns", "spa2_pattern_full", "spa2_fwd", "spa2_bwd", "spa2_bwd_static", "spa2_bwd_delta",
                     "spa2_bwd_dkdv", "spa2_bwd_dq", "spa2_error_workspace_bytes", "spa2_error_terms",
                     "spa2_vd_loss_workspace_bytes", "spa2_vd_loss", "spa2_vd_loss_grad", "spa2_vd_loss_and_grad",
+                    "spa2_mask_fwd", "spa2_mask_fwd_workspace_bytes",
                     "spa2_vd_rescale")
 
 

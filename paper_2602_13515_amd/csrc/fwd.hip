@@ -21,7 +21,7 @@ struct FwdArgs {
   const uint16_t* q; const uint16_t* k; const uint16_t* v;
   uint16_t* o; uint16_t* o_res; float* lse;
   const int32_t* row_cnt; const int32_t* row_idx; const int32_t* row_order;
-  int H, N, Tm, Tn, chunk;
+  int BH, H, N, Tm, Tn, chunk;
   int64_t sb, sh, sn;
   float scale_log2;     // scale * log2(e): softmax is evaluated with exp2
   SplitPlan sp;         // long rows cut into parts (split.hip); sp.pool_slots == 0: every row is walked whole
@@ -73,7 +73,19 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   // Which row, and which part of its list.  The first sp.pool_slots workgroups of the launch are the parts of split
   // rows; the others take one row each, unless it is split.
   int bh, i, part = 0, parts = 0, part_len = 0;
-  if ((int)blockIdx.x < a.sp.pool_slots) {
+  int slot = blockIdx.x;
+  if (a.sp.fixed_len) {       // a small launch: the sizes say which part of which row (with_fixed_parts)
+    const int rows = a.BH * 8 * a.chunk;
+    const HeadBlock hb = xcd_map(blockIdx.x % rows, a.Tm, a.chunk);
+    if (!hb.valid) return;
+    bh = hb.bh; i = hb.blk;
+    const int unit = bh * a.Tm + i, all = min(max(a.row_cnt[unit], 0), a.Tn);
+    part = blockIdx.x / rows;
+    parts = all > a.sp.fixed_len ? (all + a.sp.fixed_len - 1) / a.sp.fixed_len : 0;
+    if (part >= max(parts, 1)) return;
+    if (parts) part_len = (all + parts - 1) / parts;
+    slot = unit * a.sp.fixed_parts + part;
+  } else if ((int)blockIdx.x < a.sp.pool_slots) {
     if ((int)blockIdx.x >= a.sp.header[0]) return;
     const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
     const int unit = pt[0];
@@ -383,7 +395,7 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
 
   const float l_tot = sum_halves(l_run);
   if (parts) {                // one part of a split row
-    const int64_t first = blockIdx.x - part;
+    const int64_t first = slot - part;
     float* ps = a.sp.pool + (first + part) * a.sp.slot_floats;
 #pragma unroll
     for (int mb = 0; mb < D / 32; ++mb)
@@ -433,7 +445,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v;
   a.o = (uint16_t*)o; a.o_res = (uint16_t*)o_res; a.lse = lse;
   a.row_cnt = row_cnt; a.row_idx = row_idx; a.row_order = row_order;
-  a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn;
+  a.BH = m.B * m.H; a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn;
   a.chunk = (m.Tm + 7) / 8;
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale_log2 = scale * LOG2E;
@@ -442,7 +454,8 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_FWD, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid((unsigned)(plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(256);
+  const dim3 grid((unsigned)(plan.fixed_len ? plan.fixed_parts * m.B * m.H * 8 * a.chunk
+                                            : plan.pool_slots + m.B * m.H * 8 * a.chunk)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(fwd_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(fwd_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

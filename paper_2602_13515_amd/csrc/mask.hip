@@ -41,6 +41,7 @@ struct PoolArgs {
                     // or [BH][Tn][d] for select16_kernel (k_rows)
   int H, N, Tm, Tn, TnP, k_rows;
   int64_t sb, sh, sn;
+  int32_t* zero; int zeros;   // integers that this launch sets to zero for a later one
 };
 
 // Sum of the valid token rows of one block, as 8 channels per thread.  All loads of the block are issued before
@@ -80,6 +81,7 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
   const int len = is_q ? BQ : BKV;
   const uint16_t* x = (is_q ? a.q : a.k) + (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   const int tid = threadIdx.x;
+  if ((int64_t)blockIdx.x * 256 + tid < a.zeros) a.zero[blockIdx.x * 256 + tid] = 0;
   const int rsub = tid / LPR, col = (tid % LPR) * 8;
   const int tok0 = blk * len;
   const int valid = min(len, a.N - tok0);
@@ -104,7 +106,13 @@ __global__ __launch_bounds__(256) void pool_kernel(PoolArgs a) {
 }
 
 hipError_t launch_pool(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, hipStream_t stream) {
+  return launch_pool_zero(q, k, m, qbar, kbar, nullptr, 0, stream);
+}
+
+hipError_t launch_pool_zero(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, int32_t* zero, int zeros,
+                            hipStream_t stream) {
   PoolArgs a;
+  a.zero = zero; a.zeros = zeros;
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.qbar = qbar; a.kbar_t = kbar;
   a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.TnP = m.Tn; a.k_rows = select16_waves(m) ? 1 : 0;
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;

@@ -12,7 +12,6 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/extension.h>
 
-#include <algorithm>
 #include <cfloat>
 
 #include "spa2.h"
@@ -123,15 +122,12 @@ struct Attention : torch::autograd::Function<Attention> {
     const PatternLayout layout(s, training);
     const Tensor buf = build ? bytes(layout.total, q) : Tensor();
     spa2_pattern pattern = build ? layout.in(buf) : given_pattern(given);
-    // one scratch buffer for the two stages, which run one after the other; a log-sum-exp that nobody reads lies behind it
-    const int64_t mask_ws = build ? (int64_t)spa2_mask_workspace_bytes(&s) : 0, fwd_ws = (int64_t)spa2_fwd_workspace_bytes(&s);
-    const int64_t lse_at = (std::max(mask_ws, fwd_ws) + 255) & ~(int64_t)255;
+    // one scratch buffer for mask and forward; a log-sum-exp that nobody reads lies behind it
+    const int64_t need = (int64_t)(build ? spa2_mask_fwd_workspace_bytes(&s) : spa2_fwd_workspace_bytes(&s));
+    const int64_t lse_at = (need + 255) & ~(int64_t)255;
     const Tensor ws = bytes(training ? lse_at : lse_at + 4 * q.size(0) * q.size(1) * q.size(2), q);
     void* stream = stream_of(q);
     const int32_t tn = (int32_t)((q.size(2) + SPA2_BKV - 1) / SPA2_BKV);
-    if (build)
-      check(spa2_mask(q.data_ptr(), k.data_ptr(), &s, spa2_topk_blocks(k_frac, tn), (float)top_p, (float)scale, &pattern,
-                      nullptr, ws.data_ptr(), (size_t)mask_ws, stream), "spa2_mask");
     const Tensor o = like(q);
     Tensor o_res, lse;
     if (training) {
@@ -139,8 +135,14 @@ struct Attention : torch::autograd::Function<Attention> {
       lse = at::empty({q.size(0), q.size(1), q.size(2)}, q.options().dtype(at::kFloat));
     }
     float* lse_p = training ? (float*)lse.data_ptr() : (float*)((char*)ws.data_ptr() + lse_at);
-    check(spa2_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), &s, &pattern, (float)scale, o.data_ptr(),
-                   training ? o_res.data_ptr() : nullptr, lse_p, ws.data_ptr(), (size_t)fwd_ws, stream), "spa2_fwd");
+    void* o_res_p = training ? o_res.data_ptr() : nullptr;
+    if (build)
+      check(spa2_mask_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), &s, spa2_topk_blocks(k_frac, tn), (float)top_p,
+                          (float)scale, &pattern, o.data_ptr(), o_res_p, lse_p, ws.data_ptr(), (size_t)need, stream),
+            "spa2_mask_fwd");
+    else
+      check(spa2_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), &s, &pattern, (float)scale, o.data_ptr(), o_res_p, lse_p,
+                     ws.data_ptr(), (size_t)need, stream), "spa2_fwd");
     if (training) {
       ctx->save_for_backward({q, k, v, o, o_res, lse});
       ctx->saved_data["pattern"] = build ? std::vector<Tensor>{buf} : given;

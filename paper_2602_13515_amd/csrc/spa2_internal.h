@@ -37,6 +37,8 @@ struct SplitPlan {
                                // null: direct launch
   int pool_slots;
   int slot_floats;
+  int fixed_len;               // > 0: no plan, every list is cut into parts of at most fixed_len entries (with_fixed_parts);
+  int fixed_parts;             //   part p of unit u has slot u * fixed_parts + p
   bool planned;                // the tables have been written already (launch_bwd_prepare): no plan launch of its own
 };
 // Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
@@ -52,6 +54,9 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
 enum SplitKind { SPLIT_FWD, SPLIT_DQ, SPLIT_DKDV };
 hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p,
                              hipStream_t stream);
+// The same parts without a plan, where the sizes alone say that the plan would cut into pieces of its least length (and the
+// slots suffice): p with fixed_len set.  The caller zeroes p.arrive before the launch.
+SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max, SplitKind kind);
 // D = rowsum(dO * O) and the plans of the two backward kernels in one launch (split.hip).
 hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
                               const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
@@ -59,6 +64,9 @@ hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o,
 
 // Each launcher enqueues its kernels on `stream` and returns hipGetLastError().
 hipError_t launch_pool(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, hipStream_t stream);
+// the same, and zeroes `zeros` integers at `zero` (at most one per thread of the launch)
+hipError_t launch_pool_zero(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, int32_t* zero, int zeros,
+                            hipStream_t stream);
 hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, int topk_blocks, float top_p,
                          float scale, uint8_t* mask, int32_t* row_cnt, int32_t* row_idx, float* pbar_out,
                          hipStream_t stream);

@@ -66,7 +66,7 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
   SplitPlan p;
   p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
   p.queue = nullptr;
-  p.pool_slots = 0; p.slot_floats = 0; p.planned = false;
+  p.pool_slots = 0; p.slot_floats = 0; p.fixed_len = 0; p.fixed_parts = 0; p.planned = false;
   if (!ws) return p;
   // the pool shrinks if the caller gave less than the full workspace
   int64_t pool = pool_wanted(units, list_max);
@@ -80,6 +80,17 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
   p.arrive = (int32_t*)c;                 c += up256((size_t)pool * 4);
   p.pool = (float*)c;
   p.slot_floats = (int)(slot_bytes / 4);
+  return p;
+}
+
+// T <= units * list_max: where that is within 512 lo, S is lo (see above) whatever the lists are.
+SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max, SplitKind kind) {
+  int lo, mid;
+  split_range(kind, units, lo, mid);
+  const int parts = (list_max + lo - 1) / lo;
+  if (p.pool_slots && units * list_max <= 512 * (int64_t)lo && units * parts <= p.pool_slots) {
+    p.fixed_len = lo; p.fixed_parts = parts; p.planned = true;
+  }
   return p;
 }
 

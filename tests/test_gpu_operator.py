@@ -47,6 +47,20 @@ def test_native_route_gives_the_bits_of_the_python_route(B, H, N, d, layout, mon
         assert torch.equal(a, b)
 
 
+# rows cut by the sizes alone (no plan) and by the plan: 16 and 17 heads of 32 blocks stand on either side of that rule; rows
+# of one part, of two and of four, the last one short
+@pytest.mark.parametrize("H,N,d", [(2, 513, 128), (1, 1000, 64), (2, 2048, 64), (16, 2048, 128), (17, 2048, 64), (3, 1281, 128)])
+def test_small_layers_cut_rows_as_the_plan_does(H, N, d, monkeypatch):
+    q, k, v, _ = _inputs(1, H, N, d, "bhnd")
+    for k_frac in (0.3, 0.9, 1.0):
+        with torch.no_grad():
+            native = [spa2.sparge_attn2(q, k, v, k_frac, 0.0) for _ in range(2)]
+            with monkeypatch.context() as m:
+                m.setattr(autograd, "_plain", lambda *t: False)
+                planned = spa2.sparge_attn2(q, k, v, k_frac, 0.0)
+        assert torch.equal(native[0], planned) and torch.equal(native[1], planned), k_frac
+
+
 @pytest.mark.parametrize("rows,dtype,reduction", [(1, torch.float32, "mean"), (777, torch.bfloat16, "batch")])
 def test_native_loss_gives_the_bits_of_the_python_route(rows, dtype, reduction):
     g = torch.Generator().manual_seed(1)
