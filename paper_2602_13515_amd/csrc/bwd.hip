@@ -84,6 +84,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
 
   // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
   int bh, i, part = 0, parts = 0, part_len = 0;
+  bool whole = false;
   if ((int)blockIdx.x < a.sp.pool_slots) {
     if ((int)blockIdx.x >= a.sp.header[0]) return;
     const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
@@ -95,30 +96,23 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     if (!hb.valid) return;
     bh = hb.bh;
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;
-    if (a.sp.pool_slots && a.sp.unit_slot[(int64_t)bh * a.Tm + i] >= 0) return;
+    whole = a.sp.pool_slots != 0;
   }
   const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);     // wave-uniform, in a scalar register
   const int r32 = lane & 31, hf = lane >> 5;
   const int N = a.N;
-  int cnt = min(max(a.row_cnt[(int64_t)bh * a.Tm + i], 0), a.Tn);   // clamped: see fwd.hip
-  const int32_t* idx = a.row_idx + ((int64_t)bh * a.Tm + i) * a.Tn;
-  if (parts) {                // entries [part * part_len, (part + 1) * part_len) of the list
-    idx += part * part_len;
-    cnt = min(cnt - part * part_len, part_len);
-  }
+  const int64_t unit = (int64_t)bh * a.Tm + i;
+  int cnt = min(max(a.row_cnt[unit], 0), a.Tn);   // clamped: see fwd.hip
+  const int split_at = *(whole ? a.sp.unit_slot + unit : a.row_cnt + unit);
+  const int first = part * part_len;         // entries [first, first + part_len) of the list of a split row
+  const int32_t* idx = a.row_idx + unit * a.Tn + first;
+  // the index list, 64 entries at a time in one register (lane l holds entry 64c + l): reading an entry is
+  // a lane read, not a memory access whose result the loop would have to wait for.  (The first ones and the rows are
+  // requested before the count is known: see fwd.hip.)
+  int idx_v = idx[min(lane, a.Tn - 1 - first)];
   const int qrow = i * BQ + w * 32 + r32;
-
-  if (cnt == 0) {
-    if (qrow < N) {
-      uint16_t* op = a.dq + base + (int64_t)qrow * a.sn + (D / 2) * hf;
-#pragma unroll
-      for (int c = 0; c < D / 16; ++c) *(u32x4*)(op + 8 * c) = u32x4{0, 0, 0, 0};
-    }
-    return;
-  }
-
   const int qrow_ld = qrow < N ? qrow : N - 1;
   bf16x8 qf[D / 16], dof[D / 16];
   {
@@ -131,6 +125,18 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   }
   const float lse2 = a.lse[(int64_t)bh * N + qrow_ld] * LOG2E;
   const float dlt = a.delta[(int64_t)bh * N + qrow_ld];
+  requested();
+  if (whole && split_at >= 0) return;
+  if (parts) cnt = min(cnt - first, part_len);
+
+  if (cnt == 0) {
+    if (qrow < N) {
+      uint16_t* op = a.dq + base + (int64_t)qrow * a.sn + (D / 2) * hf;
+#pragma unroll
+      for (int c = 0; c < D / 16; ++c) *(u32x4*)(op + 8 * c) = u32x4{0, 0, 0, 0};
+    }
+    return;
+  }
 
   // K/V tiles are copied global -> LDS directly (no staging registers).  The destination of a wave-wide
   // 16-byte-per-lane copy is linear (wave base + 16 * lane), so the swizzle is applied on the source side: the
@@ -185,9 +191,6 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   const uint32_t kt_off0 = sm + 2 * swz_idx<D>(4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
   const uint32_t kt_off1 = sm + 2 * swz_idx<D>(8 + 4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
 
-  // the index list, 64 entries at a time in one register (lane l holds entry 64c + l): reading an entry is
-  // a lane read, not a memory access whose result the loop would have to wait for
-  int idx_v = idx[min(lane, cnt - 1)];
   auto list_entry = [&](int t) -> int {      // t uniform, inside the chunk that idx_v holds
     return min(max(__builtin_amdgcn_readlane(idx_v, t & 63), 0), a.Tn - 1);
   };

@@ -109,6 +109,13 @@ __device__ __forceinline__ void raw_copies_left() {
 #endif
 }
 
+// Everything above has been requested here: loads are not moved down behind the branches that follow.
+__device__ __forceinline__ void requested() {
+#if defined(__HIP_DEVICE_COMPILE__)
+  asm volatile("" ::: "memory");
+#endif
+}
+
 // Entry `at` of an index list into a register, waited for here: a load inside a branch that is first used behind it would
 // make the compiler wait for every outstanding memory operation there, copies included, also where the branch is not taken.
 __device__ __forceinline__ int list_load(const int32_t* idx, int at) {
