@@ -200,17 +200,36 @@ __device__ __forceinline__ bool last_part(int32_t* arrive, int parts, int* lds_w
   return *lds_word == parts - 1;
 }
 
-// Workgroup id -> (head, block) mapping that keeps one head's blocks resident
-// on all eight XCDs at once: consecutive workgroup ids go round-robin to the
-// XCDs, so XCD x receives ids x, x+8, ...; those are given a contiguous chunk
-// of the head's blocks, which share K/V tiles through that XCD's L2.
+// Workgroup id -> (head, block) mapping that keeps one head's blocks resident on all eight XCDs at once: consecutive
+// workgroup ids go round-robin to the XCDs, so XCD x receives ids x, x+8, ...; those are given a contiguous chunk of the
+// head's blocks, which share K/V tiles through that XCD's L2.  The last chunk is a short one and, where blocks are dealt to
+// the chunks by length, the first holds the longest, which counts in heads of few blocks: up to MIDDLE_HEAD every head
+// starts with another XCD, and up to SHORT_HEAD, where a chunk is a block or two and the last ones are empty, the blocks go
+// to the XCDs in turn instead.
+// Measured, us, chunk x always on XCD x / now (forward, dQ, dK/dV; d = 128 unless noted).  In turn: 11 rows and 21 columns,
+// 24 heads 32.2 / 30.7, 31.2 / 30.1, 53.0 / 50.3; the same, d = 64, 512 heads 156 / 117, 148 / 111, (drawn from a queue);
+// 16 rows and 32 columns, 40 heads 42.8 / 42.5, 37.9 / 37.4, 71.9 / 57.5 (chunks that start with another XCD: 42, 38, 67).
+// Another XCD: 65 rows, 40 heads 185 / 176, 196 / 184; 97 rows, 24 heads, d = 64 105 / 102, 116 / 114.  In turn there gives no
+// more and loses 1 to 3 % on even chunks (32 rows) and long columns (79 columns, 12 heads 62 / 65); another XCD on longer
+// heads gives nothing (157 rows) and loses 1 % of the forward pass on 591.
 struct HeadBlock { int bh; int blk; bool valid; };
+constexpr int SHORT_HEAD = 32, MIDDLE_HEAD = 128;
+// number of workgroups that xcd_map deals the blocks of all heads to
+__host__ __device__ __forceinline__ int xcd_map_wgs(int heads, int blocks_per_head, int chunk) {
+  return heads * (blocks_per_head <= SHORT_HEAD ? blocks_per_head : 8 * chunk);
+}
 __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int chunk) {
+  HeadBlock r;
+  if (blocks_per_head <= SHORT_HEAD) {
+    r.bh = wg / blocks_per_head;
+    r.blk = (wg - r.bh * blocks_per_head + 3 * r.bh) % blocks_per_head;
+    r.valid = true;
+    return r;
+  }
   const int xcd = wg & 7;
   const int slot = wg >> 3;
-  HeadBlock r;
   r.bh = slot / chunk;
-  r.blk = xcd * chunk + slot % chunk;
+  r.blk = ((xcd + (blocks_per_head <= MIDDLE_HEAD ? 3 * r.bh : 0)) & 7) * chunk + slot % chunk;
   r.valid = r.blk < blocks_per_head;
   return r;
 }
@@ -225,7 +244,7 @@ __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int ch
 __device__ __forceinline__ HeadBlock xcd_map_rows(int wg, int blocks_per_head, int chunk) {
   HeadBlock r = xcd_map(wg, blocks_per_head, chunk);
   const int s = (wg >> 3) % chunk;
-  if ((s | 3) < chunk) {                       // (the last rows of a chunk that fill no group of four stay in place)
+  if (blocks_per_head > SHORT_HEAD && (s | 3) < chunk) {    // (the last rows of a chunk that fill no group of four stay in place)
     const uint32_t rot = ((uint32_t)r.bh * 0x85EBCA6Bu + (uint32_t)(s >> 2) * 0x9E3779B1u) >> 30;   // one per group
     const int t = (s & ~3) | ((s + (int)rot) & 3);
     r.blk += t - s;

@@ -89,13 +89,16 @@ struct Walk {
       return sp.pool_slots == 0 || sp.unit_slot[(int64_t)it.bh * units_per_head + it.blk] < 0;
     };
     if (!sp.queue) {
-      const int g = blockIdx.x;
-      if (g < sp.pool_slots) {
-        if (g >= sp.header[0]) return false;
+      // parts first, whole columns right behind them (at a multiple of eight: the workgroup -> XCD phase stays).  The
+      // host does not know the number of parts and launches room for the whole pool: what is too much comes last.
+      // (Between the two it kept the columns of 24 heads of 21, 332 parts in front, waiting for 10 us: 51.7 / 49.1 us.)
+      const int g = blockIdx.x, n = sp.pool_slots ? sp.header[0] : 0, wg = g - ((n + 7) & ~7);
+      if (g < n) {
         part(g);
         return true;
       }
-      const HeadBlock hb = xcd_map(g - sp.pool_slots, units_per_head, chunk);
+      if (wg < 0 || wg >= xcd_map_wgs(heads, units_per_head, chunk)) return false;
+      const HeadBlock hb = xcd_map(wg, units_per_head, chunk);
       it.bh = hb.bh; it.blk = hb.blk;
       return hb.valid && whole();
     }
