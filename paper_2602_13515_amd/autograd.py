@@ -169,8 +169,8 @@ def sparge_attn2(q: torch.Tensor, k: torch.Tensor, v: torch.Tensor, k_frac: floa
     of building one from (q, k).  `overlap_backward` runs the two backward kernels at the same time on two
     streams (same results).  Returns O with q's shape and strides (and the pattern on request)."""
     if (pattern is not None or not return_pattern) and not overlap_backward and _plain(q, k, v):
-        # The same in native code.  Passes (us): two heads, 1,000 tokens, sampling 46 -> 28; 2,048 tokens, forward and
-        # backward 226 -> 90; 24 heads, 1,281 tokens 223 -> 133.
+        # The same in native code.  Passes (us): two heads, 1,000 tokens, sampling 46 -> 17; 2,048 tokens, forward and
+        # backward 212 -> 82; 24 heads, 1,281 tokens 211 -> 116 (with the kernels' own changes).
         if scale is None:
             scale = 1.0 / math.sqrt(q.shape[-1]) if q.dim() and q.shape[-1] else 1.0      # (those are refused there)
         given = [] if pattern is None else [pattern.mask, pattern.row_cnt, pattern.row_idx, pattern.col_cnt,

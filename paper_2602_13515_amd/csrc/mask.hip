@@ -25,7 +25,8 @@ namespace spa2 {
 // fit.  Measured, us (selection on four rows / on sixteen; the row-major keys of the latter also save the pooling pass
 // 5 to 15 %): 20,010 tokens d = 64, 20 groups of sixteen rows 15.7 / 19.7, 240 groups 36.4 / 21.9; 32,760 tokens
 // d = 128, 32 groups 21.2 / 31.4, 192 groups 34.3 / 32.1; 75,600 tokens d = 128, 222 groups 86 / 57; 131,042 tokens
-// d = 64, 128 groups 57 / 65, 256 groups 109 / 70; 16 blocks a row 13.5 / 9.7.
+// d = 64, 128 groups 57 / 65, 256 groups 109 / 70; 16 blocks a row 13.5 / 9.7 (rows of up to 64 blocks
+// take select_small_kernel by now, with the same layout of the keys).
 constexpr int SEL16_FOUR_D64 = 1536, SEL16_FOUR_D128 = 1280;     // widest rows of the four-wave workgroups
 static int select16_waves(const Dims& m) {
   const int64_t wgs = (int64_t)m.B * m.H * ((m.Tm + 15) / 16);
