@@ -52,10 +52,6 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 // column-wise, which is what an MFMA operand needs when the contraction index
 // is the row of the tile in memory.
 typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-__device__ __forceinline__ u32x2 lds_read_tr4(const uint16_t* lds_ptr) {
-  s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(lds_ptr));
-  return __builtin_bit_cast(u32x2, v);
-}
 __device__ __forceinline__ bf16x8 join_tr(u32x2 lo, u32x2 hi) {
   u32x4 u = {lo[0], lo[1], hi[0], hi[1]};
   return __builtin_bit_cast(bf16x8, u);
@@ -80,22 +76,6 @@ __device__ __forceinline__ float dot2_ones(uint32_t p, float acc) {
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// Direct global -> LDS copy, 16 bytes per lane: lane l's bytes land at lds_dst + 16 l (lds_dst wave-uniform);
-// the source is a wave-uniform base plus a 32-bit byte offset per lane.  Issued as an assembly statement so
-// that the compiler's wait-count insertion does not see it: through the builtin, LDS reads that follow a copy
-// are made to wait for it (the two cannot be told apart by address).  The caller therefore owns the
-// ordering: raw_copies_done() before the barrier that publishes the tile.  In-order completion of vector
-// memory operations keeps the compiler's own counted waits safe (they can only wait for more, never less).
-// m0 carries the LDS address and is declared clobbered; a kernel that uses this helper must not also rely on
-// the compiler keeping a value of its own in m0 across it (the builtin form of the same copy would).
-__device__ __forceinline__ void raw_copy16_to_lds(const void* src_base, uint32_t src_off, const uint16_t* lds_dst) {
-#if defined(__HIP_DEVICE_COMPILE__)      // (the host pass of hipcc parses device functions too and knows no m0)
-  // (wave-uniform by contract; the lane read makes that visible to the register allocator)
-  const uint32_t lds_addr = __builtin_amdgcn_readfirstlane((uint32_t)(size_t)(lptr_t*)lds_dst);
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :: "s"(lds_addr), "v"(src_off), "s"(src_base) : "memory", "m0");
-#endif
-}
 __device__ __forceinline__ void raw_copies_done() {
 #if defined(__HIP_DEVICE_COMPILE__)
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -147,7 +127,14 @@ __device__ f32x4 lds_ldf4(uint32_t addr);
 __device__ void lds_stf(uint32_t addr, float x);
 __device__ u32x2 lds_tr4_at(uint32_t addr);
 #endif
-// Direct global -> LDS copies as above, with the (wave-uniform) LDS byte address given as an integer.
+// Direct global -> LDS copy, 16 bytes per lane: lane l's bytes land at lds_addr + LDS_CONST + 16 l (lds_addr wave-uniform);
+// the source is a wave-uniform base plus a 32-bit byte offset per lane.  Issued as an assembly statement so
+// that the compiler's wait-count insertion does not see it: through the builtin, LDS reads that follow a copy
+// are made to wait for it (the two cannot be told apart by address).  The caller therefore owns the
+// ordering: raw_copies_done() before the barrier that publishes the tile.  In-order completion of vector
+// memory operations keeps the compiler's own counted waits safe (they can only wait for more, never less).
+// m0 carries the LDS address and is declared clobbered; a kernel that uses this helper must not also rely on
+// the compiler keeping a value of its own in m0 across it (the builtin form of the same copy would).
 // LDS_CONST is a compile-time part of the destination that is added while m0 is written.
 template <int LDS_CONST>
 __device__ __forceinline__ void raw_copy16_to_lds_at(const void* src_base, uint32_t src_off, uint32_t lds_addr) {
