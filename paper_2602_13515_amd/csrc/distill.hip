@@ -122,9 +122,9 @@ __global__ __launch_bounds__(256) void vd_grad_kernel(const void* us, const void
   }
 }
 
-// Loss and gradient for upstream = 1 in one pass, fp32: 2 reads and 1 write per element for both, where the two passes
-// above take 4 and 1.  bf16 has no such pass: its gradient could not be multiplied by another upstream without a second
-// rounding.  Same sums and products as the two passes; from the end to the start and past the cache as vd_grad_kernel.
+// Loss and gradient for upstream = 1 in one pass, fp32, for callers that know that factor: 2 reads and 1 write per element
+// for both, where the two passes above take 4 and 1.  bf16 has no such pass: its gradient could not be multiplied by
+// another upstream without a second rounding.  Same sums and products as the two passes; from the end to the start and past the cache as vd_grad_kernel.
 // Bound: HBM, 5.5 TB/s.  New predictions every time, loss + gradient pass before / this one with the rescale (for an
 // upstream of 1, for another), us: 2 x 201 MB 74 + 107 / 110 + 2, 110 + 76; 2 x 671 MB 240 + 400 / 405 + 2, 405 + 275;
 // 2 x 49 MB 21 + 25 / 28 + 2, 28 + 16.  (Two or four vectors in flight per thread instead of one: 116, 117 us on the first.)

@@ -12,8 +12,6 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/extension.h>
 
-#include <cfloat>
-
 #include "spa2.h"
 
 namespace {
@@ -194,24 +192,18 @@ void vd_check(const Tensor& us, const Tensor& uf) {
                     "predictions are contiguous tensors of one shape");
 }
 
-// fp32 predictions with a gradient to come: one pass for the loss and the gradient of the loss itself, which the backward
-// pass multiplies by the upstream derivative where that is not 1; else one pass for the loss and one for the gradient.
+// One pass for the loss, one for the gradient.  (Not spa2_vd_loss_and_grad: what the upstream derivative is, and whether a
+// backward pass comes at all, is known only after the loss.  With it, 2 x 201 MB of fp32, us: upstream 1 172 -> 115, but upstream
+// 0.5 171 -> 191 and the loss alone 74 -> 111, and a gradient that is multiplied afterwards is rounded once more.)
 struct VelocityLoss : torch::autograd::Function<VelocityLoss> {
-  static Tensor forward(AutogradContext* ctx, const Tensor& us, const Tensor& uf, double weight, bool with_grad) {
+  static Tensor forward(AutogradContext* ctx, const Tensor& us, const Tensor& uf, double weight) {
     vd_check(us, uf);
     const c10::DeviceGuard device(us.device());
     const Tensor loss = at::empty({}, us.options().dtype(at::kDouble));
     const int64_t n = (int64_t)spa2_vd_loss_workspace_bytes();
     const Tensor ws = bytes(n, us);
-    if (with_grad && us.scalar_type() == at::kFloat && 2.0 * weight >= 2.0 * (double)FLT_MIN) {
-      const Tensor grad = at::empty_like(us);
-      check(spa2_vd_loss_and_grad(us.data_ptr(), uf.data_ptr(), us.numel(), weight, (double*)loss.data_ptr(),
-                                  grad.data_ptr(), ws.data_ptr(), (size_t)n, stream_of(us)), "spa2_vd_loss_and_grad");
-      ctx->saved_data["grad"] = grad;
-    } else {
-      check(spa2_vd_loss(us.data_ptr(), uf.data_ptr(), us.numel(), vd_type(us), weight, (double*)loss.data_ptr(),
-                         ws.data_ptr(), (size_t)n, stream_of(us)), "spa2_vd_loss");
-    }
+    check(spa2_vd_loss(us.data_ptr(), uf.data_ptr(), us.numel(), vd_type(us), weight, (double*)loss.data_ptr(),
+                       ws.data_ptr(), (size_t)n, stream_of(us)), "spa2_vd_loss");
     ctx->save_for_backward({us, uf});
     ctx->saved_data["weight"] = weight;
     return loss;
@@ -225,26 +217,15 @@ struct VelocityLoss : torch::autograd::Function<VelocityLoss> {
     const Tensor upstream = grads[0].contiguous();
     TORCH_CHECK_VALUE(upstream.scalar_type() == at::kDouble && upstream.numel() == 1 && upstream.is_cuda(),
                       "upstream is a float64 CUDA tensor of one element");
-    const double weight = ctx->saved_data["weight"].toDouble();
-    Tensor grad;
-    const auto made = ctx->saved_data.find("grad");
-    if (made != ctx->saved_data.end()) {             // (given away once; a second backward pass makes its own)
-      grad = made->second.toTensor();
-      ctx->saved_data.erase(made);
-      check(spa2_vd_rescale(grad.data_ptr(), grad.numel(), weight, (const double*)upstream.data_ptr(), stream_of(us)),
-            "spa2_vd_rescale");
-    } else {
-      grad = at::empty_like(us);
-      check(spa2_vd_loss_grad(us.data_ptr(), uf.data_ptr(), us.numel(), vd_type(us), weight,
-                              (const double*)upstream.data_ptr(), grad.data_ptr(), stream_of(us)), "spa2_vd_loss_grad");
-    }
-    return {grad, Variable(), Variable(), Variable()};
+    const Tensor grad = at::empty_like(us);
+    check(spa2_vd_loss_grad(us.data_ptr(), uf.data_ptr(), us.numel(), vd_type(us), ctx->saved_data["weight"].toDouble(),
+                            (const double*)upstream.data_ptr(), grad.data_ptr(), stream_of(us)), "spa2_vd_loss_grad");
+    return {grad, Variable(), Variable()};
   }
 };
 
 Tensor velocity_loss(const Tensor& u_sparse, const Tensor& u_full, double weight) {
-  const bool with_grad = at::GradMode::is_enabled() && u_sparse.requires_grad();
-  return VelocityLoss::apply(u_sparse.contiguous(), u_full.detach().contiguous(), weight, with_grad);
+  return VelocityLoss::apply(u_sparse.contiguous(), u_full.detach().contiguous(), weight);
 }
 
 }  // namespace

@@ -62,25 +62,15 @@ def noisy_latent(x1: torch.Tensor, x0: torch.Tensor, t: torch.Tensor) -> torch.T
     return t * x1 + (1.0 - t) * x0
 
 
-_F32_TINY = torch.finfo(torch.float32).tiny
-
-
 class _VelocityDistillationLoss(torch.autograd.Function):
-    """weight * ||u_sparse - u_full||^2 through the fused kernels.  fp32 predictions with a gradient to come: one pass for
-    the loss and the gradient of the loss itself, which the backward pass multiplies by the upstream derivative where
-    that is not 1; else one pass for the loss and one for the gradient."""
+    """weight * ||u_sparse - u_full||^2 through the fused kernels: one pass for the loss, one for the gradient."""
 
     @staticmethod
     def forward(ctx, u_sparse, u_full, weight):
         u_full = u_full.detach()
         loss = torch.empty((), dtype=torch.float64, device=u_sparse.device)
         ws = torch.empty(_b.spa2_vd_loss_workspace_bytes(), dtype=torch.uint8, device=u_sparse.device)
-        ctx.grad = None
-        if ctx.needs_input_grad[0] and u_sparse.dtype == torch.float32 and 2.0 * weight >= 2.0 * _F32_TINY:
-            ctx.grad = torch.empty_like(u_sparse)
-            _b.spa2_vd_loss_and_grad(u_sparse.detach(), u_full, weight, loss, ctx.grad, ws)
-        else:
-            _b.spa2_vd_loss(u_sparse.detach(), u_full, weight, loss, ws)
+        _b.spa2_vd_loss(u_sparse.detach(), u_full, weight, loss, ws)
         ctx.save_for_backward(u_sparse, u_full)
         ctx.weight = weight
         return loss
@@ -88,12 +78,8 @@ class _VelocityDistillationLoss(torch.autograd.Function):
     @staticmethod
     def backward(ctx, upstream):
         u_sparse, u_full = ctx.saved_tensors
-        grad, ctx.grad = ctx.grad, None           # (given away once; a second backward pass makes its own)
-        if grad is not None:
-            _b.spa2_vd_rescale(grad, ctx.weight, upstream.contiguous())
-        else:
-            grad = torch.empty_like(u_sparse)
-            _b.spa2_vd_loss_grad(u_sparse.detach(), u_full, ctx.weight, upstream.contiguous(), grad)
+        grad = torch.empty_like(u_sparse)
+        _b.spa2_vd_loss_grad(u_sparse.detach(), u_full, ctx.weight, upstream.contiguous(), grad)
         return grad, None, None
 
 

@@ -105,3 +105,27 @@ def test_fused_loss_on_either_side_of_the_cache_size(dtype, n):
     bar = 2.0 ** -22 if dtype == torch.float32 else 2.0 ** -8 + 2.0 ** -22
     err = (grad.double() - 2.0 / n * diff).abs()
     assert bool((err <= bar * (2.0 / n * diff).abs() + 1e-44).all())
+
+
+# whole numbers, a power of two, a fraction, loss scaling; the factor 2 / 1,000,003 is 1.3e-8 off its fp32 value
+@pytest.mark.parametrize("upstream", [1.0, 4.0, 0.25, 0.3, 65536.0])
+@pytest.mark.parametrize("reduction", ["mean", "batch"])
+def test_gradient_is_one_product_whatever_the_upstream(upstream, reduction):
+    """fl(2 weight upstream) times the difference, rounded once: the same bits from every backward pass of a graph, also
+    where 2 weight times the difference alone leaves the normal range of fp32."""
+    import numpy as np
+    n = 1_000_003
+    rng = np.random.default_rng(4)
+    diff = (rng.standard_normal(n) * 10.0 ** rng.uniform(-3, 1, n)).astype(np.float32)
+    diff[::7] = 1e-36 * diff[::7]                        # underflows with the small factor of "mean"
+    if upstream < 1:
+        diff[::11] = np.float32(3e38)                    # overflows with the factor 2 of "batch"
+    us = torch.from_numpy(diff).to(dev())[None].requires_grad_(True)
+    loss = vd.velocity_distillation_loss(us, torch.zeros_like(us), reduction)
+    weight = 1.0 / n if reduction == "mean" else 1.0
+    want = np.float32(2.0 * weight * upstream) * diff
+    assert np.isfinite(want).all()
+    up = torch.tensor(upstream, dtype=torch.float64, device=dev())
+    for keep in (True, False):
+        (grad,) = torch.autograd.grad(loss, us, up, retain_graph=keep)
+        assert np.array_equal(grad[0].cpu().numpy(), want), (keep, int((grad[0].cpu().numpy() != want).sum()))
