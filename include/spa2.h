@@ -249,10 +249,14 @@ int spa2_vd_loss(const void* u_sparse, const void* u_full, int64_t n, int32_t dt
 int spa2_vd_loss_grad(const void* u_sparse, const void* u_full, int64_t n, int32_t dtype, double weight,
                       const double* upstream /* or NULL */, void* grad, void* stream);
 
-/* Loss and gradient in one pass over the predictions, fp32: spa2_vd_loss_and_grad writes the loss and, into grad, what
- * spa2_vd_loss_grad writes for upstream = 1; spa2_vd_rescale multiplies that gradient by upstream in place (each element
- * in fp64, rounded once) and touches nothing where upstream is 1.  2 * weight must be a normal fp32 number (else
- * SPA2_ERR_RANGE).  Other arguments and errors as for spa2_vd_loss and spa2_vd_loss_grad. */
+/* Loss and gradient in one pass over the predictions, fp32, for callers that differentiate the loss itself:
+ * spa2_vd_loss_and_grad writes the loss and, into grad, what spa2_vd_loss_grad writes for upstream = 1.
+ * spa2_vd_rescale multiplies such a gradient in place by upstream and by 2 * weight over its fp32 value (in fp64, rounded
+ * once per element), which takes the rounding of that factor back; where upstream is exactly 1 it touches nothing.  An
+ * element then differs from what spa2_vd_loss_grad writes for that upstream by up to 2^-22 of its value, powers of two
+ * included, as long as 2 * weight * (u_sparse - u_full) is a normal fp32 number: what underflowed or overflowed there
+ * stays lost, so callers with another upstream in mind use spa2_vd_loss_grad.  2 * weight must be a normal fp32 number
+ * (else SPA2_ERR_RANGE).  Other arguments and errors as for spa2_vd_loss and spa2_vd_loss_grad. */
 int spa2_vd_loss_and_grad(const void* u_sparse, const void* u_full, int64_t n, double weight, double* loss, void* grad,
                           void* workspace, size_t workspace_bytes, void* stream);
 int spa2_vd_rescale(void* grad, int64_t n, double weight, const double* upstream, void* stream);

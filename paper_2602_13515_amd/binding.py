@@ -447,7 +447,7 @@ def spa2_vd_loss_and_grad(u_sparse: torch.Tensor, u_full: torch.Tensor, weight: 
 
 
 def spa2_vd_rescale(grad: torch.Tensor, weight: float, upstream: torch.Tensor) -> None:
-    """grad of spa2_vd_loss_and_grad times upstream (a float64 device scalar), in place."""
+    """grad of spa2_vd_loss_and_grad times upstream (a float64 device scalar), in place; within 2^-22 of spa2_vd_loss_grad."""
     if grad.dtype != torch.float32 or not grad.is_contiguous() or not grad.is_cuda:
         raise ValueError("grad is a contiguous float32 CUDA tensor")
     if upstream.dtype != torch.float64 or upstream.numel() != 1 or not upstream.is_cuda:

@@ -90,10 +90,33 @@ def test_loss_and_gradient_in_one_pass(n):
         got = grad.clone()
         spa2.binding.spa2_vd_rescale(got, weight, scalar(u))
         spa2.binding.spa2_vd_loss_grad(us, uf, weight, scalar(u), ref)
-        if u != 0.3:                                          # powers of two: the same bits
+        if u != 0.3:      # 2 * 0.7 / n is within 2^-25 of its fp32 value for these n: powers of two give the same bits
             assert torch.equal(got, ref)
         else:      # on either side three roundings to fp32 of 2^-24 each: difference, factor or product, product
             assert ((got - ref).abs() <= 2.0 ** -22 * ref.abs()).all()
+
+
+# factors 2 / n that are not fp32 numbers.  Two roundings of 2^-24 on either side: both products where the gradient is rescaled,
+# factor and product where it is made for that upstream
+@pytest.mark.parametrize("n", [1_000_003, 11, 22_369_627])
+def test_rescaled_gradient_is_within_its_bound(n):
+    g = torch.Generator(device=dev()).manual_seed(n)
+    us, uf = (torch.randn(n, generator=g, device=dev()) for _ in range(2))
+    weight = 1.0 / n
+    grad, ref = torch.empty_like(us), torch.empty_like(us)
+    loss = torch.zeros((), dtype=torch.float64, device=dev())
+    ws = torch.empty(spa2.binding.spa2_vd_loss_workspace_bytes(), dtype=torch.uint8, device=dev())
+    spa2.binding.spa2_vd_loss_and_grad(us, uf, weight, loss, grad, ws)
+    exact = 2.0 * weight * (us - uf).double()
+    for u in (1.0, 2.0, 4.0, 0.3, 65536.0):
+        up = torch.tensor(u, dtype=torch.float64, device=dev())
+        got = grad.clone()
+        spa2.binding.spa2_vd_rescale(got, weight, up)
+        spa2.binding.spa2_vd_loss_grad(us, uf, weight, up, ref)
+        assert ((got - ref).abs() <= 2.0 ** -22 * ref.abs()).all(), u
+        assert ((got.double() - u * exact).abs() <= 2.0 ** -23 * (u * exact).abs() * (1 + 1e-6)).all(), u
+        if u == 1.0:
+            assert torch.equal(got, grad) and torch.equal(got, ref)
 
 
 def test_second_backward_pass_gets_a_gradient_of_its_own():
