@@ -138,18 +138,20 @@ class _SpargeAttn2(torch.autograd.Function):
         k, v, o, o_res, lse = _forward(q, k, v, scale, pattern, residual=training)
         if training:
             ctx.save_for_backward(q, k, v, o, o_res, lse)
-            ctx.pattern, ctx.scale, ctx.overlap = pattern, scale, bool(overlap_backward)
+            ctx.pattern, ctx.scale, ctx.overlap, ctx.device = pattern, scale, bool(overlap_backward), q.device
         return o
 
     @staticmethod
     def backward(ctx, d_o):
         q, k, v, o, o_res, lse = ctx.saved_tensors
-        d_o = _match(d_o.to(torch.bfloat16), q)
+        # (saved-tensor hooks may bring a tensor back in another layout, type or place)
         lay = _b._layout_of(q)
-        # (all of them, not d_o alone: saved-tensor hooks may bring a tensor back in another layout)
+        if q.device != ctx.device:
+            raise ValueError("saved token tensors come back on their GPU")
+        if lse.device != q.device or lse.dtype != torch.float32 or lse.shape != q.shape[:3] or not lse.is_contiguous():
+            raise ValueError("the log-sum-exp comes back as a contiguous fp32 [B, H, N] tensor")
+        d_o = _match(d_o.to(torch.bfloat16), q)
         _b._same_layout(q, k, v, o, o_res, d_o)
-        if not lse.is_contiguous():
-            raise ValueError("the log-sum-exp must be contiguous")
         dq, dk, dv = _like(q), _like(q), _like(q)
         ws = torch.empty(lay.bwd_ws, dtype=torch.uint8, device=q.device)
         if ctx.overlap:

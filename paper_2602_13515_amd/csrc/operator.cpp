@@ -63,6 +63,15 @@ void check_inputs(const Tensor& q, const Tensor& k, const Tensor& v) {
   TORCH_CHECK_VALUE(k.device() == q.device() && v.device() == q.device(), ONE_LAYOUT);
 }
 
+// What saved-tensor hooks bring back is checked before a kernel gets its address.  (The sizes are those of the upstream
+// gradient, which the engine has compared with the output's.)
+void check_saved(const Tensor& q, const Tensor& lse, int64_t gpu) {
+  TORCH_CHECK_VALUE(q.is_cuda() && q.device().index() == gpu && q.scalar_type() == at::kBFloat16 && q.dim() == 4 &&
+                    q.stride(3) == 1, "saved token tensors come back as bf16 [B, H, N, d] views on their GPU, d contiguous");
+  TORCH_CHECK_VALUE(lse.device() == q.device() && lse.scalar_type() == at::kFloat && lse.sizes() == q.sizes().slice(0, 3) &&
+                    lse.is_contiguous(), "the log-sum-exp comes back as a contiguous fp32 [B, H, N] tensor");
+}
+
 spa2_shape shape_of(const Tensor& q) {
   spa2_shape s;
   s.B = (int32_t)q.size(0); s.H = (int32_t)q.size(1); s.N = (int32_t)q.size(2); s.d = (int32_t)q.size(3);
@@ -145,6 +154,7 @@ struct Attention : torch::autograd::Function<Attention> {
       ctx->save_for_backward({q, k, v, o, o_res, lse});
       ctx->saved_data["pattern"] = build ? std::vector<Tensor>{buf} : given;
       ctx->saved_data["scale"] = scale;
+      ctx->saved_data["gpu"] = (int64_t)q.device().index();
     }
     return o;
   }
@@ -152,11 +162,11 @@ struct Attention : torch::autograd::Function<Attention> {
   static variable_list backward(AutogradContext* ctx, variable_list grads) {
     const variable_list saved = ctx->get_saved_variables();
     const Tensor &q = saved[0], &k = saved[1], &v = saved[2], &o = saved[3], &o_res = saved[4], &lse = saved[5];
+    check_saved(q, lse, ctx->saved_data["gpu"].toInt());
     const c10::DeviceGuard device(q.device());
     const Tensor d_o = match(grads[0].to(at::kBFloat16), q);
     // (all of them, not d_o alone: saved-tensor hooks may bring a tensor back in another layout)
     same_layout(q, {&k, &v, &o, &o_res, &d_o});
-    TORCH_CHECK_VALUE(lse.is_contiguous(), "the log-sum-exp must be contiguous");
     const spa2_shape s = shape_of(q);
     const std::vector<Tensor> kept = ctx->saved_data["pattern"].toTensorVector();
     const spa2_pattern pattern = kept.size() == 1 ? PatternLayout(s, true).in(kept[0]) : given_pattern(kept);

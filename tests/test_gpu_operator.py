@@ -156,3 +156,30 @@ def test_native_route_refuses_what_the_python_route_refuses():
     o.backward(do)
     with pytest.raises(RuntimeError):                              # a second time without retain_graph
         o.backward(do)
+
+
+# what the hooks make of the token tensors and of the log-sum-exp.  Nothing may be launched on these: the kernels would read
+# host memory, rows through wrong strides, or past the end
+BROUGHT_BACK = {
+    "on the host": (lambda x: x.cpu(), lambda x: x.cpu()),
+    "channels apart": (lambda x: x.transpose(2, 3).contiguous().transpose(2, 3), lambda x: x),
+    "in fp32": (lambda x: x.float(), lambda x: x),
+    "log-sum-exp on the host": (lambda x: x, lambda x: x.cpu()),
+    "log-sum-exp in fp64": (lambda x: x, lambda x: x.double()),
+    "log-sum-exp shorter": (lambda x: x, lambda x: x[..., :-1].contiguous()),
+}
+
+
+@pytest.mark.parametrize("change", BROUGHT_BACK)
+@pytest.mark.parametrize("given", [False, True])
+def test_native_backward_refuses_saved_tensors_of_another_place_or_kind(change, given):
+    q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
+    pattern = spa2.build_pattern(q, k, 0.1, 0.6) if given else None
+    tokens, lse = BROUGHT_BACK[change]
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    with torch.autograd.graph.saved_tensors_hooks(lambda x: x.detach(), lambda x: tokens(x) if x.dim() == 4 else lse(x)):
+        o = spa2.sparge_attn2(*leaves, 0.1, 0.6, pattern=pattern)
+    assert "CppNode" in o.grad_fn.name()
+    # (an upstream gradient of other strides is copied to those of q, wherever q is)
+    with pytest.raises(ValueError):
+        o.backward(do.transpose(1, 2).contiguous().transpose(1, 2))
