@@ -205,7 +205,9 @@ constexpr int SHORT_HEAD = 32, MIDDLE_HEAD = 128;
 __host__ __device__ __forceinline__ int xcd_map_wgs(int heads, int blocks_per_head, int chunk) {
   return heads * (blocks_per_head <= SHORT_HEAD ? blocks_per_head : 8 * chunk);
 }
-__device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int chunk) {
+// ... and how many of them are dealt to XCD x: numbers x, x + 8, x + 16, ...
+__host__ __device__ __forceinline__ int xcd_map_share(int wgs, int xcd) { return (wgs - xcd + 7) >> 3; }
+__host__ __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int chunk) {
   HeadBlock r;
   if (blocks_per_head <= SHORT_HEAD) {
     r.bh = wg / blocks_per_head;

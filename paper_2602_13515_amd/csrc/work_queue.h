@@ -1,7 +1,7 @@
 // Which column (or part of one) a workgroup of the dK/dV kernel works on, and which one next.
 //
 // A launch has one item per column that is not split, and one per part of a split column.  Items are dealt to the eight
-// XCDs: parts round-robin, columns by xcd_map (every XCD works on a contiguous chunk of the same head).
+// XCDs: parts round-robin, columns by xcd_map, in both kinds of launch.
 //   * Direct launch: one workgroup per item, the parts first.  For launches that fit the chip at once, and where the
 //     caller gave no workspace.
 //   * Queue launch (sp.queue): as many workgroups as the compute units hold stay for the whole launch and take items of
@@ -14,6 +14,10 @@
 // 851; 32,768 tokens, 24 heads, half the rows long 7540 / 7153; 20,010 tokens, 6 heads, d = 64 129 / 130.  The forward and
 // dQ kernels gain less (their launches are bound by power, an empty slot is clock for the others: 1.6 % for dQ, 0.3 % for
 // forward on the first of these) and lose on shorter launches (dQ on the last 75 / 81): they are launched directly.
+// Numbers that stand for no column are drawn as well, an atomic and two barriers each, so the queue has xcd_map's few: with
+// chunks of a head on every XCD, heads of less than eight columns left XCDs of nothing but such numbers.  Stage call, us,
+// chunks / xcd_map / direct: 2,300 heads of one column, d = 64 95 / 54 / 52, d = 128 113 / 83 / 82; 1,000 heads of 9 columns
+// 219 / 191 / 195, 324 / 301 / 307; 282 heads of 32 276 / 271 / 275; 141 heads of 64 420 / 421 / 477.
 #pragma once
 #include "spa2_device.h"
 #include "spa2_internal.h"
@@ -102,7 +106,7 @@ struct Walk {
       it.bh = hb.bh; it.blk = hb.blk;
       return hb.valid && whole();
     }
-    const int n_parts = sp.header[0], n_units = heads * chunk;
+    const int n_parts = sp.header[0], wgs = xcd_map_wgs(heads, units_per_head, chunk);
     for (;;) {
       const int np = (n_parts - xcd + 7) >> 3;           // parts g = 8 q + xcd < n_parts
       if (q < np) {
@@ -110,14 +114,15 @@ struct Walk {
         return true;
       }
       const int s = q - np;
-      if (s < n_units) {
-        it.bh = s / chunk; it.blk = xcd * chunk + s % chunk;
-        if (it.blk < units_per_head && whole()) return true;
+      if (s < xcd_map_share(wgs, xcd)) {
+        const HeadBlock hb = xcd_map(8 * s + xcd, units_per_head, chunk);
+        it.bh = hb.bh; it.blk = hb.blk;
+        if (hb.valid && whole()) return true;
       } else {                                           // this XCD is through: on to the one with most items left
         __syncthreads();
         if (wave == 0) {
           const int x = fresh_lane() & 7;
-          int left = n_units + ((n_parts - x + 7) >> 3) -
+          int left = xcd_map_share(wgs, x) + ((n_parts - x + 7) >> 3) -
                      __hip_atomic_load(counter(sp, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           left = left > 0 ? 8 * left + x : -1;
 #pragma unroll

@@ -33,3 +33,17 @@ def test_queue_gives_the_bits_of_the_direct_launch(B, H, N, d):
     for name, x, y, z in zip(("dq", "dk", "dv"), queued, direct, again):
         assert torch.equal(x, y), name
         assert torch.equal(x, z), name
+
+
+# one, three and nine columns a head: no XCD is left without
+@pytest.mark.parametrize("H,N,d", [(2100, 60, 64), (700, 190, 128), (240, 567, 64)])
+def test_queue_over_heads_of_a_few_columns(H, N, d):
+    g = torch.Generator().manual_seed(2)
+    q, k, v, do = (torch.randn((1, H, N, d), generator=g).bfloat16().to(dev()) for _ in range(4))
+    pat = spa2.alloc_pattern(1, H, N, dev())
+    spa2.spa2_pattern_full(q, pat)
+    o, lse, o_res = gpu_fwd(q, k, v, pat, residual=True)
+    queued = gpu_bwd(q, k, v, o, do, lse, pat, o_res=o_res)
+    direct = gpu_bwd(q, k, v, o, do, lse, pat, o_res=o_res, split=False)
+    for name, x, y in zip(("dq", "dk", "dv"), queued, direct):       # (five entries a column at most: nothing is cut)
+        assert torch.equal(x, y), name

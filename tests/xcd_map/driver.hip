@@ -1,0 +1,40 @@
+// Host check of how blocks are dealt to the XCDs (tests/test_xcd_map.py compiles and runs it; no GPU).
+#include <cstdio>
+#include <vector>
+
+#include "spa2_device.h"
+
+using namespace spa2;
+
+int main() {
+  int bad = 0;
+  for (int heads : {1, 2, 5, 9, 40}) {
+    for (int blocks = 1; blocks <= 300; ++blocks) {
+      const int chunk = (blocks + 7) / 8, wgs = xcd_map_wgs(heads, blocks, chunk);
+      std::vector<int> seen((size_t)heads * blocks, 0);
+      int dealt = 0, dead = 0, least = 1 << 30, most = 0;
+      for (int xcd = 0; xcd < 8; ++xcd) {          // as a queue walks them: number s of an XCD
+        int live = 0;
+        for (int s = 0; s < xcd_map_share(wgs, xcd); ++s, ++dealt) {
+          const HeadBlock hb = xcd_map(8 * s + xcd, blocks, chunk);
+          if (!hb.valid) { ++dead; continue; }
+          ++live;
+          if (hb.bh < 0 || hb.bh >= heads || hb.blk < 0 || hb.blk >= blocks) { ++bad; continue; }
+          ++seen[(size_t)hb.bh * blocks + hb.blk];
+        }
+        least = live < least ? live : least;
+        most = live > most ? live : most;
+      }
+      bool once = dealt == wgs;
+      for (int n : seen) once = once && n == 1;
+      // short heads: no number without a block, every XCD as many blocks as the others
+      const bool even = blocks > 32 || (dead == 0 && most - least <= 1);
+      if (!once || !even || dead > 7 * heads) {
+        std::printf("%d heads of %d blocks: once %d, dead %d, %d to %d an XCD\n", heads, blocks, once, dead, least, most);
+        ++bad;
+      }
+    }
+  }
+  std::printf(bad ? "FAILED %d\n" : "every block once\n", bad);
+  return bad ? 1 : 0;
+}
