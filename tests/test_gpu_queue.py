@@ -7,7 +7,7 @@ import torch
 import paper_2602_13515_amd as spa2
 from paper_2602_13515_amd import workloads as wl
 
-from gpu_util import dev, gpu_bwd, gpu_fwd, pattern_from_mask
+from gpu_util import check_plan, dev, gpu_bwd, gpu_fwd, pattern_from_mask, plan_headers, plan_offsets
 
 pytestmark = pytest.mark.gpu
 
@@ -33,6 +33,61 @@ def test_queue_gives_the_bits_of_the_direct_launch(B, H, N, d):
     for name, x, y, z in zip(("dq", "dk", "dv"), queued, direct, again):
         assert torch.equal(x, y), name
         assert torch.equal(x, z), name
+
+
+def _cut_pattern(B, H, N, seed):
+    """Most columns of two entries or so, a fifth of those of every fourth head of all row blocks: these a plan cuts.  Their
+    launch order by the library."""
+    Tm, Tn = -(-N // 128), -(-N // 64)
+    rng = np.random.default_rng(seed)
+    mask = np.zeros((B, H, Tm, Tn), dtype=np.uint8)
+    for _ in range(4):
+        np.put_along_axis(mask, rng.integers(0, Tn, size=(B, H, Tm))[..., None], 1, axis=-1)
+    mask[:, ::4, :, rng.permutation(Tn)[:Tn // 5]] = 1
+    pat = pattern_from_mask(mask, dev())
+    order = spa2.alloc_pattern(B, H, N, dev())
+    order.mask.copy_(pat.mask)
+    spa2.spa2_mask_columns(torch.empty((B, H, N, 64), dtype=torch.bfloat16, device=dev()), order)
+    return mask, pat, order.col_order
+
+
+# heads of 55 columns and of 28 (dealt in turn); full workspace, and one whose pool is too small for the first choice of
+# parts in the first case (110 columns of three parts, 255 slots)
+@pytest.mark.parametrize("H,N,d", [(40, 3500, 128), (75, 1790, 64)])
+@pytest.mark.parametrize("space", ["full", "small"])
+def test_queue_with_cut_columns(H, N, d, space):
+    """Parts and whole columns from one queue: every column against the direct launch that cuts nothing, and the same bits with
+    and without a launch order and from run to run."""
+    w = wl.Workload("queue", 1, H, N, d, 0.1, 0.5, "gaussian", True)
+    print(f"case H={H} N={N} d={d} {space}", flush=True)
+    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=5))
+    mask, pat, order = _cut_pattern(1, H, N, 7)
+    assert H * mask.shape[-1] > 2048
+    o, lse, o_res = gpu_fwd(q, k, v, pat, residual=True)
+    direct = gpu_bwd(q, k, v, o, do, lse, pat, o_res=o_res, split=False)
+    at, full = plan_offsets(q)["dkdv"], spa2.spa2_bwd_workspace_bytes(q)
+    nbytes = full if space == "full" else at + (full - at) // 5
+    runs = []
+    for col_order in (None, order, order):
+        pat.col_order = col_order
+        ws = torch.full((nbytes,), 0xA5, dtype=torch.uint8, device=dev())
+        out = tuple(torch.full_like(q, float("nan")) for _ in range(3))
+        spa2.spa2_bwd(q, k, v, o, do, lse, pat, d ** -0.5, *out, ws, o_res)
+        torch.cuda.synchronize()
+        header = plan_headers(q, ws, ("dkdv",))["dkdv"]
+        S = check_plan("dkdv", header, mask.sum(-2))
+        # (the last slot holds the queue's counters)
+        pool = 2048 if space == "full" else 256
+        assert 0 < header[0] <= pool - 1 and mask.sum(-2).max() > S, (header, pool)
+        runs.append(out)
+    for out in runs[1:]:
+        assert all(torch.equal(a, b) for a, b in zip(runs[0], out))
+    # The products are the same, the fp32 sums of up to 3,584 of them run in another order: far below 2^-12 of a row's largest
+    # value; then one rounding to bf16, up to a spacing apart (2^-7 of the value).
+    for name, x, y in zip(("dq", "dk", "dv"), runs[0], direct):
+        x, y = x.float(), y.float()
+        bar = 2.0 ** -7 * torch.maximum(x.abs(), y.abs()) + 2.0 ** -12 * y.abs().amax(-1, keepdim=True)
+        assert bool(((x - y).abs() <= bar).all()), name
 
 
 # one, three and nine columns a head: no XCD is left without
