@@ -324,7 +324,7 @@ hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid((unsigned)(plan.pool_slots + xcd_map_wgs(m.B * m.H, a.Tm, a.chunk))), block(256);
+  const dim3 grid((unsigned)(plan.pool_slots + xcd_map_wgs(m.B * m.H, a.Tm, a.chunk, SHORT_ROWS))), block(256);
   if (m.d == 128) hipLaunchKernelGGL(dq_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dq_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

@@ -76,8 +76,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   bool whole = false;         // a row of the plan that may be split: its parts are the first workgroups
   int slot = blockIdx.x;
   if (a.sp.fixed_len) {       // a small launch: the sizes say which part of which row (with_fixed_parts)
-    const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk);
-    const HeadBlock hb = xcd_map(blockIdx.x % rows, a.Tm, a.chunk);
+    const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk, SHORT_ROWS);
+    const HeadBlock hb = xcd_map(blockIdx.x % rows, a.Tm, a.chunk, SHORT_ROWS);
     if (!hb.valid) return;
     bh = hb.bh; i = hb.blk;
     const int unit = bh * a.Tm + i, all = min(max(a.row_cnt[unit], 0), a.Tn);
@@ -462,7 +462,7 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_FWD, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk);
+  const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk, SHORT_ROWS);
   const dim3 grid((unsigned)(plan.fixed_len ? plan.fixed_parts * rows : plan.pool_slots + rows)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(fwd_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(fwd_kernel<64>, grid, block, 0, stream, a);

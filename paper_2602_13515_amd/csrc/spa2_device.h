@@ -191,25 +191,27 @@ __device__ __forceinline__ bool last_part(int32_t* arrive, int parts, int* lds_w
 // workgroup ids go round-robin to the XCDs, so XCD x receives ids x, x+8, ...; those are given a contiguous chunk of the
 // head's blocks, which share K/V tiles through that XCD's L2.  The last chunk is a short one and, where blocks are dealt to
 // the chunks by length, the first holds the longest, which counts in heads of few blocks: up to MIDDLE_HEAD every head
-// starts with another XCD, and up to SHORT_HEAD, where a chunk is a block or two and the last ones are empty, the blocks go
-// to the XCDs in turn instead.
+// starts with another XCD, and up to SHORT_ROWS or SHORT_COLUMNS, where a chunk is a few blocks and the last ones are empty,
+// the blocks go to the XCDs in turn instead.
 // Measured, us, chunk x always on XCD x / now (forward, dQ, dK/dV; d = 128 unless noted).  In turn: 11 rows and 21 columns,
-// 24 heads 32.2 / 30.7, 31.2 / 30.1, 53.0 / 50.3; the same, d = 64, 512 heads 156 / 117, 148 / 111, (drawn from a queue);
-// 16 rows and 32 columns, 40 heads 42.8 / 42.5, 37.9 / 37.4, 71.9 / 57.5 (chunks that start with another XCD: 42, 38, 67).
-// Another XCD: 65 rows, 40 heads 185 / 176, 196 / 184; 97 rows, 24 heads, d = 64 105 / 102, 116 / 114.  In turn there gives no
-// more and loses 1 to 3 % on even chunks (32 rows) and long columns (79 columns, 12 heads 62 / 65); another XCD on longer
-// heads gives nothing (157 rows) and loses 1 % of the forward pass on 591.
+// 24 heads 32.2 / 30.7, 31.2 / 30.1, 53.0 / 50.3; the same, d = 64, 512 heads 156 / 117, 148 / 111, (drawn from a queue).
+// Another XCD: 65 rows, 40 heads 185 / 176, 196 / 184; 97 rows, 24 heads, d = 64 105 / 102, 116 / 114; on longer heads it
+// gives nothing (157 rows) and loses 1 % of the forward pass on 591.
+// The line between the two, us, chunks that start with another XCD / in turn.  Forward: 20 rows, 24 heads 36.0 / 30.0; 31 rows
+// 54.8 / 53.5; 32 rows, whose chunks are even, 12 heads 33.0 / 35.2, 40 heads, d = 64 45 / 49, over 48 launches of 12 to 64 heads
+// 1 % faster in chunks (dQ the same); even chunks of 1 to 3 rows -2 to +2 %.  dK/dV: 25 columns, 76 heads 141 / 114; 31 columns
+// 147 / 126; 32 columns, 60 heads 143 / 123 (few long columns: the chunks' first positions); 79 columns, 12 heads 62 / 65.
 struct HeadBlock { int bh; int blk; bool valid; };
-constexpr int SHORT_HEAD = 32, MIDDLE_HEAD = 128;
-// number of workgroups that xcd_map deals the blocks of all heads to
-__host__ __device__ __forceinline__ int xcd_map_wgs(int heads, int blocks_per_head, int chunk) {
-  return heads * (blocks_per_head <= SHORT_HEAD ? blocks_per_head : 8 * chunk);
+constexpr int SHORT_ROWS = 31, SHORT_COLUMNS = 32, MIDDLE_HEAD = 128;
+// number of workgroups that xcd_map deals the blocks of all heads to (short_head: SHORT_ROWS or SHORT_COLUMNS)
+__host__ __device__ __forceinline__ int xcd_map_wgs(int heads, int blocks_per_head, int chunk, int short_head) {
+  return heads * (blocks_per_head <= short_head ? blocks_per_head : 8 * chunk);
 }
 // ... and how many of them are dealt to XCD x: numbers x, x + 8, x + 16, ...
 __host__ __device__ __forceinline__ int xcd_map_share(int wgs, int xcd) { return (wgs - xcd + 7) >> 3; }
-__host__ __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int chunk) {
+__host__ __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_head, int chunk, int short_head) {
   HeadBlock r;
-  if (blocks_per_head <= SHORT_HEAD) {
+  if (blocks_per_head <= short_head) {
     r.bh = wg / blocks_per_head;
     r.blk = (wg - r.bh * blocks_per_head + 3 * r.bh) % blocks_per_head;
     r.valid = true;
@@ -230,10 +232,10 @@ __host__ __device__ __forceinline__ HeadBlock xcd_map(int wg, int blocks_per_hea
 // 5438 -> 4526 us, dQ 7847 -> 6310 us; rows without such a structure (75,600 tokens, 40 heads) 7665 -> 7607 and
 // 10498 -> 10589 us.  A queue that 512 resident workgroups draw rows from evens out as much, but costs 3 us a row: 4 %
 // on rows of 36 tiles.
-__device__ __forceinline__ HeadBlock xcd_map_rows(int wg, int blocks_per_head, int chunk) {
-  HeadBlock r = xcd_map(wg, blocks_per_head, chunk);
+__host__ __device__ __forceinline__ HeadBlock xcd_map_rows(int wg, int blocks_per_head, int chunk) {
+  HeadBlock r = xcd_map(wg, blocks_per_head, chunk, SHORT_ROWS);
   const int s = (wg >> 3) % chunk;
-  if (blocks_per_head > SHORT_HEAD && (s | 3) < chunk) {    // (the last rows of a chunk that fill no group of four stay in place)
+  if (blocks_per_head > SHORT_ROWS && (s | 3) < chunk) {    // (the last rows of a chunk that fill no group of four stay in place)
     const uint32_t rot = ((uint32_t)r.bh * 0x85EBCA6Bu + (uint32_t)(s >> 2) * 0x9E3779B1u) >> 30;   // one per group
     const int t = (s & ~3) | ((s + (int)rot) & 3);
     r.blk += t - s;

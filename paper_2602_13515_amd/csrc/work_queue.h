@@ -101,12 +101,12 @@ struct Walk {
         part(g);
         return true;
       }
-      if (wg < 0 || wg >= xcd_map_wgs(heads, units_per_head, chunk)) return false;
-      const HeadBlock hb = xcd_map(wg, units_per_head, chunk);
+      if (wg < 0 || wg >= xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS)) return false;
+      const HeadBlock hb = xcd_map(wg, units_per_head, chunk, SHORT_COLUMNS);
       it.bh = hb.bh; it.blk = hb.blk;
       return hb.valid && whole();
     }
-    const int n_parts = sp.header[0], wgs = xcd_map_wgs(heads, units_per_head, chunk);
+    const int n_parts = sp.header[0], wgs = xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS);
     for (;;) {
       const int np = (n_parts - xcd + 7) >> 3;           // parts g = 8 q + xcd < n_parts
       if (q < np) {
@@ -115,7 +115,7 @@ struct Walk {
       }
       const int s = q - np;
       if (s < xcd_map_share(wgs, xcd)) {
-        const HeadBlock hb = xcd_map(8 * s + xcd, units_per_head, chunk);
+        const HeadBlock hb = xcd_map(8 * s + xcd, units_per_head, chunk, SHORT_COLUMNS);
         it.bh = hb.bh; it.blk = hb.blk;
         if (hb.valid && whole()) return true;
       } else {                                           // this XCD is through: on to the one with most items left

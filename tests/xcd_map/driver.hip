@@ -6,17 +6,18 @@
 
 using namespace spa2;
 
-int main() {
+static int deal(bool rows) {
+  const int short_head = rows ? SHORT_ROWS : SHORT_COLUMNS;
   int bad = 0;
   for (int heads : {1, 2, 5, 9, 40}) {
     for (int blocks = 1; blocks <= 300; ++blocks) {
-      const int chunk = (blocks + 7) / 8, wgs = xcd_map_wgs(heads, blocks, chunk);
+      const int chunk = (blocks + 7) / 8, wgs = xcd_map_wgs(heads, blocks, chunk, short_head);
       std::vector<int> seen((size_t)heads * blocks, 0);
       int dealt = 0, dead = 0, least = 1 << 30, most = 0;
       for (int xcd = 0; xcd < 8; ++xcd) {          // as a queue walks them: number s of an XCD
         int live = 0;
         for (int s = 0; s < xcd_map_share(wgs, xcd); ++s, ++dealt) {
-          const HeadBlock hb = xcd_map(8 * s + xcd, blocks, chunk);
+          const HeadBlock hb = rows ? xcd_map_rows(8 * s + xcd, blocks, chunk) : xcd_map(8 * s + xcd, blocks, chunk, short_head);
           if (!hb.valid) { ++dead; continue; }
           ++live;
           if (hb.bh < 0 || hb.bh >= heads || hb.blk < 0 || hb.blk >= blocks) { ++bad; continue; }
@@ -28,12 +29,23 @@ int main() {
       bool once = dealt == wgs;
       for (int n : seen) once = once && n == 1;
       // short heads: no number without a block, every XCD as many blocks as the others
-      const bool even = blocks > 32 || (dead == 0 && most - least <= 1);
+      const bool even = blocks > short_head || (dead == 0 && most - least <= 1);
       if (!once || !even || dead > 7 * heads) {
-        std::printf("%d heads of %d blocks: once %d, dead %d, %d to %d an XCD\n", heads, blocks, once, dead, least, most);
+        std::printf("%s: %d heads of %d blocks: once %d, dead %d, %d to %d an XCD\n", rows ? "rows" : "columns", heads, blocks, once, dead, least, most);
         ++bad;
       }
     }
+  }
+  return bad;
+}
+
+int main() {
+  int bad = deal(true) + deal(false);
+  // 32 rows: four neighbours to every XCD (one below that, and 32 columns, are dealt in turn)
+  for (int wg = 0; wg < 2 * 32; ++wg) {
+    const HeadBlock hb = xcd_map_rows(wg, 32, 4);
+    if (hb.blk / 4 != ((wg & 7) + 3 * hb.bh) % 8) ++bad;
+    if (xcd_map(wg, 32, 4, SHORT_COLUMNS).blk != (wg % 32 + 3 * (wg / 32)) % 32) ++bad;
   }
   std::printf(bad ? "FAILED %d\n" : "every block once\n", bad);
   return bad ? 1 : 0;
