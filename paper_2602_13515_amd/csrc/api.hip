@@ -305,6 +305,30 @@ int spa2_vd_loss_grad(const void* u_sparse, const void* u_full, int64_t n, int32
   return launch_vd_grad(u_sparse, u_full, n, dtype == SPA2_DTYPE_BF16, weight, upstream, grad, (hipStream_t)stream) ==
                  hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
 }
+
+// 2 * weight is a factor of every element of such a gradient
+static bool vd_factor_ok(double weight) { return isnormal((float)(2.0 * weight)); }
+
+int spa2_vd_loss_and_grad(const void* u_sparse, const void* u_full, int64_t n, double weight, double* loss, void* grad,
+                          void* workspace, size_t workspace_bytes, void* stream) {
+  int rc = check_vd(u_sparse, u_full, n, SPA2_DTYPE_F32, weight);
+  if (rc != SPA2_OK) return rc;
+  if (!loss || !grad) return SPA2_ERR_NULL;
+  if (!aligned16(grad)) return SPA2_ERR_ALIGN;
+  if (!vd_factor_ok(weight)) return SPA2_ERR_RANGE;
+  if (!workspace || workspace_bytes < vd_ws_bytes()) return SPA2_ERR_WORKSPACE;
+  if (!aligned16(workspace)) return SPA2_ERR_ALIGN;
+  return launch_vd_loss_grad((const float*)u_sparse, (const float*)u_full, n, weight, loss, (float*)grad, workspace,
+                             (hipStream_t)stream) == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+}
+
+int spa2_vd_rescale(void* grad, int64_t n, double weight, const double* upstream, void* stream) {
+  int rc = check_vd(grad, grad, n, SPA2_DTYPE_F32, weight);
+  if (rc != SPA2_OK) return rc;
+  if (!upstream) return SPA2_ERR_NULL;
+  if (!vd_factor_ok(weight)) return SPA2_ERR_RANGE;
+  return launch_vd_rescale((float*)grad, n, weight, upstream, (hipStream_t)stream) == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+}
 }  // extern "C"
 
 // ---------------------------------------------------------------- spa2_bwd without a workspace argument

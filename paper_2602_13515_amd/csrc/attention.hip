@@ -14,10 +14,7 @@ SplitPlan fwd_section(const Dims& m, void* ws, size_t bytes) {
 size_t fwd_bytes(const Dims& m) {
   return round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m)));
 }
-size_t pool_offset(const Dims& m) {
-  char base[1];
-  return (size_t)((char*)fwd_section(m, base, fwd_bytes(m)).pool - base);
-}
+size_t pool_offset(const Dims& m) { return split_pool_offset((int64_t)m.B * m.H * m.Tm, m.Tn); }
 }  // namespace
 
 extern "C" {
@@ -40,7 +37,7 @@ int spa2_mask_fwd(const void* q, const void* k, const void* v, const spa2_shape*
   if (!workspace || workspace_bytes < spa2_mask_fwd_workspace_bytes(shape)) return SPA2_ERR_WORKSPACE;
   if (!aligned16(workspace)) return SPA2_ERR_ALIGN;
   const int64_t units = (int64_t)m.B * m.H * m.Tm;
-  const SplitPlan plan = with_fixed_parts(fwd_section(m, workspace, fwd_bytes(m)), units, m.Tn, SPLIT_FWD);
+  const SplitPlan plan = with_fixed_parts(fwd_section(m, workspace, fwd_bytes(m)), units, m.Tn);
   char* means = (char*)workspace + pool_offset(m);
   const MaskWs w = mask_ws(m);
   if (launch_pool_zero(q, k, m, (float*)(means + w.qbar), (float*)(means + w.kbar), plan.arrive,

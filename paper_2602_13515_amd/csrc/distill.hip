@@ -5,8 +5,6 @@
 // 1 write for the gradient), 16 bytes per lane and request.  The difference is taken in fp32, squared and summed
 // in fp64; partial sums go workgroup by workgroup to the workspace and are added in a fixed order, so the loss is
 // deterministic.
-#include <math.h>
-
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
@@ -201,40 +199,21 @@ hipError_t launch_vd_grad(const void* us, const void* uf, int64_t n, bool bf16, 
   return hipGetLastError();
 }
 
-}  // namespace spa2
-
-using namespace spa2;
-
-extern "C" {
-
-int spa2_vd_loss_and_grad(const void* us, const void* uf, int64_t n, double weight, double* loss, void* grad,
-                          void* workspace, size_t workspace_bytes, void* stream) {
-  if (!us || !uf || !loss || !grad) return SPA2_ERR_NULL;
-  if (n <= 0) return SPA2_ERR_SHAPE;
-  if (((uintptr_t)us | (uintptr_t)uf | (uintptr_t)grad) & 15u) return SPA2_ERR_ALIGN;
-  const float coef = (float)(2.0 * weight);
-  if (!(weight > 0.0) || !isfinite(weight) || !isnormal(coef)) return SPA2_ERR_RANGE;
-  if (!workspace || workspace_bytes < vd_ws_bytes()) return SPA2_ERR_WORKSPACE;
-  if ((uintptr_t)workspace & 15u) return SPA2_ERR_ALIGN;
+hipError_t launch_vd_loss_grad(const float* us, const float* uf, int64_t n, double weight, double* loss, float* grad, void* ws,
+                               hipStream_t stream) {
   const unsigned grid = vd_grid(n, false);
   const auto kernel = 12 * n > VD_CACHE_BYTES ? vd_loss_grad_kernel<true> : vd_loss_grad_kernel<false>;
-  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, (hipStream_t)stream, (const float*)us, (const float*)uf, n, coef,
-                     (float*)grad, (double*)workspace);
-  if (hipGetLastError() != hipSuccess) return SPA2_ERR_LAUNCH;
-  hipLaunchKernelGGL(vd_loss_finish, dim3(1), dim3(256), 0, (hipStream_t)stream, (const double*)workspace, (int)grid, weight,
-                     loss);
-  return hipGetLastError() == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+  hipLaunchKernelGGL(kernel, dim3(grid), dim3(256), 0, stream, us, uf, n, (float)(2.0 * weight), grad, (double*)ws);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(vd_loss_finish, dim3(1), dim3(256), 0, stream, (const double*)ws, (int)grid, weight, loss);
+  return hipGetLastError();
 }
 
-int spa2_vd_rescale(void* grad, int64_t n, double weight, const double* upstream, void* stream) {
-  if (!grad || !upstream) return SPA2_ERR_NULL;
-  if (n <= 0) return SPA2_ERR_SHAPE;
-  if ((uintptr_t)grad & 15u) return SPA2_ERR_ALIGN;
-  const float coef = (float)(2.0 * weight);
-  if (!(weight > 0.0) || !isfinite(weight) || !isnormal(coef)) return SPA2_ERR_RANGE;
-  hipLaunchKernelGGL(vd_rescale_kernel, dim3(vd_grid(n, false)), dim3(256), 0, (hipStream_t)stream, (float*)grad, n,
-                     2.0 * weight / (double)coef, upstream);
-  return hipGetLastError() == hipSuccess ? SPA2_OK : SPA2_ERR_LAUNCH;
+hipError_t launch_vd_rescale(float* grad, int64_t n, double weight, const double* upstream, hipStream_t stream) {
+  hipLaunchKernelGGL(vd_rescale_kernel, dim3(vd_grid(n, false)), dim3(256), 0, stream, grad, n,
+                     2.0 * weight / (double)(float)(2.0 * weight), upstream);
+  return hipGetLastError();
 }
 
-}  // extern "C"
+}  // namespace spa2

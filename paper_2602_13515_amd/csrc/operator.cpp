@@ -13,6 +13,7 @@
 #include <torch/extension.h>
 
 #include "spa2.h"
+#include "spa2_internal.h"
 
 namespace {
 
@@ -83,14 +84,13 @@ spa2_shape shape_of(const Tensor& q) {
 // The pattern's arrays in one buffer.  Column lists and launch order only where a backward pass will read them; the
 // order only where the key blocks do not all run at once (two workgroups a compute unit): without it a launch takes them
 // in the order of the sequence.
-constexpr int64_t RESIDENT = 512;
 struct PatternLayout {
   int64_t off[6] = {0, 0, 0, 0, 0, 0}, total = 0;
   bool columns, order;
   PatternLayout(const spa2_shape& s, bool cols) : columns(cols) {
     const int64_t bh = (int64_t)s.B * s.H;
     const int64_t tm = ((int64_t)s.N + SPA2_BQ - 1) / SPA2_BQ, tn = ((int64_t)s.N + SPA2_BKV - 1) / SPA2_BKV;
-    order = cols && bh * tn > RESIDENT;
+    order = cols && bh * tn > spa2::RESIDENT_WGS;
     const int64_t size[6] = {bh * tm * tn, 4 * bh * tm, 4 * bh * tm * tn, cols ? 4 * bh * tn : 0,
                              cols ? 4 * bh * tn * tm : 0, order ? 4 * bh * tn : 0};
     for (int x = 0; x < 6; ++x) { off[x] = total; total += (size[x] + 255) & ~(int64_t)255; }

@@ -26,7 +26,9 @@ inline Dims make_dims(const spa2_shape& s) {
 // workspace; pool_slots == 0 means "no splitting" and every other member is then null.
 constexpr int SPLIT_POOL_MAX = 2048;         // partial-result slots of one launch at most
 constexpr int QUEUE_STRIDE = 64;             // ints between the counters of two XCDs (atomics on one line stand in a row)
-constexpr int QUEUE_WGS = 512;               // workgroups of a queue launch: two per compute unit
+// Workgroups that run at a time, two per compute unit (fwd_kernel<64>, whose registers and LDS would let three, is cut and
+// ordered for two as well): those of a queue launch, and what the split plan cuts for.
+constexpr int RESIDENT_WGS = 512;
 struct SplitPlan {
   const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection)
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
@@ -45,18 +47,19 @@ struct SplitPlan {
 // queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
 // 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.
 inline SplitPlan with_queue(SplitPlan p, int64_t units) {
-  if (p.pool_slots && units > 4 * QUEUE_WGS) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
+  if (p.pool_slots && units > 4 * RESIDENT_WGS) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
   return p;
 }
 size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes);
+size_t split_pool_offset(int64_t units, int list_max);       // where the slots of a full workspace begin
 SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes);
 // Plan of the launch of kernel `kind`, which walks `units` lists of at most list_max entries.
 enum SplitKind { SPLIT_FWD, SPLIT_DQ, SPLIT_DKDV };
 hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p,
                              hipStream_t stream);
-// The same parts without a plan, where the sizes alone say that the plan would cut into pieces of its least length (and the
+// The forward kernel's parts without a plan, where the sizes alone say that the plan would cut into pieces of its least length (and the
 // slots suffice): p with fixed_len set.  The caller zeroes p.arrive before the launch.
-SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max, SplitKind kind);
+SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max);
 // D = rowsum(dO * O) and the plans of the two backward kernels in one launch (split.hip).
 hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
                               const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
@@ -99,5 +102,8 @@ hipError_t launch_vd_loss(const void* u_sparse, const void* u_full, int64_t n, b
                           void* ws, hipStream_t stream);
 hipError_t launch_vd_grad(const void* u_sparse, const void* u_full, int64_t n, bool bf16, double weight,
                           const double* upstream, void* grad, hipStream_t stream);
+hipError_t launch_vd_loss_grad(const float* u_sparse, const float* u_full, int64_t n, double weight, double* loss, float* grad,
+                               void* ws, hipStream_t stream);
+hipError_t launch_vd_rescale(float* grad, int64_t n, double weight, const double* upstream, hipStream_t stream);
 
 }  // namespace spa2

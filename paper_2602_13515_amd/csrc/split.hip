@@ -11,7 +11,7 @@
 // The plan is computed on the device from the list lengths (the host never reads the pattern):
 //   T = total number of list entries of the launch,
 //   S = max(min(max(T / 512, lo), mid), min(T / 2048, 48), T / 8192)   (quotients rounded up),
-// with 512 the number of workgroups that run at a time (two per compute unit).  Small launches are cut until the slots
+// with 512 (RESIDENT_WGS) the number of workgroups that run at a time.  Small launches are cut until the slots
 // are filled, down to lo entries, below which a part is mostly prologue and merge; ordinary ones into quarters of the
 // mean work of a slot, but not below mid (parts of 8 instead of 16 cost more than they balance) nor above 48; on the
 // largest only lists of more than a sixteenth of a slot's mean work are cut, which the natural launch order would
@@ -62,6 +62,8 @@ size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes) {
   return tables_bytes(units, pool) + (size_t)pool * slot_bytes;
 }
 
+size_t split_pool_offset(int64_t units, int list_max) { return tables_bytes(units, pool_wanted(units, list_max)); }
+
 SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes) {
   SplitPlan p;
   p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
@@ -84,11 +86,11 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
 }
 
 // T <= units * list_max: where that is within 512 lo, S is lo (see above) whatever the lists are.
-SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max, SplitKind kind) {
+SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max) {
   int lo, mid;
-  split_range(kind, units, lo, mid);
+  split_range(SPLIT_FWD, units, lo, mid);
   const int parts = (list_max + lo - 1) / lo;
-  if (p.pool_slots && units * list_max <= 512 * (int64_t)lo && units * parts <= p.pool_slots) {
+  if (p.pool_slots && units * list_max <= (int64_t)RESIDENT_WGS * lo && units * parts <= p.pool_slots) {
     p.fixed_len = lo; p.fixed_parts = parts; p.planned = true;
   }
   return p;
@@ -175,7 +177,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a) {
   unsigned long long mine = 0;
   each_quad([&](int, const i32x4& c) { mine += (unsigned long long)c[0] + c[1] + c[2] + c[3]; });
   const long long T = (long long)block_sum<NT>(mine, red);
-  const long long s_small = min(max((T + 511) / 512, (long long)a.lo), (long long)a.mid);
+  const long long s_small = min(max((T + RESIDENT_WGS - 1) / RESIDENT_WGS, (long long)a.lo), (long long)a.mid);
   const long long s_large = max(min((T + 2047) / 2048, (long long)SPLIT_CAP), (T + 8191) / 8192);
   int S = (int)max(min(max(s_small, s_large), (long long)a.list_max), 1ll);
   float inv_s;
@@ -239,7 +241,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a) {
     a.arrive[g] = 0;
   }
   if (t == 0) { a.header[0] = n; a.header[1] = S; }
-  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = QUEUE_WGS / 8;      // (the first ones go by workgroup number)
+  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = RESIDENT_WGS / 8;      // (the first ones go by workgroup number)
 }
 
 template <int NT>

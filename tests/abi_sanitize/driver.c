@@ -93,6 +93,61 @@ int main(void) {
   EXPECT(spa2_vd_loss(fake, fake, 8, SPA2_DTYPE_F32, 1.0, (double*)fake, fake, 64, 0), SPA2_ERR_WORKSPACE);
   EXPECT(spa2_vd_loss_grad(fake, fake, 8, SPA2_DTYPE_F32, 1.0, 0, 0, 0), SPA2_ERR_NULL);
 
+  EXPECT(spa2_vd_loss_and_grad(0, fake, 8, 1.0, (double*)fake, fake, fake, big, 0), SPA2_ERR_NULL);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, 0, fake, fake, big, 0), SPA2_ERR_NULL);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, (double*)fake, 0, fake, big, 0), SPA2_ERR_NULL);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 0, 1.0, (double*)fake, fake, fake, big, 0), SPA2_ERR_SHAPE);
+  EXPECT(spa2_vd_loss_and_grad(fake, odd, 8, 1.0, (double*)fake, fake, fake, big, 0), SPA2_ERR_ALIGN);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, (double*)fake, odd, fake, big, 0), SPA2_ERR_ALIGN);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, (double*)fake, fake, odd, big, 0), SPA2_ERR_ALIGN);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, -1.0, (double*)fake, fake, fake, big, 0), SPA2_ERR_RANGE);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, NAN, (double*)fake, fake, fake, big, 0), SPA2_ERR_RANGE);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 5e-39, (double*)fake, fake, fake, big, 0), SPA2_ERR_RANGE);  /* 2w is subnormal */
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1e300, (double*)fake, fake, fake, big, 0), SPA2_ERR_RANGE);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, (double*)fake, fake, 0, big, 0), SPA2_ERR_WORKSPACE);
+  EXPECT(spa2_vd_loss_and_grad(fake, fake, 8, 1.0, (double*)fake, fake, fake, spa2_vd_loss_workspace_bytes() - 1, 0),
+         SPA2_ERR_WORKSPACE);
+  EXPECT(spa2_vd_rescale(0, 8, 1.0, (double*)fake, 0), SPA2_ERR_NULL);
+  EXPECT(spa2_vd_rescale(fake, 8, 1.0, 0, 0), SPA2_ERR_NULL);
+  EXPECT(spa2_vd_rescale(fake, -1, 1.0, (double*)fake, 0), SPA2_ERR_SHAPE);
+  EXPECT(spa2_vd_rescale(odd, 8, 1.0, (double*)fake, 0), SPA2_ERR_ALIGN);
+  EXPECT(spa2_vd_rescale(fake, 8, 0.0, (double*)fake, 0), SPA2_ERR_RANGE);
+  EXPECT(spa2_vd_rescale(fake, 8, 5e-39, (double*)fake, 0), SPA2_ERR_RANGE);
+
+  /* pattern and forward pass in one call: what either refuses, and a workspace that is a byte short, on either side of the
+     sizes that need no plan */
+#define MASK_FWD(q, k, v, s, topk, p, sc, pat, o, ores, lse, ws, n) \
+  spa2_mask_fwd(q, k, v, s, topk, p, sc, pat, o, ores, (float*)(lse), ws, n, 0)
+  {
+    const spa2_shape plan = shape(1, 17, 2048, 64, 128, 64, 0);
+    const spa2_shape* sizes[2] = {&ok, &plan};
+    for (int x = 0; x < 2; ++x) {
+      const size_t need = spa2_mask_fwd_workspace_bytes(sizes[x]);
+      if (need < spa2_fwd_workspace_bytes(sizes[x]) || need < spa2_mask_workspace_bytes(sizes[x])) { printf("mask_fwd size\n"); ++failures; }
+      EXPECT(MASK_FWD(fake, fake, fake, sizes[x], 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, need - 1), SPA2_ERR_WORKSPACE);
+    }
+    if (spa2_mask_fwd_workspace_bytes(0) != 0 || spa2_mask_fwd_workspace_bytes(&d96) != 0) { printf("mask_fwd size\n"); ++failures; }
+  }
+  EXPECT(MASK_FWD(fake, fake, fake, 0, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(0, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(fake, fake, 0, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, 0, fake, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &half, fake, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &full, 0, 0, fake, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, 0, 0, fake, big), SPA2_ERR_NULL);
+  EXPECT(MASK_FWD(odd, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_ALIGN);
+  EXPECT(MASK_FWD(fake, fake, odd, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_ALIGN);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, odd, fake, fake, big), SPA2_ERR_ALIGN);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, odd, big), SPA2_ERR_ALIGN);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.1f, &full, fake, 0, fake, 0, big), SPA2_ERR_WORKSPACE);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 6, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_RANGE);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 0, 0.0f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_RANGE);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, NAN, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_RANGE);
+  EXPECT(MASK_FWD(fake, fake, fake, &ok, 1, 0.5f, 0.0f, &full, fake, 0, fake, fake, big), SPA2_ERR_RANGE);
+  EXPECT(MASK_FWD(fake, fake, fake, &d96, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_UNSUPPORTED);
+  EXPECT(MASK_FWD(fake, fake, fake, &longrow, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_SHAPE);
+  EXPECT(MASK_FWD(fake, fake, fake, &huge, 1, 0.5f, 0.1f, &full, fake, 0, fake, fake, big), SPA2_ERR_SHAPE);
+
   /* host helpers and size queries over their whole argument range */
   if (spa2_topk_blocks(0.2, 10) != 2 || spa2_topk_blocks(0.0, 10) != 0 || spa2_topk_blocks(5.0, 10) != 10 ||
       spa2_topk_blocks(NAN, 10) != 0 || spa2_topk_blocks(0.5, -3) != 0 || spa2_topk_blocks(1e300, 0x7fffffff) != 0x7fffffff) {

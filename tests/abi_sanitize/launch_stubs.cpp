@@ -11,6 +11,9 @@ namespace spa2 {
   std::abort();
 }
 hipError_t launch_pool(const void*, const void*, const Dims&, float*, float*, hipStream_t) { reached("launch_pool"); }
+hipError_t launch_pool_zero(const void*, const void*, const Dims&, float*, float*, int32_t*, int, hipStream_t) {
+  reached("launch_pool_zero");
+}
 hipError_t launch_select(const float*, const float*, const Dims&, int, float, float, uint8_t*, int32_t*, int32_t*, float*,
                          hipStream_t) { reached("launch_select"); }
 hipError_t launch_columns(const uint8_t*, const Dims&, int32_t*, int32_t*, int32_t*, hipStream_t) { reached("launch_columns"); }
@@ -37,6 +40,10 @@ hipError_t launch_error_terms(const void*, const void*, const float*, const floa
 }
 size_t vd_ws_bytes() { return 2048 * 8; }
 hipError_t launch_vd_loss(const void*, const void*, int64_t, bool, double, double*, void*, hipStream_t) { reached("launch_vd_loss"); }
+hipError_t launch_vd_loss_grad(const float*, const float*, int64_t, double, double*, float*, void*, hipStream_t) {
+  reached("launch_vd_loss_grad");
+}
+hipError_t launch_vd_rescale(float*, int64_t, double, const double*, hipStream_t) { reached("launch_vd_rescale"); }
 hipError_t launch_vd_grad(const void*, const void*, int64_t, bool, double, const double*, void*, hipStream_t) {
   reached("launch_vd_grad");
 }

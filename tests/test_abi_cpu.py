@@ -210,7 +210,7 @@ def test_header_is_plain_c():
 
 
 def test_argument_checks_under_host_sanitizers():
-    """The argument-check layer (csrc/api.hip) compiled with AddressSanitizer and UndefinedBehaviorSanitizer on the
+    """The argument-check layer (csrc/api.hip, csrc/attention.hip) compiled with AddressSanitizer and UndefinedBehaviorSanitizer on the
     host side, linked against launcher stubs that abort, and driven by tests/abi_sanitize/driver.c with every kind
     of rejected call: no sanitizer report, no launcher reached, every error code as documented."""
     import shutil
@@ -233,8 +233,9 @@ def test_argument_checks_under_host_sanitizers():
             [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "api.hip"), "-o", o("api.o")],
             [hipcc, *dev, *xsan, *inc, "-x", "hip", "-c", os.path.join(here, "launch_stubs.cpp"), "-o", o("stubs.o")],
         [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "split.hip"), "-o", o("split.o")],
+            [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "attention.hip"), "-o", o("attention.o")],
             [hipcc, "--offload-arch=gfx950", "-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize",
-             o("api.o"), o("stubs.o"), o("split.o"), o("driver.o"), "-o", o("abi_check")],
+             o("api.o"), o("stubs.o"), o("split.o"), o("attention.o"), o("driver.o"), "-o", o("abi_check")],
         ]
         for cmd in steps:
             r = subprocess.run(cmd, capture_output=True, text=True)
