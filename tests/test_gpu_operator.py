@@ -1,4 +1,6 @@
 """The operators' native route (plain CUDA tensors) against the Python autograd functions behind the other calls."""
+import ctypes
+
 import pytest
 import torch
 
@@ -7,7 +9,7 @@ from paper_2602_13515_amd import autograd
 from paper_2602_13515_amd import workloads as wl
 from paper_2602_13515_amd.distill import _VelocityDistillationLoss, velocity_distillation_loss
 
-from gpu_util import dev
+from gpu_util import Guarded, dev, gpu_fwd, gpu_mask, guarded_pattern
 
 pytestmark = pytest.mark.gpu
 
@@ -183,3 +185,114 @@ def test_native_backward_refuses_saved_tensors_of_another_place_or_kind(change, 
     # (an upstream gradient of other strides is copied to those of q, wherever q is)
     with pytest.raises(ValueError):
         o.backward(do.transpose(1, 2).contiguous().transpose(1, 2))
+
+
+# 16 and 17 heads of 32 blocks stand on either side of the sizes that need no plan; ragged blocks; a row of one block
+@pytest.mark.parametrize("H,N,d", [(16, 2048, 64), (17, 2048, 64), (2, 1000, 128), (1, 40, 128), (5, 10090, 64)])
+@pytest.mark.parametrize("columns", [True, False])
+def test_pattern_and_forward_in_a_workspace_of_exactly_the_reported_size(H, N, d, columns):
+    """spa2_mask_fwd between guard zones against spa2_mask and spa2_fwd: same bits, nothing written outside a buffer."""
+    q, k, v, _ = _inputs(1, H, N, d, "bhnd")
+    tn = -(-N // 64)
+    topk, scale = spa2.spa2_topk_blocks(0.3, tn), d ** -0.5
+    lib, g = spa2.binding._load(), Guarded()
+    lay = spa2.binding._layout_of(q)
+    need = int(lib.spa2_mask_fwd_workspace_bytes(lay.ref))
+    pat = guarded_pattern(g, 1, H, N, dev(), columns)
+    new = lambda: g.alloc(q.shape, q.dtype, dev(), float("nan"))
+    o, o_res, lse = new(), new(), g.alloc((1, H, N), torch.float32, dev(), float("nan"))
+    ws = g.alloc((need,), torch.uint8, dev(), 0xA5)
+    c = pat._c()
+    call = lambda nbytes: lib.spa2_mask_fwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), lay.ref, topk, 0.6, scale, ctypes.byref(c),
+                                            o.data_ptr(), o_res.data_ptr(), lse.data_ptr(), ws.data_ptr(), nbytes,
+                                            spa2.binding._stream(q))
+    assert call(need - 1) == -6 and call(need) == 0
+    torch.cuda.synchronize()
+    g.check("spa2_mask_fwd")
+    ref, _ = gpu_mask(q, k, topk, 0.6, scale, want_pbar=False, columns=columns)
+    assert torch.equal(pat.mask, ref.mask) and torch.equal(pat.row_cnt, ref.row_cnt)
+    for a, b in zip((o, lse, o_res), gpu_fwd(q, k, v, ref, scale, residual=True)):
+        assert torch.equal(a, b)
+    if columns:
+        assert torch.equal(pat.col_cnt, ref.col_cnt) and torch.equal(pat.col_idx, ref.col_idx)
+
+
+SAVED = ("q", "k", "v", "o", "o_res", "lse")         # in the order in which they are saved
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_native_backward_takes_saved_tensors_that_come_back_as_copies(given):
+    q, k, v, do = _inputs(1, 3, 1281, 128, "bnhd")
+    pattern = spa2.build_pattern(q, k, 0.1, 0.6) if given else None
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    want = torch.autograd.grad(spa2.sparge_attn2(*leaves, 0.1, 0.6, pattern=pattern), leaves, do)
+    packed = []
+    pack = lambda x: (packed.append(x), x.detach().cpu())[1]
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda x: x.to(dev())):
+        o = spa2.sparge_attn2(*leaves, 0.1, 0.6, pattern=pattern)
+    assert "CppNode" in o.grad_fn.name() and len(packed) == len(SAVED)
+    del packed[:]
+    for a, b in zip(torch.autograd.grad(o, leaves, do), want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("which", SAVED)
+def test_native_backward_refuses_each_saved_tensor_in_another_layout(which):
+    q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    count = []
+
+    def pack(x):
+        count.append(0)
+        return (x.detach().transpose(1, 2).contiguous().transpose(1, 2) if SAVED[len(count) - 1] == which else x.detach())
+
+    with torch.autograd.graph.saved_tensors_hooks(pack, lambda x: x):
+        o = spa2.sparge_attn2(*leaves, 0.1, 0.6)
+    assert "CppNode" in o.grad_fn.name() and len(count) == len(SAVED)
+    with pytest.raises(ValueError):
+        o.backward(do)
+
+
+@pytest.mark.parametrize("early_stop", [True, False])
+def test_native_route_under_non_reentrant_checkpoint(early_stop):
+    """The recomputation is ended by an exception that the pack hook throws through the native call."""
+    from torch.utils.checkpoint import checkpoint, set_checkpoint_early_stop
+    q, k, v, do = _inputs(1, 2, 1000, 64, "bhnd")
+    uf = torch.randn(q.shape, device=dev())
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    layer = lambda a, b, c: spa2.sparge_attn2(2 * a, b, c, 0.1, 0.6)
+    head = lambda x: velocity_distillation_loss(x.float(), uf)
+    want = torch.autograd.grad(layer(*leaves), leaves, do)
+    want_loss = torch.autograd.grad(head(layer(*leaves)), leaves)
+    with set_checkpoint_early_stop(early_stop):
+        o = checkpoint(layer, *leaves, use_reentrant=False)
+        got = torch.autograd.grad(o, leaves, do)
+        loss = checkpoint(lambda *t: head(layer(*t)), *leaves, use_reentrant=False)
+        got_loss = torch.autograd.grad(loss, leaves)
+    for a, b in zip((*got, *got_loss), (*want, *want_loss)):
+        assert torch.equal(a, b)
+
+
+def test_an_exception_of_a_pack_hook_leaves_the_native_call_as_it_is():
+    class Refused(Exception):
+        pass
+
+    def refuse(x):
+        raise Refused
+
+    q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
+    leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+    with pytest.raises(Refused), torch.autograd.graph.saved_tensors_hooks(refuse, lambda x: x):
+        spa2.sparge_attn2(*leaves, 0.1, 0.6)
+    spa2.sparge_attn2(*leaves, 0.1, 0.6).backward(do)
+    assert all(bool(t.grad.isfinite().all()) for t in leaves)
+
+
+def test_gradients_of_either_route_have_no_second_derivative(monkeypatch):
+    q, k, v, do = _inputs(1, 2, 300, 64, "bhnd")
+    for native in (True, False):
+        if not native:
+            monkeypatch.setattr(autograd, "_plain", lambda *t: False)
+        leaves = [t.detach().requires_grad_(True) for t in (q, k, v)]
+        grads = torch.autograd.grad(spa2.sparge_attn2(*leaves, 0.1, 0.6), leaves, do, create_graph=True)
+        assert not any(g.requires_grad for g in grads), native
