@@ -892,7 +892,8 @@ __global__ __launch_bounds__(64 * COL_SEGS) void columns_kernel(const uint8_t* m
 
 // Launch order of the key blocks of one head for the dK/dV kernel: longest column first (equal lengths: lower index
 // first), dealt round-robin to the eight XCD chunks of the schedule (position x*chunk + s belongs to XCD x), so that
-// every XCD gets the same mix of long and short columns and the long ones start early.
+// every XCD gets the same mix of long and short columns and the long ones start early.  (Heads of up to SHORT_COLUMNS are
+// launched position by position (xcd_map): there neighbouring positions, chunks of the order, are what mixes the lengths.)
 // A column's rank is the number of columns that precede it in that order, counted directly: a workgroup ranks 64
 // columns of a head against all of them, RANK_SEGS threads a column, the head's keys in LDS.  (T_n^2 comparisons, but
 // no chain of dependent steps: the bitonic sort of a head by one workgroup before took 11.6 us at 512 columns of 12
