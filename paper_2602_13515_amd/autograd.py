@@ -148,8 +148,8 @@ class _SpargeAttn2(torch.autograd.Function):
         lay = _b._layout_of(q)
         if q.device != ctx.device:
             raise ValueError("saved token tensors come back on their GPU")
-        if lse.device != q.device or lse.dtype != torch.float32 or lse.shape != q.shape[:3] or not lse.is_contiguous():
-            raise ValueError("the log-sum-exp comes back as a contiguous fp32 [B, H, N] tensor")
+        if lse.device != q.device or lse.dtype != torch.float32 or lse.numel() != q.shape[:3].numel() or not lse.is_contiguous():
+            raise ValueError("the log-sum-exp comes back as B * H * N contiguous fp32 numbers")
         d_o = _match(d_o.to(torch.bfloat16), q)
         _b._same_layout(q, k, v, o, o_res, d_o)
         dq, dk, dv = _like(q), _like(q), _like(q)

@@ -69,8 +69,8 @@ void check_inputs(const Tensor& q, const Tensor& k, const Tensor& v) {
 void check_saved(const Tensor& q, const Tensor& lse, int64_t gpu) {
   TORCH_CHECK_VALUE(q.is_cuda() && q.device().index() == gpu && q.scalar_type() == at::kBFloat16 && q.dim() == 4 &&
                     q.stride(3) == 1, "saved token tensors come back as bf16 [B, H, N, d] views on their GPU, d contiguous");
-  TORCH_CHECK_VALUE(lse.device() == q.device() && lse.scalar_type() == at::kFloat && lse.sizes() == q.sizes().slice(0, 3) &&
-                    lse.is_contiguous(), "the log-sum-exp comes back as a contiguous fp32 [B, H, N] tensor");
+  TORCH_CHECK_VALUE(lse.device() == q.device() && lse.scalar_type() == at::kFloat && lse.is_contiguous() &&
+                    lse.numel() == q.size(0) * q.size(1) * q.size(2), "the log-sum-exp comes back as B * H * N contiguous fp32 numbers");
 }
 
 spa2_shape shape_of(const Tensor& q) {

@@ -228,7 +228,8 @@ def test_native_backward_takes_saved_tensors_that_come_back_as_copies(given):
     want = torch.autograd.grad(spa2.sparge_attn2(*leaves, 0.1, 0.6, pattern=pattern), leaves, do)
     packed = []
     pack = lambda x: (packed.append(x), x.detach().cpu())[1]
-    with torch.autograd.graph.saved_tensors_hooks(pack, lambda x: x.to(dev())):
+    unpack = lambda x: (x if x.dim() == 4 else x.flatten()).to(dev())          # (of the log-sum-exp only the numbers count)
+    with torch.autograd.graph.saved_tensors_hooks(pack, unpack):
         o = spa2.sparge_attn2(*leaves, 0.1, 0.6, pattern=pattern)
     assert "CppNode" in o.grad_fn.name() and len(packed) == len(SAVED)
     del packed[:]
