@@ -48,18 +48,18 @@ size_t dq_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dq_slot_float
 // dQ = acc * scale -> bf16; a lane owns one query row, accumulator register v of block mb is channel
 // 32 mb + 8 (v / 4) + 4 hf + v % 4.
 template <int D>
-__device__ __forceinline__ void dq_store_rows(const DqArgs& a, int64_t base, int qrow, int hf, const f32x16 (&acc)[D / 32]) {
-  if (qrow < a.N) {
-    uint16_t* op = a.dq + base + (int64_t)qrow * a.sn + 4 * hf;
+__device__ __forceinline__ void dq_store_rows(const DqArgs& a, int64_t base, int q0, int lane, uint32_t area,
+                                              const f32x16 (&acc)[D / 32]) {
+  __syncthreads();          // (other waves may still be reading what lies in `area`)
 #pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
+  for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        u32x2 pk = {pack_bf16(acc[mb][4 * g + 0] * a.scale, acc[mb][4 * g + 1] * a.scale),
-                    pack_bf16(acc[mb][4 * g + 2] * a.scale, acc[mb][4 * g + 3] * a.scale)};
-        *(u32x2*)(op + 32 * mb + 8 * g) = pk;
-      }
-  }
+    for (int g = 0; g < 4; ++g) {
+      u32x2 pk = {pack_bf16(acc[mb][4 * g + 0] * a.scale, acc[mb][4 * g + 1] * a.scale),
+                  pack_bf16(acc[mb][4 * g + 2] * a.scale, acc[mb][4 * g + 3] * a.scale)};
+      row_piece_put<D>(area, lane & 31, 4 * mb + g, lane >> 5, pk);
+    }
+  rows_store<D>(area, a.dq + base + (int64_t)q0 * a.sn, a.sn, min(32, a.N - q0), lane);
 }
 
 // Transposed formulation, a lane owns one query row (see fwd.hip):
@@ -306,7 +306,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
       }
     }
   }
-  dq_store_rows<D>(a, base, qrow, hf, acc);
+  dq_store_rows<D>(a, base, i * BQ + 32 * w, lane, sm + w * (32 * D * 2), acc);
 }
 
 hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,

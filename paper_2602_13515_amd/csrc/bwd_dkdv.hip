@@ -326,7 +326,7 @@ __device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item
   constexpr int REGION = 2 * NMB * 4 * 64 * 4;        // floats per wave
   static_assert(REGION * 4 == 2 * STAGE_B, "the sums that a wave hands over fill exactly its two stages");
   float* scratch = (float*)smem;
-  const int le = fresh_lane(), he = le >> 5, key = j * BKV + 32 * w + (le & 31);
+  const int le = fresh_lane(), he = le >> 5, key0w = j * BKV + 32 * w;        // first of the keys that this wave finishes
   auto hand_over = [&](auto KH) {
     f32x4* out = (f32x4*)(scratch + w * REGION) + le;
     static_for<0, 8 * NMB>([&](auto C) {
@@ -359,22 +359,28 @@ __device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item
     if (w == 0) finish(Int<0>{}, put);
     else        finish(Int<1>{}, put);
   } else {
-    if (key >= N) return;
-    const int64_t out_off = base + (int64_t)key * a.sn + 4 * he;
+    u32x2 done[8 * NMB];
     auto put = [&](int t, int mb, int g, f32x4 x) {
       const float sc = t == 0 ? -a.scale : 1.f;
-      const u32x2 pk2 = {pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
-      *(u32x2*)((t == 0 ? a.dk : a.dv) + out_off + 32 * mb + 8 * g) = pk2;
+      done[(t * NMB + mb) * 4 + g] = u32x2{pack_bf16(x[0] * sc, x[1] * sc), pack_bf16(x[2] * sc, x[3] * sc)};
     };
     if (w == 0) finish(Int<0>{}, put);
     else        finish(Int<1>{}, put);
+    // (the sums that this wave has just read are what the other one handed over: their place is free)
+    const uint32_t area = lds_addr_of(scratch + (1 - w) * REGION);
+    static_for<0, 8 * NMB>([&](auto C) {
+      constexpr int c = decltype(C)::v;
+      row_piece_put<D>(area + (c / (4 * NMB)) * (32 * D * 2), le & 31, c % (4 * NMB), he, done[c]);
+    });
+    rows_store<D>(area, a.dk + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
+    rows_store<D>(area + 32 * D * 2, a.dv + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
     return;
   }
   // the last part of a split column to arrive adds all of them in part order
   {
     const int64_t first = item.slot - part;
-    if (!last_part(a.sp.arrive + first, parts, (int*)stat_s) || key >= N) return;
-    const int64_t out_off = base + (int64_t)key * a.sn + 4 * he;
+    if (!last_part(a.sp.arrive + first, parts, (int*)stat_s)) return;
+    const uint32_t area = lds_addr_of(scratch + w * REGION);
     const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * le;
 #pragma unroll
     for (int round = 0; round < 2; ++round) {
@@ -391,15 +397,14 @@ __device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item
       }
       const float sc = round == 0 ? -a.scale : 1.f;
 #pragma unroll
-      for (int mb = 0; mb < NMB; ++mb) {
-        uint16_t* out = (round == 0 ? a.dk : a.dv) + out_off + 32 * mb;
+      for (int mb = 0; mb < NMB; ++mb)
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
           const f32x2 lo = x[mb * 8 + 2 * g], hi = x[mb * 8 + 2 * g + 1];
           u32x2 pk2 = {pack_bf16(lo[0] * sc, lo[1] * sc), pack_bf16(hi[0] * sc, hi[1] * sc)};
-          *(u32x2*)(out + 8 * g) = pk2;
+          row_piece_put<D>(area, le & 31, 4 * mb + g, he, pk2);
         }
-      }
+      rows_store<D>(area, (round == 0 ? a.dk : a.dv) + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
     }
   }
 }

@@ -33,33 +33,37 @@ struct FwdArgs {
 template <int D> constexpr int fwd_slot_floats() { return 256 * (D / 2) + 512; }
 size_t fwd_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? fwd_slot_floats<128>() : fwd_slot_floats<64>()) * 4; }
 
-// O_i = diag(l)^-1 O (Alg. 1 step 18) -> bf16 (+ optional residual), LSE = m ln 2 + log l.
+// O_i = diag(l)^-1 O (Alg. 1 step 18) -> bf16 (+ optional residual), LSE = m ln 2 + log l.  q0: first row of the wave;
+// area: LDS of the wave's own for both outputs, which the other waves may still be reading.
 template <int D>
-__device__ __forceinline__ void fwd_store_rows(const FwdArgs& a, int bh, int64_t base, int qrow, int hf,
+__device__ __forceinline__ void fwd_store_rows(const FwdArgs& a, int bh, int64_t base, int q0, int lane, uint32_t area,
                                                const f32x16 (&oacc)[D / 32], float m_run, float l_tot) {
   const float inv = 1.f / l_tot;
-  if (qrow < a.N) {
-    uint16_t* op = a.o + base + (int64_t)qrow * a.sn + 4 * hf;
+  const int r32 = lane & 31, hf = lane >> 5, valid = min(32, a.N - q0);
+  constexpr int RES = 32 * D * 2;
+  __syncthreads();
 #pragma unroll
-    for (int mb = 0; mb < D / 32; ++mb)
+  for (int mb = 0; mb < D / 32; ++mb)
 #pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        float x[4];
+    for (int g = 0; g < 4; ++g) {
+      float x[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) x[e] = oacc[mb][4 * g + e] * inv;
-        const u32x2 pk2 = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
-        *(u32x2*)(op + 32 * mb + 8 * g) = pk2;
-        if (a.o_res) {      // what the rounding to bf16 dropped, itself rounded to bf16
-          const float r0 = x[0] - __builtin_bit_cast(float, pk2[0] << 16);
-          const float r1 = x[1] - __builtin_bit_cast(float, pk2[0] & 0xffff0000u);
-          const float r2 = x[2] - __builtin_bit_cast(float, pk2[1] << 16);
-          const float r3 = x[3] - __builtin_bit_cast(float, pk2[1] & 0xffff0000u);
-          const u32x2 pr = {pack_bf16(r0, r1), pack_bf16(r2, r3)};
-          *(u32x2*)(a.o_res + (op - a.o) + 32 * mb + 8 * g) = pr;
-        }
+      for (int e = 0; e < 4; ++e) x[e] = oacc[mb][4 * g + e] * inv;
+      const u32x2 pk2 = {pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3])};
+      row_piece_put<D>(area, r32, 4 * mb + g, hf, pk2);
+      if (a.o_res) {      // what the rounding to bf16 dropped, itself rounded to bf16
+        const float r0 = x[0] - __builtin_bit_cast(float, pk2[0] << 16);
+        const float r1 = x[1] - __builtin_bit_cast(float, pk2[0] & 0xffff0000u);
+        const float r2 = x[2] - __builtin_bit_cast(float, pk2[1] << 16);
+        const float r3 = x[3] - __builtin_bit_cast(float, pk2[1] & 0xffff0000u);
+        const u32x2 pr = {pack_bf16(r0, r1), pack_bf16(r2, r3)};
+        row_piece_put<D>(area + RES, r32, 4 * mb + g, hf, pr);
       }
-    if (hf == 0) a.lse[(int64_t)bh * a.N + qrow] = m_run * LN2 + __logf(l_tot);
-  }
+    }
+  const int64_t off = base + (int64_t)q0 * a.sn;
+  rows_store<D>(area, a.o + off, a.sn, valid, lane);
+  if (a.o_res) rows_store<D>(area + RES, a.o_res + off, a.sn, valid, lane);
+  if (hf == 0 && r32 < valid) a.lse[(int64_t)bh * a.N + q0 + r32] = m_run * LN2 + __logf(l_tot);
 }
 
 template <int D>
@@ -402,6 +406,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   last_step(sA, t);
 
   const float l_tot = sum_halves(l_run);
+  constexpr int OUT_B = 2 * 32 * D * 2;      // a wave's rows of O and of the residual, on their way out
+  static_assert(4 * OUT_B <= 5 * TILE_B, "the outputs of four waves fit the tiles' LDS");
   if (parts) {                // one part of a split row
     const int64_t first = slot - part;
     float* ps = a.sp.pool + (first + part) * a.sp.slot_floats;
@@ -439,11 +445,11 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
         oacc[c / 8][2 * (c % 8) + 1] = fmaf(x[c][1], sc, oacc[c / 8][2 * (c % 8) + 1]);
       }
     }
-    fwd_store_rows<D>(a, bh, base, qrow, hf, oacc, m, l);
+    fwd_store_rows<D>(a, bh, base, i * BQ + 32 * w, lane, sm + w * OUT_B, oacc, m, l);
     return;
   }
   // O_i = diag(l)^-1 O (step 18) and the log-sum-exp the backward pass needs
-  fwd_store_rows<D>(a, bh, base, qrow, hf, oacc, m_run, l_tot);
+  fwd_store_rows<D>(a, bh, base, i * BQ + 32 * w, lane, sm + w * OUT_B, oacc, m_run, l_tot);
 }
 
 hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m, const int32_t* row_cnt,
