@@ -184,6 +184,15 @@ int spa2_bwd(const void* q, const void* k, const void* v, const void* o, const v
              const void* d_o, const float* lse, const spa2_shape* shape, const spa2_pattern* pattern,
              float scale, void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes, void* stream);
 
+/* The same without the pattern's column lists: they are made on the way, from pattern->mask, in launches that the backward
+ * pass needs anyway (pattern->col_* are neither read nor written).  For patterns that serve one forward and one backward
+ * pass; nothing but mask and row_* has to be kept between the two.  Results are those of spa2_mask_columns and spa2_bwd.
+ *   workspace: spa2_bwd_rows_workspace_bytes(shape) bytes, all of them (else SPA2_ERR_WORKSPACE). */
+size_t spa2_bwd_rows_workspace_bytes(const spa2_shape* shape);
+int spa2_bwd_rows(const void* q, const void* k, const void* v, const void* o, const void* o_res /* or NULL */,
+                  const void* d_o, const float* lse, const spa2_shape* shape, const spa2_pattern* pattern,
+                  float scale, void* dq, void* dk, void* dv, void* workspace, size_t workspace_bytes, void* stream);
+
 /* The three stages of spa2_bwd, callable one by one (spa2_bwd gives exactly the results of their sequence; a caller
  * that needs only dQ, or only dK and dV, skips the other):
  *   spa2_bwd_delta  D = rowsum(dO * (o + o_res)), fp32 [B,H,N], left in `workspace`;

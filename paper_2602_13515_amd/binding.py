@@ -81,6 +81,10 @@ def _load():
     lib.spa2_fwd.argtypes = [vp, vp, vp, shp, pat, f32, vp, vp, vp, vp, sz, vp]
     lib.spa2_bwd.restype = ctypes.c_int
     lib.spa2_bwd.argtypes = [vp, vp, vp, vp, vp, vp, vp, shp, pat, f32, vp, vp, vp, vp, sz, vp]
+    lib.spa2_bwd_rows_workspace_bytes.restype = sz
+    lib.spa2_bwd_rows_workspace_bytes.argtypes = [shp]
+    lib.spa2_bwd_rows.restype = ctypes.c_int
+    lib.spa2_bwd_rows.argtypes = lib.spa2_bwd.argtypes
     lib.spa2_bwd_static.restype = ctypes.c_int
     lib.spa2_bwd_static.argtypes = [vp, vp, vp, vp, vp, vp, vp, shp, pat, f32, vp, vp, vp, vp]
     lib.spa2_mask_pool.restype = ctypes.c_int
@@ -118,7 +122,7 @@ EXPORTED_SYMBOLS = ("spa2_version", "spa2_strerror", "spa2_topk_blocks", "spa2_m
                     "spa2_mask_columns", "spa2_pattern_full", "spa2_fwd", "spa2_bwd", "spa2_bwd_static", "spa2_bwd_delta",
                     "spa2_bwd_dkdv", "spa2_bwd_dq", "spa2_error_workspace_bytes", "spa2_error_terms",
                     "spa2_vd_loss_workspace_bytes", "spa2_vd_loss", "spa2_vd_loss_grad", "spa2_vd_loss_and_grad",
-                    "spa2_mask_fwd", "spa2_mask_fwd_workspace_bytes",
+                    "spa2_mask_fwd", "spa2_mask_fwd_workspace_bytes", "spa2_bwd_rows", "spa2_bwd_rows_workspace_bytes",
                     "spa2_vd_rescale")
 
 

@@ -11,9 +11,11 @@
 //   dkdv_kernel   one workgroup per key block, walking the query blocks that selected it.
 // dQ is produced by a second, row-oriented pass instead of atomics: results are
 // deterministic and there is no fp32 dQ scratch tensor.
+#include "columns.h"
 #include "row_delta.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
+#include "split_plan.h"
 
 namespace spa2 {
 
@@ -39,6 +41,11 @@ struct DqArgs {
   int64_t sb, sh, sn;
   float scale, scale_log2;
   SplitPlan sp;         // long rows cut into parts (split.hip); sp.pool_slots == 0: every row is walked whole
+  // What the dK/dV kernel needs of the column lists, made by workgroups of this launch: its plan by the first of `front`
+  // in front of the parts (a multiple of eight: the workgroup -> XCD phase stays), its launch order by `orders` at the end.
+  PlanArgs col_plan;
+  OrderArgs col_order;
+  int front, orders;
 };
 
 // Partial result of one part of a split row: the fp32 accumulators as [pair of registers][thread] (see fwd.hip).
@@ -81,18 +88,29 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   // (S^T) and transposed (dQ^T), V along rows (dP^T).  (Aligned: compile-time parts are XORed into addresses.)
   constexpr int TILE_B = BKV * D * 2, STAGE_B = 2 * TILE_B;
   __shared__ __align__(1024) unsigned char smem[2 * STAGE_B];   // stage s: K tile, then V tile
+  static_assert(sizeof(PlanLds<256>) <= 2 * STAGE_B && sizeof(OrderLds<SIDE_ORDER_MAX, 4>) <= 2 * STAGE_B, "other work fits the tiles' LDS");
 
   // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
   int bh, i, part = 0, parts = 0, part_len = 0;
   bool whole = false;
-  if ((int)blockIdx.x < a.sp.pool_slots) {
-    if ((int)blockIdx.x >= a.sp.header[0]) return;
-    const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
+  const int slot = (int)blockIdx.x - a.front;
+  if (slot < 0) {
+    if (blockIdx.x == 0) plan_block<256>(a.col_plan, *(PlanLds<256>*)smem);
+    return;
+  }
+  if ((int)blockIdx.x >= (int)gridDim.x - a.orders) {
+    const int o = (int)blockIdx.x - ((int)gridDim.x - a.orders);
+    order_block<SIDE_ORDER_MAX, 4>(a.col_order, o / a.col_order.groups, o % a.col_order.groups, *(OrderLds<SIDE_ORDER_MAX, 4>*)smem);
+    return;
+  }
+  if (slot < a.sp.pool_slots) {
+    if (slot >= a.sp.header[0]) return;
+    const int32_t* pt = a.sp.part_table + 4 * slot;
     const int unit = pt[0];
     part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
-    const HeadBlock hb = xcd_map_rows(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
+    const HeadBlock hb = xcd_map_rows(slot - a.sp.pool_slots, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;
@@ -282,7 +300,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   }
 
   if (parts) {                // one part of a split row; the last one to arrive adds all of them in part order
-    const int64_t first = blockIdx.x - part;
+    const int64_t first = slot - part;
     const float* p0 = a.sp.pool + first * a.sp.slot_floats;
     float* ps = a.sp.pool + (first + part) * a.sp.slot_floats;
 #pragma unroll
@@ -309,10 +327,11 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   dq_store_rows<D>(a, base, i * BQ + 32 * w, lane, sm + w * (32 * D * 2), acc);
 }
 
-hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
-                         const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
-                         const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, hipStream_t stream) {
-  DqArgs a;
+static hipError_t launch_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
+                            const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
+                            const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, const PlanArgs* col_plan,
+                            const OrderArgs* col_order, hipStream_t stream) {
+  DqArgs a = {};
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.lse = lse; a.delta = delta; a.dq = (uint16_t*)dq;
   a.row_cnt = row_cnt; a.row_idx = row_idx; a.row_order = row_order;
@@ -324,10 +343,28 @@ hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid((unsigned)(plan.pool_slots + xcd_map_wgs(m.B * m.H, a.Tm, a.chunk, SHORT_ROWS))), block(256);
+  if (col_plan) { a.col_plan = *col_plan; a.front = 8; }
+  if (col_order) { a.col_order = *col_order; a.orders = m.B * m.H * col_order->groups; }
+  const dim3 grid((unsigned)(a.front + plan.pool_slots + xcd_map_wgs(m.B * m.H, a.Tm, a.chunk, SHORT_ROWS) + a.orders)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(dq_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dq_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();
+}
+
+hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
+                         const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
+                         const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, hipStream_t stream) {
+  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan, nullptr, nullptr, stream);
+}
+
+hipError_t launch_bwd_dq_columns(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
+                                 const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
+                                 const int32_t* row_order, float scale, void* dq, const SplitPlan& plan,
+                                 const int32_t* col_cnt, int32_t* col_order, const SplitPlan& col_plan, hipStream_t stream) {
+  const PlanArgs p = plan_args(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, col_plan);
+  const OrderArgs o = order_args(col_cnt, m, col_order);
+  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan,
+                   col_plan.pool_slots ? &p : nullptr, col_order ? &o : nullptr, stream);
 }
 
 }  // namespace spa2

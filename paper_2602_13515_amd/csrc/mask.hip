@@ -12,6 +12,7 @@
 //                   score product on the fp64 matrix cores.
 //   select_small_kernel  the same for rows of up to 64 blocks, one wave a row after the score product.
 //   columns_kernel  the same pattern listed per key block (for dK/dV).
+#include "columns.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
@@ -842,111 +843,27 @@ hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, in
 }
 
 // ------------------------------------------------------------------ column lists
-// One workgroup lists 64 key blocks of one head: thread (seg, c) takes one of COL_SEGS runs of query blocks of column c,
-// reads its mask bytes into one bit each (COL_BATCH loads in flight), and, after the counts of the column's runs have
-// been exchanged through LDS, writes its ascending piece of the list at the right offset.  Runs of up to 64 query
-// blocks (T_m <= 1024) stay in a register between the two steps; longer ones are read again, 64 at a time.
-// Bound: load latency; a loop that read one byte at a time, twice, took 33 us for 4 heads of 1024 x 2048 blocks and 56 us
-// for 40 of 591 x 1182, this takes 12 and 26 us.
-constexpr int COL_SEGS = 16, COL_BATCH = 16;
-__global__ __launch_bounds__(64 * COL_SEGS) void columns_kernel(const uint8_t* mask, int Tm, int Tn, int32_t* col_cnt,
-                                                                int32_t* col_idx) {
+__global__ __launch_bounds__(64 * COL_SEGS) void columns_kernel(ColumnArgs a) {
   __shared__ int seg_cnt[COL_SEGS][64];
-  const int bh = blockIdx.y;
-  const int c = threadIdx.x & 63, seg = threadIdx.x >> 6;
-  const int j = blockIdx.x * 64 + c;
-  const int per = (Tm + COL_SEGS - 1) / COL_SEGS;
-  const int i0 = min(Tm, seg * per), i1 = min(Tm, i0 + per);
-  const bool live = j < Tn;
-  const uint8_t* mp = mask + (int64_t)bh * Tm * Tn + min(j, Tn - 1);
-  // bit x: query block i + x (below i1, 64 of them at most) selected this column
-  auto bits_from = [&](int i) -> uint64_t {
-    uint64_t bits = 0;
-    for (int x0 = 0; x0 < 64 && i + x0 < i1; x0 += COL_BATCH) {
-      uint8_t b[COL_BATCH];
-#pragma unroll
-      for (int x = 0; x < COL_BATCH; ++x) b[x] = mp[(int64_t)min(i + x0 + x, i1 - 1) * Tn];
-#pragma unroll
-      for (int x = 0; x < COL_BATCH; ++x) bits |= (uint64_t)(b[x] != 0 && i + x0 + x < i1 ? 1u : 0u) << (x0 + x);
-    }
-    return bits;
-  };
-  const uint64_t first = bits_from(i0);
-  int n = __builtin_popcountll(first);
-  for (int i = i0 + 64; i < i1; i += 64) n += __builtin_popcountll(bits_from(i));
-  seg_cnt[seg][c] = n;
-  __syncthreads();
-  if (!live) return;
-  int at = 0;
-  for (int s2 = 0; s2 < seg; ++s2) at += seg_cnt[s2][c];
-  int32_t* out = col_idx + ((int64_t)bh * Tn + j) * Tm;
-  for (int i = i0; i < i1; i += 64) {
-    uint64_t bits = i == i0 ? first : bits_from(i);
-    while (bits) {
-      out[at++] = i + __builtin_ctzll(bits);
-      bits &= bits - 1;
-    }
-  }
-  if (seg == COL_SEGS - 1) col_cnt[(int64_t)bh * Tn + j] = at;
+  columns_block<COL_SEGS>(a, blockIdx.y, blockIdx.x, seg_cnt);
 }
 
-// Launch order of the key blocks of one head for the dK/dV kernel: longest column first (equal lengths: lower index
-// first), dealt round-robin to the eight XCD chunks of the schedule (position x*chunk + s belongs to XCD x), so that
-// every XCD gets the same mix of long and short columns and the long ones start early.  (Heads of up to SHORT_COLUMNS are
-// launched position by position (xcd_map): there neighbouring positions, chunks of the order, are what mixes the lengths.)
-// A column's rank is the number of columns that precede it in that order, counted directly: a workgroup ranks 64
-// columns of a head against all of them, RANK_SEGS threads a column, the head's keys in LDS.  (T_n^2 comparisons, but
-// no chain of dependent steps: the bitonic sort of a head by one workgroup before took 11.6 us at 512 columns of 12
-// heads and 23.6 us at 2048 columns of 4, this takes 4.8 and 5.5 us.)
-constexpr int RANK_SEGS = 16;
 template <int NP>
-__global__ __launch_bounds__(64 * RANK_SEGS) void col_order_kernel(const int32_t* col_cnt, int Tn, int32_t* col_order) {
-  constexpr int PER = NP / RANK_SEGS;                  // keys that one thread compares with
-  __shared__ __align__(16) uint32_t keys[NP];
-  __shared__ uint32_t before[RANK_SEGS][64];
-  const int bh = blockIdx.y, tid = threadIdx.x, c = tid & 63, seg = tid >> 6;
-  for (int j = tid; j < NP; j += 64 * RANK_SEGS)       // distinct keys: length, then lower index; padding below all
-    keys[j] = j < Tn ? ((uint32_t)min(col_cnt[(int64_t)bh * Tn + j], 0xffff) << 16) | (uint32_t)(0xffff - j) : 0u;
-  __syncthreads();
-  const int j = blockIdx.x * 64 + c;
-  const uint32_t mine = keys[min(j, NP - 1)];
-  uint32_t n = 0;
-  for (int x = seg * PER; x < min((seg + 1) * PER, Tn); x += 4) {       // (a wave reads one address: broadcast)
-    const u32x4 k4 = *(const u32x4*)(keys + x);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) n += k4[e] > mine ? 1u : 0u;
-  }
-  before[seg][c] = n;
-  __syncthreads();
-  if (seg != 0 || j >= Tn) return;
-  uint32_t rank = 0;
-#pragma unroll
-  for (int x = 0; x < RANK_SEGS; ++x) rank += before[x][c];
-  // the schedule position that is dealt as number `rank`: rounds of all XCDs while the shortest chunk lasts, then of
-  // those that still have positions (chunk x has min(chunk, T_n - x * chunk) of them)
-  const int chunk = (Tn + 7) / 8;
-  int left = (int)rank, s = 0, live = 8;
-  while (live > 0) {
-    const int len = min(max(Tn - (live - 1) * chunk, 0), chunk);        // the last live chunk is the shortest
-    const int rounds = max(len - s, 0);
-    if (left < rounds * live) break;
-    left -= rounds * live;
-    s += rounds;
-    --live;
-  }
-  const int pos = (left % live) * chunk + s + left / live;
-  col_order[(int64_t)bh * Tn + pos] = j;
+__global__ __launch_bounds__(64 * RANK_SEGS) void col_order_kernel(OrderArgs a) {
+  __shared__ OrderLds<NP, RANK_SEGS> lds;
+  order_block<NP, RANK_SEGS>(a, blockIdx.y, blockIdx.x, lds);
 }
 
 hipError_t launch_columns(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx,
                           int32_t* col_order, hipStream_t stream) {
-  const dim3 grid((unsigned)((m.Tn + 63) / 64), (unsigned)(m.B * m.H)), block(256);
-  hipLaunchKernelGGL(columns_kernel, grid, dim3(64 * COL_SEGS), 0, stream, mask, m.Tm, m.Tn, col_cnt, col_idx);
+  const dim3 grid((unsigned)((m.Tn + 63) / 64), (unsigned)(m.B * m.H));
+  hipLaunchKernelGGL(columns_kernel, grid, dim3(64 * COL_SEGS), 0, stream, column_args(mask, m, col_cnt, col_idx));
   if (col_order) {
     const dim3 b2(64 * RANK_SEGS);
-    if (m.Tn <= 512)       hipLaunchKernelGGL(col_order_kernel<512>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
-    else if (m.Tn <= 2048) hipLaunchKernelGGL(col_order_kernel<2048>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
-    else                   hipLaunchKernelGGL(col_order_kernel<8192>, grid, b2, 0, stream, col_cnt, m.Tn, col_order);
+    const OrderArgs a = order_args(col_cnt, m, col_order);
+    if (m.Tn <= 512)       hipLaunchKernelGGL(col_order_kernel<512>, grid, b2, 0, stream, a);
+    else if (m.Tn <= 2048) hipLaunchKernelGGL(col_order_kernel<2048>, grid, b2, 0, stream, a);
+    else                   hipLaunchKernelGGL(col_order_kernel<8192>, grid, b2, 0, stream, a);
   }
   return hipGetLastError();
 }

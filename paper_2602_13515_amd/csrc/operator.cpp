@@ -81,29 +81,20 @@ spa2_shape shape_of(const Tensor& q) {
   return s;
 }
 
-// The pattern's arrays in one buffer.  Column lists and launch order only where a backward pass will read them; the
-// order only where the key blocks do not all run at once (two workgroups a compute unit): without it a launch takes them
-// in the order of the sequence.
+// The arrays of a pattern of our own in one buffer.  The backward pass makes the column lists (spa2_bwd_rows).
 struct PatternLayout {
-  int64_t off[6] = {0, 0, 0, 0, 0, 0}, total = 0;
-  bool columns, order;
-  PatternLayout(const spa2_shape& s, bool cols) : columns(cols) {
+  int64_t off[3] = {0, 0, 0}, total = 0;
+  explicit PatternLayout(const spa2_shape& s) {
     const int64_t bh = (int64_t)s.B * s.H;
     const int64_t tm = ((int64_t)s.N + SPA2_BQ - 1) / SPA2_BQ, tn = ((int64_t)s.N + SPA2_BKV - 1) / SPA2_BKV;
-    order = cols && bh * tn > spa2::RESIDENT_WGS;
-    const int64_t size[6] = {bh * tm * tn, 4 * bh * tm, 4 * bh * tm * tn, cols ? 4 * bh * tn : 0,
-                             cols ? 4 * bh * tn * tm : 0, order ? 4 * bh * tn : 0};
-    for (int x = 0; x < 6; ++x) { off[x] = total; total += (size[x] + 255) & ~(int64_t)255; }
+    const int64_t size[3] = {bh * tm * tn, 4 * bh * tm, 4 * bh * tm * tn};
+    for (int x = 0; x < 3; ++x) { off[x] = total; total += (size[x] + 255) & ~(int64_t)255; }
   }
   spa2_pattern in(const Tensor& buf) const {
     char* p = (char*)buf.data_ptr();
-    spa2_pattern r;
+    spa2_pattern r = {};
     r.mask = (uint8_t*)(p + off[0]);
     r.row_cnt = (int32_t*)(p + off[1]); r.row_idx = (int32_t*)(p + off[2]);
-    r.col_cnt = columns ? (int32_t*)(p + off[3]) : nullptr;
-    r.col_idx = columns ? (int32_t*)(p + off[4]) : nullptr;
-    r.row_order = nullptr;
-    r.col_order = order ? (int32_t*)(p + off[5]) : nullptr;
     return r;
   }
 };
@@ -126,7 +117,7 @@ struct Attention : torch::autograd::Function<Attention> {
     const Tensor k = match(k_in, q), v = match(v_in, q);
     const spa2_shape s = shape_of(q);
     const bool build = given.empty();
-    const PatternLayout layout(s, training);
+    const PatternLayout layout(s);
     const Tensor buf = build ? bytes(layout.total, q) : Tensor();
     spa2_pattern pattern = build ? layout.in(buf) : given_pattern(given);
     // one scratch buffer for mask and forward; a log-sum-exp that nobody reads lies behind it
@@ -169,13 +160,16 @@ struct Attention : torch::autograd::Function<Attention> {
     same_layout(q, {&k, &v, &o, &o_res, &d_o});
     const spa2_shape s = shape_of(q);
     const std::vector<Tensor> kept = ctx->saved_data["pattern"].toTensorVector();
-    const spa2_pattern pattern = kept.size() == 1 ? PatternLayout(s, true).in(kept[0]) : given_pattern(kept);
+    const bool built = kept.size() == 1;
+    const spa2_pattern pattern = built ? PatternLayout(s).in(kept[0]) : given_pattern(kept);
     const Tensor dq = like(q), dk = like(q), dv = like(q);
-    const int64_t bwd_ws = (int64_t)spa2_bwd_workspace_bytes(&s);
-    const Tensor ws = bytes(bwd_ws, q);
-    check(spa2_bwd(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), o_res.data_ptr(), d_o.data_ptr(),
-                   (const float*)lse.data_ptr(), &s, &pattern, (float)ctx->saved_data["scale"].toDouble(), dq.data_ptr(),
-                   dk.data_ptr(), dv.data_ptr(), ws.data_ptr(), (size_t)bwd_ws, stream_of(q)), "spa2_bwd");
+    const int64_t need = (int64_t)(built ? spa2_bwd_rows_workspace_bytes(&s) : spa2_bwd_workspace_bytes(&s));
+    const Tensor ws = bytes(need, q);
+    check((built ? spa2_bwd_rows : spa2_bwd)(q.data_ptr(), k.data_ptr(), v.data_ptr(), o.data_ptr(), o_res.data_ptr(),
+                                             d_o.data_ptr(), (const float*)lse.data_ptr(), &s, &pattern,
+                                             (float)ctx->saved_data["scale"].toDouble(), dq.data_ptr(), dk.data_ptr(),
+                                             dv.data_ptr(), ws.data_ptr(), (size_t)need, stream_of(q)),
+          built ? "spa2_bwd_rows" : "spa2_bwd");
     return {dq, dk, dv, Variable(), Variable(), Variable(), Variable(), Variable()};
   }
 };

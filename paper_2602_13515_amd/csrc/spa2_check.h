@@ -35,6 +35,38 @@ inline MaskWs mask_ws(const Dims& m) {
   return w;
 }
 
+// Backward workspace: D (fp32, one value per token row), then the split plans and partial-result pools of the dQ
+// and the dK/dV kernel.  Only D is mandatory: with less than the full size the kernels walk every list whole.
+struct BwdWs { size_t d_bytes, dq_off, dq_bytes, dkdv_off, dkdv_bytes, total; };
+inline BwdWs bwd_ws(const Dims& m) {
+  BwdWs w;
+  w.d_bytes = round256((size_t)m.B * m.H * m.N * sizeof(float));
+  w.dq_off = w.d_bytes;
+  w.dq_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m)));
+  w.dkdv_off = w.dq_off + w.dq_bytes;
+  w.dkdv_bytes = round256(split_ws_bytes((int64_t)m.B * m.H * m.Tn, m.Tm, dkdv_slot_bytes(m)));
+  w.total = w.dkdv_off + w.dkdv_bytes;
+  return w;
+}
+inline size_t bwd_ws_min_bytes(const Dims& m) { return bwd_ws(m).d_bytes; }
+
+// the part of a workspace section that the caller's buffer really covers
+inline SplitPlan section_plan(void* ws, size_t ws_bytes, size_t off, size_t bytes, int64_t units, int list_max,
+                              size_t slot_bytes) {
+  if (!ws || ws_bytes <= off) return split_layout(nullptr, 0, units, list_max, slot_bytes);
+  const size_t have = ws_bytes - off < bytes ? ws_bytes - off : bytes;
+  return split_layout((char*)ws + off, have, units, list_max, slot_bytes);
+}
+inline SplitPlan dq_plan(const Dims& m, void* ws, size_t ws_bytes) {
+  const BwdWs w = bwd_ws(m);
+  return section_plan(ws, ws_bytes, w.dq_off, w.dq_bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m));
+}
+inline SplitPlan dkdv_plan(const Dims& m, void* ws, size_t ws_bytes) {
+  const BwdWs w = bwd_ws(m);
+  const int64_t units = (int64_t)m.B * m.H * m.Tn;
+  return with_queue(section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, units, m.Tm, dkdv_slot_bytes(m)), units);
+}
+
 // what spa2_mask asks of everything but its workspace
 inline int check_mask(const void* q, const void* k, const spa2_shape* shape, int32_t topk_blocks, float top_p, float scale,
                       const spa2_pattern* out) {

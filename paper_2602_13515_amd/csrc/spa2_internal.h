@@ -65,6 +65,18 @@ hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o,
                               const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
                               const SplitPlan& col_plan, hipStream_t stream);
 
+// D, the plan of the dQ kernel and the pattern's column lists in one launch; and the dQ launch that makes the plan and the
+// launch order (col_order, or null) of the dK/dV kernel on its way (bwd.hip).
+hipError_t launch_bwd_prepare_columns(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
+                                      const int32_t* row_cnt, const SplitPlan& row_plan, const uint8_t* mask,
+                                      int32_t* col_cnt, int32_t* col_idx, hipStream_t stream);
+// (heads of up to SIDE_ORDER_MAX columns: the keys they are ordered by have to fit the LDS of the tiles)
+constexpr int SIDE_ORDER_MAX = 4096;
+hipError_t launch_bwd_dq_columns(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
+                                 const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
+                                 const int32_t* row_order, float scale, void* dq, const SplitPlan& plan,
+                                 const int32_t* col_cnt, int32_t* col_order, const SplitPlan& col_plan, hipStream_t stream);
+
 // Each launcher enqueues its kernels on `stream` and returns hipGetLastError().
 hipError_t launch_pool(const void* q, const void* k, const Dims& m, float* qbar, float* kbar, hipStream_t stream);
 // the same, and zeroes `zeros` integers at `zero` (at most one per thread of the launch)

@@ -21,9 +21,11 @@
 //   32,760 tokens, 12 heads (T = 91 k):    474 /   615 /   936 before,  445 /   595 /   928 now
 //   20,010 tokens, 6 heads, d = 64:         99 /   109 /   184 before,   76 /    93 /   165 now
 //   32,760 tokens, 3 heads, every tile:   2267 before, 1663 now
+#include "columns.h"
 #include "row_delta.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
+#include "split_plan.h"
 
 namespace spa2 {
 
@@ -31,7 +33,6 @@ namespace {
 inline size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 }
 
-constexpr int SPLIT_CAP = 48;
 // lo and mid of the rule above.  An entry of a column is twice the work of one of a row.  Measured on 264 rows of 7
 // entries (dQ) and 504 columns of 3 to 9: lo = 8 / 4 takes 38 / 61 us, lo = 4 / 2 59 / 61 us, lo = 16 / 8 38 / 64 us;
 // on 32 rows of 29 and 64 columns of 14 (d = 64) 28 / 33, 28 / 36 and 34 / 41 us.  The forward kernel cuts that finely
@@ -96,14 +97,7 @@ SplitPlan with_fixed_parts(SplitPlan p, int64_t units, int list_max) {
   return p;
 }
 
-// What one plan reads and writes.
-struct PlanArgs {
-  const int32_t* cnt;
-  int units, list_max, lo, mid, pool;
-  int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive; int32_t* queue;
-};
-
-static PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p) {
+PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p) {
   PlanArgs a;
   a.cnt = cnt; a.units = (int)units; a.list_max = list_max;
   split_range(kind, units, a.lo, a.mid);
@@ -114,138 +108,11 @@ static PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, Split
   return a;
 }
 
-typedef __attribute__((ext_vector_type(4))) int i32x4;
-
-// Sum over the NT threads of a workgroup (red: one entry per wave).
 template <int NT>
-__device__ __forceinline__ unsigned long long block_sum(unsigned long long x, unsigned long long* red) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-  __syncthreads();                                   // (the previous sum has been read)
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-  __syncthreads();
-  unsigned long long t = 0;
-#pragma unroll
-  for (int i = 0; i < NT / 64; ++i) t += red[i];
-  return t;
+__global__ __launch_bounds__(NT) void split_plan_kernel(PlanArgs a) {
+  __shared__ PlanLds<NT> lds;
+  plan_block<NT>(a, lds);
 }
-
-// Number of parts of at most S entries that a list of c entries is cut into (0: it is not cut).  inv_s = 1 / S; the
-// rounded quotient is off by one at most (c < 2^25 entries, S of at least 4 for lists that long) and put right.
-__device__ __forceinline__ int parts_of(int c, int S, float inv_s) {
-  if (c <= S) return 0;
-  int q = (int)((float)c * inv_s);
-  q += q * S < c ? 1 : 0;
-  q += q * S < c ? 1 : 0;
-  return q - ((q - 1) * S >= c ? 1 : 0);
-}
-
-// One workgroup of NT threads makes one plan: sum of the lengths (fixes S), number of parts at S (S grows until they
-// fit the pool), then every split unit gets its slots by a scan over the threads.
-// Bound: latency, of three passes over the lengths (each thread's first four stay in registers) and of fetching the
-// code, which every launch runs once: it is kept short (four sizes S a round, unrolled, took 6.4 us instead of 3.6 on
-// 16 units).  Slots come from a scan: LDS counters, which every split unit added to, took 20 us instead of 13 for the
-// columns of a 20,010-token layer (256 threads).
-template <int NT>
-__device__ __forceinline__ void plan_block(const PlanArgs& a) {
-  __shared__ unsigned long long red[NT / 64];
-  __shared__ int wave_slots[NT / 64], wave_items[NT / 64];
-  __shared__ uint16_t owner[SPLIT_POOL_MAX];         // slot -> entry of the list of split units
-  __shared__ i32x4 item[SPLIT_POOL_MAX / 2];         // (unit, first slot, parts, entries per part) of a split unit
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  const bool vec_ok = ((uintptr_t)a.cnt & 15) == 0;
-  auto load4 = [&](int u) -> i32x4 {                 // lengths of units u .. u+3 (0 past the end), clamped
-    i32x4 c = {0, 0, 0, 0};
-    if (vec_ok && u + 4 <= a.units) c = *(const i32x4*)(a.cnt + u);
-    else {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) if (u + x < a.units) c[x] = a.cnt[u + x];
-    }
-#pragma unroll
-    for (int x = 0; x < 4; ++x) c[x] = min(max(c[x], 0), a.list_max);
-    return c;
-  };
-  const i32x4 held = load4(4 * t);
-  auto each_quad = [&](auto&& f) {                   // f(first unit, lengths) for every quad of this thread, in order
-    i32x4 c = held, next = {0, 0, 0, 0};
-#pragma unroll 1
-    for (int u = 4 * t; u < a.units; u += 4 * NT, c = next) {
-      if (u + 4 * NT < a.units) next = load4(u + 4 * NT);
-      f(u, c);
-    }
-  };
-  unsigned long long mine = 0;
-  each_quad([&](int, const i32x4& c) { mine += (unsigned long long)c[0] + c[1] + c[2] + c[3]; });
-  const long long T = (long long)block_sum<NT>(mine, red);
-  const long long s_small = min(max((T + RESIDENT_WGS - 1) / RESIDENT_WGS, (long long)a.lo), (long long)a.mid);
-  const long long s_large = max(min((T + 2047) / 2048, (long long)SPLIT_CAP), (T + 8191) / 8192);
-  int S = (int)max(min(max(s_small, s_large), (long long)a.list_max), 1ll);
-  float inv_s;
-  int n_slots, n_items;                              // of this thread's units
-#pragma unroll 1
-  for (;;) {
-    inv_s = 1.f / (float)S;
-    n_slots = 0; n_items = 0;
-    each_quad([&](int, const i32x4& c) {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) {
-        n_slots = min(n_slots + parts_of(c[x], S, inv_s), 1 << 20);         // (more than any pool: no overflow)
-        n_items += c[x] > S ? 1 : 0;
-      }
-    });
-    const int total = (int)block_sum<NT>((unsigned long long)n_slots, red);
-    if (total <= a.pool) break;
-    // half of what would bring lists much longer than S down to the pool, a quarter at least (ends: no list is longer
-    // than list_max)
-    S += max(S / 4 + 1, (int)min(0.5f * (float)S * (float)(total - a.pool) / (float)a.pool, (float)S));
-  }
-  // slots and places in the list of split units: exclusive scan over the threads
-  int at_slot = n_slots, at_item = n_items;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int ys = __shfl_up(at_slot, off, 64), yi = __shfl_up(at_item, off, 64);
-    if (lane >= off) { at_slot += ys; at_item += yi; }
-  }
-  if (lane == 63) { wave_slots[w] = at_slot; wave_items[w] = at_item; }
-  at_slot -= n_slots; at_item -= n_items;
-  __syncthreads();
-  int n = 0;
-#pragma unroll
-  for (int x = 0; x < NT / 64; ++x) {
-    if (x < w) { at_slot += wave_slots[x]; at_item += wave_items[x]; }
-    n += wave_slots[x];
-  }
-  each_quad([&](int u, const i32x4& c) {
-    i32x4 slot;
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      slot[x] = -1;
-      if (c[x] > S) {
-        const int parts = parts_of(c[x], S, inv_s);
-        slot[x] = at_slot;
-        item[at_item] = i32x4{u + x, at_slot, parts, (c[x] + parts - 1) / parts};
-        for (int p = 0; p < parts; ++p) owner[at_slot + p] = (uint16_t)at_item;
-        at_slot += parts; ++at_item;
-      }
-    }
-    if (u + 4 <= a.units) *(i32x4*)(a.unit_slot + u) = slot;
-    else {
-#pragma unroll
-      for (int x = 0; x < 4; ++x) if (u + x < a.units) a.unit_slot[u + x] = slot[x];
-    }
-  });
-  __syncthreads();
-  for (int g = t; g < n; g += NT) {
-    const i32x4 it = item[owner[g]];
-    *(i32x4*)(a.part_table + 4 * g) = i32x4{it[0], g - it[1], it[2], it[3]};
-    a.arrive[g] = 0;
-  }
-  if (t == 0) { a.header[0] = n; a.header[1] = S; }
-  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = RESIDENT_WGS / 8;      // (the first ones go by workgroup number)
-}
-
-template <int NT>
-__global__ __launch_bounds__(NT) void split_plan_kernel(PlanArgs a) { plan_block<NT>(a); }
 
 hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, SplitKind kind, const SplitPlan& p,
                              hipStream_t stream) {
@@ -257,34 +124,54 @@ hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, Sp
   return hipGetLastError();
 }
 
-// The pass over O and dO with the two plans of the backward kernels in front of it (workgroups 0 .. n_plans-1): the
-// plans, one workgroup each, then cost no time of their own (two launches of 8 to 27 us before) wherever the pass
-// takes longer than they do.
-struct PrepareArgs { DeltaArgs d; PlanArgs plan[2]; int n_plans; };
+// The pass over O and dO with work of its own workgroups in front of it: the plans of the backward kernels, one workgroup
+// each (two launches of 8 to 27 us before), and, where the pattern came without them, the column lists (a launch of 4 to 27
+// us before).  Neither costs time of its own wherever the pass takes longer than they do.
+struct PrepareArgs { DeltaArgs d; PlanArgs plan[2]; int n_plans; ColumnArgs cols; int n_cols; };
 
 template <int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(PrepareArgs a) {
-  if ((int)blockIdx.x < a.n_plans) {
-    plan_block<256>(a.plan[blockIdx.x]);
+  __shared__ union { PlanLds<256> plan; int seg_cnt[4][64]; } lds;
+  int w = blockIdx.x;
+  if (w < a.n_plans) {
+    plan_block<256>(a.plan[w], lds.plan);
     return;
   }
-  const int w = blockIdx.x - a.n_plans;
+  w -= a.n_plans;
+  if (w < a.n_cols) {
+    columns_block<4>(a.cols, w / a.cols.groups, w % a.cols.groups, lds.seg_cnt);
+    return;
+  }
+  w -= a.n_cols;
   delta_block<D>(a.d, w / a.d.chunks, w % a.d.chunks);
+}
+
+static hipError_t launch_prepare(const PrepareArgs& a, const Dims& m, hipStream_t stream) {
+  const dim3 grid((unsigned)(a.n_plans + a.n_cols + m.B * m.H * a.d.chunks)), block(256);
+  if (m.d == 128) hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, block, 0, stream, a);
+  else            hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, block, 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
                               const int32_t* row_cnt, const SplitPlan& row_plan, const int32_t* col_cnt,
                               const SplitPlan& col_plan, hipStream_t stream) {
-  PrepareArgs a;
+  PrepareArgs a = {};
   a.d = delta_args(o, o_res, d_o, m, delta);
-  a.n_plans = 0;
   if (col_plan.pool_slots) a.plan[a.n_plans++] = plan_args(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, col_plan);
   if (row_plan.pool_slots) a.plan[a.n_plans++] = plan_args(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, row_plan);
-  for (int x = a.n_plans; x < 2; ++x) a.plan[x] = PlanArgs{};
-  const dim3 grid((unsigned)(a.n_plans + m.B * m.H * a.d.chunks)), block(256);
-  if (m.d == 128) hipLaunchKernelGGL(bwd_prepare_kernel<128>, grid, block, 0, stream, a);
-  else            hipLaunchKernelGGL(bwd_prepare_kernel<64>, grid, block, 0, stream, a);
-  return hipGetLastError();
+  return launch_prepare(a, m, stream);
+}
+
+hipError_t launch_bwd_prepare_columns(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
+                                      const int32_t* row_cnt, const SplitPlan& row_plan, const uint8_t* mask,
+                                      int32_t* col_cnt, int32_t* col_idx, hipStream_t stream) {
+  PrepareArgs a = {};
+  a.d = delta_args(o, o_res, d_o, m, delta);
+  if (row_plan.pool_slots) a.plan[a.n_plans++] = plan_args(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, row_plan);
+  a.cols = column_args(mask, m, col_cnt, col_idx);
+  a.n_cols = m.B * m.H * a.cols.groups;
+  return launch_prepare(a, m, stream);
 }
 
 }  // namespace spa2

@@ -1,0 +1,44 @@
+"""The backward pass that makes its own column lists against spa2_mask_columns and spa2_bwd: same bits."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2602_13515_amd as spa2
+from paper_2602_13515_amd import workloads as wl
+
+from gpu_util import Guarded, dev, gpu_bwd, gpu_fwd, gpu_mask
+
+pytestmark = pytest.mark.gpu
+
+
+# one block; a head of 64 and of 65 key blocks (edges of the listing and ranking workgroups), of 21 (blocks dealt in turn);
+# runs of query blocks longer than a register holds (513 > 4 x 64 query blocks); more columns than a direct launch takes;
+# 4096 and 4097 key blocks, on either side of what the dQ launch orders
+@pytest.mark.parametrize("B,H,N,d", [(1, 1, 40, 128), (2, 3, 4096, 64), (1, 2, 4100, 128), (4, 6, 1281, 128), (1, 1, 65600, 64),
+                                     (1, 12, 11200, 64), (1, 1, 262144, 64), (1, 1, 262145, 64)])
+def test_backward_from_the_mask_gives_the_bits_of_columns_and_backward(B, H, N, d):
+    w = wl.Workload("rows", B, H, N, d, 0.05, 0.3, "lowrank", True)
+    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=2))
+    scale = d ** -0.5
+    pat, _ = gpu_mask(q, k, spa2.spa2_topk_blocks(0.05 if N < 200000 else 0.002, -(-N // 64)), 0.3 if N < 200000 else 0.0,
+                      scale, want_pbar=False)
+    o, lse, o_res = gpu_fwd(q, k, v, pat, scale, residual=True)
+    want = gpu_bwd(q, k, v, o, do, lse, pat, scale, o_res=o_res)
+    lib, g, lay = spa2.binding._load(), Guarded(), spa2.binding._layout_of(q)
+    need = int(lib.spa2_bwd_rows_workspace_bytes(lay.ref))
+    ws = g.alloc((need,), torch.uint8, dev(), 0xA5)
+    out = [g.alloc(q.shape, q.dtype, dev(), float("nan")) for _ in range(3)]
+    rows = spa2.Pattern(pat.mask, pat.row_cnt, pat.row_idx, None, None, None, None)
+    c = rows._c()
+    ptr = lambda *ts: [t.data_ptr() for t in ts]
+    call = lambda nbytes: lib.spa2_bwd_rows(*ptr(q, k, v, o, o_res, do, lse), lay.ref, ctypes.byref(c), scale, *ptr(*out),
+                                            ws.data_ptr(), nbytes, spa2.binding._stream(q))
+    assert call(need - 1) == -6
+    print(f"case B={B} H={H} N={N} d={d}", flush=True)
+    for _ in range(2):
+        assert call(need) == 0
+        torch.cuda.synchronize()
+        g.check("spa2_bwd_rows")
+        for name, x, y in zip(("dq", "dk", "dv"), out, want):
+            assert torch.equal(x, y), name
