@@ -34,6 +34,39 @@ struct DkvArgs {
 template <int D> constexpr int dkdv_slot_floats() { return 2 * 2 * (D / 32) * 16 * 64; }
 size_t dkdv_slot_bytes(const Dims& m) { return (size_t)(m.d == 128 ? dkdv_slot_floats<128>() : dkdv_slot_floats<64>()) * 4; }
 
+// The last part of a split column to arrive adds all of them in part order and stores the rows that wave w finishes, key0w ..
+// (area: 32 * D * 2 bytes of LDS of the wave's own).
+template <int D>
+__device__ __forceinline__ void dkdv_merge(const DkvArgs& a, const WorkItem& item, int64_t base, int key0w, int w, int lane,
+                                           uint32_t area) {
+  constexpr int NMB = D / 32;
+  const float* p0 = a.sp.pool + (int64_t)(item.slot - item.part) * a.sp.slot_floats + 2 * lane;
+#pragma unroll
+  for (int round = 0; round < 2; ++round) {
+    f32x2 x[NMB * 8];
+#pragma unroll
+    for (int c = 0; c < NMB * 8; ++c) x[c] = f32x2{0.f, 0.f};
+    for (int p = 0; p < item.parts; ++p) {
+      const float* ps = p0 + (int64_t)p * a.sp.slot_floats + (round * 2 + w) * NMB * 8 * 128;
+      f32x2 y[NMB * 8];
+#pragma unroll
+      for (int c = 0; c < NMB * 8; ++c) y[c] = part_load2(ps + c * 128);
+#pragma unroll
+      for (int c = 0; c < NMB * 8; ++c) { x[c][0] += y[c][0]; x[c][1] += y[c][1]; }
+    }
+    const float sc = round == 0 ? -a.scale : 1.f;
+#pragma unroll
+    for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x2 lo = x[mb * 8 + 2 * g], hi = x[mb * 8 + 2 * g + 1];
+        u32x2 pk2 = {pack_bf16(lo[0] * sc, lo[1] * sc), pack_bf16(hi[0] * sc, hi[1] * sc)};
+        row_piece_put<D>(area, lane & 31, 4 * mb + g, lane >> 5, pk2);
+      }
+    rows_store<D>(area, (round == 0 ? a.dk : a.dv) + base + (int64_t)key0w * a.sn, a.sn, a.N - key0w, lane);
+  }
+}
+
 // One workgroup of two waves per key block j (64 keys); one wave per SIMD (512 registers), four waves per CU.
 // The query blocks that selected j are taken in halves of 64 rows; wave w owns the 32 queries 32w.. of the half
 // and ALL 64 keys of the block.  It keeps K_j^T, V_j^T (B operands) and its dK^T, dV^T accumulators (d x 64
@@ -376,52 +409,276 @@ __device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item
     rows_store<D>(area + 32 * D * 2, a.dv + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
     return;
   }
-  // the last part of a split column to arrive adds all of them in part order
-  {
-    const int64_t first = item.slot - part;
-    if (!last_part(a.sp.arrive + first, parts, (int*)stat_s)) return;
-    const uint32_t area = lds_addr_of(scratch + w * REGION);
-    const float* p0 = a.sp.pool + first * a.sp.slot_floats + 2 * le;
+  if (!last_part(a.sp.arrive + item.slot - part, parts, (int*)stat_s)) return;
+  dkdv_merge<D>(a, item, base, key0w, w, le, lds_addr_of(scratch + w * REGION));
+}
+
+// Head dimension 64: one workgroup of two waves per key block, two waves per SIMD (256 registers), eight per CU.  Wave w owns
+// keys 32w .. 32w + 31 and all 64 query rows of a step, in two halves of 32; K^T, V^T (32 registers) and the sums (64) stay
+// in registers.  An operand fragment from LDS feeds one product instead of the two of dkdv_item, but the sums need no
+// exchange at the end, and a second wave on the SIMD works where this one waits: the exponentials per product are twice
+// those of d = 128, a single wave kept the matrix cores busy 39 % of the time.  Rows are staged once for both waves (each
+// copies 32 of them, a step ahead), one barrier a step.
+//   S rh = Q K^T, rh = 0, 1   | copies of the next step; D into the accumulators of dP 0
+//   D - dP 0, D - dP 1        | exponentials of half 0, of half 1
+//   dV of half 0, of half 1   | dS of half 0, of half 1
+//   dK of half 0, of half 1   | barrier, first fragments of the next step
+// Bound: the copies out of the memory-side cache (9 TB/s over all compute units while every slot is busy).  Measured, us, a
+// training pass, one wave a SIMD with 64 keys a wave / this: 20,010 tokens, 6 heads 280 / 270; 40,296 tokens, 32 heads
+// 4202 / 3983.  256 columns of 4 entries, a workgroup a compute unit: 20.0 / 19.5 (the kernel).
+__device__ __forceinline__ void dkdv_item64(const DkvArgs& a, const WorkItem& item, Walk& walk, unsigned char* smem,
+                                            unsigned char* stat_s) {
+  constexpr int D = 64, NK = D / 16, NMB = D / 32;
+  constexpr int HQ = 64;                             // query rows per step
+  constexpr int CPR = D / 8, RPI = 64 / CPR, NCP = 32 / RPI;         // (see dkdv_item)
+  constexpr int TILE_B = HQ * D * 2, HALF_B = TILE_B / 2, STAGE_B = 2 * TILE_B;    // Q rows, then dO rows
+  constexpr int STAT_B = 512;                        // a wave's 32 rows: LSE at +0, D at +256
+  const int bh = item.bh, j = item.blk, part = item.part, parts = item.parts, part_len = item.part_len;
+  const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
+  const int lane = fresh_lane(), w = walk.wave;
+  const int r32 = lane & 31, hf = lane >> 5;
+  const int N = a.N;
+  int cnt = min(max(a.col_cnt[(int64_t)bh * a.Tn + j], 0), a.Tm);   // clamped: see fwd.hip
+  const int32_t* idx = a.col_idx + ((int64_t)bh * a.Tn + j) * a.Tm;
+  if (parts) {                // entries [part * part_len, (part + 1) * part_len) of the list
+    idx += part * part_len;
+    cnt = min(cnt - part * part_len, part_len);
+  }
+  const int key0w = j * BKV + 32 * w, key = key0w + r32;
+  if (cnt == 0) {             // no query block selected this key block: zero gradients
+    if (key < N) {
+      const int64_t out_off = base + (int64_t)key * a.sn + 32 * hf;
 #pragma unroll
-    for (int round = 0; round < 2; ++round) {
-      f32x2 x[NMB * 8];
-#pragma unroll
-      for (int c = 0; c < NMB * 8; ++c) x[c] = f32x2{0.f, 0.f};
-      for (int p = 0; p < parts; ++p) {
-        const float* ps = p0 + (int64_t)p * a.sp.slot_floats + (round * 2 + w) * NMB * 8 * 128;
-        f32x2 y[NMB * 8];
-#pragma unroll
-        for (int c = 0; c < NMB * 8; ++c) y[c] = part_load2(ps + c * 128);
-#pragma unroll
-        for (int c = 0; c < NMB * 8; ++c) { x[c][0] += y[c][0]; x[c][1] += y[c][1]; }
+      for (int c = 0; c < 4; ++c) {
+        *(u32x4*)(a.dk + out_off + 8 * c) = u32x4{0, 0, 0, 0};
+        *(u32x4*)(a.dv + out_off + 8 * c) = u32x4{0, 0, 0, 0};
       }
-      const float sc = round == 0 ? -a.scale : 1.f;
+    }
+    return;
+  }
+
+  // K^T / V^T fragments: lane = key, 8 consecutive channels per 16-wide k step (keys past N repeat the last token)
+  bf16x8 kf[NK], vf[NK];
+  {
+    const int64_t off = base + (int64_t)min(key, N - 1) * a.sn + 8 * hf;
 #pragma unroll
-      for (int mb = 0; mb < NMB; ++mb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const f32x2 lo = x[mb * 8 + 2 * g], hi = x[mb * 8 + 2 * g + 1];
-          u32x2 pk2 = {pack_bf16(lo[0] * sc, lo[1] * sc), pack_bf16(hi[0] * sc, hi[1] * sc)};
-          row_piece_put<D>(area, le & 31, 4 * mb + g, he, pk2);
-        }
-      rows_store<D>(area, (round == 0 ? a.dk : a.dv) + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
+    for (int kk = 0; kk < NK; ++kk) {
+      kf[kk] = *(const bf16x8*)(a.k + off + 16 * kk);
+      vf[kk] = *(const bf16x8*)(a.v + off + 16 * kk);
     }
   }
+  f32x16 dk_acc[NMB], dv_acc[NMB];
+#pragma unroll
+  for (int mb = 0; mb < NMB; ++mb)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) { dk_acc[mb][v] = 0.f; dv_acc[mb][v] = 0.f; }
+
+  // copies of rows 32w .. 32w + 31 of a step (swizzled and clamped as in dkdv_item)
+  uint32_t voff[NCP], soff = 0;
+  int rows_set = -1;
+  auto set_rows = [&](int last) {            // last: last valid row of the 32 (uniform)
+    if (last == rows_set) return;
+    rows_set = last;
+    const int l = fresh_lane();
+#pragma unroll
+    for (int r = 0; r < NCP; ++r) {
+      const int row_l = RPI * r + l / CPR;
+      voff[r] = (uint32_t)((min(row_l, last) * a.sn + (((l % CPR) ^ swz<D>(row_l)) * 8)) * 2);
+    }
+    soff = (uint32_t)(min(l & 31, last) * 4);
+  };
+  const char* q_head = (const char*)(a.q + base);
+  const char* o_head = (const char*)(a.d_o + base);
+  const char* lse_head = (const char*)(a.lse + (int64_t)bh * N);
+  const char* dlt_head = (const char*)(a.delta + (int64_t)bh * N);
+  const uint64_t row_bytes = (uint64_t)a.sn * 2;
+  const uint32_t sm = lds_addr_of(smem), stat = lds_addr_of(stat_s);
+  const uint32_t sm_w = sm + w * HALF_B, stat_w = stat + w * STAT_B;         // this wave's rows of a stage
+  auto copy_stats = [&](int row, uint32_t stat_addr) {
+    raw_copy4_to_lds_at<0>(lse_head + (uint64_t)row * 4, soff, stat_addr);
+    raw_copy4_to_lds_at<256>(dlt_head + (uint64_t)row * 4, soff, stat_addr);
+  };
+  // Query rows past N get an LSE of +infinity once their copy has landed: their P is then exactly zero.
+  auto mark_rows_past_end = [&](int row0, uint32_t stat_addr) {
+    if (row0 + 32 <= N) return;
+    const int row_l = fresh_lane() & 31;
+    if (row0 + row_l >= N) lds_stf(stat_addr + 4 * row_l, INFINITY);
+  };
+
+  int idx_v = idx[min(lane, cnt - 1)];       // the index list, 64 entries at a time (see dkdv_item)
+  auto step_row = [&](int u) -> int {        // this wave's first row of step u (uniform, inside the chunk that idx_v holds)
+    const int i = min(max(__builtin_amdgcn_readlane(idx_v, (u >> 1) & 63), 0), a.Tm - 1);
+    return i * BQ + (u & 1) * HQ + 32 * w;
+  };
+  const int s16 = lane & 15, hb16 = (lane >> 4) & 1;
+  const uint32_t a_off = sm + 2 * swz_idx<D>(r32, 8 * hf);
+  const uint32_t t_off0 = sm + 2 * swz_idx<D>(4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
+  const uint32_t t_off1 = sm + 2 * swz_idx<D>(8 + 4 * hf + (s16 >> 2), 16 * hb16 + 4 * (s16 & 3));
+
+  const int steps = 2 * cnt;                 // step u: half u & 1 of list entry u >> 1
+  {
+    const int row0 = step_row(0), row_b = min(row0, N - 1);
+    set_rows(min(31, N - 1 - row_b));
+    copy_stats(row_b, stat_w);
+    static_for<0, NCP>([&](auto R) {
+      constexpr int r = decltype(R)::v;
+      raw_copy16_to_lds_at<r * 1024>(q_head + (uint64_t)row_b * row_bytes, voff[r], sm_w);
+      raw_copy16_to_lds_at<TILE_B + r * 1024>(o_head + (uint64_t)row_b * row_bytes, voff[r], sm_w);
+    });
+    raw_copies_done();
+    mark_rows_past_end(row0, stat_w);
+    __syncthreads();
+  }
+#pragma unroll
+  for (int kk = 0; kk < NK; ++kk) vf[kk] = __builtin_bit_cast(bf16x8, __builtin_bit_cast(u32x4, vf[kk]) ^ 0x80008000u);   // -V^T (see dkdv_item)
+
+  constexpr int PD = 4, PDT = 2;             // how many row / transposed fragments ahead an LDS read is issued
+  constexpr int NR = 2 * NK, NX = 4 * NMB;   // row fragments of one tensor and step; transposed ones (rh, c, mb)
+  bf16x8 fr[PD];
+  auto row_frag = [&](uint32_t at, int y) -> bf16x8 {         // y = (tensor, rh, kk)
+    return lds_ld16((at ^ ((y % NK) << 5)) + (y / NR) * TILE_B + ((y / NK) % 2) * HALF_B);
+  };
+#pragma unroll
+  for (int x = 0; x < PD; ++x) fr[x] = row_frag(a_off, x);
+
+  for (int u = 0; u < steps; ++u) {
+    const int st = u & 1;
+    const int un = min(u + 1, steps - 1);    // past the end the last step is requested again (nobody reads it)
+    if (((u + 1) & 127) == 0 && u + 1 < steps) idx_v = list_load(idx, min(((u + 1) >> 1) + fresh_lane(), cnt - 1));   // next 64 entries
+    const int row_nx = step_row(un), row_b = min(row_nx, N - 1);
+    set_rows(min(31, N - 1 - row_b));
+    const uint32_t nx_stage = sm_w + (st ^ 1) * STAGE_B, nx_stat = stat_w + (st ^ 1) * 2 * STAT_B;
+    const char* qn = q_head + (uint64_t)row_b * row_bytes;
+    const char* on = o_head + (uint64_t)row_b * row_bytes;
+    uint32_t q_rd = a_off + st * STAGE_B, q_t0 = t_off0 + st * STAGE_B, q_t1 = t_off1 + st * STAGE_B;
+    const uint32_t lb = stat + st * 2 * STAT_B + 16 * hf;
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(q_rd), "+v"(q_t0), "+v"(q_t1));    // (the XORed addresses are not kept over the loop)
+#endif
+    auto tr_frag = [&](int tile, int x) -> bf16x8 {     // tile 0 = Q, 1 = dO; x = (rh, c, mb)
+      const uint32_t o = tile * TILE_B + (x / NMB) * 32 * D;
+      return join_tr(lds_tr4_at((q_t0 ^ ((x % NMB) << 6)) + o), lds_tr4_at((q_t1 ^ ((x % NMB) << 6)) + o));
+    };
+    f32x16 s[2], dp[2];
+    f32x4 l_raw, l_neg;
+    uint32_t pk[2][8], dsk[2][8];
+    auto load_d = [&](int rh) {              // D, as the initial value of dP
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        const f32x4 d0 = lds_ldf4(lb + 256 + STAT_B * rh + 32 * g);
+#pragma unroll
+        for (int x = 0; x < 4; ++x) dp[rh][4 * g + x] = d0[x];
+      }
+    };
+    // exp unit e = (rh, g, pair): two queries of accumulator group g (registers 4g .. 4g+3)
+    auto exp_unit = [&](auto E) {
+      constexpr int e = decltype(E)::v, rh = e >> 3, g = (e >> 1) & 3, v = 4 * g + 2 * (e & 1);
+      if constexpr ((e & 1) == 0) {
+#pragma unroll
+        for (int x = 0; x < 4; ++x) l_neg[x] = -LOG2E * l_raw[x];
+        if constexpr (e < 14) l_raw = lds_ldf4(lb + STAT_B * ((e + 2) >> 3) + 32 * (((e + 2) >> 1) & 3));
+      }
+      s[rh][v] = fast_exp2(fmaf(s[rh][v], a.scale_log2, l_neg[v & 3]));
+      s[rh][v + 1] = fast_exp2(fmaf(s[rh][v + 1], a.scale_log2, l_neg[(v & 3) + 1]));
+      pk[rh][v >> 1] = pack_bf16(s[rh][v], s[rh][v + 1]);
+    };
+    auto ds_unit = [&](auto E) {             // the same two queries of -dS = P * (D - dP)
+      constexpr int e = decltype(E)::v, rh = e >> 3, v = 4 * ((e >> 1) & 3) + 2 * (e & 1);
+      dsk[rh][v >> 1] = pack_bf16(s[rh][v] * dp[rh][v], s[rh][v + 1] * dp[rh][v + 1]);
+    };
+    auto quad = [](const uint32_t (&p)[8], int c) -> bf16x8 {
+      return __builtin_bit_cast(bf16x8, u32x4{p[4 * c], p[4 * c + 1], p[4 * c + 2], p[4 * c + 3]});
+    };
+    const f32x16 zero = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // ---- S = Q K^T of both halves; the next step's LSE, D, Q and dO rows are requested
+    static_for<0, NR>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, rh = y / NK, kk = y % NK;
+      s[rh] = mfma32(fr[y % PD], kf[kk], kk == 0 ? zero : s[rh]);
+      fr[y % PD] = row_frag(q_rd, y + PD);
+      if constexpr (y == 0) copy_stats(row_b, nx_stat);
+      if constexpr (y < NCP) raw_copy16_to_lds_at<y * 1024>(qn, voff[y], nx_stage);
+      else                   raw_copy16_to_lds_at<TILE_B + (y - NCP) * 1024>(on, voff[y - NCP], nx_stage);
+      if constexpr (y == NK) load_d(0);
+      if constexpr (y == NR - 1) l_raw = lds_ldf4(lb);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- D - dP = D + dO (-V)^T, with exp(S - LSE) between the products
+    bf16x8 ft[PDT];
+    static_for<0, NR>([&](auto Y) {
+      constexpr int y = decltype(Y)::v, rh = y / NK, kk = y % NK;
+      dp[rh] = mfma32(fr[y % PD], vf[kk], dp[rh]);
+      if constexpr (y + PD < NR) fr[y % PD] = row_frag(q_rd, NR + y + PD);
+      if constexpr (y == 0) load_d(1);
+      static_for<y * 2, y * 2 + 2>(exp_unit);
+      if constexpr (y >= NR - PDT) ft[y - (NR - PDT)] = tr_frag(1, y - (NR - PDT));
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- dV^T += dO^T P.  Step x = (rh, c, mb): the 16 queries 16c.. of half rh, output block mb
+    static_for<0, NX>([&](auto X) {
+      constexpr int x = decltype(X)::v, mb = x % NMB, c = (x / NMB) % 2, rh = x / (2 * NMB);
+      dv_acc[mb] = mfma32(ft[x % PDT], quad(pk[rh], c), dv_acc[mb]);
+      ft[x % PDT] = x + PDT < NX ? tr_frag(1, x + PDT) : tr_frag(0, x + PDT - NX);
+      static_for<x * 2, x * 2 + 2>(ds_unit);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    // ---- -dK^T += Q^T (-dS).  When the last fragments of this step have been read and the next step's rows have landed,
+    // both waves change stages
+    static_for<0, NX>([&](auto X) {
+      constexpr int x = decltype(X)::v, mb = x % NMB, c = (x / NMB) % 2, rh = x / (2 * NMB);
+      dk_acc[mb] = mfma32(ft[x % PDT], quad(dsk[rh], c), dk_acc[mb]);
+      if constexpr (x + PDT < NX) ft[x % PDT] = tr_frag(0, x + PDT);
+      if constexpr (x == NX - PDT) {
+        raw_copies_done();
+        mark_rows_past_end(row_nx, nx_stat);
+        __syncthreads();
+#pragma unroll
+        for (int f = 0; f < PD; ++f) fr[f] = row_frag(a_off + (st ^ 1) * STAGE_B, f);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    });
+  }
+  walk.draw(a.sp);
+  // The stage that nobody was to read has landed (the barrier of the last step): its LDS, and with one more barrier the
+  // other stage's, is free.
+  const int le = fresh_lane();
+  if (parts) {                  // one part of a split column: leave the sums to the last part
+    float* ps = a.sp.pool + (int64_t)item.slot * a.sp.slot_floats + 2 * le;
+    static_for<0, 2 * NMB * 8>([&](auto C) {
+      constexpr int c = decltype(C)::v, t = c / (8 * NMB), mb = (c / 8) % NMB, v = 2 * (c % 8);
+      const f32x16& x = t == 0 ? dk_acc[mb] : dv_acc[mb];
+      part_store2(ps + ((t * 2 + w) * NMB * 8 + c % (8 * NMB)) * 128, x[v], x[v + 1]);
+    });
+    if (!last_part(a.sp.arrive + item.slot - part, parts, (int*)stat_s)) return;
+    dkdv_merge<D>(a, item, base, key0w, w, le, sm + w * TILE_B);
+    return;
+  }
+  __syncthreads();
+  const uint32_t area = sm + w * TILE_B;             // dK, then dV rows of this wave
+  static_for<0, 2 * NMB * 4>([&](auto C) {
+    constexpr int c = decltype(C)::v, t = c / (4 * NMB), mb = (c / 4) % NMB, v = 4 * (c % 4);
+    const f32x16& x = t == 0 ? dk_acc[mb] : dv_acc[mb];
+    const float sc = t == 0 ? -a.scale : 1.f;
+    row_piece_put<D>(area + t * (32 * D * 2), le & 31, c % (4 * NMB), le >> 5,
+                     u32x2{pack_bf16(x[v] * sc, x[v + 1] * sc), pack_bf16(x[v + 2] * sc, x[v + 3] * sc)});
+  });
+  rows_store<D>(area, a.dk + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
+  rows_store<D>(area + 32 * D * 2, a.dv + base + (int64_t)key0w * a.sn, a.sn, N - key0w, le);
 }
 
 template <int D>
-__global__ __attribute__((amdgpu_flat_work_group_size(128, 128), amdgpu_waves_per_eu(1, 1)))
+__global__ __attribute__((amdgpu_flat_work_group_size(128, 128), amdgpu_waves_per_eu(D == 128 ? 1 : 2, D == 128 ? 1 : 2)))
 void dkdv_kernel(DkvArgs) {
-  // (aligned: compile-time parts are XORed into addresses)
-  __shared__ __align__(1024) unsigned char smem[2 * 2 * 2 * 32 * D * 2];    // wave w, stage s at (2w + s) * STAGE_B
-  __shared__ __align__(1024) unsigned char stat_s[2 * 2 * 512];             // wave w, stage s
+  // two stages of 64 rows of Q and dO (aligned: compile-time parts are XORed into addresses)
+  __shared__ __align__(1024) unsigned char smem[2 * 2 * 64 * D * 2];
+  __shared__ __align__(1024) unsigned char stat_s[2 * 2 * 512];
   __shared__ int word;
   Walk walk(&word);
   for (;;) {
     const DkvArgs& a = fresh_args<DkvArgs>();
     WorkItem item;
     if (!walk.take(item, a.sp, a.Tn, a.chunk, a.BH, a.col_order)) return;
-    dkdv_item<D>(a, item, walk, smem, stat_s);
+    if constexpr (D == 128) dkdv_item<D>(a, item, walk, smem, stat_s);
+    else                    dkdv_item64(a, item, walk, smem, stat_s);
     if (!walk.advance(a.sp)) return;
   }
 }
@@ -442,7 +699,7 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
     const hipError_t e = launch_split_plan(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(plan.queue ? RESIDENT_WGS : (unsigned)(plan.pool_slots + xcd_map_wgs(a.BH, a.Tn, a.chunk, SHORT_COLUMNS))), block(128);
+  const dim3 grid(plan.queue ? (unsigned)plan.resident : (unsigned)(plan.pool_slots + xcd_map_wgs(a.BH, a.Tn, a.chunk, SHORT_COLUMNS))), block(128);
   if (m.d == 128) hipLaunchKernelGGL(dkdv_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dkdv_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

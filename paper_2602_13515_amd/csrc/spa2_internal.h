@@ -29,6 +29,7 @@ constexpr int QUEUE_STRIDE = 64;             // ints between the counters of two
 // Workgroups that run at a time, two per compute unit (fwd_kernel<64>, whose registers and LDS would let three, is cut and
 // ordered for two as well): those of a queue launch, and what the split plan cuts for.
 constexpr int RESIDENT_WGS = 512;
+inline int dkdv_resident(const Dims& m) { return m.d == 128 ? RESIDENT_WGS : 2 * RESIDENT_WGS; }     // (of the dK/dV kernel)
 struct SplitPlan {
   const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection)
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
@@ -41,13 +42,15 @@ struct SplitPlan {
   int slot_floats;
   int fixed_len;               // > 0: no plan, every list is cut into parts of at most fixed_len entries (with_fixed_parts);
   int fixed_parts;             //   part p of unit u has slot u * fixed_parts + p
+  int resident;                // workgroups of the launch that run at a time
   bool planned;                // the tables have been written already (launch_bwd_prepare): no plan launch of its own
 };
 // Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
 // queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
 // 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.
-inline SplitPlan with_queue(SplitPlan p, int64_t units) {
-  if (p.pool_slots && units > 4 * RESIDENT_WGS) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
+inline SplitPlan with_queue(SplitPlan p, int64_t units, int resident) {
+  p.resident = resident;
+  if (p.pool_slots && units > 4 * resident) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
   return p;
 }
 size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes);

@@ -70,6 +70,7 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
   p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
   p.queue = nullptr;
   p.pool_slots = 0; p.slot_floats = 0; p.fixed_len = 0; p.fixed_parts = 0; p.planned = false;
+  p.resident = RESIDENT_WGS;
   if (!ws) return p;
   // the pool shrinks if the caller gave less than the full workspace
   int64_t pool = pool_wanted(units, list_max);
@@ -102,7 +103,7 @@ PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind ki
   a.cnt = cnt; a.units = (int)units; a.list_max = list_max;
   split_range(kind, units, a.lo, a.mid);
   a.pool = p.queue ? p.pool_slots - 1 : p.pool_slots;
-  a.queue = p.queue;
+  a.queue = p.queue; a.resident = p.resident;
   a.header = (int32_t*)p.header; a.unit_slot = (int32_t*)p.unit_slot; a.part_table = (int32_t*)p.part_table;
   a.arrive = p.arrive;
   return a;

@@ -11,7 +11,7 @@ constexpr int SPLIT_CAP = 48;
 // What one plan reads and writes.
 struct PlanArgs {
   const int32_t* cnt;
-  int units, list_max, lo, mid, pool;
+  int units, list_max, lo, mid, pool, resident;
   int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive; int32_t* queue;
 };
 
@@ -87,8 +87,9 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
   unsigned long long mine = 0;
   each_quad([&](int, const i32x4& c) { mine += (unsigned long long)c[0] + c[1] + c[2] + c[3]; });
   const long long T = (long long)block_sum<NT>(mine, red);
-  const long long s_small = min(max((T + RESIDENT_WGS - 1) / RESIDENT_WGS, (long long)a.lo), (long long)a.mid);
-  const long long s_large = max(min((T + 2047) / 2048, (long long)SPLIT_CAP), (T + 8191) / 8192);
+  const long long s_small = min(max((T + a.resident - 1) / a.resident, (long long)a.lo), (long long)a.mid);
+  const long long s_large = max(min((T + 4 * a.resident - 1) / (4 * a.resident), (long long)SPLIT_CAP),
+                                (T + 16 * a.resident - 1) / (16 * a.resident));
   int S = (int)max(min(max(s_small, s_large), (long long)a.list_max), 1ll);
   float inv_s;
   int n_slots, n_items;                              // of this thread's units
@@ -151,7 +152,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
     a.arrive[g] = 0;
   }
   if (t == 0) { a.header[0] = n; a.header[1] = S; }
-  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = RESIDENT_WGS / 8;      // (the first ones go by workgroup number)
+  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = a.resident / 8;      // (the first ones go by workgroup number)
 }
 
 }  // namespace spa2
