@@ -136,8 +136,8 @@ int spa2_fwd(const void* q, const void* k, const void* v, const spa2_shape* shap
   if (rc != SPA2_OK) return rc;
   if (workspace && !aligned16(workspace)) return SPA2_ERR_ALIGN;
   const Dims m = make_dims(*shape);
-  const SplitPlan plan = section_plan(workspace, workspace_bytes, 0, spa2_fwd_workspace_bytes(shape),
-                                      (int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m));
+  const SplitPlan plan = with_stretches(section_plan(workspace, workspace_bytes, 0, spa2_fwd_workspace_bytes(shape),
+                                                  (int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m)), m);
   if (launch_fwd(q, k, v, m, pattern->row_cnt, pattern->row_idx, pattern->row_order, scale, o, o_res, lse, plan,
                  (hipStream_t)stream) != hipSuccess)
     return SPA2_ERR_LAUNCH;

@@ -9,7 +9,7 @@ using namespace spa2;
 namespace {
 // Workspace: the forward section, whose pool is free until the forward kernel runs: the pooled means lie there.
 SplitPlan fwd_section(const Dims& m, void* ws, size_t bytes) {
-  return split_layout(ws, bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m));
+  return with_stretches(split_layout(ws, bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m)), m);
 }
 size_t fwd_bytes(const Dims& m) {
   return round256(split_ws_bytes((int64_t)m.B * m.H * m.Tm, m.Tn, fwd_slot_bytes(m)));

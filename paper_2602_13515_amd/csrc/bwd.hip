@@ -13,6 +13,7 @@
 // deterministic and there is no fp32 dQ scratch tensor.
 #include "columns.h"
 #include "row_delta.h"
+#include "row_map.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
 #include "split_plan.h"
@@ -37,7 +38,7 @@ struct DqArgs {
   const uint16_t* q; const uint16_t* k; const uint16_t* v; const uint16_t* d_o;
   const float* lse; const float* delta; uint16_t* dq;
   const int32_t* row_cnt; const int32_t* row_idx; const int32_t* row_order;
-  int H, N, Tm, Tn, chunk;
+  int BH, H, N, Tm, Tn, chunk;
   int64_t sb, sh, sn;
   float scale, scale_log2;
   SplitPlan sp;         // long rows cut into parts (split.hip); sp.pool_slots == 0: every row is walked whole
@@ -110,7 +111,8 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
     part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
-    const HeadBlock hb = xcd_map_rows(slot - a.sp.pool_slots, a.Tm, a.chunk);
+    const int wg = slot - a.sp.pool_slots;
+    const HeadBlock hb = launched_row(a.sp, wg, a.BH, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     i = a.row_order ? min(max(a.row_order[(int64_t)bh * a.Tm + hb.blk], 0), a.Tm - 1) : hb.blk;
@@ -335,7 +337,7 @@ static hipError_t launch_dq(const void* q, const void* k, const void* v, const v
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.lse = lse; a.delta = delta; a.dq = (uint16_t*)dq;
   a.row_cnt = row_cnt; a.row_idx = row_idx; a.row_order = row_order;
-  a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.chunk = (m.Tm + 7) / 8;
+  a.BH = m.B * m.H; a.H = m.H; a.N = m.N; a.Tm = m.Tm; a.Tn = m.Tn; a.chunk = (m.Tm + 7) / 8;
   a.sb = m.sb; a.sh = m.sh; a.sn = m.sn;
   a.scale = scale; a.scale_log2 = scale * LOG2E;
   a.sp = plan;
@@ -345,7 +347,8 @@ static hipError_t launch_dq(const void* q, const void* k, const void* v, const v
   }
   if (col_plan) { a.col_plan = *col_plan; a.front = 8; }
   if (col_order) { a.col_order = *col_order; a.orders = m.B * m.H * col_order->groups; }
-  const dim3 grid((unsigned)(a.front + plan.pool_slots + xcd_map_wgs(m.B * m.H, a.Tm, a.chunk, SHORT_ROWS) + a.orders)), block(256);
+  const int rows = launched_rows(a.BH, a.Tm, a.chunk);
+  const dim3 grid((unsigned)(a.front + plan.pool_slots + rows + a.orders)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(dq_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dq_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

@@ -12,6 +12,7 @@
 // B-operand layout the second product wants, so P never leaves registers, and
 // the running maximum / sum of Alg. 1 (m_ij, l_ij) are per-lane scalars that
 // need one exchange between the two halves of the wave per tile.
+#include "row_map.h"
 #include "spa2_device.h"
 #include "spa2_internal.h"
 
@@ -80,8 +81,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
   bool whole = false;         // a row of the plan that may be split: its parts are the first workgroups
   int slot = blockIdx.x;
   if (a.sp.fixed_len) {       // a small launch: the sizes say which part of which row (with_fixed_parts)
-    const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk, SHORT_ROWS);
-    const HeadBlock hb = xcd_map(blockIdx.x % rows, a.Tm, a.chunk, SHORT_ROWS);
+    const int rows = stretch_wgs(a.BH * a.Tm);
+    const HeadBlock hb = stretch_row(blockIdx.x % rows, a.BH, a.Tm);
     if (!hb.valid) return;
     bh = hb.bh; i = hb.blk;
     const int unit = bh * a.Tm + i, all = min(max(a.row_cnt[unit], 0), a.Tn);
@@ -97,7 +98,8 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
     part = pt[1]; parts = pt[2]; part_len = pt[3];
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
-    const HeadBlock hb = xcd_map_rows(blockIdx.x - a.sp.pool_slots, a.Tm, a.chunk);
+    const int wg = blockIdx.x - a.sp.pool_slots;
+    const HeadBlock hb = launched_row(a.sp, wg, a.BH, a.Tm, a.chunk);
     if (!hb.valid) return;
     bh = hb.bh;
     // optional launch order: position hb.blk of this head's schedule -> query block (clamped: caller data)
@@ -468,8 +470,8 @@ hipError_t launch_fwd(const void* q, const void* k, const void* v, const Dims& m
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_FWD, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const int rows = xcd_map_wgs(a.BH, a.Tm, a.chunk, SHORT_ROWS);
-  const dim3 grid((unsigned)(plan.fixed_len ? plan.fixed_parts * rows : plan.pool_slots + rows)), block(256);
+  const dim3 grid((unsigned)(plan.fixed_len ? plan.fixed_parts * stretch_wgs(a.BH * a.Tm)
+                                            : plan.pool_slots + launched_rows(a.BH, a.Tm, a.chunk))), block(256);
   if (m.d == 128) hipLaunchKernelGGL(fwd_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(fwd_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

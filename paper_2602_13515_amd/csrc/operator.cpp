@@ -13,7 +13,6 @@
 #include <torch/extension.h>
 
 #include "spa2.h"
-#include "spa2_internal.h"
 
 namespace {
 

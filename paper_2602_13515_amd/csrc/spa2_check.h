@@ -59,7 +59,7 @@ inline SplitPlan section_plan(void* ws, size_t ws_bytes, size_t off, size_t byte
 }
 inline SplitPlan dq_plan(const Dims& m, void* ws, size_t ws_bytes) {
   const BwdWs w = bwd_ws(m);
-  return section_plan(ws, ws_bytes, w.dq_off, w.dq_bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m));
+  return with_stretches(section_plan(ws, ws_bytes, w.dq_off, w.dq_bytes, (int64_t)m.B * m.H * m.Tm, m.Tn, dq_slot_bytes(m)), m);
 }
 inline SplitPlan dkdv_plan(const Dims& m, void* ws, size_t ws_bytes) {
   const BwdWs w = bwd_ws(m);

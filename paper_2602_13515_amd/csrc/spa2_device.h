@@ -89,6 +89,16 @@ __device__ __forceinline__ void raw_copies_left() {
 #endif
 }
 
+// A number that an earlier launch has written, at a uniform address: as a scalar load (the compiler makes a vector load of it
+// where the kernel may write through another pointer).
+__device__ __forceinline__ int scalar_ld(const int32_t* p) {
+#if defined(__HIP_DEVICE_COMPILE__)
+  return *(__attribute__((address_space(4))) const int32_t*)p;
+#else
+  return *p;
+#endif
+}
+
 // Everything above has been requested here: loads are not moved down behind the branches that follow.
 __device__ __forceinline__ void requested() {
 #if defined(__HIP_DEVICE_COMPILE__)
@@ -272,6 +282,22 @@ __host__ __device__ __forceinline__ HeadBlock xcd_map_rows(int wg, int blocks_pe
     r.valid = r.blk < blocks_per_head;
   }
   return r;
+}
+
+// Rotation inside groups of four, as above, of place s of an XCD's stretch of n rows.
+__host__ __device__ __forceinline__ int rotated_row(int s, int n, int xcd) {
+  if ((s | 3) >= n) return s;
+  const uint32_t rot = ((uint32_t)xcd * 0x85EBCA6Bu + (uint32_t)(s >> 2) * 0x9E3779B1u) >> 30;
+  return (s & ~3) | ((s + (int)rot) & 3);
+}
+// Rows (or columns) in stretches, an eighth of all of them for each XCD, one head after the other (with_stretches).
+__host__ __device__ __forceinline__ int stretch_first(int units, int xcd) { return (int)((int64_t)units * xcd >> 3); }
+__host__ __device__ __forceinline__ int stretch_wgs(int units) { return (units + 7) & ~7; }
+__host__ __device__ __forceinline__ HeadBlock stretch_row(int wg, int heads, int blocks_per_head) {
+  const int units = heads * blocks_per_head, x = wg & 7, s = wg >> 3;
+  const int lo = stretch_first(units, x), n = stretch_first(units, x + 1) - lo;
+  const int u = lo + rotated_row(s, n, x);
+  return HeadBlock{u / blocks_per_head, u % blocks_per_head, s < n};
 }
 
 }  // namespace spa2

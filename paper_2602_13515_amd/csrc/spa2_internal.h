@@ -31,7 +31,7 @@ constexpr int QUEUE_STRIDE = 64;             // ints between the counters of two
 constexpr int RESIDENT_WGS = 512;
 inline int dkdv_resident(const Dims& m) { return m.d == 128 ? RESIDENT_WGS : 2 * RESIDENT_WGS; }     // (of the dK/dV kernel)
 struct SplitPlan {
-  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection)
+  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection), [2] see stretches
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
   const int32_t* part_table;   // [pool_slots][4] (unit, part, parts of the unit, list entries per part) of pool slot g
   int32_t* arrive;             // [pool_slots] parts of the unit that have left their result, at its first slot
@@ -43,8 +43,21 @@ struct SplitPlan {
   int fixed_len;               // > 0: no plan, every list is cut into parts of at most fixed_len entries (with_fixed_parts);
   int fixed_parts;             //   part p of unit u has slot u * fixed_parts + p
   int resident;                // workgroups of the launch that run at a time
+  bool stretches;              // header[2] says whether an XCD takes an eighth of all rows or of every head (with_stretches)
   bool planned;                // the tables have been written already (launch_bwd_prepare): no plan launch of its own
 };
+// Which rows an XCD takes, where heads are short: an eighth of all rows, one head after the other, so that the workgroups that
+// run on an XCD at a time are of one head or a few, whose keys and values its 4 MB of L2 then serve.  (With an eighth of every
+// head on every XCD the 64 workgroups of an XCD were of 16 heads where a head has 32 rows.)  Where heads are of unlike density,
+// so that an eighth has a sixteenth more list entries than the mean, an eighth of every head is what evens out: the plan says
+// which (header[2]).  From 512 rows an eighth of a head fills an XCD as well, and eight heads at a time do not fit the
+// memory-side cache.  Measured, us, an eighth of every head / of all (forward, dQ): 24 heads of 4000 tokens 45.2 / 39.0, 44.2 /
+// 42.1; 16 heads of 8192 75.4 / 70.7, 82.7 / 81.0; 32 heads of 8192, d = 64 202.7 / 194.3, 225.9 / 224.1; 24 heads of 32,760
+// 845 / 822, 1011 / 1004.
+inline SplitPlan with_stretches(SplitPlan p, const Dims& m) {
+  p.stretches = p.pool_slots && m.Tm < 512;
+  return p;
+}
 // Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
 // queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
 // 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.

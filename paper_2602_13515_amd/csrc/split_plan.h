@@ -54,6 +54,7 @@ struct PlanLds {
   i32x4 item[SPLIT_POOL_MAX / 2];                    // (unit, first slot, parts, entries per part) of a split unit
   unsigned long long red[NT / 64];
   int wave_slots[NT / 64], wave_items[NT / 64];
+  unsigned long long work[8];                        // list entries of every eighth of the units
   uint16_t owner[SPLIT_POOL_MAX];                    // slot -> entry of the list of split units
 };
 template <int NT>
@@ -84,9 +85,20 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
       f(u, c);
     }
   };
-  unsigned long long mine = 0;
-  each_quad([&](int, const i32x4& c) { mine += (unsigned long long)c[0] + c[1] + c[2] + c[3]; });
-  const long long T = (long long)block_sum<NT>(mine, red);
+  if (t < 8) lds.work[t] = 0;
+  __syncthreads();
+  const float eighth = 8.f / (float)a.units;
+  each_quad([&](int u, const i32x4& c) {
+    const int x0 = min((int)((float)u * eighth), 7), x3 = min((int)((float)(u + 3) * eighth), 7);
+    if (x0 == x3) atomicAdd(&lds.work[x0], (unsigned long long)c[0] + c[1] + c[2] + c[3]);
+    else
+#pragma unroll
+      for (int e = 0; e < 4; ++e) atomicAdd(&lds.work[min((int)((float)(u + e) * eighth), 7)], (unsigned long long)c[e]);
+  });
+  __syncthreads();
+  long long T = 0, most = 0;
+#pragma unroll
+  for (int x = 0; x < 8; ++x) { T += (long long)lds.work[x]; most = max(most, (long long)lds.work[x]); }
   const long long s_small = min(max((T + a.resident - 1) / a.resident, (long long)a.lo), (long long)a.mid);
   const long long s_large = max(min((T + 4 * a.resident - 1) / (4 * a.resident), (long long)SPLIT_CAP),
                                 (T + 16 * a.resident - 1) / (16 * a.resident));
@@ -151,7 +163,7 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
     *(i32x4*)(a.part_table + 4 * g) = i32x4{it[0], g - it[1], it[2], it[3]};
     a.arrive[g] = 0;
   }
-  if (t == 0) { a.header[0] = n; a.header[1] = S; }
+  if (t == 0) { a.header[0] = n; a.header[1] = S; a.header[2] = 8 * most <= T + T / 16 ? 1 : 0; }
   if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = a.resident / 8;      // (the first ones go by workgroup number)
 }
 
