@@ -49,6 +49,7 @@ int spa2_bwd_rows(const void* q, const void* k, const void* v, const void* o, co
   int32_t* col_idx = (int32_t*)((char*)workspace + w.idx);
   int32_t* col_order = (int32_t*)((char*)workspace + w.order);
   SplitPlan rows = dq_plan(m, workspace, workspace_bytes), cols = dkdv_plan(m, workspace, workspace_bytes);
+  cols = columns_in_stretches(cols, m);
   float* delta = (float*)workspace;
   hipStream_t st = (hipStream_t)stream;
   if (m.Tn > SIDE_ORDER_MAX) {            // (262,144 tokens and more: two launches are nothing there)

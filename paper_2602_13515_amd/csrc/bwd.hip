@@ -45,8 +45,9 @@ struct DqArgs {
   // What the dK/dV kernel needs of the column lists, made by workgroups of this launch: its plan by the first of `front`
   // in front of the parts (a multiple of eight: the workgroup -> XCD phase stays), its launch order by `orders` at the end.
   PlanArgs col_plan;
-  OrderArgs col_order;
+  OrderArgs col_order; ListArgs col_list;        // (one of them, by whether the launch is in stretches)
   int front, orders;
+  bool stretches;
 };
 
 // Partial result of one part of a split row: the fp32 accumulators as [pair of registers][thread] (see fwd.hip).
@@ -89,7 +90,8 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   // (S^T) and transposed (dQ^T), V along rows (dP^T).  (Aligned: compile-time parts are XORed into addresses.)
   constexpr int TILE_B = BKV * D * 2, STAGE_B = 2 * TILE_B;
   __shared__ __align__(1024) unsigned char smem[2 * STAGE_B];   // stage s: K tile, then V tile
-  static_assert(sizeof(PlanLds<256>) <= 2 * STAGE_B && sizeof(OrderLds<SIDE_ORDER_MAX, 4>) <= 2 * STAGE_B, "other work fits the tiles' LDS");
+  static_assert(sizeof(PlanLds<256>) <= 2 * STAGE_B && sizeof(OrderLds<SIDE_ORDER_MAX, 4>) <= 2 * STAGE_B &&
+                sizeof(ListLds) <= 2 * STAGE_B, "other work fits the tiles' LDS");
 
   // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
   int bh, i, part = 0, parts = 0, part_len = 0;
@@ -101,14 +103,15 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   }
   if ((int)blockIdx.x >= (int)gridDim.x - a.orders) {
     const int o = (int)blockIdx.x - ((int)gridDim.x - a.orders);
-    order_block<SIDE_ORDER_MAX, 4>(a.col_order, o / a.col_order.groups, o % a.col_order.groups, *(OrderLds<SIDE_ORDER_MAX, 4>*)smem);
+    if (a.stretches) list_block(a.col_list, o / a.col_list.groups, o % a.col_list.groups, *(ListLds*)smem);
+    else order_block<SIDE_ORDER_MAX, 4>(a.col_order, o / a.col_order.groups, o % a.col_order.groups, *(OrderLds<SIDE_ORDER_MAX, 4>*)smem);
     return;
   }
   if (slot < a.sp.pool_slots) {
-    if (slot >= a.sp.header[0]) return;
+    if (slot >= scalar_ld(a.sp.header)) return;
     const int32_t* pt = a.sp.part_table + 4 * slot;
-    const int unit = pt[0];
-    part = pt[1]; parts = pt[2]; part_len = pt[3];
+    const int unit = scalar_ld(pt);
+    part = scalar_ld(pt + 1); parts = scalar_ld(pt + 2); part_len = scalar_ld(pt + 3);
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
     const int wg = slot - a.sp.pool_slots;
@@ -331,8 +334,8 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
 
 static hipError_t launch_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                             const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
-                            const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, const PlanArgs* col_plan,
-                            const OrderArgs* col_order, hipStream_t stream) {
+                            const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, const SplitPlan* col_plan,
+                            const int32_t* col_cnt, int32_t* col_order, hipStream_t stream) {
   DqArgs a = {};
   a.q = (const uint16_t*)q; a.k = (const uint16_t*)k; a.v = (const uint16_t*)v; a.d_o = (const uint16_t*)d_o;
   a.lse = lse; a.delta = delta; a.dq = (uint16_t*)dq;
@@ -345,8 +348,18 @@ static hipError_t launch_dq(const void* q, const void* k, const void* v, const v
     const hipError_t e = launch_split_plan(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, plan, stream);
     if (e != hipSuccess) return e;
   }
-  if (col_plan) { a.col_plan = *col_plan; a.front = 8; }
-  if (col_order) { a.col_order = *col_order; a.orders = m.B * m.H * col_order->groups; }
+  if (col_plan && col_plan->pool_slots) {
+    a.col_plan = plan_args(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, *col_plan);
+    a.front = 8;
+  }
+  if (col_plan && col_plan->stretches) {
+    a.stretches = true;
+    a.col_list = list_args(col_cnt, m, col_order, (int64_t)m.B * m.H * m.Tn <= 3 * col_plan->resident);
+    a.orders = 8 * a.col_list.groups;
+  } else if (col_plan && col_order) {
+    a.col_order = order_args(col_cnt, m, col_order);
+    a.orders = m.B * m.H * a.col_order.groups;
+  }
   const int rows = launched_rows(a.BH, a.Tm, a.chunk);
   const dim3 grid((unsigned)(a.front + plan.pool_slots + rows + a.orders)), block(256);
   if (m.d == 128) hipLaunchKernelGGL(dq_kernel<128>, grid, block, 0, stream, a);
@@ -357,17 +370,15 @@ static hipError_t launch_dq(const void* q, const void* k, const void* v, const v
 hipError_t launch_bwd_dq(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                          const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
                          const int32_t* row_order, float scale, void* dq, const SplitPlan& plan, hipStream_t stream) {
-  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan, nullptr, nullptr, stream);
+  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan, nullptr, nullptr, nullptr, stream);
 }
 
 hipError_t launch_bwd_dq_columns(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                                  const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
                                  const int32_t* row_order, float scale, void* dq, const SplitPlan& plan,
                                  const int32_t* col_cnt, int32_t* col_order, const SplitPlan& col_plan, hipStream_t stream) {
-  const PlanArgs p = plan_args(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, col_plan);
-  const OrderArgs o = order_args(col_cnt, m, col_order);
-  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan,
-                   col_plan.pool_slots ? &p : nullptr, col_order ? &o : nullptr, stream);
+  return launch_dq(q, k, v, d_o, lse, delta, m, row_cnt, row_idx, row_order, scale, dq, plan, &col_plan, col_cnt, col_order,
+                   stream);
 }
 
 }  // namespace spa2

@@ -699,7 +699,8 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
     const hipError_t e = launch_split_plan(col_cnt, (int64_t)m.B * m.H * m.Tn, m.Tm, SPLIT_DKDV, plan, stream);
     if (e != hipSuccess) return e;
   }
-  const dim3 grid(plan.queue ? (unsigned)plan.resident : (unsigned)(plan.pool_slots + xcd_map_wgs(a.BH, a.Tn, a.chunk, SHORT_COLUMNS))), block(128);
+  const int columns = plan.stretches ? stretch_wgs(a.BH * a.Tn) : xcd_map_wgs(a.BH, a.Tn, a.chunk, SHORT_COLUMNS);
+  const dim3 grid((unsigned)(plan.queue ? plan.resident : plan.pool_slots + columns)), block(128);
   if (m.d == 128) hipLaunchKernelGGL(dkdv_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dkdv_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

@@ -122,4 +122,46 @@ __device__ __forceinline__ void order_block(const OrderArgs& a, int bh, int grou
   a.col_order[(int64_t)bh * Tn + pos] = j;
 }
 
+// Launch order of the columns of all heads in stretches (stretch_first): place lo_x + s of the list is what XCD x takes as its
+// s-th, a number bh * T_n + j.  One head after the other, longest column first, in long launches; longest first over the
+// whole stretch (by_length) in launches of up to three rounds, whose last ones to start should be short.  Backward pass, us, by
+// head / by length: 24 heads of 2000 tokens 66.7 / 62.3 (1.5 rounds), of 4000 132.7 / 121.3 (3), 32 heads of 8192, d = 64,
+// (4) 576 / 587.  Ranks are counted, as above.
+struct ListArgs {
+  const int32_t* col_cnt; int32_t* list;
+  int Tn, units, groups, by_length;          // groups of 64 columns a stretch
+};
+inline ListArgs list_args(const int32_t* col_cnt, const Dims& m, int32_t* list, bool by_length) {
+  const int units = m.B * m.H * m.Tn;
+  return ListArgs{col_cnt, list, m.Tn, units, ((units + 7) / 8 + 63) / 64, by_length};
+}
+struct ListLds {
+  __attribute__((aligned(16))) uint32_t keys[SIDE_ORDER_MAX];
+  uint32_t before[4][64];
+};
+__device__ __forceinline__ void list_block(const ListArgs& a, int xcd, int group, ListLds& lds) {
+  const int lo = stretch_first(a.units, xcd), n = stretch_first(a.units, xcd + 1) - lo, h0 = lo / a.Tn;
+  const int tid = threadIdx.x, c = tid & 63, seg = tid >> 6;
+  const int padded = (n + 15) & ~15, per = padded / 4;
+  // distinct keys: (lower head,) length (T_m < 512), lower number; padding below all
+  for (int s = tid; s < padded; s += 256) {
+    const uint32_t len = s < n ? (uint32_t)min(max(a.col_cnt[lo + s], 0), 511) : 0u;
+    const uint32_t head = a.by_length ? 0u : (uint32_t)(2047 - min((lo + s) / a.Tn - h0, 2047));
+    lds.keys[s] = s < n ? (head << 21) | (len << 12) | (uint32_t)(4095 - s) : 0u;
+  }
+  __syncthreads();
+  const int s = group * 64 + c;
+  const uint32_t mine = lds.keys[min(s, max(n - 1, 0))];
+  uint32_t before = 0;
+  for (int x = seg * per; x < (seg + 1) * per; x += 4) {       // (a wave reads one address: broadcast)
+    const u32x4 k4 = *(const u32x4*)(lds.keys + x);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) before += k4[e] > mine ? 1u : 0u;
+  }
+  lds.before[seg][c] = before;
+  __syncthreads();
+  if (seg != 0 || s >= n) return;
+  a.list[lo + (int)(lds.before[0][c] + lds.before[1][c] + lds.before[2][c] + lds.before[3][c])] = lo + s;
+}
+
 }  // namespace spa2

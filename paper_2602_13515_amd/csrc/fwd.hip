@@ -92,10 +92,10 @@ __global__ __launch_bounds__(256, 2) void fwd_kernel(FwdArgs a) {
     if (parts) part_len = (all + parts - 1) / parts;
     slot = unit * a.sp.fixed_parts + part;
   } else if ((int)blockIdx.x < a.sp.pool_slots) {
-    if ((int)blockIdx.x >= a.sp.header[0]) return;
+    if ((int)blockIdx.x >= scalar_ld(a.sp.header)) return;
     const int32_t* pt = a.sp.part_table + 4 * blockIdx.x;
-    const int unit = pt[0];
-    part = pt[1]; parts = pt[2]; part_len = pt[3];
+    const int unit = scalar_ld(pt);
+    part = scalar_ld(pt + 1); parts = scalar_ld(pt + 2); part_len = scalar_ld(pt + 3);
     bh = unit / a.Tm; i = unit % a.Tm;
   } else {
     const int wg = blockIdx.x - a.sp.pool_slots;

@@ -30,6 +30,7 @@ constexpr int QUEUE_STRIDE = 64;             // ints between the counters of two
 // ordered for two as well): those of a queue launch, and what the split plan cuts for.
 constexpr int RESIDENT_WGS = 512;
 inline int dkdv_resident(const Dims& m) { return m.d == 128 ? RESIDENT_WGS : 2 * RESIDENT_WGS; }     // (of the dK/dV kernel)
+constexpr int SIDE_ORDER_MAX = 4096;         // columns that a side workgroup orders: their keys have to fit the LDS of tiles
 struct SplitPlan {
   const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection), [2] see stretches
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
@@ -66,6 +67,15 @@ inline SplitPlan with_queue(SplitPlan p, int64_t units, int resident) {
   if (p.pool_slots && units > 4 * resident) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
   return p;
 }
+// Columns in stretches, where spa2_bwd_rows lists them for it: heads as above, and stretches whose columns a workgroup can rank.
+// (Eighths of unlike work: a direct launch takes the stretches in turn, a queue evens out by itself.)  Measured, us, backward
+// pass, an eighth of every head / of all: 4 samples of 1281 tokens, 6 heads 73.8 / 68.7; 24 heads of 4000 145.2 / 120.2; 6 heads
+// of 9000 165.3 / 154.7; 16 heads of 8192 269 / 246; 40 heads of 3000, d = 64 132.5 / 115.0; 20,010 tokens, 6 heads, d = 64 183.6 /
+// 176.4; 24 heads of 32,760 2805 / 2728, half the rows long 12470 / 12170.
+inline SplitPlan columns_in_stretches(SplitPlan p, const Dims& m) {
+  p.stretches = p.pool_slots && m.Tm < 512 && (int64_t)m.B * m.H * m.Tn <= 8 * SIDE_ORDER_MAX;
+  return p;
+}
 size_t split_ws_bytes(int64_t units, int list_max, size_t slot_bytes);
 size_t split_pool_offset(int64_t units, int list_max);       // where the slots of a full workspace begin
 SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, size_t slot_bytes);
@@ -86,8 +96,7 @@ hipError_t launch_bwd_prepare(const void* o, const void* o_res, const void* d_o,
 hipError_t launch_bwd_prepare_columns(const void* o, const void* o_res, const void* d_o, const Dims& m, float* delta,
                                       const int32_t* row_cnt, const SplitPlan& row_plan, const uint8_t* mask,
                                       int32_t* col_cnt, int32_t* col_idx, hipStream_t stream);
-// (heads of up to SIDE_ORDER_MAX columns: the keys they are ordered by have to fit the LDS of the tiles)
-constexpr int SIDE_ORDER_MAX = 4096;
+// (heads of up to SIDE_ORDER_MAX columns)
 hipError_t launch_bwd_dq_columns(const void* q, const void* k, const void* v, const void* d_o, const float* lse,
                                  const float* delta, const Dims& m, const int32_t* row_cnt, const int32_t* row_idx,
                                  const int32_t* row_order, float scale, void* dq, const SplitPlan& plan,

@@ -1,7 +1,7 @@
 // Which column (or part of one) a workgroup of the dK/dV kernel works on, and which one next.
 //
 // A launch has one item per column that is not split, and one per part of a split column.  Items are dealt to the eight
-// XCDs: parts round-robin, columns by xcd_map, in both kinds of launch.
+// XCDs: parts round-robin, columns by xcd_map or in stretches (columns_in_stretches), in both kinds of launch.
 //   * Direct launch: one workgroup per item, the parts first.  For launches that fit the chip at once, and where the
 //     caller gave no workspace.
 //   * Queue launch (sp.queue): as many workgroups as the compute units hold stay for the whole launch and take items of
@@ -83,30 +83,45 @@ struct Walk {
     it.part = 0; it.parts = 0; it.part_len = 0; it.slot = 0;
     auto part = [&](int g) {                             // part g of the plan's table
       const int32_t* pt = sp.part_table + 4 * g;
-      it.bh = pt[0] / units_per_head; it.blk = pt[0] % units_per_head;
-      it.part = pt[1]; it.parts = pt[2]; it.part_len = pt[3];
+      const int unit = scalar_ld(pt);
+      it.bh = unit / units_per_head; it.blk = unit % units_per_head;
+      it.part = scalar_ld(pt + 1); it.parts = scalar_ld(pt + 2); it.part_len = scalar_ld(pt + 3);
       it.slot = g;
     };
     // position it.blk of the schedule -> block by the caller's launch order, then: is it one to walk whole?
     auto whole = [&]() -> bool {
-      if (order) it.blk = min(max(order[(int64_t)it.bh * units_per_head + it.blk], 0), units_per_head - 1);   // caller data
-      return sp.pool_slots == 0 || sp.unit_slot[(int64_t)it.bh * units_per_head + it.blk] < 0;
+      if (order) it.blk = min(max(scalar_ld(order + (int64_t)it.bh * units_per_head + it.blk), 0), units_per_head - 1);   // caller data
+      return sp.pool_slots == 0 || scalar_ld(sp.unit_slot + (int64_t)it.bh * units_per_head + it.blk) < 0;
+    };
+    const int units = heads * units_per_head;
+    auto in_stretch = [&](int x, int s) -> bool {        // place s of XCD x's stretch: `order` is the list of all of them
+      const int at = stretch_first(units, x) + s;
+      if (at >= stretch_first(units, x + 1)) return false;
+      const int u = min(max(scalar_ld(order + at), 0), units - 1);
+      it.bh = u / units_per_head; it.blk = u % units_per_head;
+      return scalar_ld(sp.unit_slot + u) < 0;
     };
     if (!sp.queue) {
       // parts first, whole columns right behind them (at a multiple of eight: the workgroup -> XCD phase stays).  The
       // host does not know the number of parts and launches room for the whole pool: what is too much comes last.
       // (Between the two it kept the columns of 24 heads of 21, 332 parts in front, waiting for 10 us: 51.7 / 49.1 us.)
-      const int g = blockIdx.x, n = sp.pool_slots ? sp.header[0] : 0, wg = g - ((n + 7) & ~7);
+      const int g = blockIdx.x, n = sp.pool_slots ? scalar_ld(sp.header) : 0, wg = g - ((n + 7) & ~7);
       if (g < n) {
         part(g);
         return true;
       }
-      if (wg < 0 || wg >= xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS)) return false;
+      if (wg < 0) return false;
+      // (eighths of unlike work: the stretches in turn, so that every XCD gets the same)
+      if (sp.stretches) return in_stretch((scalar_ld(sp.header + 2) != 0 ? wg : wg + (wg >> 3)) & 7, wg >> 3);
+      if (wg >= xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS)) return false;
       const HeadBlock hb = xcd_map(wg, units_per_head, chunk, SHORT_COLUMNS);
       it.bh = hb.bh; it.blk = hb.blk;
       return hb.valid && whole();
     }
-    const int n_parts = sp.header[0], wgs = xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS);
+    const int n_parts = scalar_ld(sp.header), wgs = xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS);
+    auto share = [&](int x) -> int {
+      return sp.stretches ? stretch_first(units, x + 1) - stretch_first(units, x) : xcd_map_share(wgs, x);
+    };
     for (;;) {
       const int np = (n_parts - xcd + 7) >> 3;           // parts g = 8 q + xcd < n_parts
       if (q < np) {
@@ -114,15 +129,19 @@ struct Walk {
         return true;
       }
       const int s = q - np;
-      if (s < xcd_map_share(wgs, xcd)) {
-        const HeadBlock hb = xcd_map(8 * s + xcd, units_per_head, chunk, SHORT_COLUMNS);
-        it.bh = hb.bh; it.blk = hb.blk;
-        if (hb.valid && whole()) return true;
+      if (s < share(xcd)) {
+        if (sp.stretches) {
+          if (in_stretch(xcd, s)) return true;
+        } else {
+          const HeadBlock hb = xcd_map(8 * s + xcd, units_per_head, chunk, SHORT_COLUMNS);
+          it.bh = hb.bh; it.blk = hb.blk;
+          if (hb.valid && whole()) return true;
+        }
       } else {                                           // this XCD is through: on to the one with most items left
         __syncthreads();
         if (wave == 0) {
           const int x = fresh_lane() & 7;
-          int left = xcd_map_share(wgs, x) + ((n_parts - x + 7) >> 3) -
+          int left = share(x) + ((n_parts - x + 7) >> 3) -
                      __hip_atomic_load(counter(sp, x), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
           left = left > 0 ? 8 * left + x : -1;
 #pragma unroll

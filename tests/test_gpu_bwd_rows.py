@@ -14,15 +14,22 @@ pytestmark = pytest.mark.gpu
 
 # one block; a head of 64 and of 65 key blocks (edges of the listing and ranking workgroups), of 21 (blocks dealt in turn);
 # runs of query blocks longer than a register holds (513 > 4 x 64 query blocks); more columns than a direct launch takes;
-# 4096 and 4097 key blocks, on either side of what the dQ launch orders
+# 4096 and 4097 key blocks, on either side of what the dQ launch orders; 32,768 and 33,390 columns in all, on either side of
+# what it lists in stretches; launches from a queue (4,100 columns) and direct ones, in one round and in several
 @pytest.mark.parametrize("B,H,N,d", [(1, 1, 40, 128), (2, 3, 4096, 64), (1, 2, 4100, 128), (4, 6, 1281, 128), (1, 1, 65600, 64),
-                                     (1, 12, 11200, 64), (1, 1, 262144, 64), (1, 1, 262145, 64)])
-def test_backward_from_the_mask_gives_the_bits_of_columns_and_backward(B, H, N, d):
+                                     (1, 12, 11200, 64), (1, 1, 262144, 64), (1, 1, 262145, 64), (8, 64, 4096, 64),
+                                     (6, 105, 3392, 64), (1, 41, 6400, 128), (1, 25, 3900, 128)])
+@pytest.mark.parametrize("alike", [True, False])
+def test_backward_from_the_mask_gives_the_bits_of_columns_and_backward(B, H, N, d, alike):
     w = wl.Workload("rows", B, H, N, d, 0.05, 0.3, "lowrank", True)
-    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=2))
+    q, k, v, do = (t.to(dev()) for t in wl.make_inputs(w, seed=2, **({"device": "cuda"} if B * H > 100 else {})))
     scale = d ** -0.5
-    pat, _ = gpu_mask(q, k, spa2.spa2_topk_blocks(0.05 if N < 200000 else 0.002, -(-N // 64)), 0.3 if N < 200000 else 0.0,
-                      scale, want_pbar=False)
+    if not alike:                       # the first heads select everything that the others select a few blocks of
+        if N > 20000:
+            pytest.skip("one size of head is enough")
+        q[:, :max(1, H // 8)] *= 0.01
+    pat, _ = gpu_mask(q, k, spa2.spa2_topk_blocks(0.05 if N < 200000 else 0.002, -(-N // 64)),
+                      (0.3 if alike else 0.7) if N < 200000 else 0.0, scale, want_pbar=False)
     o, lse, o_res = gpu_fwd(q, k, v, pat, scale, residual=True)
     want = gpu_bwd(q, k, v, o, do, lse, pat, scale, o_res=o_res)
     lib, g, lay = spa2.binding._load(), Guarded(), spa2.binding._layout_of(q)
