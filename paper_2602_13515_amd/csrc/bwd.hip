@@ -90,7 +90,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   // (S^T) and transposed (dQ^T), V along rows (dP^T).  (Aligned: compile-time parts are XORed into addresses.)
   constexpr int TILE_B = BKV * D * 2, STAGE_B = 2 * TILE_B;
   __shared__ __align__(1024) unsigned char smem[2 * STAGE_B];   // stage s: K tile, then V tile
-  static_assert(sizeof(PlanLds<256>) <= 2 * STAGE_B && sizeof(OrderLds<SIDE_ORDER_MAX, 4>) <= 2 * STAGE_B &&
+  static_assert(sizeof(PlanLds<256>) <= 2 * STAGE_B && sizeof(OrderLds<SIDE_ORDER_MAX, 4, 64>) <= 2 * STAGE_B &&
                 sizeof(ListLds) <= 2 * STAGE_B, "other work fits the tiles' LDS");
 
   // Which row, and which part of its list (see fwd.hip: the first sp.pool_slots workgroups are the parts of split rows)
@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256, 2) void dq_kernel(DqArgs a) {
   if ((int)blockIdx.x >= (int)gridDim.x - a.orders) {
     const int o = (int)blockIdx.x - ((int)gridDim.x - a.orders);
     if (a.stretches) list_block(a.col_list, o / a.col_list.groups, o % a.col_list.groups, *(ListLds*)smem);
-    else order_block<SIDE_ORDER_MAX, 4>(a.col_order, o / a.col_order.groups, o % a.col_order.groups, *(OrderLds<SIDE_ORDER_MAX, 4>*)smem);
+    else order_block(a.col_order, o / a.col_order.groups, o % a.col_order.groups, *(OrderLds<SIDE_ORDER_MAX, 4, 64>*)smem);
     return;
   }
   if (slot < a.sp.pool_slots) {
@@ -357,7 +357,7 @@ static hipError_t launch_dq(const void* q, const void* k, const void* v, const v
     a.col_list = list_args(col_cnt, m, col_order, (int64_t)m.B * m.H * m.Tn <= 3 * col_plan->resident);
     a.orders = 8 * a.col_list.groups;
   } else if (col_plan && col_order) {
-    a.col_order = order_args(col_cnt, m, col_order);
+    a.col_order = order_args(col_cnt, m, col_order, 64);
     a.orders = m.B * m.H * a.col_order.groups;
   }
   const int rows = launched_rows(a.BH, a.Tm, a.chunk);

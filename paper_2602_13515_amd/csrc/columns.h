@@ -6,25 +6,25 @@
 
 namespace spa2 {
 
-// One workgroup lists 64 key blocks of one head: thread (seg, c) takes one of SEGS runs of query blocks of column c,
+// One workgroup lists COLS key blocks of one head: thread (seg, c) takes one of SEGS runs of query blocks of column c,
 // reads its mask bytes into one bit each (COL_BATCH loads in flight), and, after the counts of the column's runs have
 // been exchanged through LDS, writes its ascending piece of the list at the right offset.  Runs of up to 64 query
 // blocks (T_m <= 64 SEGS) stay in a register between the two steps; longer ones are read again, 64 at a time.
 // Bound: load latency; a loop that read one byte at a time, twice, took 33 us for 4 heads of 1024 x 2048 blocks and 56 us
-// for 40 of 591 x 1182, this takes 12 and 26 us with the sixteen runs of a launch of its own.
-constexpr int COL_SEGS = 16, COL_BATCH = 16;
+// for 40 of 591 x 1182; as a launch of its own, with 64 columns a workgroup, this takes 12 and 26 us.
+constexpr int COL_BATCH = 16;
 struct ColumnArgs {
   const uint8_t* mask; int32_t* col_cnt; int32_t* col_idx;
-  int Tm, Tn, groups;          // groups of 64 key blocks a head
+  int Tm, Tn, groups;          // groups of `cols` key blocks a head
 };
-inline ColumnArgs column_args(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx) {
-  return ColumnArgs{mask, col_cnt, col_idx, m.Tm, m.Tn, (m.Tn + 63) / 64};
+inline ColumnArgs column_args(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx, int cols) {
+  return ColumnArgs{mask, col_cnt, col_idx, m.Tm, m.Tn, (m.Tn + cols - 1) / cols};
 }
-template <int SEGS>
-__device__ __forceinline__ void columns_block(const ColumnArgs& a, int bh, int group, int (&seg_cnt)[SEGS][64]) {
+template <int SEGS, int COLS>
+__device__ __forceinline__ void columns_block(const ColumnArgs& a, int bh, int group, int (&seg_cnt)[SEGS][COLS]) {
   const int Tm = a.Tm, Tn = a.Tn;
-  const int c = threadIdx.x & 63, seg = threadIdx.x >> 6;
-  const int j = group * 64 + c;
+  const int c = threadIdx.x % COLS, seg = threadIdx.x / COLS;
+  const int j = group * COLS + c;
   const int per = (Tm + SEGS - 1) / SEGS;
   const int i0 = min(Tm, seg * per), i1 = min(Tm, i0 + per);
   const bool live = j < Tn;
@@ -64,35 +64,34 @@ __device__ __forceinline__ void columns_block(const ColumnArgs& a, int bh, int g
 // first), dealt round-robin to the eight XCD chunks of the schedule (position x*chunk + s belongs to XCD x), so that
 // every XCD gets the same mix of long and short columns and the long ones start early.  (Heads of up to SHORT_COLUMNS are
 // launched position by position (xcd_map): there neighbouring positions, chunks of the order, are what mixes the lengths.)
-// A column's rank is the number of columns that precede it in that order, counted directly: a workgroup ranks 64
+// A column's rank is the number of columns that precede it in that order, counted directly: a workgroup ranks COLS
 // columns of a head against all of them, SEGS threads a column, the head's keys in LDS.  (T_n^2 comparisons, but
 // no chain of dependent steps: the bitonic sort of a head by one workgroup before took 11.6 us at 512 columns of 12
-// heads and 23.6 us at 2048 columns of 4, this takes 4.8 and 5.5 us with the sixteen threads of a launch of its own.)
-constexpr int RANK_SEGS = 16;
+// heads and 23.6 us at 2048 columns of 4, this takes 4.8 and 5.5 us with the 1024 threads of a launch of its own.)
 struct OrderArgs {
   const int32_t* col_cnt; int32_t* col_order;
   int Tn, groups;
 };
-inline OrderArgs order_args(const int32_t* col_cnt, const Dims& m, int32_t* col_order) {
-  return OrderArgs{col_cnt, col_order, m.Tn, (m.Tn + 63) / 64};
+inline OrderArgs order_args(const int32_t* col_cnt, const Dims& m, int32_t* col_order, int cols) {
+  return OrderArgs{col_cnt, col_order, m.Tn, (m.Tn + cols - 1) / cols};
 }
-template <int NP, int SEGS>
+template <int NP, int SEGS, int COLS>
 struct OrderLds {
   __attribute__((aligned(16))) uint32_t keys[NP];
-  uint32_t before[SEGS][64];
+  uint32_t before[SEGS][COLS];
 };
-template <int NP, int SEGS>
-__device__ __forceinline__ void order_block(const OrderArgs& a, int bh, int group, OrderLds<NP, SEGS>& lds) {
+template <int NP, int SEGS, int COLS>
+__device__ __forceinline__ void order_block(const OrderArgs& a, int bh, int group, OrderLds<NP, SEGS, COLS>& lds) {
   const int Tn = a.Tn;
   auto &keys = lds.keys;
   auto &before = lds.before;
-  const int tid = threadIdx.x, c = tid & 63, seg = tid >> 6;
+  const int tid = threadIdx.x, c = tid % COLS, seg = tid / COLS;
   const int padded = (Tn + 4 * SEGS - 1) / (4 * SEGS) * (4 * SEGS);      // (Tn <= NP: fits)
   const int per = padded / SEGS;                       // keys that one thread compares with, a multiple of four
-  for (int j = tid; j < padded; j += 64 * SEGS)        // distinct keys: length, then lower index; padding below all
+  for (int j = tid; j < padded; j += COLS * SEGS)      // distinct keys: length, then lower index; padding below all
     keys[j] = j < Tn ? ((uint32_t)min(a.col_cnt[(int64_t)bh * Tn + j], 0xffff) << 16) | (uint32_t)(0xffff - j) : 0u;
   __syncthreads();
-  const int j = group * 64 + c;
+  const int j = group * COLS + c;
   const uint32_t mine = keys[min(j, Tn - 1)];
   uint32_t n = 0;
   for (int x = seg * per; x < min((seg + 1) * per, Tn); x += 4) {       // (a wave reads one address: broadcast)

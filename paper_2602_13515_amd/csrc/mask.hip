@@ -843,28 +843,41 @@ hipError_t launch_select(const float* qbar, const float* kbar, const Dims& m, in
 }
 
 // ------------------------------------------------------------------ column lists
-__global__ __launch_bounds__(64 * COL_SEGS) void columns_kernel(ColumnArgs a) {
-  __shared__ int seg_cnt[COL_SEGS][64];
-  columns_block<COL_SEGS>(a, blockIdx.y, blockIdx.x, seg_cnt);
+// Workgroups of 1024 threads; how many key blocks they share is the launch's choice (see launch_columns).
+template <int COLS>
+__global__ __launch_bounds__(1024) void columns_kernel(ColumnArgs a) {
+  __shared__ int seg_cnt[1024 / COLS][COLS];
+  columns_block(a, blockIdx.y, blockIdx.x, seg_cnt);
 }
 
-template <int NP>
-__global__ __launch_bounds__(64 * RANK_SEGS) void col_order_kernel(OrderArgs a) {
-  __shared__ OrderLds<NP, RANK_SEGS> lds;
-  order_block<NP, RANK_SEGS>(a, blockIdx.y, blockIdx.x, lds);
+template <int NP, int COLS>
+__global__ __launch_bounds__(1024) void col_order_kernel(OrderArgs a) {
+  __shared__ OrderLds<NP, 1024 / COLS, COLS> lds;
+  order_block(a, blockIdx.y, blockIdx.x, lds);
+}
+
+template <int COLS>
+static void launch_columns_of(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx, int32_t* col_order,
+                              hipStream_t stream) {
+  const ColumnArgs c = column_args(mask, m, col_cnt, col_idx, COLS);
+  const dim3 grid((unsigned)c.groups, (unsigned)(m.B * m.H)), block(1024);
+  hipLaunchKernelGGL(columns_kernel<COLS>, grid, block, 0, stream, c);
+  if (!col_order) return;
+  const OrderArgs a = order_args(col_cnt, m, col_order, COLS);
+  if (m.Tn <= 512)       hipLaunchKernelGGL((col_order_kernel<512, COLS>), grid, block, 0, stream, a);
+  else if (m.Tn <= 2048) hipLaunchKernelGGL((col_order_kernel<2048, COLS>), grid, block, 0, stream, a);
+  else                   hipLaunchKernelGGL((col_order_kernel<8192, COLS>), grid, block, 0, stream, a);
 }
 
 hipError_t launch_columns(const uint8_t* mask, const Dims& m, int32_t* col_cnt, int32_t* col_idx,
                           int32_t* col_order, hipStream_t stream) {
-  const dim3 grid((unsigned)((m.Tn + 63) / 64), (unsigned)(m.B * m.H));
-  hipLaunchKernelGGL(columns_kernel, grid, dim3(64 * COL_SEGS), 0, stream, column_args(mask, m, col_cnt, col_idx));
-  if (col_order) {
-    const dim3 b2(64 * RANK_SEGS);
-    const OrderArgs a = order_args(col_cnt, m, col_order);
-    if (m.Tn <= 512)       hipLaunchKernelGGL(col_order_kernel<512>, grid, b2, 0, stream, a);
-    else if (m.Tn <= 2048) hipLaunchKernelGGL(col_order_kernel<2048>, grid, b2, 0, stream, a);
-    else                   hipLaunchKernelGGL(col_order_kernel<8192>, grid, b2, 0, stream, a);
-  }
+  // With 64 columns a workgroup, launches of up to 128 leave half the compute units idle; with 32 each thread's run of rows is
+  // half as long as well, which counts where it takes more than one round of loads (T_m > 256).  us, both launches, 64 / 32:
+  // 1 head of 131,072 tokens 14.3 / 10.3, 4 heads (128 workgroups) 16.6 / 12.3, 5 heads 17.1 / 19.3, 8 heads 17.8 / 23.8;
+  // 1 head of 262,144 28.3 / 15.6; 4 of 65,536 14.5 / 12.0; 12 of 32,768 10.2 / 10.3; 24 of 4096 10.1 / 11.3.
+  const bool few = (int64_t)m.B * m.H * ((m.Tn + 63) / 64) <= 128 && m.Tm > 256;
+  if (few) launch_columns_of<32>(mask, m, col_cnt, col_idx, col_order, stream);
+  else     launch_columns_of<64>(mask, m, col_cnt, col_idx, col_order, stream);
   return hipGetLastError();
 }
 

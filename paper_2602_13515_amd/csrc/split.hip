@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(PrepareArgs a) {
   }
   w -= a.n_plans;
   if (w < a.n_cols) {
-    columns_block<4>(a.cols, w / a.cols.groups, w % a.cols.groups, lds.seg_cnt);
+    columns_block<4, 64>(a.cols, w / a.cols.groups, w % a.cols.groups, lds.seg_cnt);
     return;
   }
   w -= a.n_cols;
@@ -170,7 +170,7 @@ hipError_t launch_bwd_prepare_columns(const void* o, const void* o_res, const vo
   PrepareArgs a = {};
   a.d = delta_args(o, o_res, d_o, m, delta);
   if (row_plan.pool_slots) a.plan[a.n_plans++] = plan_args(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, row_plan);
-  a.cols = column_args(mask, m, col_cnt, col_idx);
+  a.cols = column_args(mask, m, col_cnt, col_idx, 64);
   a.n_cols = m.B * m.H * a.cols.groups;
   return launch_prepare(a, m, stream);
 }
