@@ -54,7 +54,7 @@ struct PlanLds {
   i32x4 item[SPLIT_POOL_MAX / 2];                    // (unit, first slot, parts, entries per part) of a split unit
   unsigned long long red[NT / 64];
   int wave_slots[NT / 64], wave_items[NT / 64];
-  unsigned long long work[8];                        // list entries of every eighth of the units
+  unsigned long long work[8][32];                    // list entries of every eighth of the units, in 32 shares
   uint16_t owner[SPLIT_POOL_MAX];                    // slot -> entry of the list of split units
 };
 template <int NT>
@@ -85,20 +85,29 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
       f(u, c);
     }
   };
-  if (t < 8) lds.work[t] = 0;
+  // (shares by lane: with one counter an eighth the 64 atomics of a wave stood in a row: 23,640 units 19.8 / 16.3 us, 942 units
+  // 8.0 / 7.4)
+  for (int x = t; x < 8 * 32; x += NT) lds.work[x / 32][x % 32] = 0;
   __syncthreads();
   const float eighth = 8.f / (float)a.units;
   each_quad([&](int u, const i32x4& c) {
     const int x0 = min((int)((float)u * eighth), 7), x3 = min((int)((float)(u + 3) * eighth), 7);
-    if (x0 == x3) atomicAdd(&lds.work[x0], (unsigned long long)c[0] + c[1] + c[2] + c[3]);
+    if (x0 == x3) atomicAdd(&lds.work[x0][t % 32], (unsigned long long)c[0] + c[1] + c[2] + c[3]);
     else
 #pragma unroll
-      for (int e = 0; e < 4; ++e) atomicAdd(&lds.work[min((int)((float)(u + e) * eighth), 7)], (unsigned long long)c[e]);
+      for (int e = 0; e < 4; ++e) atomicAdd(&lds.work[min((int)((float)(u + e) * eighth), 7)][t % 32], (unsigned long long)c[e]);
   });
   __syncthreads();
-  long long T = 0, most = 0;
+  long long T = 0, most = 0;                         // (every wave adds up all shares: a lane four of one eighth)
+  {
+    const int x = lane >> 3, k = 4 * (lane & 7);
+    T = (long long)(lds.work[x][k] + lds.work[x][k + 1] + lds.work[x][k + 2] + lds.work[x][k + 3]);
 #pragma unroll
-  for (int x = 0; x < 8; ++x) { T += (long long)lds.work[x]; most = max(most, (long long)lds.work[x]); }
+    for (int off = 1; off < 8; off <<= 1) T += __shfl_xor(T, off, 64);
+    most = T;
+#pragma unroll
+    for (int off = 8; off < 64; off <<= 1) { T += __shfl_xor(T, off, 64); most = max(most, (long long)__shfl_xor(most, off, 64)); }
+  }
   const long long s_small = min(max((T + a.resident - 1) / a.resident, (long long)a.lo), (long long)a.mid);
   const long long s_large = max(min((T + 4 * a.resident - 1) / (4 * a.resident), (long long)SPLIT_CAP),
                                 (T + 16 * a.resident - 1) / (16 * a.resident));
