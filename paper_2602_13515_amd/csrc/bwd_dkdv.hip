@@ -67,7 +67,7 @@ __device__ __forceinline__ void dkdv_merge(const DkvArgs& a, const WorkItem& ite
   }
 }
 
-// One workgroup of two waves per key block j (64 keys); one wave per SIMD (512 registers), four waves per CU.
+// Head dimension 128: one workgroup of two waves per key block j (64 keys); one wave per SIMD (512 registers), four per CU.
 // The query blocks that selected j are taken in halves of 64 rows; wave w owns the 32 queries 32w.. of the half
 // and ALL 64 keys of the block.  It keeps K_j^T, V_j^T (B operands) and its dK^T, dV^T accumulators (d x 64
 // keys each) in registers for the whole column, so every operand fragment that comes from LDS feeds two MFMAs
@@ -91,7 +91,7 @@ __device__ __forceinline__ void dkdv_merge(const DkvArgs& a, const WorkItem& ite
 // Bound: the board's power, then issue slots: 3480 cycles a step for 2048 of matrix products (4170 before this order,
 // when dS of the first 16 queries had no product to hide behind, LSE and D were waited for as they were read and every
 // copy stood behind a branch), 1.80 instead of 1.95 GHz.  Measured, us, before / after: 75,600 tokens, 40 heads
-// 14772 / 13440; 32,760 tokens, 12 heads 1026 / 921; 20,010 tokens, 6 heads, d = 64 155 / 134.
+// 14772 / 13440; 32,760 tokens, 12 heads 1026 / 921.
 // The two waves add their partial sums through LDS at the end of the column.
 template <int D>
 __device__ __forceinline__ void dkdv_item(const DkvArgs& a, const WorkItem& item, Walk& walk, unsigned char* smem,

@@ -9,9 +9,10 @@
 // the order of execution.
 //
 // The plan is computed on the device from the list lengths (the host never reads the pattern):
-//   T = total number of list entries of the launch (512 below: workgroups that run at a time, 1024 for dK/dV at d = 64),
+//   T = total number of list entries of the launch,
 //   S = max(min(max(T / 512, lo), mid), min(T / 2048, 48), T / 8192)   (quotients rounded up),
-// with quotients of 1024, 4096 and 16384 for dK/dV at d = 64, whose launches run twice as many workgroups at a time.  Small launches are cut until the slots
+// with 512 (RESIDENT_WGS) the number of workgroups that run at a time; dK/dV at d = 64 runs 1024, and its divisors are
+// twice these.  Small launches are cut until the slots
 // are filled, down to lo entries, below which a part is mostly prologue and merge; ordinary ones into quarters of the
 // mean work of a slot, but not below mid (parts of 8 instead of 16 cost more than they balance) nor above 48; on the
 // largest only lists of more than a sixteenth of a slot's mean work are cut, which the natural launch order would
