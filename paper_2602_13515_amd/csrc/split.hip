@@ -104,7 +104,7 @@ PlanArgs plan_args(const int32_t* cnt, int64_t units, int list_max, SplitKind ki
   a.cnt = cnt; a.units = (int)units; a.list_max = list_max;
   split_range(kind, units, a.lo, a.mid);
   a.pool = kind == SPLIT_DKDV ? p.pool_slots - 1 : p.pool_slots;      // (the last slot is the queue's, whether there is one or not)
-  a.queue = p.queue; a.resident = p.resident;
+  a.queue = p.queue; a.slots_log2 = __builtin_ctz(p.resident); a.eighths = p.stretches;
   a.header = (int32_t*)p.header; a.unit_slot = (int32_t*)p.unit_slot; a.part_table = (int32_t*)p.part_table;
   a.arrive = p.arrive;
   return a;

@@ -11,7 +11,9 @@ constexpr int SPLIT_CAP = 48;
 // What one plan reads and writes.
 struct PlanArgs {
   const int32_t* cnt;
-  int units, list_max, lo, mid, pool, resident;
+  int units, list_max, lo, mid, pool;
+  int slots_log2;              // of the workgroups that run at a time
+  bool eighths;                // header[2] is read (SplitPlan::stretches)
   int32_t* header; int32_t* unit_slot; int32_t* part_table; int32_t* arrive; int32_t* queue;
 };
 
@@ -85,32 +87,41 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
       f(u, c);
     }
   };
-  // (shares by lane: with one counter an eighth the 64 atomics of a wave stood in a row: 23,640 units 19.8 / 16.3 us, 942 units
-  // 8.0 / 7.4)
-  for (int x = t; x < 8 * 32; x += NT) lds.work[x / 32][x % 32] = 0;
-  __syncthreads();
-  const float eighth = 8.f / (float)a.units;
-  each_quad([&](int u, const i32x4& c) {
-    const int x0 = min((int)((float)u * eighth), 7), x3 = min((int)((float)(u + 3) * eighth), 7);
-    if (x0 == x3) atomicAdd(&lds.work[x0][t % 32], (unsigned long long)c[0] + c[1] + c[2] + c[3]);
-    else
+  // The work of the eighths is summed only where it is read, and the shares of the slots are shifts: plan launch, us, without
+  // eighths at all / summed always, with divisions / this: 942 units 6.0 / 7.1 / 6.5, 768 6.7 / 8.6 / 8.0, 3072 8.5 / 9.2 / 8.4,
+  // 23,640 (nobody reads them) 13.8 / 14.5 / 13.5, 2048 (nobody) 9.0 / 9.7 / 9.2.
+  long long T = 0, most = 0;
+  if (!a.eighths) {
+    unsigned long long mine = 0;
+    each_quad([&](int, const i32x4& c) { mine += (unsigned long long)c[0] + c[1] + c[2] + c[3]; });
+    T = (long long)block_sum<NT>(mine, red);
+  } else {
+    // (shares by lane: the 64 atomics of a wave on one counter stand in a row, 942 units 8.0 us)
+    for (int x = t; x < 8 * 32; x += NT) lds.work[x / 32][x % 32] = 0;
+    __syncthreads();
+    const float eighth = 8.f / (float)a.units;
+    each_quad([&](int u, const i32x4& c) {
+      const int x0 = min((int)((float)u * eighth), 7), x3 = min((int)((float)(u + 3) * eighth), 7);
+      if (x0 == x3) atomicAdd(&lds.work[x0][t % 32], (unsigned long long)c[0] + c[1] + c[2] + c[3]);
+      else
 #pragma unroll
-      for (int e = 0; e < 4; ++e) atomicAdd(&lds.work[min((int)((float)(u + e) * eighth), 7)][t % 32], (unsigned long long)c[e]);
-  });
-  __syncthreads();
-  long long T = 0, most = 0;                         // (every wave adds up all shares: a lane four of one eighth)
-  {
-    const int x = lane >> 3, k = 4 * (lane & 7);
-    T = (long long)(lds.work[x][k] + lds.work[x][k + 1] + lds.work[x][k + 2] + lds.work[x][k + 3]);
+        for (int e = 0; e < 4; ++e) atomicAdd(&lds.work[min((int)((float)(u + e) * eighth), 7)][t % 32], (unsigned long long)c[e]);
+    });
+    __syncthreads();
+    // (every wave adds up all shares: a lane four of one eighth)
+    {
+      const int x = lane >> 3, k = 4 * (lane & 7);
+      T = (long long)(lds.work[x][k] + lds.work[x][k + 1] + lds.work[x][k + 2] + lds.work[x][k + 3]);
 #pragma unroll
-    for (int off = 1; off < 8; off <<= 1) T += __shfl_xor(T, off, 64);
-    most = T;
+      for (int off = 1; off < 8; off <<= 1) T += __shfl_xor(T, off, 64);
+      most = T;
 #pragma unroll
-    for (int off = 8; off < 64; off <<= 1) { T += __shfl_xor(T, off, 64); most = max(most, (long long)__shfl_xor(most, off, 64)); }
+      for (int off = 8; off < 64; off <<= 1) { T += __shfl_xor(T, off, 64); most = max(most, (long long)__shfl_xor(most, off, 64)); }
+    }
   }
-  const long long s_small = min(max((T + a.resident - 1) / a.resident, (long long)a.lo), (long long)a.mid);
-  const long long s_large = max(min((T + 4 * a.resident - 1) / (4 * a.resident), (long long)SPLIT_CAP),
-                                (T + 16 * a.resident - 1) / (16 * a.resident));
+  auto share = [&](int k) -> long long { return (T + (1ll << k) - 1) >> k; };       // T / 2^k, rounded up
+  const long long s_small = min(max(share(a.slots_log2), (long long)a.lo), (long long)a.mid);
+  const long long s_large = max(min(share(a.slots_log2 + 2), (long long)SPLIT_CAP), share(a.slots_log2 + 4));
   int S = (int)max(min(max(s_small, s_large), (long long)a.list_max), 1ll);
   float inv_s;
   int n_slots, n_items;                              // of this thread's units
@@ -172,8 +183,8 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
     *(i32x4*)(a.part_table + 4 * g) = i32x4{it[0], g - it[1], it[2], it[3]};
     a.arrive[g] = 0;
   }
-  if (t == 0) { a.header[0] = n; a.header[1] = S; a.header[2] = 8 * most <= T + T / 16 ? 1 : 0; }
-  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = a.resident / 8;      // (the first ones go by workgroup number)
+  if (t == 0) { a.header[0] = n; a.header[1] = S; a.header[2] = 8 * most <= T + T / 16 ? 1 : 0; }      // (1 where nobody asks)
+  if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = 1 << (a.slots_log2 - 3);      // (the first ones go by workgroup number)
 }
 
 }  // namespace spa2

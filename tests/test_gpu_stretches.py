@@ -42,3 +42,17 @@ def test_rows_in_stretches_and_by_heads(H, N, d, alike):
     assert int(ws[:12].view(torch.int32)[2]) == int(even)
     if H >= 21 and N > 128:
         assert bool(even) == alike
+
+
+# heads of 511 and 512 rows, on either side of the rule: the eighths are summed only where somebody reads what comes of it
+@pytest.mark.parametrize("Tm", [511, 512])
+def test_plan_sums_the_eighths_only_where_they_are_read(Tm):
+    N = 128 * Tm
+    mask = np.zeros((1, 2, Tm, 2 * Tm), dtype=np.uint8)
+    mask[..., 0] = 1
+    mask[0, 0, :, :8] = 1                               # the first head has eight times the entries of the second
+    pat = pattern_from_mask(mask, dev())
+    q = torch.zeros((1, 2, N, 64), dtype=torch.bfloat16, device=dev())
+    ws = torch.zeros(spa2.spa2_fwd_workspace_bytes(q), dtype=torch.uint8, device=dev())
+    spa2.spa2_fwd(q, q, q, pat, 0.125, torch.empty_like(q), torch.empty((1, 2, N), device=dev()), None, ws)
+    assert int(ws[:12].view(torch.int32)[2]) == (0 if Tm < 512 else 1)
