@@ -129,11 +129,11 @@ hipError_t launch_split_plan(const int32_t* cnt, int64_t units, int list_max, Sp
 // The pass over O and dO with work of its own workgroups in front of it: the plans of the backward kernels, one workgroup
 // each (two launches of 8 to 27 us before), and, where the pattern came without them, the column lists (a launch of 4 to 27
 // us before).  Neither costs time of its own wherever the pass takes longer than they do.
-struct PrepareArgs { DeltaArgs d; PlanArgs plan[2]; int n_plans; ColumnArgs cols; int n_cols; };
+struct PrepareArgs { DeltaArgs d; PlanArgs plan[2]; int n_plans; ColumnArgs cols; int n_cols, col_width; };
 
 template <int D>
 __global__ __launch_bounds__(256) void bwd_prepare_kernel(PrepareArgs a) {
-  __shared__ union { PlanLds<256> plan; int seg_cnt[4][64]; } lds;
+  __shared__ union { PlanLds<256> plan; int cnt64[4][64], cnt32[8][32], cnt16[16][16]; } lds;
   int w = blockIdx.x;
   if (w < a.n_plans) {
     plan_block<256>(a.plan[w], lds.plan);
@@ -141,7 +141,10 @@ __global__ __launch_bounds__(256) void bwd_prepare_kernel(PrepareArgs a) {
   }
   w -= a.n_plans;
   if (w < a.n_cols) {
-    columns_block<4, 64>(a.cols, w / a.cols.groups, w % a.cols.groups, lds.seg_cnt);
+    const int bh = w / a.cols.groups, group = w % a.cols.groups;
+    if (a.col_width == 64)      columns_block(a.cols, bh, group, lds.cnt64);
+    else if (a.col_width == 32) columns_block(a.cols, bh, group, lds.cnt32);
+    else                        columns_block(a.cols, bh, group, lds.cnt16);
     return;
   }
   w -= a.n_cols;
@@ -171,7 +174,15 @@ hipError_t launch_bwd_prepare_columns(const void* o, const void* o_res, const vo
   PrepareArgs a = {};
   a.d = delta_args(o, o_res, d_o, m, delta);
   if (row_plan.pool_slots) a.plan[a.n_plans++] = plan_args(row_cnt, (int64_t)m.B * m.H * m.Tm, m.Tn, SPLIT_DQ, row_plan);
-  a.cols = column_args(mask, m, col_cnt, col_idx, 64);
+  // Columns a workgroup shares.  Long columns (runs of more than 64 query blocks a thread, read in rounds that wait for each
+  // other, and a second time) of few heads take longer than D: there fewer columns and more runs.  us, the launch, 64 / 32 / 16:
+  // 1 head of 131,072 tokens 30.6 / 18.4 / 13.9, d = 128 37.2 / 25.2 / 21.8, of 262,144 59.1 / 37.4 / 32.0, of 65,536, d = 128
+  // 18.8 / 13.0 / 12.7; 2 of 131,072 (64 workgroups) 37.0 / 25.6 / 23.4, 4 48.5 / 39.7 / 42.6, 8 89.0 / 85.9 / 92.4; 4 of 65,536
+  // 23.8 / 20.5 / 21.7; 40 of 75,600 (760) 411.9 / 416.1 / 422.2; shorter columns (T_m <= 256): within 0.8 of each other up to 12
+  // heads of 32,768, 25.6 / 26.4 / 27.2 there.
+  const int64_t wgs = (int64_t)m.B * m.H * ((m.Tn + 63) / 64);
+  a.col_width = m.Tm <= 256 || wgs > 128 ? 64 : wgs > 64 ? 32 : 16;
+  a.cols = column_args(mask, m, col_cnt, col_idx, a.col_width);
   a.n_cols = m.B * m.H * a.cols.groups;
   return launch_prepare(a, m, stream);
 }

@@ -13,12 +13,14 @@ pytestmark = pytest.mark.gpu
 
 
 # one block; a head of 64 and of 65 key blocks (edges of the listing and ranking workgroups), of 21 (blocks dealt in turn);
-# runs of query blocks longer than a register holds (513 > 4 x 64 query blocks); more columns than a direct launch takes;
+# 257 query blocks, listed 16, 32 and 64 columns a workgroup (9, 72 and 135 workgroups of 64); runs of query blocks longer than a
+# register holds (15 heads of 257, 65 a thread; one of 2048, 128 a thread); more columns than a direct launch takes;
 # 4096 and 4097 key blocks, on either side of what the dQ launch orders; 32,768 and 33,390 columns in all, on either side of
 # what it lists in stretches; launches from a queue (4,100 columns) and direct ones, in one round and in several
 @pytest.mark.parametrize("B,H,N,d", [(1, 1, 40, 128), (2, 3, 4096, 64), (1, 2, 4100, 128), (4, 6, 1281, 128), (1, 1, 65600, 64),
                                      (1, 12, 11200, 64), (1, 1, 262144, 64), (1, 1, 262145, 64), (8, 64, 4096, 64),
-                                     (6, 105, 3392, 64), (1, 41, 6400, 128), (1, 25, 3900, 128)])
+                                     (6, 105, 3392, 64), (1, 41, 6400, 128), (1, 25, 3900, 128),
+                                     (1, 1, 32832, 64), (1, 8, 32832, 64), (1, 15, 32832, 64)])
 @pytest.mark.parametrize("alike", [True, False])
 def test_backward_from_the_mask_gives_the_bits_of_columns_and_backward(B, H, N, d, alike):
     w = wl.Workload("rows", B, H, N, d, 0.05, 0.3, "lowrank", True)
