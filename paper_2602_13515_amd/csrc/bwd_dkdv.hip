@@ -672,7 +672,8 @@ void dkdv_kernel(DkvArgs) {
   __shared__ __align__(1024) unsigned char smem[2 * 2 * 64 * D * 2];
   __shared__ __align__(1024) unsigned char stat_s[2 * 2 * 512];
   __shared__ int word;
-  Walk walk(&word);
+  Walk walk(&word, fresh_args<DkvArgs>().sp);
+  if (walk.idle(fresh_args<DkvArgs>().sp)) return;
   for (;;) {
     const DkvArgs& a = fresh_args<DkvArgs>();
     WorkItem item;
@@ -700,7 +701,7 @@ hipError_t launch_bwd_dkdv(const void* q, const void* k, const void* v, const vo
     if (e != hipSuccess) return e;
   }
   const int columns = plan.stretches ? stretch_wgs(a.BH * a.Tn) : xcd_map_wgs(a.BH, a.Tn, a.chunk, SHORT_COLUMNS);
-  const dim3 grid((unsigned)(plan.queue ? plan.resident : plan.pool_slots + columns)), block(128);
+  const dim3 grid((unsigned)(plan.queue && !plan.queue_if_full ? plan.resident : plan.pool_slots + columns)), block(128);
   if (m.d == 128) hipLaunchKernelGGL(dkdv_kernel<128>, grid, block, 0, stream, a);
   else            hipLaunchKernelGGL(dkdv_kernel<64>, grid, block, 0, stream, a);
   return hipGetLastError();

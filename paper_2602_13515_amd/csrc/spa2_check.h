@@ -64,7 +64,7 @@ inline SplitPlan dq_plan(const Dims& m, void* ws, size_t ws_bytes) {
 inline SplitPlan dkdv_plan(const Dims& m, void* ws, size_t ws_bytes) {
   const BwdWs w = bwd_ws(m);
   const int64_t units = (int64_t)m.B * m.H * m.Tn;
-  return with_queue(section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, units, m.Tm, dkdv_slot_bytes(m)), units, dkdv_resident(m));
+  return with_queue(section_plan(ws, ws_bytes, w.dkdv_off, w.dkdv_bytes, units, m.Tm, dkdv_slot_bytes(m)), units, m.Tm, dkdv_resident(m));
 }
 
 // what spa2_mask asks of everything but its workspace

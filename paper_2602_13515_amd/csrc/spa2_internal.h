@@ -32,13 +32,15 @@ constexpr int RESIDENT_WGS = 512;
 inline int dkdv_resident(const Dims& m) { return m.d == 128 ? RESIDENT_WGS : 2 * RESIDENT_WGS; }     // (of the dK/dV kernel)
 constexpr int SIDE_ORDER_MAX = 4096;         // columns that a side workgroup orders: their keys have to fit the LDS of tiles
 struct SplitPlan {
-  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection), [2] see stretches
+  const int32_t* header;       // [0] number of parts, [1] S = list entries per part at most (for inspection), [2] see stretches,
+                               // [3] see queue_if_full
   const int32_t* unit_slot;    // [units] first pool slot of a split unit (its part p uses slot + p), -1 if not split
   const int32_t* part_table;   // [pool_slots][4] (unit, part, parts of the unit, list entries per part) of pool slot g
   int32_t* arrive;             // [pool_slots] parts of the unit that have left their result, at its first slot
   float* pool;                 // [pool_slots][slot_floats] fp32 partial results
   int32_t* queue;              // counters of a queue launch (work_queue.h), QUEUE_STRIDE apart, in the last slot's place; or
                                // null: direct launch
+  bool queue_if_full;          // header[3] says whether the launch, as large as a direct one, draws from the queue (with_queue)
   int pool_slots;
   int slot_floats;
   int fixed_len;               // > 0: no plan, every list is cut into parts of at most fixed_len entries (with_fixed_parts);
@@ -62,9 +64,19 @@ inline SplitPlan with_stretches(SplitPlan p, const Dims& m) {
 // Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
 // queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
 // 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.
-inline SplitPlan with_queue(SplitPlan p, int64_t units, int resident) {
+// At d = 64 (1024 at a time) also where the columns are long and of full length, or nearly (the plan says so: header[3]), and the
+// last round of a direct launch would be up to three quarters full: all end at a time there, and the last round's workgroups go
+// four to the compute units that are free first.  Every tile, us, direct / queue [one wave a SIMD, in 3 rounds of 512 instead of
+// 1.5]: 12 heads of 8192 458 / 416 [421], 11 447 / 400 [406], 18 633 / 591 [673], 24 of 4000 236 / 214 [223], 3 of 32,768 1793 / 1620
+// [1564], 48 of 2048 126 / 116 [133]; 14 of 8192 (three quarters full) 500 / 505, 16 (full) 522 / 522, 32 1038 / 1075; 96 heads of 1024
+// (8 query blocks) 70 / 66, 72 55 / 58, 600 of 128 17 / 23.  Nine tenths of the tiles: 24 of 4000 210 / 217, 12 of 8192 404 / 382; half
+// 123 / 125, 227 / 224; a tenth or less 33 / 47, 47 / 62.
+inline SplitPlan with_queue(SplitPlan p, int64_t units, int list_max, int resident) {
   p.resident = resident;
-  if (p.pool_slots && units > 4 * resident) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
+  const bool always = units > 4 * resident;
+  const int64_t last = units % resident;
+  p.queue_if_full = !always && resident > RESIDENT_WGS && list_max >= 16 && units > resident && last && 4 * last <= 3 * resident;
+  if (p.pool_slots && (always || p.queue_if_full)) p.queue = (int32_t*)(p.pool + (size_t)(p.pool_slots - 1) * p.slot_floats);
   return p;
 }
 // Columns in stretches, where spa2_bwd_rows lists them for it: heads as above, and stretches whose columns a workgroup can rank.

@@ -71,7 +71,7 @@ SplitPlan split_layout(void* ws, size_t ws_bytes, int64_t units, int list_max, s
   p.header = nullptr; p.unit_slot = nullptr; p.part_table = nullptr; p.arrive = nullptr; p.pool = nullptr;
   p.queue = nullptr;
   p.pool_slots = 0; p.slot_floats = 0; p.fixed_len = 0; p.fixed_parts = 0; p.planned = false;
-  p.resident = RESIDENT_WGS; p.stretches = false;
+  p.resident = RESIDENT_WGS; p.stretches = false; p.queue_if_full = false;
   if (!ws) return p;
   // the pool shrinks if the caller gave less than the full workspace
   int64_t pool = pool_wanted(units, list_max);

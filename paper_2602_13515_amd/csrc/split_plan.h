@@ -183,7 +183,11 @@ __device__ __forceinline__ void plan_block(const PlanArgs& a, PlanLds<NT>& lds) 
     *(i32x4*)(a.part_table + 4 * g) = i32x4{it[0], g - it[1], it[2], it[3]};
     a.arrive[g] = 0;
   }
-  if (t == 0) { a.header[0] = n; a.header[1] = S; a.header[2] = 8 * most <= T + T / 16 ? 1 : 0; }      // (1 where nobody asks)
+  if (t == 0) {
+    a.header[0] = n; a.header[1] = S;
+    a.header[2] = 8 * most <= T + T / 16 ? 1 : 0;      // (1 where nobody asks)
+    a.header[3] = 16 * T >= 15ll * a.units * a.list_max ? 1 : 0;
+  }
   if (a.queue && t < 8) a.queue[t * QUEUE_STRIDE] = 1 << (a.slots_log2 - 3);      // (the first ones go by workgroup number)
 }
 

@@ -4,7 +4,7 @@
 // XCDs: parts round-robin, columns by xcd_map or in stretches (columns_in_stretches), in both kinds of launch.
 //   * Direct launch: one workgroup per item, the parts first.  For launches that fit the chip at once, and where the
 //     caller gave no workspace.
-//   * Queue launch (sp.queue): as many workgroups as the compute units hold stay for the whole launch and take items of
+//   * Queue launch (sp.queue, see with_queue): as many workgroups as the compute units hold stay for the whole launch and take items of
 //     their XCD, in the same order, from a counter in the workspace that the plan has set; when their XCD has none left
 //     they take items of the XCD that has most.
 // Why the queue: the dispatcher deals the workgroups of an XCD to its shader engines in turn and in order, and an engine
@@ -41,17 +41,21 @@ struct WorkItem {
 };
 
 // The walk of one workgroup over its items (uniform; every thread makes every call):
-//   Walk w(word); while (w.take(...)) { ... w.draw(sp) near the end ...; w.advance(sp) }
+//   Walk w(word, sp); while (w.take(...)) { ... w.draw(sp) near the end ...; w.advance(sp) }
 // word: LDS of the caller's that is free between the barriers that advance() contains.
 struct Walk {
   int xcd, q, drawn;
   int wave;                        // number of the calling wave (scalar)
   bool out;                        // a draw is on its way
+  bool queued;
   int* word;
 
-  __device__ __forceinline__ explicit Walk(int* lds_word)
+  __device__ __forceinline__ Walk(int* lds_word, const SplitPlan& sp)
       : xcd(blockIdx.x & 7), q(blockIdx.x >> 3), drawn(0), wave(__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)),
-        out(false), word(lds_word) {}
+        out(false), queued(sp.queue && (!sp.queue_if_full || scalar_ld(sp.header + 3) != 0)), word(lds_word) {}
+
+  // a workgroup beyond those that stay, in a launch that was made for both ways (queue_if_full)
+  __device__ __forceinline__ bool idle(const SplitPlan& sp) const { return queued && (int)blockIdx.x >= sp.resident; }
 
   __device__ __forceinline__ bool first_thread() const { return wave == 0 && fresh_lane() == 0; }
 
@@ -59,14 +63,14 @@ struct Walk {
 
   // requests the number of the next item (the first one is the workgroup's own number: the counters start behind these)
   __device__ __forceinline__ void draw(const SplitPlan& sp) {
-    if (!sp.queue || out) return;
+    if (!queued || out) return;
     out = true;
     if (first_thread()) drawn = __hip_atomic_fetch_add(counter(sp, xcd), 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 
   // after an item: its number is known to all threads.  False: the launch is direct, there is no next one.
   __device__ __forceinline__ bool advance(const SplitPlan& sp) {
-    if (!sp.queue) return false;
+    if (!queued) return false;
     draw(sp);
     out = false;
     __syncthreads();                                     // (all threads are through with the LDS of this item)
@@ -101,7 +105,7 @@ struct Walk {
       it.bh = u / units_per_head; it.blk = u % units_per_head;
       return scalar_ld(sp.unit_slot + u) < 0;
     };
-    if (!sp.queue) {
+    if (!queued) {
       // parts first, whole columns right behind them (at a multiple of eight: the workgroup -> XCD phase stays).  The
       // host does not know the number of parts and launches room for the whole pool: what is too much comes last.
       // (Between the two it kept the columns of 24 heads of 21, 332 parts in front, waiting for 10 us: 51.7 / 49.1 us.)

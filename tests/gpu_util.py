@@ -123,6 +123,19 @@ def plan_headers(q, ws, names=("dq", "dkdv")):
     return {n: tuple(ws[off[n]:off[n] + 8].view(torch.int32).tolist()) for n in names}
 
 
+def dkdv_drawn(q, ws):
+    """How many items each of the eight counters of the dK/dV queue has given out, in a backward workspace of full size that was
+    zeros before the call: more than what the plan sets them to where the launch drew from the queue, just that where it was made
+    for both ways and went the direct one, nothing where there is no queue."""
+    B, H, N, d = q.shape
+    Tm, Tn = -(-N // spa2.BQ), -(-N // spa2.BKV)
+    units, per_unit, pool, up = B * H * Tn, min(max(Tm // 2, 1), 16), 8, lambda x: -(-x // 256) * 256
+    while pool < 2048 and pool < per_unit * units:
+        pool *= 2
+    at = plan_offsets(q)["dkdv"] + 256 + up(units * 4) + up(pool * 16) + up(pool * 4) + (pool - 1) * 128 * d * 4
+    return ws[at:at + 2048].view(torch.int32)[::64].tolist()
+
+
 def check_plan(name, header, lengths):
     """The plan cut every list longer than its part length, and no other.  Returns the part length."""
     parts, S = header
@@ -162,6 +175,8 @@ def gpu_bwd(q, k, v, o, do, lse, pat, scale=None, o_res=None, split=True, plans=
     g.check("spa2_bwd")
     if plans is not None:
         plans.update(plan_headers(q, ws))
+        if split:
+            plans["drawn"] = dkdv_drawn(q, ws)
     return dq, dk, dv
 
 
