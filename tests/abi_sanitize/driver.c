@@ -83,6 +83,56 @@ int main(void) {
   EXPECT(spa2_bwd_static(fake, fake, fake, fake, 0, fake, (float*)fake, &toolong, &full, 0.1f, fake, fake, fake, 0),
          SPA2_ERR_WORKSPACE);
 
+  /* the backward pass that lists the columns itself: column lists may be missing, mask and row lists may not; a workspace that is a
+     byte short, with the columns ranked by the launch of dQ (up to 4096 a head) and by one of their own */
+#define BWD_ROWS(q, k, v, o, ores, d_o, lse, s, pat, sc, dq, dk, dv, ws, n) \
+  spa2_bwd_rows(q, k, v, o, ores, d_o, (const float*)(lse), s, pat, sc, dq, dk, dv, ws, n, 0)
+#define BWD_ROWS_OF(s, pat, sc, ws, n) BWD_ROWS(fake, fake, fake, fake, 0, fake, fake, s, pat, sc, fake, fake, fake, ws, n)
+  {
+    const spa2_shape edge = shape(1, 2, 64 * 4096, 64, 128, 64, 0), beyond = shape(1, 2, 64 * 4097, 64, 128, 64, 0);
+    const spa2_shape* sizes[3] = {&ok, &edge, &beyond};
+    const spa2_shape* bad[6] = {0, &d96, &bq64, &n0, &sn132, &huge};
+    spa2_pattern no_mask = rows_only, no_cnt = rows_only, no_idx = rows_only;
+    no_mask.mask = 0; no_cnt.row_cnt = 0; no_idx.row_idx = 0;
+    for (int x = 0; x < 3; ++x) {
+      const size_t need = spa2_bwd_rows_workspace_bytes(sizes[x]);
+      if (need <= spa2_bwd_workspace_bytes(sizes[x])) { printf("bwd_rows size\n"); ++failures; }
+      EXPECT(BWD_ROWS_OF(sizes[x], &rows_only, 0.1f, fake, need - 1), SPA2_ERR_WORKSPACE);
+      EXPECT(BWD_ROWS_OF(sizes[x], &rows_only, 0.1f, 0, need), SPA2_ERR_WORKSPACE);
+      EXPECT(BWD_ROWS_OF(sizes[x], &rows_only, 0.1f, odd, need), SPA2_ERR_ALIGN);
+    }
+    for (int x = 0; x < 6; ++x)
+      if (spa2_bwd_rows_workspace_bytes(bad[x]) != 0) { printf("bwd_rows size of a bad shape\n"); ++failures; }
+    EXPECT(BWD_ROWS_OF(&ok, 0, 0.1f, fake, big), SPA2_ERR_NULL);
+    EXPECT(BWD_ROWS_OF(&ok, &none, 0.1f, fake, big), SPA2_ERR_NULL);
+    EXPECT(BWD_ROWS_OF(&ok, &no_mask, 0.1f, fake, big), SPA2_ERR_NULL);
+    EXPECT(BWD_ROWS_OF(&ok, &no_cnt, 0.1f, fake, big), SPA2_ERR_NULL);
+    EXPECT(BWD_ROWS_OF(&ok, &no_idx, 0.1f, fake, big), SPA2_ERR_NULL);
+    for (int x = 0; x < 10; ++x) {             /* each tensor missing, then misaligned (o_res may be missing, lse is fp32) */
+      void* t[10];
+      for (int y = 0; y < 10; ++y) t[y] = fake;
+      t[x] = 0;
+      if (x != 4)
+        EXPECT(BWD_ROWS(t[0], t[1], t[2], t[3], t[4], t[5], t[6], &ok, &rows_only, 0.1f, t[7], t[8], t[9], fake, big), SPA2_ERR_NULL);
+      t[x] = odd;
+      if (x != 6)
+        EXPECT(BWD_ROWS(t[0], t[1], t[2], t[3], t[4], t[5], t[6], &ok, &rows_only, 0.1f, t[7], t[8], t[9], fake, big), SPA2_ERR_ALIGN);
+    }
+    EXPECT(BWD_ROWS_OF(&ok, &rows_only, 0.0f, fake, big), SPA2_ERR_RANGE);
+    EXPECT(BWD_ROWS_OF(&ok, &rows_only, -1.0f, fake, big), SPA2_ERR_RANGE);
+    EXPECT(BWD_ROWS_OF(&ok, &rows_only, NAN, fake, big), SPA2_ERR_RANGE);
+    EXPECT(BWD_ROWS_OF(&ok, &rows_only, INFINITY, fake, big), SPA2_ERR_RANGE);
+    EXPECT(BWD_ROWS_OF(0, &rows_only, 0.1f, fake, big), SPA2_ERR_NULL);
+    EXPECT(BWD_ROWS_OF(&d96, &rows_only, 0.1f, fake, big), SPA2_ERR_UNSUPPORTED);
+    EXPECT(BWD_ROWS_OF(&bq64, &rows_only, 0.1f, fake, big), SPA2_ERR_UNSUPPORTED);
+    EXPECT(BWD_ROWS_OF(&n0, &rows_only, 0.1f, fake, big), SPA2_ERR_SHAPE);
+    EXPECT(BWD_ROWS_OF(&sn132, &rows_only, 0.1f, fake, big), SPA2_ERR_ALIGN);
+    EXPECT(BWD_ROWS_OF(&wide, &rows_only, 0.1f, fake, big), SPA2_ERR_SHAPE);
+    EXPECT(BWD_ROWS_OF(&many, &rows_only, 0.1f, fake, big), SPA2_ERR_SHAPE);
+    EXPECT(BWD_ROWS_OF(&huge, &rows_only, 0.1f, fake, big), SPA2_ERR_SHAPE);
+    EXPECT(BWD_ROWS_OF(&longrow, &rows_only, 0.1f, fake, big), SPA2_ERR_SHAPE);
+  }
+
   EXPECT(spa2_error_terms(fake, fake, (float*)fake, (float*)fake, &ok, 0, fake, big, 0), SPA2_ERR_NULL);
   EXPECT(spa2_error_terms(fake, fake, (float*)fake, (float*)fake, &ok, (double*)fake, fake, 8, 0), SPA2_ERR_WORKSPACE);
   EXPECT(spa2_vd_loss(0, fake, 8, SPA2_DTYPE_BF16, 1.0, (double*)fake, fake, big, 0), SPA2_ERR_NULL);

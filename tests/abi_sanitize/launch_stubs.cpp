@@ -30,6 +30,11 @@ hipError_t launch_bwd_dq(const void*, const void*, const void*, const void*, con
                          const int32_t*, const int32_t*, const int32_t*, float, void*, const SplitPlan&, hipStream_t) {
   reached("launch_bwd_dq");
 }
+hipError_t launch_bwd_dq_columns(const void*, const void*, const void*, const void*, const float*, const float*, const Dims&,
+                                 const int32_t*, const int32_t*, const int32_t*, float, void*, const SplitPlan&, const int32_t*,
+                                 int32_t*, const SplitPlan&, hipStream_t) {
+  reached("launch_bwd_dq_columns");
+}
 hipError_t launch_bwd_dkdv(const void*, const void*, const void*, const void*, const float*, const float*, const Dims&,
                            const int32_t*, const int32_t*, const int32_t*, float, void*, void*, const SplitPlan&, hipStream_t) {
   reached("launch_bwd_dkdv");

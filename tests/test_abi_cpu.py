@@ -104,6 +104,18 @@ def test_argument_validation_happens_on_the_host():
     args = [fake, fake, fake, fake, None, fake, fake]
     assert b(*args, ctypes.byref(ok), ctypes.byref(norows), 0.1, fake, fake, fake, fake, big, None) == -1
     assert b(*args, ctypes.byref(ok), ctypes.byref(full), 0.1, fake, fake, fake, fake, 8, None) == -6
+    # the backward pass that lists the columns itself asks for mask and row lists only
+    r = lib.spa2_bwd_rows
+    rargs = [ctypes.byref(ok), ctypes.byref(norows), 0.1, fake, fake, fake]
+    need = lib.spa2_bwd_rows_workspace_bytes(ctypes.byref(ok))
+    assert need > lib.spa2_bwd_workspace_bytes(ctypes.byref(ok))
+    assert r(*args, *rargs, fake, need - 1, None) == -6 and r(*args, *rargs, None, need, None) == -6
+    assert r(*args, *rargs, odd, need, None) == -4 and r(odd, *args[1:], *rargs, fake, need, None) == -4
+    assert r(None, *args[1:], *rargs, fake, need, None) == -1
+    assert r(*args, ctypes.byref(ok), ctypes.byref(pat), 0.1, fake, fake, fake, fake, need, None) == -1      # empty pattern
+    assert r(*args, ctypes.byref(ok), ctypes.byref(norows), 0.0, fake, fake, fake, fake, need, None) == -5
+    assert r(*args, ctypes.byref(_shape(N=64 * 8193, d=64)), ctypes.byref(norows), 0.1, fake, fake, fake, fake, 1 << 50, None) == -2
+    assert lib.spa2_bwd_rows_workspace_bytes(ctypes.byref(_shape(d=100))) == 0
     assert lib.spa2_pattern_full(ctypes.byref(ok), None, None) == -1
     vd, vg = lib.spa2_vd_loss, lib.spa2_vd_loss_grad
     assert vd(None, fake, 8, 0, 1.0, fake, fake, big, None) == -1
@@ -210,7 +222,7 @@ def test_header_is_plain_c():
 
 
 def test_argument_checks_under_host_sanitizers():
-    """The argument-check layer (csrc/api.hip, csrc/attention.hip) compiled with AddressSanitizer and UndefinedBehaviorSanitizer on the
+    """The argument-check layer (csrc/api.hip, csrc/attention.hip, csrc/backward.hip) compiled with AddressSanitizer and UndefinedBehaviorSanitizer on the
     host side, linked against launcher stubs that abort, and driven by tests/abi_sanitize/driver.c with every kind
     of rejected call: no sanitizer report, no launcher reached, every error code as documented."""
     import shutil
@@ -234,8 +246,9 @@ def test_argument_checks_under_host_sanitizers():
             [hipcc, *dev, *xsan, *inc, "-x", "hip", "-c", os.path.join(here, "launch_stubs.cpp"), "-o", o("stubs.o")],
         [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "split.hip"), "-o", o("split.o")],
             [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "attention.hip"), "-o", o("attention.o")],
+            [hipcc, *dev, *xsan, *inc, "-c", os.path.join(ROOT, "paper_2602_13515_amd", "csrc", "backward.hip"), "-o", o("backward.o")],
             [hipcc, "--offload-arch=gfx950", "-fsanitize=address", "-fsanitize=undefined", "-fno-gpu-sanitize",
-             o("api.o"), o("stubs.o"), o("split.o"), o("attention.o"), o("driver.o"), "-o", o("abi_check")],
+             o("api.o"), o("stubs.o"), o("split.o"), o("attention.o"), o("backward.o"), o("driver.o"), "-o", o("abi_check")],
         ]
         for cmd in steps:
             r = subprocess.run(cmd, capture_output=True, text=True)
