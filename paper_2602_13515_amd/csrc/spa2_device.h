@@ -293,6 +293,8 @@ __host__ __device__ __forceinline__ int rotated_row(int s, int n, int xcd) {
 // Rows (or columns) in stretches, an eighth of all of them for each XCD, one head after the other (with_stretches).
 __host__ __device__ __forceinline__ int stretch_first(int units, int xcd) { return (int)((int64_t)units * xcd >> 3); }
 __host__ __device__ __forceinline__ int stretch_wgs(int units) { return (units + 7) & ~7; }
+// The stretch that workgroup wg takes its place wg >> 3 of, where the XCDs take the stretches in turn.
+__host__ __device__ __forceinline__ int stretch_in_turn(int wg) { return (wg + (wg >> 3)) & 7; }
 __host__ __device__ __forceinline__ HeadBlock stretch_row(int wg, int heads, int blocks_per_head) {
   const int units = heads * blocks_per_head, x = wg & 7, s = wg >> 3;
   const int lo = stretch_first(units, x), n = stretch_first(units, x + 1) - lo;

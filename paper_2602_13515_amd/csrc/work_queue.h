@@ -116,7 +116,7 @@ struct Walk {
       }
       if (wg < 0) return false;
       // (eighths of unlike work: the stretches in turn, so that every XCD gets the same)
-      if (sp.stretches) return in_stretch((scalar_ld(sp.header + 2) != 0 ? wg : wg + (wg >> 3)) & 7, wg >> 3);
+      if (sp.stretches) return in_stretch(scalar_ld(sp.header + 2) != 0 ? wg & 7 : stretch_in_turn(wg), wg >> 3);
       if (wg >= xcd_map_wgs(heads, units_per_head, chunk, SHORT_COLUMNS)) return false;
       const HeadBlock hb = xcd_map(wg, units_per_head, chunk, SHORT_COLUMNS);
       it.bh = hb.bh; it.blk = hb.blk;

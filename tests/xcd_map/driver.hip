@@ -39,8 +39,44 @@ static int deal(bool rows) {
   return bad;
 }
 
+// Rows in stretches (stretch_row), columns in stretches, an XCD its own or all in turn: every one once, each XCD an eighth of them,
+// rows one head after the other but for the rotation inside groups of four.
+static int stretches() {
+  int bad = 0;
+  for (int heads : {1, 2, 5, 9, 40}) {
+    for (int blocks = 1; blocks <= 300; ++blocks) {
+      const int units = heads * blocks, wgs = stretch_wgs(units);
+      std::vector<int> row((size_t)units, 0), own((size_t)units, 0), turn((size_t)units, 0);
+      int live[8] = {0}, in_turn[8] = {0}, off = 0;
+      for (int wg = 0; wg < wgs; ++wg) {
+        const int x = wg & 7, s = wg >> 3;
+        const HeadBlock hb = stretch_row(wg, heads, blocks);
+        if (hb.valid) {
+          const int u = hb.bh * blocks + hb.blk, at = u - stretch_first(units, x);
+          if (hb.bh < 0 || hb.bh >= heads || hb.blk < 0 || hb.blk >= blocks) { ++bad; continue; }
+          ++row[u]; ++live[x];
+          off += at / 4 != s / 4;
+        }
+        if (stretch_first(units, x) + s < stretch_first(units, x + 1)) ++own[stretch_first(units, x) + s];
+        const int y = stretch_in_turn(wg);
+        if (y < 0 || y > 7) { ++bad; continue; }
+        if (stretch_first(units, y) + s < stretch_first(units, y + 1)) { ++turn[stretch_first(units, y) + s]; ++in_turn[x]; }
+      }
+      bool once = stretch_first(units, 0) == 0 && stretch_first(units, 8) == units && wgs >= units && wgs % 8 == 0;
+      for (int u = 0; u < units; ++u) once = once && row[u] == 1 && own[u] == 1 && turn[u] == 1;
+      for (int x = 0; x < 8; ++x)
+        once = once && live[x] >= units / 8 && live[x] <= (units + 7) / 8 && in_turn[x] >= units / 8 && in_turn[x] <= (units + 7) / 8;
+      if (!once || off) {
+        std::printf("stretches: %d heads of %d blocks: once %d, out of order %d\n", heads, blocks, once, off);
+        ++bad;
+      }
+    }
+  }
+  return bad;
+}
+
 int main() {
-  int bad = deal(true) + deal(false);
+  int bad = deal(true) + deal(false) + stretches();
   // 32 rows: four neighbours to every XCD (one below that, and 32 columns, are dealt in turn)
   for (int wg = 0; wg < 2 * 32; ++wg) {
     const HeadBlock hb = xcd_map_rows(wg, 32, 4);
