@@ -53,17 +53,23 @@ struct SplitPlan {
 // run on an XCD at a time are of one head or a few, whose keys and values its 4 MB of L2 then serve.  (With an eighth of every
 // head on every XCD the 64 workgroups of an XCD were of 16 heads where a head has 32 rows.)  Where heads are of unlike density,
 // so that an eighth has a sixteenth more list entries than the mean, an eighth of every head is what evens out: the plan says
-// which (header[2]).  From 512 rows an eighth of a head fills an XCD as well, and eight heads at a time do not fit the
-// memory-side cache.  Measured, us, an eighth of every head / of all (forward, dQ): 24 heads of 4000 tokens 45.2 / 39.0, 44.2 /
-// 42.1; 16 heads of 8192 75.4 / 70.7, 82.7 / 81.0; 32 heads of 8192, d = 64 202.7 / 194.3, 225.9 / 224.1; 24 heads of 32,760
-// 845 / 822, 1011 / 1004.
+// which (header[2]).  From 512 rows an eighth of a head fills an XCD as well.  Measured, us, an eighth of every head / of all
+// (forward, dQ): 24 heads of 4000 tokens 45.2 / 39.0, 44.2 / 42.1; 16 heads of 8192 75.4 / 70.7, 82.7 / 81.0; 32 heads of 8192, d = 64
+// 202.7 / 194.3, 225.9 / 224.1; 24 heads of 32,760 846 / 841, 1025 / 1014, d = 64 487 / 478, 610 / 602; 384 rows: 12 heads of 49,152
+// 945 / 947, 1140 / 1140, d = 64 526 / 517, 645 / 640; 511 rows: 6 of 65,408 810 / 808, 988 / 1002, d = 64 468 / 484, 585 / 586; 591:
+// 12 of 75,600 1996 / 2045, 2641 / 2637, d = 64 1237 / 1245, 1463 / 1485; 1024: 4 of 131,072 2055 / 2127, 2686 / 2634, d = 64 1222 /
+// 1224, 1418 / 1453.
 inline SplitPlan with_stretches(SplitPlan p, const Dims& m) {
   p.stretches = p.pool_slots && m.Tm < 512;
   return p;
 }
 // Whether a launch draws its units from a queue (work_queue.h): where every workgroup gets more than four.  dK/dV, direct /
-// queue, us: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280; d = 64: 750
-// 42.8 / 48.7, 1500 93.8 / 97.1, 3000 167.6 / 166.2.
+// queue, us, d = 128: 750 columns 51.6 / 59.3 and 66.0 / 72.8, 1500 105.0 / 103.6 and 153.4 / 155.1, 3000 289 / 280.  d = 64, a
+// twentieth of the tiles, half the rows long, nine tenths of the tiles: 1536 columns 47 / 62, 127 / 130, 407 / 400; 3584 100 / 102,
+// 252 / 257, 850 / 809; 4096 110 / 115, 286 / 292, 907 / 938; 5120 127 / 136, 354 / 355, 1134 / 1191; 8192 197 / 204, 562 / 562, 1814 /
+// 1862; 12,288 288 / 296, 863 / 864, 2694 / 2731; and in heads of 32,768 tokens 5120 378 / 393, 1519 / 1497, 4628 / 4767; 8192 543 /
+// 563, 2652 / 2447, 7442 / 7313; 12,288 791 / 816, 3922 / 3571, 10,932 / 10,859.  (Beyond the line the queue evens out long columns, up
+// to a tenth, and costs short ones a twentieth.)
 // At d = 64 (1024 at a time) also where the columns are long and of full length, or nearly (the plan says so: header[3]), and the
 // last round of a direct launch would be up to three quarters full: all end at a time there, and the last round's workgroups go
 // four to the compute units that are free first.  Every tile, us, direct / queue [one wave a SIMD, in 3 rounds of 512 instead of
@@ -83,7 +89,9 @@ inline SplitPlan with_queue(SplitPlan p, int64_t units, int list_max, int reside
 // (Eighths of unlike work: a direct launch takes the stretches in turn, a queue evens out by itself.)  Measured, us, backward
 // pass, an eighth of every head / of all: 4 samples of 1281 tokens, 6 heads 73.8 / 68.7; 24 heads of 4000 145.2 / 120.2; 6 heads
 // of 9000 165.3 / 154.7; 16 heads of 8192 269 / 246; 40 heads of 3000, d = 64 132.5 / 115.0; 20,010 tokens, 6 heads, d = 64 183.6 /
-// 176.4; 24 heads of 32,760 2805 / 2728, half the rows long 12470 / 12170.
+// 176.4; 24 heads of 32,760 2805 / 2728, half the rows long 12470 / 12170.  The line at 512 rows is that of the length in the list's
+// keys; dK/dV would gain beyond it too: 12 heads of 65,408 (511 rows) 3137 / 2975, 12 of 75,600 (591) 4038 / 3882, 4 of 131,072 (1024),
+// d = 64 2086 / 1906.
 inline SplitPlan columns_in_stretches(SplitPlan p, const Dims& m) {
   p.stretches = p.pool_slots && m.Tm < 512 && (int64_t)m.B * m.H * m.Tn <= 8 * SIDE_ORDER_MAX;
   return p;

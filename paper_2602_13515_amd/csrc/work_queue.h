@@ -11,13 +11,12 @@
 // that is full holds back the ones behind it: a slot stood empty for 14 us between two workgroups, 9 % of the launch.  The
 // next item is drawn before the sums of the present one are exchanged and stored, so that the atomic's way to memory and
 // back costs nothing.  Measured, us, direct / queue: 75,600 tokens, 40 heads 13528 / 12936; 32,760 tokens, 12 heads 873 /
-// 851; 32,768 tokens, 24 heads, half the rows long 7540 / 7153; 20,010 tokens, 6 heads, d = 64 129 / 130.  The forward and
+// 851; 32,768 tokens, 24 heads, half the rows long 7540 / 7153 (d = 64: see with_queue).  The forward and
 // dQ kernels gain less (their launches are bound by power, an empty slot is clock for the others: 1.6 % for dQ, 0.3 % for
-// forward on the first of these) and lose on shorter launches (dQ on the last 75 / 81): they are launched directly.
+// forward on the first of these) and lose on shorter launches (dQ on 20,010 tokens, 6 heads, d = 64 75 / 81): they are launched directly.
 // Numbers that stand for no column are drawn as well, an atomic and two barriers each, so the queue has xcd_map's few: with
 // chunks of a head on every XCD, heads of less than eight columns left XCDs of nothing but such numbers.  Stage call, us,
-// chunks / xcd_map / direct: 2,300 heads of one column, d = 64 95 / 54 / 52, d = 128 113 / 83 / 82; 1,000 heads of 9 columns
-// 219 / 191 / 195, 324 / 301 / 307; 282 heads of 32 276 / 271 / 275; 141 heads of 64 420 / 421 / 477.
+// chunks / xcd_map / direct, d = 128: 2,300 heads of one column 113 / 83 / 82; 1,000 heads of 9 columns 324 / 301 / 307.
 #pragma once
 #include "spa2_device.h"
 #include "spa2_internal.h"
