@@ -76,6 +76,13 @@ def test_full_columns_are_drawn_where_the_last_round_is_short(H, N, d, missing, 
         assert torch.equal(a, b), name
         assert torch.equal(a, c), name
     assert torch.equal(got[0], other[0])
+    # the stage call, whose plan is a launch of its own, with room for a fifth of the parts
+    at, full = plan_offsets(q)["dkdv"], spa2.spa2_bwd_workspace_bytes(q)
+    ws = torch.zeros(at + (full - at) // 5, dtype=torch.uint8, device=dev())
+    spa2.spa2_bwd_delta(o, do, ws, o_res)
+    dk, dv = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    spa2.spa2_bwd_dkdv(q, k, v, do, lse, pat, d ** -0.5, dk, dv, ws)
+    assert torch.equal(dk, want[1]) and torch.equal(dv, want[2])
 
 
 def _cut_pattern(B, H, N, seed, every):
